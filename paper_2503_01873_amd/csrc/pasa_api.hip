@@ -169,6 +169,39 @@ int wanted_splits(int B, int Hq, int Nq, int N)
     return ns < 2 ? 1 : (int)ns;
 }
 
+// Workgroups of pasa_rows, without a key split: blocks of 16 rows, of the heads of a KV head together below 16 rows each.
+long row_blocks(int B, int Hkv, int G, int Nq)
+{
+    return (long)B * Hkv * (Nq < 16 ? ((long)G * Nq + 15) / 16 : (long)G * ((Nq + 15) / 16));
+}
+
+// Which calls go to pasa_rows (workgroups of 16 query rows, keys shared out among their wavefronts) instead of pasa_fwd
+// (256 rows of one head): launches of up to two rounds of its workgroups (one at d = 64, where a workgroup has half as
+// much to do per key), and every call whose rows of a KV head fit one workgroup, which then reads its keys once and not
+// once per query head.  28 heads on 4, d = 128, causal, pasa_fwd -> pasa_rows in us: 1 row of 512 / 2048 / 32768 keys 14.8
+// -> 6.0, 37.8 -> 13.8, 77.9 -> 18.9; 128 rows 16.6 -> 7.4, 40.2 -> 15.6, 522 -> 165; 256 rows (two rounds) 20.3 -> 12.8,
+// 48.0 -> 26.7, 615 -> 276.  Beyond: whole prompts of 512 / 1024 rows (four and seven rounds) 20.4 -> 23.0, 29.9 -> 50.7;
+// d = 64, one head of 4096 rows (one round) 41.4 -> 15.1, of 8192 rows 43.9 -> 45.7.
+bool few_rows(int variant, int B, int Hkv, int G, int Nq, int d)
+{
+    if (variant != PASA_MIXED && variant != PASA_DIRECT) return false;
+    const long blocks = row_blocks(B, Hkv, G, Nq);
+    return (long)G * Nq <= 16 || blocks <= kComputeUnits * (d / 64);
+}
+
+// Workgroups that share the keys of a row block: as many as fill the chip, each with a unit of 64 keys for each of its
+// eight wavefronts at least.  Not up to 2048 keys (four units per wavefront): the merge kernel and its launch cost as much
+// there (1 row of 28 heads, 2048 keys: 10.2 us split, 13.8 not; 1024 keys: 8.1 not split), and a row's result stays
+// independent of the rows that are given with it.
+int rows_splits(int B, int Hkv, int G, int Nq, int N, int keys)
+{
+    const long blocks = row_blocks(B, Hkv, G, Nq), units = ((long)keys + 63) / 64;
+    if (N <= 2048) return 1;
+    long ns = kComputeUnits / blocks;
+    if (ns > (units + 7) / 8) ns = (units + 7) / 8;
+    return ns < 1 ? 1 : (int)ns;
+}
+
 size_t split_row_bytes(int d) { return (size_t)d * 4 + 16; }
 
 size_t split_region_bytes(int B, int Hq, int N, int d)
@@ -413,7 +446,11 @@ int fwd_chunk_impl(const void* q, void* o, int B, int Hq, int Hkv, int Nq, int r
     p.overflow_group = overflow_group;
     p.gate = gate;
     // key split: as many ways as the rule wants and the bytes behind the fixed regions hold
-    int ns = (gate != nullptr || pr.variant == PASA_STRICT16) ? 1 : wanted_splits(B, Hq, Nq, N);
+    const int keys = p.causal && p.row0 < N - Nq ? p.row0 + Nq : N;      // that some row sees
+    const bool rows = overflow_group == nullptr && pr.overflow_s == nullptr && pr.nonfinite_o == nullptr &&
+                      few_rows(pr.variant, B, Hkv, Hq / Hkv, Nq, d);
+    int ns = (gate != nullptr || pr.variant == PASA_STRICT16) ? 1
+             : rows ? rows_splits(B, Hkv, Hq / Hkv, Nq, N, keys) : wanted_splits(B, Hq, Nq, N);
     const size_t rows_all = (size_t)B * Hq * Nq, room = workspace_bytes - need;
     while (ns > 1 && (size_t)ns * rows_all * split_row_bytes(d) > room) --ns;
     p.nsplit = ns;
@@ -421,7 +458,7 @@ int fwd_chunk_impl(const void* q, void* o, int B, int Hq, int Hkv, int Nq, int r
     p.part_lr = split_base;                                              // [ns][rows][2] doubles
     p.part_o = split_base + (size_t)ns * rows_all * 16;                  // [ns][rows][d] floats
     p.stream = static_cast<hipStream_t>(stream);
-    return pasa_launch_fwd(p) == hipSuccess ? PASA_OK : PASA_ELAUNCH;
+    return (rows ? pasa_launch_rows(p) : pasa_launch_fwd(p)) == hipSuccess ? PASA_OK : PASA_ELAUNCH;
 }
 
 }  // namespace

@@ -58,6 +58,14 @@ hipError_t pasa_launch_shift_gemm(const void* k, void* ws, void* plain_out, int 
 
 hipError_t pasa_launch_fwd(const PasaLaunch& p);
 
+// The same for few query rows (PASA_K_MIXED and PASA_K_DIRECT, no counters): workgroups of 16 rows, of all the heads of
+// a KV head together where fewer than 16 are given; p.nsplit workgroups share the keys of each.
+hipError_t pasa_launch_rows(const PasaLaunch& p);
+
+// Merges the nsplit partial states of rows_all rows that pasa_launch_fwd or pasa_launch_rows has left.
+hipError_t pasa_launch_merge(const void* part_o, const void* part_lr, void* o, size_t rows_all, int d, int nsplit,
+                             int io_bf16, unsigned long long* nonfinite_o, hipStream_t stream);
+
 // Sets n 64-bit words to zero with a small kernel (not a memset, so that the call may sit in a captured graph).
 hipError_t pasa_launch_zero(unsigned long long* p, int n, hipStream_t stream);
 

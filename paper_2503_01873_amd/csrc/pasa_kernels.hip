@@ -1049,52 +1049,6 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     }
 }
 
-// Merge of the key splits of one call: per query row, the splits' stored outputs and sums are brought to the highest of
-// their levels (the log-sum-exp rule on R = m + Inva * F + Lc, the absolute level a split's stored output refers to)
-// and added; then Algorithm 1's final quotient.  One thread per 8 channels of a row.
-template <int D>
-__global__ __launch_bounds__(256) void pasa_merge_splits(const float* __restrict__ part_o, const double* __restrict__ part_lr,
-                                                         _Float16* __restrict__ o, size_t rows_all, int nsplit, int io_bf16,
-                                                         unsigned long long* nonfinite_o)
-{
-    constexpr int TPR = D / 8;                       // threads per row
-    const size_t grow = (size_t)blockIdx.x * (256 / TPR) + threadIdx.x / TPR;
-    if (grow >= rows_all) return;
-    const int c0 = (threadIdx.x % TPR) * 8;
-    double rmax = -__builtin_inf();
-    for (int s = 0; s < nsplit; ++s) {
-        const double r = part_lr[((size_t)s * rows_all + grow) * 2 + 1];
-        rmax = r > rmax ? r : rmax;
-    }
-    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    float lsum = 0.f;
-    for (int s = 0; s < nsplit; ++s) {
-        const double r = part_lr[((size_t)s * rows_all + grow) * 2 + 1];
-        if (!(r > -__builtin_inf())) continue;       // this split saw none of the row's keys (its output is not written)
-        const float wgt = __builtin_amdgcn_exp2f((float)(r - rmax) * LOG2E);
-        lsum += wgt * (float)part_lr[((size_t)s * rows_all + grow) * 2];
-        const float4* src = reinterpret_cast<const float4*>(part_o + ((size_t)s * rows_all + grow) * D + c0);
-        const float4 a = src[0], b4 = src[1];
-        acc[0] += wgt * a.x; acc[1] += wgt * a.y; acc[2] += wgt * a.z; acc[3] += wgt * a.w;
-        acc[4] += wgt * b4.x; acc[5] += wgt * b4.y; acc[6] += wgt * b4.z; acc[7] += wgt * b4.w;
-    }
-    const float inv = 1.0f / lsum;
-    h8 out;
-    u16x8 outb;
-    unsigned n_bad = 0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float v32 = acc[e] * inv;
-        out[e] = (_Float16)v32;
-        outb[e] = f32_to_bf16_rn(v32);
-        const float fv = io_bf16 ? __uint_as_float((unsigned)outb[e] << 16) : (float)out[e];
-        n_bad += (fv != fv || __builtin_fabsf(fv) == __builtin_inff()) ? 1u : 0u;
-    }
-    if (io_bf16) *reinterpret_cast<u16x8*>(o + grow * D + c0) = outb;
-    else *reinterpret_cast<h8*>(o + grow * D + c0) = out;
-    if (nonfinite_o != nullptr && n_bad) atomicAdd(nonfinite_o, (unsigned long long)n_bad);
-}
-
 template <int D, int VAR, bool CAUSAL, bool INSTR>
 hipError_t launch_fwd(const PasaLaunch& p)
 {
@@ -1121,12 +1075,7 @@ hipError_t launch_fwd(const PasaLaunch& p)
                        nsplit > 1 ? (float*)p.part_o : nullptr, nsplit > 1 ? (double*)p.part_lr : nullptr);
     e = hipGetLastError();
     if (e != hipSuccess || nsplit == 1) return e;
-    const size_t rows_all = (size_t)p.B * p.Hq * p.Nq;
-    constexpr int RPB = 256 / (D / 8);                          // rows per block of the merge
-    hipLaunchKernelGGL(pasa_merge_splits<D>, dim3((unsigned)((rows_all + RPB - 1) / RPB)), dim3(256), 0, p.stream,
-                       (const float*)p.part_o, (const double*)p.part_lr, (_Float16*)p.o, rows_all, nsplit, p.io_bf16,
-                       p.nonfinite_o);
-    return hipGetLastError();
+    return pasa_launch_merge(p.part_o, p.part_lr, p.o, (size_t)p.B * p.Hq * p.Nq, D, nsplit, p.io_bf16, p.nonfinite_o, p.stream);
 }
 
 template <int D, int VAR>

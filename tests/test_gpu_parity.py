@@ -515,6 +515,39 @@ def test_decoding_against_a_cache(Nq):
     assert compare(o2, o3)["maxabs"] <= 2e-3
 
 
+# ------------------------------------------------------------------ few query rows: blocks of 16, keys in units of 64
+
+@pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT])
+@pytest.mark.parametrize("Nq,G,N,row0,causal,d", [
+    (1, 1, 1, 0, True, 128),            # one row, one key
+    (1, 7, 63, 62, True, 64),           # seven heads in one block, one unit that is not full
+    (2, 8, 64, 62, True, 128),          # exactly 16 rows of two positions; exactly one unit
+    (3, 7, 65, 62, True, 128),          # 21 rows: a second block of 5; a unit of one key
+    (15, 3, 1025, 600, True, 64),       # heads share blocks; keys past the last position
+    (16, 2, 640, 624, True, 128),       # a block for each head from here on
+    (17, 2, 513, 0, True, 64),          # causal from the start: the second block has one row
+    (40, 1, 2049, 2030, True, 128),     # positions past the last key; the first length whose keys are split
+    (5, 4, 4161, 4156, True, 128),      # split, with a last unit of one key in a tile of 65
+    (33, 1, 3000, 0, False, 64),
+])
+def test_few_rows(Nq, G, N, row0, causal, d, variant):
+    rng = np.random.default_rng(Nq * 1000 + N)
+    B, Hkv = 2, 2
+    q = rng.standard_normal((B, Hkv * G, Nq, d)).astype(np.float16)
+    k = (rng.standard_normal((B, Hkv, N, d)) + 3).astype(np.float16)
+    v = rng.standard_normal((B, Hkv, N, d)).astype(np.float16)
+    scale = f32(d ** -0.5)
+    o = gpu_attn_chunks(q, k, v, causal, scale, [(0, Nq, row0)], variant=variant)
+    if variant == P.DIRECT:
+        ref = np.stack([[po.direct_rows(q[b, h], k[b, h // G], v[b, h // G], scale, causal, BETA, 128, po.MIXED, row0)
+                         for h in range(Hkv * G)] for b in range(B)])
+    else:
+        ref = _rows_ref(q, k, v, scale, causal, 0, Nq, row0)
+    c = compare(o, ref)
+    print(VARIANT_NAME[variant], Nq, G, N, row0, c)
+    assert np.isfinite(o).all() and c["maxabs"] <= 2e-3
+
+
 # ------------------------------------------------------------------ key split: few workgroups, many key tiles
 
 @pytest.mark.parametrize("variant", [P.MIXED, P.S16, P.DIRECT])
