@@ -169,36 +169,52 @@ int wanted_splits(int B, int Hq, int Nq, int N)
     return ns < 2 ? 1 : (int)ns;
 }
 
-// Workgroups of pasa_rows, without a key split: blocks of 16 rows, of the heads of a KV head together below 16 rows each.
-long row_blocks(int B, int Hkv, int G, int Nq)
+// Workgroups of pasa_rows with `rb` blocks of 16 rows, without a key split: the rows of a KV head's query heads are one
+// list when fewer than 16 are given, one list per query head otherwise.
+long rows_workgroups(int B, int Hkv, int G, int Nq, int rb)
 {
-    return (long)B * Hkv * (Nq < 16 ? ((long)G * Nq + 15) / 16 : (long)G * ((Nq + 15) / 16));
+    const int R = 16 * rb;
+    return (long)B * Hkv * (Nq < 16 ? ((long)G * Nq + R - 1) / R : (long)G * ((Nq + R - 1) / R));
 }
 
-// Which calls go to pasa_rows (workgroups of 16 query rows, keys shared out among their wavefronts) instead of pasa_fwd
-// (256 rows of one head): launches of up to two rounds of its workgroups (one at d = 64, where a workgroup has half as
-// much to do per key), and every call whose rows of a KV head fit one workgroup, which then reads its keys once and not
-// once per query head.  28 heads on 4, d = 128, causal, pasa_fwd -> pasa_rows in us: 1 row of 512 / 2048 / 32768 keys 14.8
-// -> 6.0, 37.8 -> 13.8, 77.9 -> 18.9; 128 rows 16.6 -> 7.4, 40.2 -> 15.6, 522 -> 165; 256 rows (two rounds) 20.3 -> 12.8,
-// 48.0 -> 26.7, 615 -> 276.  Beyond: whole prompts of 512 / 1024 rows (four and seven rounds) 20.4 -> 23.0, 29.9 -> 50.7;
-// d = 64, one head of 4096 rows (one round) 41.4 -> 15.1, of 8192 rows 43.9 -> 45.7.
-bool few_rows(int variant, int B, int Hkv, int G, int Nq, int d)
+// Blocks of 16 rows per workgroup.  One while that gives a workgroup to every compute unit at most: 28 heads on 4, d = 128,
+// us with one / two blocks: 128 rows (224 workgroups of one) of 2048 / 32768 keys 14.6 / 18.3, 157 / 185; 256 rows 22.6 /
+// 18.5, 295 / 189 (all before neighbours shared an L2).
+int rows_blocks(int B, int Hkv, int G, int Nq)
+{
+    return (long)G * Nq <= 16 || rows_workgroups(B, Hkv, G, Nq, 1) <= kComputeUnits ? 1 : 2;
+}
+
+// Which calls go to pasa_rows (workgroups of 16 or 32 query rows, the keys shared out among their wavefronts) instead of
+// pasa_fwd (256 rows of one head).  Every call whose rows of a KV head fit one block (a decoding step reads its keys once
+// and not once per query head); otherwise the one that two measured rates say is faster.  Here 256 workgroups of 32 rows
+// pass a tile in 0.74 us.  There a workgroup passes a tile in 2.0 us when few run, and 256 of them in 4.1 us when all their
+// rows are real, less when fewer are.  28 heads on 4, d = 128, causal, pasa_fwd -> pasa_rows in us: 1 row of 512 / 2048 / 32768
+// keys 14.7 -> 6.2, 37.8 -> 12.6, 78 -> 18.7; 128 rows 16.5 -> 6.8, 40.3 -> 13.3, 522 -> 147; 512 rows of 2048 / 32768 keys 48.0 ->
+// 25.2, 617 -> 318; whole prompts of 512 / 1024 rows 20.3 -> 11.0, 30.0 -> 25.6, of 1500 / 2048 rows 39.1 / 42.2, 50.8 / 71.1 (not
+// taken).  14 sequences, 28 heads on 4, 1 / 20 / 64 rows of 6000 keys 189 -> 34, 189 -> 65, 192 -> 124.
+bool few_rows(int variant, int B, int Hq, int Hkv, int Nq, int row0, int N, int causal)
 {
     if (variant != PASA_MIXED && variant != PASA_DIRECT) return false;
-    const long blocks = row_blocks(B, Hkv, G, Nq);
-    return (long)G * Nq <= 16 || blocks <= kComputeUnits * (d / 64);
+    if ((long)(Hq / Hkv) * Nq <= 16) return true;
+    const double most = causal && row0 < N - Nq ? row0 + Nq : N;                            // keys that the last row sees
+    const double mean = causal && row0 + Nq / 2 < N ? row0 + Nq / 2 : N;                    // ... that a row sees on average
+    const double here = 0.74 / 256 * rows_workgroups(B, Hkv, Hq / Hkv, Nq, 2) * mean;       // us per 128 keys
+    const double real = Nq < 256 ? Nq / 256.0 : 1.0;
+    const double alone = 2.0 * most, full = (2.0 + 2.1 * real) / 256 * B * Hq * ((Nq + 255) / 256) * mean;
+    return here <= 0.92 * (alone > full ? alone : full);
 }
 
-// Workgroups that share the keys of a row block: as many as fill the chip, each with a unit of 64 keys for each of its
-// eight wavefronts at least.  Not up to 2048 keys (four units per wavefront): the merge kernel and its launch cost as much
-// there (1 row of 28 heads, 2048 keys: 10.2 us split, 13.8 not; 1024 keys: 8.1 not split), and a row's result stays
+// Workgroups that share the keys of a row block: as many as make two to a compute unit, each with a unit of 64 keys for
+// each of its four wavefronts at least.  Not up to 2048 keys: the merge kernel and its launch cost as much
+// there (1 row of 28 heads, 2048 keys: 10.2 us split, 13.0 not; 1024 keys: 8.1 not split), and a row's result stays
 // independent of the rows that are given with it.
-int rows_splits(int B, int Hkv, int G, int Nq, int N, int keys)
+int rows_splits(int B, int Hkv, int G, int Nq, int rb, int N, int keys)
 {
-    const long blocks = row_blocks(B, Hkv, G, Nq), units = ((long)keys + 63) / 64;
+    const long groups = rows_workgroups(B, Hkv, G, Nq, rb), units = ((long)keys + 63) / 64;
     if (N <= 2048) return 1;
-    long ns = kComputeUnits / blocks;
-    if (ns > (units + 7) / 8) ns = (units + 7) / 8;
+    long ns = 2 * kComputeUnits / groups;
+    if (ns > (units + 3) / 4) ns = (units + 3) / 4;
     return ns < 1 ? 1 : (int)ns;
 }
 
@@ -448,9 +464,10 @@ int fwd_chunk_impl(const void* q, void* o, int B, int Hq, int Hkv, int Nq, int r
     // key split: as many ways as the rule wants and the bytes behind the fixed regions hold
     const int keys = p.causal && p.row0 < N - Nq ? p.row0 + Nq : N;      // that some row sees
     const bool rows = overflow_group == nullptr && pr.overflow_s == nullptr && pr.nonfinite_o == nullptr &&
-                      few_rows(pr.variant, B, Hkv, Hq / Hkv, Nq, d);
+                      few_rows(pr.variant, B, Hq, Hkv, Nq, row0, N, causal);
+    const int rb = rows_blocks(B, Hkv, Hq / Hkv, Nq);
     int ns = (gate != nullptr || pr.variant == PASA_STRICT16) ? 1
-             : rows ? rows_splits(B, Hkv, Hq / Hkv, Nq, N, keys) : wanted_splits(B, Hq, Nq, N);
+             : rows ? rows_splits(B, Hkv, Hq / Hkv, Nq, rb, N, keys) : wanted_splits(B, Hq, Nq, N);
     const size_t rows_all = (size_t)B * Hq * Nq, room = workspace_bytes - need;
     while (ns > 1 && (size_t)ns * rows_all * split_row_bytes(d) > room) --ns;
     p.nsplit = ns;
@@ -458,7 +475,7 @@ int fwd_chunk_impl(const void* q, void* o, int B, int Hq, int Hkv, int Nq, int r
     p.part_lr = split_base;                                              // [ns][rows][2] doubles
     p.part_o = split_base + (size_t)ns * rows_all * 16;                  // [ns][rows][d] floats
     p.stream = static_cast<hipStream_t>(stream);
-    return (rows ? pasa_launch_rows(p) : pasa_launch_fwd(p)) == hipSuccess ? PASA_OK : PASA_ELAUNCH;
+    return (rows ? pasa_launch_rows(p, rb) : pasa_launch_fwd(p)) == hipSuccess ? PASA_OK : PASA_ELAUNCH;
 }
 
 }  // namespace

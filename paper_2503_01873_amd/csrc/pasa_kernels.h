@@ -58,9 +58,9 @@ hipError_t pasa_launch_shift_gemm(const void* k, void* ws, void* plain_out, int 
 
 hipError_t pasa_launch_fwd(const PasaLaunch& p);
 
-// The same for few query rows (PASA_K_MIXED and PASA_K_DIRECT, no counters): workgroups of 16 rows, of all the heads of
+// The same for few query rows (PASA_K_MIXED and PASA_K_DIRECT, no counters): workgroups of 16 * row_blocks rows (1 or 2), of all the heads of
 // a KV head together where fewer than 16 are given; p.nsplit workgroups share the keys of each.
-hipError_t pasa_launch_rows(const PasaLaunch& p);
+hipError_t pasa_launch_rows(const PasaLaunch& p, int row_blocks);
 
 // Merges the nsplit partial states of rows_all rows that pasa_launch_fwd or pasa_launch_rows has left.
 hipError_t pasa_launch_merge(const void* part_o, const void* part_lr, void* o, size_t rows_all, int d, int nsplit,

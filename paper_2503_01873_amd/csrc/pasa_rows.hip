@@ -2,7 +2,7 @@
 // splits that it shares with pasa_fwd.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-#include <atomic>
+#include <type_traits>
 
 #include "pasa_kernels.h"
 
@@ -11,7 +11,11 @@ typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef float f2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
+
+#define PASA_FENCE() __builtin_amdgcn_sched_barrier(0)
 
 namespace {
 
@@ -40,18 +44,27 @@ __device__ inline h8 load_frag(__amdgpu_buffer_rsrc_t src, int voff, int soff)
     return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(src, voff, soff, 0));
 }
 
-// largest value / sum over the four lanes l, l^16, l^32, l^48 that share a query row
+// x of the even and of the odd one of each pair of 16-lane rows, in both; x of the lower and of the upper 32 lanes, in both
+__device__ inline void rows16(float x, float& even, float& odd)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    even = __uint_as_float(r[0]);
+    odd = __uint_as_float(r[1]);
+}
+__device__ inline void rows32(float x, float& low, float& high)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    low = __uint_as_float(r[0]);
+    high = __uint_as_float(r[1]);
+}
+// largest value over the four lanes l, l^16, l^32, l^48 that share a query row
 __device__ inline float max_row(float x)
 {
-    x = __builtin_fmaxf(x, __shfl_xor(x, 16));
-    return __builtin_fmaxf(x, __shfl_xor(x, 32));
+    float a, b;
+    rows16(x, a, b);
+    rows32(__builtin_fmaxf(a, b), a, b);
+    return __builtin_fmaxf(a, b);
 }
-__device__ inline float sum_row(float x)
-{
-    x += __shfl_xor(x, 16);
-    return x + __shfl_xor(x, 32);
-}
-
 // One workgroup = NW wavefronts owns 16 * RB rows and a range of the keys in units of 64.  The rows come from lists: with fewer than 16 rows given, the rows of ALL the
 // heads that share a KV head are one list (they are contiguous in q and o), so that a decoding step reads its keys once;
 // otherwise each head is a list, so that a block's rows are neighbours in position.  Every wavefront sweeps units of its
@@ -68,11 +81,16 @@ __device__ inline float sum_row(float x)
 // inva * Sbar' (MIXED: what the two correction terms of Algorithm 1's step 3 add up to, m + inva * F + Lc; F cancels)
 // or scale * (q . k0) (DIRECT).
 //
-// What bounds it: few rows, the keys' way from memory (one row of 32768 keys, 28 heads on 4: 67 MB in 16 us; a large read
-// reaches 6 TB/s here); more rows, the L2 (every 16 rows read all keys: 27 TB/s at 256 rows of 28 heads).  A wavefront has
-// the 16 KB of a unit's keys and the 16 KB of its values in flight at once, eight wavefronts of a compute unit 256 KB.
+// What bounds it: a few rows, the keys' way from memory (one row of 32768 keys, 28 heads on 4: 67 MB, 15 us; a large read
+// reaches 6 TB/s here); more rows, the vector memory path into the registers (36 KB for a unit and wavefront, 46 bytes a
+// clock and compute unit in 128 rows of 32768 keys, 147 us), which is why 32 rows take hardly longer than 16.  So a lane's
+// work per score is kept to a multiply-add, an exponential and half a pack: row sums come from the matrix core (P against
+// ones), the pseudo-average needs no exchange (the even rows of its A operand are the high parts of the tile's mean, the
+// odd rows the low parts), and the level is kept in absolute terms.  (With row sums in lanes and the products for eight
+// tiles at a time shared out by shuffles, 32 rows took twice as long as 16.)  Four wavefronts per workgroup: two workgroups
+// share a compute unit, so that one loads while the other merges (28 heads of 512 rows 16.8 -> 11.7 us against eight).
 template <int D, int RB, int NW>
-__global__ __launch_bounds__(64 * NW)
+__global__ __launch_bounds__(64 * NW, 2)
 void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, const _Float16* __restrict__ kmean,
                _Float16* __restrict__ o, int lists, int list_rows, int Nq, int row0, int N, int causal, int nblk, int nsplit,
                int units, float coef, int tail_by_count, int io_bf16, const unsigned long long* gate,
@@ -91,15 +109,22 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lq = lane & 15, g = lane >> 4;
 
-    // grid: split fastest, then row block, then list of rows, then (batch, KV head)
+    // Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of its own: every XCD gets a contiguous range of the
+    // work, in which the row blocks that read the same keys follow one another.  14 x 28 heads on 4, 64 rows of
+    // 6000 keys: 124 us; with neighbours on different XCDs, where every L2 fetches every key, 241 us
     int idx = blockIdx.x;
-    const int split = idx % nsplit;
-    idx /= nsplit;
+    {
+        const int x = idx & 7, whole = gridDim.x >> 3, rest = gridDim.x & 7;
+        idx = x * whole + (x < rest ? x : rest) + (idx >> 3);
+    }
     const int blk = idx % nblk;
     idx /= nblk;
-    const size_t grp = idx / lists;              // b * Hkv + hk
+    const int list = idx % lists;
+    idx /= lists;
+    const int split = idx % nsplit;
+    const size_t grp = idx / nsplit;             // b * Hkv + hk
     if (gate != nullptr && gate[grp] == 0) return;   // adaptive start: nothing overflowed here
-    const size_t list0 = (grp * lists + idx % lists) * (size_t)list_rows;   // first row of the list, in q and o
+    const size_t list0 = (grp * lists + list) * (size_t)list_rows;   // first row of the list, in q and o
     const int p0 = blk * ROWS;
     int p1 = p0 + ROWS - 1;
     if (p1 > list_rows - 1) p1 = list_rows - 1;
@@ -128,89 +153,116 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
     // lane offsets of the fragments
     const int kv = (g * T + 16 * (lq >> 3) + (lq & 7)) * 16;     // row r of a block is key 16 (r / 8) + r % 8 of its 32: see kfrag
     const int vv = ((g >> 1) * 2 * D + (g & 1) * D + lq) * 16;
-    const int mv = (g * 32 + lq) * 16;
+    const int mv = (g * 32 + 4 * (lq & 1)) * 16;                 // rows 8 (t / 4) + t % 4 (high) and 4 further down (low)
 
-    h8 K[4 * KS], V[2 * CB];
-    auto load_k = [&](int u) {
-        const int base = (u >> 1) * TILE_BYTES + (u & 1) * (U * 16);
+    // Three register buffers of half a unit's keys or values (8 KB each at d = 128) take the four halves in turn: A holds K' of
+    // the first half of the channels, then V of the second half of the keys; B K' of the other channels; C V of the other keys.
+    // Each is loaded again as soon as the products with it are done.
+    constexpr int HF = CB;                                       // fragments of a half
+    h8 A[HF], B[HF], C[HF];
+    auto load_k = [&](h8 (&dst)[HF], int u, int half) {
+        const int base = (u >> 1) * TILE_BYTES + (u & 1) * (U * 16) + half * (KS / 2) * (4 * T * 16);
 #pragma unroll
-        for (int n = 0; n < 4 * KS; ++n) {                       // block n % 4, k-step n / 4
-            const int i = (n % 4) >> 1, s = n & 1;
-            K[n] = load_frag(tiles, kv, base + (n / 4) * (4 * T * 16) + i * (32 * 16) + s * (8 * 16));
-        }
+        for (int n = 0; n < HF; ++n)                             // block n % 4, k-step n / 4 of the half
+            dst[n] = load_frag(tiles, kv, base + (n / 4) * (4 * T * 16) + ((n % 4) >> 1) * (32 * 16) + (n & 1) * (8 * 16));
     };
-    auto load_v = [&](int u) {
-        const int base = (u >> 1) * TILE_BYTES + 2 * T * D + (u & 1) * (U * 2 * D);
+    h8 Am[KS];                                                   // even rows: high, odd rows: low part of the tile's mean
+    auto load_m = [&](int u) {
+        const int t = u >> 1;
 #pragma unroll
-        for (int n = 0; n < 2 * CB; ++n)                         // channel block n % CB, k-step n / CB
-            V[n] = load_frag(tiles, vv, base + (n / CB) * (4 * D * 16) + (n % CB) * (16 * 16));
+        for (int ks = 0; ks < KS; ++ks)
+            Am[ks] = load_frag(means, mv, (t >> 4) * (64 * D) + ((t & 12) * 2 + (t & 3)) * 16 + ks * (4 * 32 * 16));
+    };
+    auto load_v = [&](h8 (&dst)[HF], int u, int half) {
+        const int base = (u >> 1) * TILE_BYTES + 2 * T * D + (u & 1) * (U * 2 * D) + half * (4 * D * 16);
+#pragma unroll
+        for (int n = 0; n < HF; ++n) dst[n] = load_frag(tiles, vv, base + n * (16 * 16));   // channel block n
     };
 
-    h8 Q[RB][KS];
+    constexpr bool QLDS = RB > 1;                // the query fragments wait in LDS: the registers are needed for RB * 2 blocks
+    __shared__ __attribute__((aligned(16))) h8 lds_q[QLDS ? RB * KS * 64 : 1];
+    h8 Qr[QLDS ? 1 : RB][KS];
+    auto Qf = [&](int rb, int ks) { return QLDS ? lds_q[(rb * KS + ks) * 64 + lane] : Qr[QLDS ? 0 : rb][ks]; };
     f4 O[RB][CB];
-    float l[RB];
+    f4 L[RB];                                    // row sums of P, the same in all elements
     double R[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        l[rb] = 0.f;
+        L[rb] = (f4)0.f;
         R[rb] = -__builtin_inf();
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) O[rb][cb] = (f4)0.f;
     }
 
     if (u0 < ue) {
-        load_k(u0);
-        int last[RB];                            // last key that the lane's row sees
+        load_m(u0);
+        load_k(B, u0, 1);
+        load_k(A, u0, 0);
+        load_v(C, u0, 0);
+    }
+    int last[RB];                                // last key that the lane's row sees
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            const int p = p0 + 16 * rb + lq;
-            const bool real = p < list_rows;
-            last[rb] = N - 1;
-            if (causal && real && row0 + p % Nq < N - 1) last[rb] = row0 + p % Nq;
-            const _Float16* src = q + (list0 + (real ? p : p0)) * D + 8 * g;
+    for (int rb = 0; rb < RB; ++rb) {
+        const int p = p0 + 16 * rb + lq;
+        const bool real = p < list_rows;
+        last[rb] = N - 1;
+        if (causal && real && row0 + p % Nq < N - 1) last[rb] = row0 + p % Nq;
+        const _Float16* src = q + (list0 + (real ? p : p0)) * D + 8 * g;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const h8 raw = *reinterpret_cast<const h8*>(src + 32 * ks);
-                const h8 val = io_bf16 ? q_from_bf16(__builtin_bit_cast(u16x8, raw)) : raw;
-                Q[rb][ks] = real ? val : (h8)(_Float16)0;
-            }
+        for (int ks = 0; ks < KS; ++ks) {
+            if (QLDS && (rb * KS + ks) % NW != wave) continue;      // one fragment for each wavefront
+            const h8 raw = *reinterpret_cast<const h8*>(src + 32 * ks);
+            const h8 val = io_bf16 ? q_from_bf16(__builtin_bit_cast(u16x8, raw)) : raw;
+            const h8 qv = real ? val : (h8)(_Float16)0;
+            if (QLDS) lds_q[(rb * KS + ks) * 64 + lane] = qv;
+            else Qr[QLDS ? 0 : rb][ks] = qv;
         }
-        f4 M[RB];                                // q . (mean rows) of eight tiles: see below
-        int m8 = -1;
-        for (int u = u0; u < ue; u += NW) {
+    }
+    if (QLDS) __syncthreads();
+    if (u0 < ue) {
+        auto unit = [&](int u, auto more_c) {
+            constexpr bool more = decltype(more_c)::value;
             const int t = u >> 1;
-            if ((t >> 3) != m8) {
-                // the means of eight tiles: A rows 16 (t8 & 1) .. +15 of the mean block; lanes g = 0 (2) then hold the products
-                // with the high parts of tiles 0-3 (4-7) of the eight, lanes g = 1 (3) those with the low parts
-                m8 = t >> 3;
-                h8 A[KS];
+            // q . mean of the tile: every lane gets the product with the high part in element 0, with the low part in 1
+            f4 M[RB];
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-                    A[ks] = load_frag(means, mv, (m8 >> 1) * (64 * D) + (m8 & 1) * (16 * 16) + ks * (4 * 32 * 16));
+            for (int rb = 0; rb < RB; ++rb) M[rb] = (f4)0.f;
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb) {
-                    M[rb] = (f4)0.f;
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks)
-                        M[rb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[ks], Q[rb][ks], M[rb], 0, 0, 0);
-                }
-            }
-            load_v(u);
-            f4 S[RB][4];
-#pragma unroll
-            for (int n = 0; n < 4 * KS; ++n)
+            for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb)
-                    S[rb][n % 4] = __builtin_amdgcn_mfma_f32_16x16x32_f16(K[n], Q[rb][n / 4], n < 4 ? (f4)0.f : S[rb][n % 4], 0, 0, 0);
-            if (u + NW < ue) load_k(u + NW);
+                    M[rb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Am[ks], Qf(rb, ks), M[rb], 0, 0, 0);
+            PASA_FENCE();
+            if (more) load_m(u + NW);
+            f4 S[RB][4];
+            auto gemm1 = [&](const h8 (&k)[HF], int half, bool clear) {
+#pragma unroll
+                for (int ks = 0; ks < KS / 2; ++ks) {
+                    h8 qf[RB];
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb) qf[rb] = Qf(rb, half * (KS / 2) + ks);
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+#pragma unroll
+                        for (int rb = 0; rb < RB; ++rb)
+                            S[rb][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(k[4 * ks + b], qf[rb], clear && ks == 0 ? (f4)0.f : S[rb][b], 0, 0, 0);
+                }
+                PASA_FENCE();
+            };
+            PASA_FENCE();
+            gemm1(B, 1, true);
+            if (more) load_k(B, u + NW, 1);
+            PASA_FENCE();
+            gemm1(A, 0, false);
+            load_v(A, u, 1);
+            PASA_FENCE();
 
-            const int e = t & 3, half = (t >> 2) & 1;
             const int tail = N - t * T;          // keys of this tile, when fewer than 128
             h8 P[RB][2];
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
-                const float me = e == 0 ? M[rb][0] : e == 1 ? M[rb][1] : e == 2 ? M[rb][2] : M[rb][3];
-                float v = __shfl(me, lq + 32 * half) + __shfl(me, lq + 32 * half + 16) * 0.00048828125f;
+                if (rb > 0) PASA_FENCE();
+                float v = M[rb][0] + M[rb][1] * 0.00048828125f;  // low parts are stored times 2^11
                 if (tail_by_count && tail < T) v *= (float)T * (1.0f / (float)tail);
                 if (u * U + U - 1 > first_pos) {
 #pragma unroll
@@ -226,42 +278,56 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
                     for (int i = 0; i < 4; ++i) mx = __builtin_fmaxf(mx, S[rb][b][i]);
                 mx = max_row(mx);
                 const bool unseen = mx == -__builtin_inff();     // the row sees no key of this unit
+                // c: level of this unit's scores relative to the stored output's (first unit: +inf, which clears the zeros)
                 const double lev = (double)mx + (double)coef * (double)v;
-                const bool first = R[rb] == -__builtin_inf();
-                float c = first ? (float)(lev - lev) : (float)(lev - R[rb]);      // first: 0, or NaN for a level that is none
-                const bool move = !unseen && (first || c > CMAX);
-                if (__builtin_amdgcn_ballot_w64(move && !first) != 0ull) {
-                    const float r = (move && !first) ? __builtin_amdgcn_exp2f(-c * LOG2E) : 1.f;
-                    l[rb] *= r;
+                float c = (float)(lev - R[rb]);
+                const bool move = c > CMAX;
+                if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
+                    const float r = move ? __builtin_amdgcn_exp2f(-c * LOG2E) : 1.f;
+                    R[rb] = move ? lev : R[rb];
+                    c = move ? 0.f : c;
+                    L[rb] *= r;
 #pragma unroll
                     for (int cb = 0; cb < CB; ++cb) O[rb][cb] *= r;
-                }
-                if (move) {
-                    R[rb] = lev;
-                    if (!first) c = 0.f;
                 }
                 const float nml = unseen ? 0.f : (c - mx) * LOG2E;
 #pragma unroll
                 for (int b = 0; b < 4; ++b)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const _Float16 ph = (_Float16)__builtin_amdgcn_exp2f(__builtin_fmaf(S[rb][b][i], LOG2E, nml));
-                        P[rb][b >> 1][4 * (b & 1) + i] = ph;
-                        l[rb] += (float)ph;
+                    for (int i = 0; i < 4; i += 2) {
+                        const f2 e = {__builtin_amdgcn_exp2f(__builtin_fmaf(S[rb][b][i], LOG2E, nml)),
+                                      __builtin_amdgcn_exp2f(__builtin_fmaf(S[rb][b][i + 1], LOG2E, nml))};
+                        const h2 ph = __builtin_convertvector(e, h2);
+                        P[rb][b >> 1][4 * (b & 1) + i] = ph[0];
+                        P[rb][b >> 1][4 * (b & 1) + i + 1] = ph[1];
                     }
             }
+            auto gemm2 = [&](const h8 (&v)[HF], int half) {
 #pragma unroll
-            for (int n = 0; n < 2 * CB; ++n)
+                for (int n = 0; n < HF; ++n)
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb)
-                    O[rb][n % CB] = __builtin_amdgcn_mfma_f32_16x16x32_f16(V[n], P[rb][n / CB], O[rb][n % CB], 0, 0, 0);
-        }
+                    for (int rb = 0; rb < RB; ++rb)
+                        O[rb][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v[n], P[rb][half], O[rb][n], 0, 0, 0);
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb)                  // the row sums of the rounded P
+                    L[rb] = __builtin_amdgcn_mfma_f32_16x16x32_f16((h8)(_Float16)1, P[rb][half], L[rb], 0, 0, 0);
+                PASA_FENCE();
+            };
+            PASA_FENCE();
+            gemm2(C, 0);
+            if (more) load_v(C, u + NW, 0);
+            PASA_FENCE();
+            gemm2(A, 1);
+            if (more) load_k(A, u + NW, 0);
+        };
+        int u = u0;
+        for (; u + NW < ue; u += NW) unit(u, std::true_type{});
+        unit(u, std::false_type{});
     }
 
     // ---- the wavefronts' states brought to the highest of their levels and added ----
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        l[rb] = sum_row(l[rb]);
         if (g == 0) lds_r[wave][16 * rb + lq] = R[rb];
     }
     __syncthreads();
@@ -271,7 +337,7 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
 #pragma unroll
         for (int w = 0; w < NW; ++w) rmax = __builtin_fmax(rmax, lds_r[w][16 * rb + lq]);
         const float wgt = R[rb] == -__builtin_inf() ? 0.f : __builtin_amdgcn_exp2f((float)(R[rb] - rmax) * LOG2E);
-        if (g == 0) lds_l[wave][16 * rb + lq] = wgt * l[rb];
+        if (g == 0) lds_l[wave][16 * rb + lq] = wgt * L[rb][0];
         float* dst = lds_o + (wave * ROWS + 16 * rb + lq) * LD + 4 * g;
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<f4*>(dst + 16 * cb) = O[rb][cb] * wgt;
@@ -294,7 +360,7 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
                 double rmax = -__builtin_inf();
                 for (int w = 0; w < NW; ++w) rmax = __builtin_fmax(rmax, lds_r[w][r]);
                 part_lr[((size_t)split * rows_all + grow) * 2] = ls;
-                part_lr[((size_t)split * rows_all + grow) * 2 + 1] = rmax;
+                part_lr[((size_t)split * rows_all + grow) * 2 + 1] = ls == ls ? rmax : ls;     // NaN stays NaN
             }
         } else {
             const float inv = 1.0f / ls;
@@ -427,7 +493,8 @@ hipError_t pasa_launch_merge(const void* part_o, const void* part_lr, void* o, s
     return hipGetLastError();
 }
 
-hipError_t pasa_launch_rows(const PasaLaunch& p)
+hipError_t pasa_launch_rows(const PasaLaunch& p, int row_blocks)
 {
-    return p.d == 128 ? launch_rows<128, 1, 8>(p) : launch_rows<64, 1, 8>(p);
+    if (p.d == 128) return row_blocks == 1 ? launch_rows<128, 1, 4>(p) : launch_rows<128, 2, 4>(p);
+    return row_blocks == 1 ? launch_rows<64, 1, 4>(p) : launch_rows<64, 2, 4>(p);
 }
