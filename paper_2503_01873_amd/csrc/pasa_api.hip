@@ -185,26 +185,6 @@ int rows_blocks(int B, int Hkv, int G, int Nq)
     return (long)G * Nq <= 16 || rows_workgroups(B, Hkv, G, Nq, 1) <= kComputeUnits ? 1 : 2;
 }
 
-// Which calls go to pasa_rows (workgroups of 16 or 32 query rows, the keys shared out among their wavefronts) instead of
-// pasa_fwd (256 rows of one head).  Every call whose rows of a KV head fit one block (a decoding step reads its keys once
-// and not once per query head); otherwise the one that two measured rates say is faster.  Here 256 workgroups of 32 rows
-// pass a tile in 0.74 us.  There a workgroup passes a tile in 2.0 us when few run, and 256 of them in 4.1 us when all their
-// rows are real, less when fewer are.  28 heads on 4, d = 128, causal, pasa_fwd -> pasa_rows in us: 1 row of 512 / 2048 / 32768
-// keys 14.7 -> 6.2, 37.8 -> 12.6, 78 -> 18.7; 128 rows 16.5 -> 6.8, 40.3 -> 13.3, 522 -> 147; 512 rows of 2048 / 32768 keys 48.0 ->
-// 25.2, 617 -> 318; whole prompts of 512 / 1024 rows 20.3 -> 11.0, 30.0 -> 25.6, of 1500 / 2048 rows 39.1 / 42.2, 50.8 / 71.1 (not
-// taken).  14 sequences, 28 heads on 4, 1 / 20 / 64 rows of 6000 keys 189 -> 34, 189 -> 65, 192 -> 124.
-bool few_rows(int variant, int B, int Hq, int Hkv, int Nq, int row0, int N, int causal)
-{
-    if (variant != PASA_MIXED && variant != PASA_DIRECT) return false;
-    if ((long)(Hq / Hkv) * Nq <= 16) return true;
-    const double most = causal && row0 < N - Nq ? row0 + Nq : N;                            // keys that the last row sees
-    const double mean = causal && row0 + Nq / 2 < N ? row0 + Nq / 2 : N;                    // ... that a row sees on average
-    const double here = 0.74 / 256 * rows_workgroups(B, Hkv, Hq / Hkv, Nq, 2) * mean;       // us per 128 keys
-    const double real = Nq < 256 ? Nq / 256.0 : 1.0;
-    const double alone = 2.0 * most, full = (2.0 + 2.1 * real) / 256 * B * Hq * ((Nq + 255) / 256) * mean;
-    return here <= 0.92 * (alone > full ? alone : full);
-}
-
 // Workgroups that share the keys of a row block: as many as make two to a compute unit, each with a unit of 64 keys for
 // each of its four wavefronts at least.  Not up to 2048 keys: the merge kernel and its launch cost as much
 // there (1 row of 28 heads, 2048 keys: 10.2 us split, 13.0 not; 1024 keys: 8.1 not split), and a row's result stays
@@ -218,7 +198,84 @@ int rows_splits(int B, int Hkv, int G, int Nq, int rb, int N, int keys)
     return ns < 1 ? 1 : (int)ns;
 }
 
+// pasa_fwd4: as many workgroups as are resident at once (three to a compute unit), pieces of 8 tiles at least.  Like above,
+// not up to 2048 keys.
+int fwd4_splits(int B, int Hq, int Nq, int N)
+{
+    const long units = ((long)Nq + 127) / 128 * Hq * B, pieces = ((long)N + 1023) / 1024;
+    if (N <= 2048) return 1;
+    long ns = 3 * kComputeUnits / units;
+    if (ns > pieces) ns = pieces;
+    return ns < 1 ? 1 : ns > kMaxSplit ? kMaxSplit : (int)ns;
+}
+
 size_t split_row_bytes(int d) { return (size_t)d * 4 + 16; }
+
+// The kernel of a call, in how many pieces its keys are swept (as many as the kernel's rule wants and the `room` bytes behind
+// the fixed regions of the workspace hold), and the blocks of 16 rows per workgroup of pasa_rows.
+struct Plan {
+    enum { FWD, FWD4, ROWS } kernel;
+    int nsplit, row_blocks;
+};
+
+int fitting(int ns, size_t rows_all, int d, size_t room)
+{
+    while (ns > 1 && (size_t)ns * rows_all * split_row_bytes(d) > room) --ns;
+    return ns;
+}
+
+// pasa_fwd (256 rows of one head per workgroup) takes every call; pasa_rows (16 or 32 query rows, the keys shared out
+// among the wavefronts) and, at d = 64, pasa_fwd4 (128 rows of one head, four wavefronts) take those of MIXED and DIRECT
+// without counters.  pasa_rows takes every call whose rows of a KV head fit one block (a decoding step reads its keys once
+// and not once per query head); otherwise the measured rates say which is fastest, in us per tile of 128 keys:
+//   pasa_rows  0.74 for 256 workgroups of 32 rows (d = 64: 0.52)
+//   pasa_fwd   2.0 for a workgroup alone, 4.1 for 256 of them (d = 64: 2.55) when all their rows are real, less when fewer are
+//   pasa_fwd4  1.7 / 2.6 / 3.7 for one / two / three workgroups on every compute unit
+// and a fixed 7 us for the first and the last tiles of pasa_fwd and pasa_fwd4 and 6 us for a merge.
+// d = 128, 28 heads on 4, causal, pasa_fwd -> pasa_rows in us: 1 row of 512 / 2048 / 32768
+// keys 14.7 -> 6.2, 37.8 -> 12.6, 78 -> 18.7; 128 rows 16.5 -> 6.8, 40.3 -> 13.3, 522 -> 147; 512 rows of 2048 / 32768 keys 48.0 ->
+// 25.2, 617 -> 318; whole prompts of 512 / 1024 rows 20.3 -> 11.0, 30.0 -> 25.6, of 1500 / 2048 rows 39.1 / 42.2, 50.8 / 71.1 (not
+// taken).  14 sequences, 28 heads on 4, 1 / 20 / 64 rows of 6000 keys 189 -> 34, 189 -> 65, 192 -> 124.
+// d = 64, us of pasa_fwd -> pasa_fwd4: 14 x 5 heads of 1000 / 2000 / 4000 rows, not causal, 50.7 -> 34.8, 134 -> 103, 420 -> 356, causal
+// 26.5 -> 24.1, 70 -> 60, 224 -> 206; 2 x 16 heads of 4000 rows, not causal (a round and a third of pasa_fwd4) 174 / 184 (not
+// taken); one head of 16384 rows, causal, both split: 79 -> 67, and 101 with pasa_rows (not taken).
+Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hkv, int Nq, int row0, int N, int d, int causal,
+               size_t room)
+{
+    const size_t rows_all = (size_t)B * Hq * Nq;
+    Plan p = {Plan::FWD, 1, 0};
+    if (may_split && variant != PASA_STRICT16) p.nsplit = fitting(wanted_splits(B, Hq, Nq, N), rows_all, d, room);
+    if (counters || (variant != PASA_MIXED && variant != PASA_DIRECT)) return p;
+
+    const int G = Hq / Hkv;
+    const long most = causal && row0 < N - Nq ? row0 + Nq : N;                              // keys that the last row sees
+    const long mean = causal && row0 + Nq / 2 < N ? row0 + Nq / 2 : N;                      // ... that a row sees on average
+    Plan r = {Plan::ROWS, 1, rows_blocks(B, Hkv, G, Nq)};
+    if (may_split) r.nsplit = fitting(rows_splits(B, Hkv, G, Nq, r.row_blocks, N, (int)most), rows_all, d, room);
+    if ((long)G * Nq <= 16) return r;
+
+    const double T = kShiftTile, most_t = most / T, mean_t = mean / T, merge = 6.0;
+    const double real = Nq < 256 ? Nq / 256.0 : 1.0;
+    const double rows_us = (d == 64 ? 0.52 : 0.74) / 256 * rows_workgroups(B, Hkv, G, Nq, 2) * mean_t;
+    const double U = (double)B * Hq * ((Nq + 255) / 256);
+    if (d == 128) {
+        const double alone = 2.0 * most_t, full = (2.0 + 2.1 * real) / 256 * U * mean_t;
+        return rows_us <= 0.92 * (alone > full ? alone : full) ? r : p;
+    }
+    // d = 64: equal items (not causal) come in rounds, unequal ones even out
+    const double U_ns = U * p.nsplit, alone = 2.0 * most_t / p.nsplit;
+    const double full = (causal ? U_ns / 256 * mean_t : U_ns <= 256 ? (0.75 + 0.25 * U_ns / 256) * most_t : ceil(U_ns / 256) * most_t) *
+                        (2.0 + 0.55 * real) / p.nsplit;
+    const double fwd_us = 7.0 + (alone > full ? alone : full) + (p.nsplit > 1 ? merge : 0.0);
+    Plan f = {Plan::FWD4, 1, 0};
+    if (may_split) f.nsplit = fitting(fwd4_splits(B, Hq, Nq, N), rows_all, d, room);
+    const double W = (double)B * Hq * ((Nq + 127) / 128) * f.nsplit, rest = fmod(W, 768.0);
+    const double rounds = floor(W / 768) * 3.7 + (rest == 0 ? 0.0 : rest <= 256 ? 1.7 : rest <= 512 ? 2.6 : 3.7);
+    const double alone4 = 1.7 * most_t, full4 = causal ? W / 768 * 3.7 * mean_t : rounds * most_t;
+    const double fwd4_us = 7.0 + (alone4 > full4 ? alone4 : full4) / f.nsplit + (f.nsplit > 1 ? merge : 0.0);
+    if (rows_us + 5.0 <= 0.92 * (fwd_us < fwd4_us ? fwd_us : fwd4_us)) return r;
+    return fwd4_us <= 1.02 * fwd_us ? f : p;
+}
 
 size_t split_region_bytes(int B, int Hq, int N, int d)
 {
@@ -462,20 +519,18 @@ int fwd_chunk_impl(const void* q, void* o, int B, int Hq, int Hkv, int Nq, int r
     p.overflow_group = overflow_group;
     p.gate = gate;
     // key split: as many ways as the rule wants and the bytes behind the fixed regions hold
-    const int keys = p.causal && p.row0 < N - Nq ? p.row0 + Nq : N;      // that some row sees
-    const bool rows = overflow_group == nullptr && pr.overflow_s == nullptr && pr.nonfinite_o == nullptr &&
-                      few_rows(pr.variant, B, Hq, Hkv, Nq, row0, N, causal);
-    const int rb = rows_blocks(B, Hkv, Hq / Hkv, Nq);
-    int ns = (gate != nullptr || pr.variant == PASA_STRICT16) ? 1
-             : rows ? rows_splits(B, Hkv, Hq / Hkv, Nq, rb, N, keys) : wanted_splits(B, Hq, Nq, N);
-    const size_t rows_all = (size_t)B * Hq * Nq, room = workspace_bytes - need;
-    while (ns > 1 && (size_t)ns * rows_all * split_row_bytes(d) > room) --ns;
+    const size_t rows_all = (size_t)B * Hq * Nq;
+    const bool counters = overflow_group != nullptr || pr.overflow_s != nullptr || pr.nonfinite_o != nullptr;
+    const Plan plan = plan_call(pr.variant, counters, gate == nullptr, B, Hq, Hkv, Nq, p.row0, N, d, causal, workspace_bytes - need);
+    const int ns = plan.nsplit;
     p.nsplit = ns;
     char* split_base = static_cast<char*>(workspace) + need;
     p.part_lr = split_base;                                              // [ns][rows][2] doubles
     p.part_o = split_base + (size_t)ns * rows_all * 16;                  // [ns][rows][d] floats
     p.stream = static_cast<hipStream_t>(stream);
-    return (rows ? pasa_launch_rows(p, rb) : pasa_launch_fwd(p)) == hipSuccess ? PASA_OK : PASA_ELAUNCH;
+    const hipError_t e = plan.kernel == Plan::ROWS ? pasa_launch_rows(p, plan.row_blocks)
+                         : plan.kernel == Plan::FWD4 ? pasa_launch_fwd4(p) : pasa_launch_fwd(p);
+    return e == hipSuccess ? PASA_OK : PASA_ELAUNCH;
 }
 
 }  // namespace

@@ -62,6 +62,9 @@ hipError_t pasa_launch_fwd(const PasaLaunch& p);
 // a KV head together where fewer than 16 are given; p.nsplit workgroups share the keys of each.
 hipError_t pasa_launch_rows(const PasaLaunch& p, int row_blocks);
 
+// The same for d = 64 (PASA_K_MIXED and PASA_K_DIRECT, no counters): workgroups of 128 rows of one head.
+hipError_t pasa_launch_fwd4(const PasaLaunch& p);
+
 // Merges the nsplit partial states of rows_all rows that pasa_launch_fwd or pasa_launch_rows has left.
 hipError_t pasa_launch_merge(const void* part_o, const void* part_lr, void* o, size_t rows_all, int d, int nsplit,
                              int io_bf16, unsigned long long* nonfinite_o, hipStream_t stream);

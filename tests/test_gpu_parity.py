@@ -550,6 +550,52 @@ def test_few_rows(Nq, G, N, row0, causal, d, variant):
     assert np.isfinite(o).all() and c["maxabs"] <= 2e-3
 
 
+@pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT])
+@pytest.mark.parametrize("B,H,Nq,N,row0,causal,bf16", [
+    (14, 6, 1000, 1000, 0, False, False),      # eight row tiles, the last of 104 rows; a tile of 104 keys
+    (14, 6, 1000, 1000, 0, False, True),
+    (14, 8, 1100, 1100, 0, True, False),       # nine key tiles: pseudo-averages a second time; heads divide over the XCDs
+    (15, 5, 905, 905, 0, True, False),         # ... and do not; a tile of 9 keys
+    (14, 8, 900, 1200, 350, True, False),      # rows that straddle tiles, positions past the last key
+    (1, 2, 9000, 9000, 0, True, False),        # the keys of a row tile in pieces
+])
+def test_many_rows_d64(B, H, Nq, N, row0, causal, bf16, variant):
+    """d = 64, launches of many row tiles (their workgroups run free of one another): three heads against the oracle."""
+    import torch
+    rng = np.random.default_rng(N + Nq)
+    d, scale, dev = 64, f32(0.125), torch.device("cuda:0")
+    draw = (lambda *s: po.fl(rng.standard_normal(s), "bf16").astype(np.float32)) if bf16 else (lambda *s: rng.standard_normal(s).astype(np.float16))
+    q, k, v = draw(B, H, Nq, d), draw(B, H, N, d), draw(B, H, N, d)
+    k = po.fl(k + 2.0, "bf16").astype(np.float32) if bf16 else (k + 2.0).astype(np.float16)
+    bits = (lambda x: torch.from_numpy(bf16_bits(x).view(np.float16)).to(dev)) if bf16 else (lambda x: torch.from_numpy(x).to(dev))
+    tq, tk, tv = bits(q), bits(k), bits(v)
+    flat = torch.full((tq.numel() + 4096,), float("nan"), dtype=torch.float16, device=dev)
+    to = flat[:tq.numel()].view(tq.shape)
+    wsb = P.pasa_attn_fwd_workspace(B, H, H, N, d)
+    ws = torch.empty(wsb, dtype=torch.uint8, device=dev)
+    kw = dict(variant=variant, io_dtype=P.IO_BF16 if bf16 else P.IO_F16)
+    P.pasa_prepare_kv(tk, tv, B, H, N, d, scale, ws, wsb, **kw)
+    P.pasa_attn_fwd_chunk(tq, to, B, H, H, Nq, row0, N, d, causal, scale, ws, wsb, **kw)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(flat[tq.numel():]).all())
+    o = to.cpu().numpy()
+    if bf16:
+        o = (o.view(np.uint16).astype(np.uint32) << 16).view(np.float32)
+        q, k, v = (po.from_bf16(x) for x in (q, k, v))
+    assert np.isfinite(o).all()
+    for b, h in ((0, 0), (B // 2, H // 2), (B - 1, H - 1)):
+        rows = slice(0, Nq) if Nq < 2000 else slice(Nq - 700, Nq)
+        at = row0 + rows.start
+        rows_of = po.direct_rows if variant == P.DIRECT else po.pasa_rows
+        ref = rows_of(q[b, h][rows], k[b, h], v[b, h], scale, causal, BETA, 128, po.MIXED, at, **({"out_fmt": "bf16"} if bf16 and variant == P.MIXED else {}))
+        c = compare(o[b, h][rows], ref)
+        print(VARIANT_NAME[variant], (b, h), c)
+        if bf16:
+            assert c["maxabs"] <= 8e-3 and c["p999"] <= 4e-3      # one bf16 step of an output in [1, 2) is 7.8e-3
+        else:
+            assert c["maxabs"] <= 2e-3
+
+
 # ------------------------------------------------------------------ key split: few workgroups, many key tiles
 
 @pytest.mark.parametrize("variant", [P.MIXED, P.S16, P.DIRECT])
