@@ -214,7 +214,7 @@ size_t split_row_bytes(int d) { return (size_t)d * 4 + 16; }
 // The kernel of a call, in how many pieces its keys are swept (as many as the kernel's rule wants and the `room` bytes behind
 // the fixed regions of the workspace hold), and the blocks of 16 rows per workgroup of pasa_rows.
 struct Plan {
-    enum { FWD, FWD4, ROWS } kernel;
+    enum { FWD, HALVES, FWD4, ROWS } kernel;
     int nsplit, row_blocks;
 };
 
@@ -224,48 +224,77 @@ int fitting(int ns, size_t rows_all, int d, size_t room)
     return ns;
 }
 
-// pasa_fwd (256 rows of one head per workgroup) takes every call; pasa_rows (16 or 32 query rows, the keys shared out
-// among the wavefronts) and, at d = 64, pasa_fwd4 (128 rows of one head, four wavefronts) take those of MIXED and DIRECT
-// without counters.  pasa_rows takes every call whose rows of a KV head fit one block (a decoding step reads its keys once
-// and not once per query head); otherwise the measured rates say which is fastest, in us per tile of 128 keys:
-//   pasa_rows  0.74 for 256 workgroups of 32 rows (d = 64: 0.52)
-//   pasa_fwd   2.0 for a workgroup alone, 4.1 for 256 of them (d = 64: 2.55) when all their rows are real, less when fewer are
-//   pasa_fwd4  1.7 / 2.6 / 3.7 for one / two / three workgroups on every compute unit
-// and a fixed 7 us for the first and the last tiles of pasa_fwd and pasa_fwd4 and 6 us for a merge.
-// d = 128, 28 heads on 4, causal, pasa_fwd -> pasa_rows in us: 1 row of 512 / 2048 / 32768
-// keys 14.7 -> 6.2, 37.8 -> 12.6, 78 -> 18.7; 128 rows 16.5 -> 6.8, 40.3 -> 13.3, 522 -> 147; 512 rows of 2048 / 32768 keys 48.0 ->
-// 25.2, 617 -> 318; whole prompts of 512 / 1024 rows 20.3 -> 11.0, 30.0 -> 25.6, of 1500 / 2048 rows 39.1 / 42.2, 50.8 / 71.1 (not
-// taken).  14 sequences, 28 heads on 4, 1 / 20 / 64 rows of 6000 keys 189 -> 34, 189 -> 65, 192 -> 124.
-// d = 64, us of pasa_fwd -> pasa_fwd4: 14 x 5 heads of 1000 / 2000 / 4000 rows, not causal, 50.7 -> 34.8, 134 -> 103, 420 -> 356, causal
-// 26.5 -> 24.1, 70 -> 60, 224 -> 206; 2 x 16 heads of 4000 rows, not causal (a round and a third of pasa_fwd4) 174 / 184 (not
-// taken); one head of 16384 rows, causal, both split: 79 -> 67, and 101 with pasa_rows (not taken).
+// pasa_fwd (256 rows of one head per workgroup) takes every call.  Without counters, at d = 128 and not for the variants whose
+// state has no merge (STRICT16) or that only serve comparison (NAIVE16), it can run as workgroups of 128 rows whose two
+// groups of wavefronts take the even and the odd key tiles (HALVES).  MIXED and DIRECT without counters can also go to
+// pasa_rows (16 or 32 query rows, the keys shared out among the wavefronts) and, at d = 64, to pasa_fwd4 (128 rows of one
+// head, four wavefronts).  pasa_rows takes every call whose rows of a KV head fit one block (a decoding step reads its keys
+// once and not once per query head); otherwise the estimate below, from measured rates, says which is fastest.
+//
+// 28 heads on 4, d = 128, us of pasa_fwd / HALVES / pasa_rows.  Causal prompts of 512 / 1024 / 2048 / 3000 rows: 20.2 / 16.1 / 11.0,
+// 29.7 / 21.7 / 25.6, 50.7 / 45.9 / 71, 81 / 88 / -.  128 / 512 / 1024 rows at the end of 16384 keys: 262 / 174 / 75, 309 / 174 / 164, 310 /
+// 234 / 323.  8 heads of 3000 / 4096 rows, not causal: 60.5 (split) / 48.0 / 54.9, 80.0 (split) / 72.8 / 94.8.
+// 14 sequences, 1 / 20 / 64 rows of 6000 keys, pasa_fwd / pasa_rows: 189 / 34, 189 / 65, 192 / 124.
+// d = 64, pasa_fwd / pasa_fwd4: 14 x 5 heads of 1000 / 2000 / 4000 rows, not causal, 50.7 / 34.8, 134 / 103, 420 / 356, causal
+// 26.5 / 24.1, 70 / 60, 224 / 206; 2 x 16 heads of 4000 rows, not causal (a round and a third of pasa_fwd4) 174 / 184;
+// one head of 16384 rows, causal, both split: 79 / 67, and 101 with pasa_rows.
+
+// Equal workgroups, `slots` of them at once, each `fixed` us and `tiles` steps of 2.4 us -- 3.95 when all compute units
+// are busy (power), which takes part of the way with the square of the share that is.
+double equal_rounds(double workgroups, double slots, double fixed, double tiles)
+{
+    const double whole = floor(workgroups / slots), rest = (workgroups - whole * slots) / slots;
+    return whole * (fixed + 3.95 * tiles) + (rest > 0 ? fixed + (2.4 + 1.55 * rest * rest) * tiles : 0.0);
+}
+
+// Causal: `most` steps in the longest workgroup and `mean` on average, longest first.
+double unequal_rounds(double workgroups, double slots, double fixed, double most, double mean)
+{
+    const double chain = fixed + 2.55 * most, work = workgroups / slots * (fixed + 3.55 * mean);
+    return chain > work ? chain + 0.1 * work : work + 0.1 * chain;
+}
+
 Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hkv, int Nq, int row0, int N, int d, int causal,
                size_t room)
 {
     const size_t rows_all = (size_t)B * Hq * Nq;
+    const double merge = 6.0;                                                               // us
     Plan p = {Plan::FWD, 1, 0};
     if (may_split && variant != PASA_STRICT16) p.nsplit = fitting(wanted_splits(B, Hq, Nq, N), rows_all, d, room);
-    if (counters || (variant != PASA_MIXED && variant != PASA_DIRECT)) return p;
+    if (counters || variant == PASA_STRICT16 || variant == PASA_NAIVE16 || (variant == PASA_S16 && d == 64)) return p;
+
+    // keys that the last row sees, and that a row sees on average; in tiles
+    const int most = causal && row0 < N - Nq ? row0 + Nq : N, mean = causal && row0 < N - Nq / 2 ? row0 + Nq / 2 : N;
+    const double most_t = most / (double)kShiftTile, mean_t = mean / (double)kShiftTile;
+    const bool equal = mean_t > 0.8 * most_t;
+    const double U = (double)B * Hq * ((Nq + 255) / 256), real = Nq < 256 ? 0.85 + 0.15 * Nq / 256.0 : 1.0;
 
     const int G = Hq / Hkv;
-    const long most = causal && row0 < N - Nq ? row0 + Nq : N;                              // keys that the last row sees
-    const long mean = causal && row0 + Nq / 2 < N ? row0 + Nq / 2 : N;                      // ... that a row sees on average
     Plan r = {Plan::ROWS, 1, rows_blocks(B, Hkv, G, Nq)};
-    if (may_split) r.nsplit = fitting(rows_splits(B, Hkv, G, Nq, r.row_blocks, N, (int)most), rows_all, d, room);
-    if ((long)G * Nq <= 16) return r;
-
-    const double T = kShiftTile, most_t = most / T, mean_t = mean / T, merge = 6.0;
-    const double real = Nq < 256 ? Nq / 256.0 : 1.0;
-    const double rows_us = (d == 64 ? 0.52 : 0.74) / 256 * rows_workgroups(B, Hkv, G, Nq, 2) * mean_t;
-    const double U = (double)B * Hq * ((Nq + 255) / 256);
-    if (d == 128) {
-        const double alone = 2.0 * most_t, full = (2.0 + 2.1 * real) / 256 * U * mean_t;
-        return rows_us <= 0.92 * (alone > full ? alone : full) ? r : p;
+    double rows_us = INFINITY;
+    if (variant != PASA_S16) {
+        if (may_split) r.nsplit = fitting(rows_splits(B, Hkv, G, Nq, r.row_blocks, N, most), rows_all, d, room);
+        if ((long)G * Nq <= 16) return r;
+        const double uneven = !equal && B * Hq == 1 ? 1.3 : 1.0;     // one causal head: no even ranges for the XCDs
+        const double work = uneven * rows_workgroups(B, Hkv, G, Nq, 2) * (5.5 / 512 + (d == 64 ? 0.52 : 0.68) / 256 * mean_t);
+        const double alone = 0.55 * most_t / r.nsplit;
+        rows_us = 4.0 + (work > alone ? work : alone) + (r.nsplit > 1 ? merge : 0.0);
     }
-    // d = 64: equal items (not causal) come in rounds, unequal ones even out
+    if (d == 128) {
+        const double most_h = ceil(ceil(most_t) / 2), mean_h = mean_t / 2 + 0.25, W = (double)B * Hq * ((Nq + 127) / 128);
+        const double fwd_us = (equal ? equal_rounds(U * p.nsplit, 256, 8.0, most_t / p.nsplit)
+                                     : unequal_rounds(U * p.nsplit, 256, 8.0, most_t / p.nsplit, mean_t / p.nsplit)) * real +
+                              (p.nsplit > 1 ? merge : 0.0);
+        const double halves_us = equal ? equal_rounds(W, 256, 10.0, most_h) : unequal_rounds(W, 256, 10.0, most_h, mean_h);
+        if (rows_us < 0.98 * (fwd_us < halves_us ? fwd_us : halves_us)) return r;
+        if (halves_us < 0.98 * fwd_us) p = {Plan::HALVES, 1, 0};
+        return p;
+    }
+    // d = 64: a step of pasa_fwd takes 2.0 to 2.55 us, one of pasa_fwd4 1.7 / 2.6 / 3.7 with one / two / three workgroups on every
+    // compute unit
     const double U_ns = U * p.nsplit, alone = 2.0 * most_t / p.nsplit;
     const double full = (causal ? U_ns / 256 * mean_t : U_ns <= 256 ? (0.75 + 0.25 * U_ns / 256) * most_t : ceil(U_ns / 256) * most_t) *
-                        (2.0 + 0.55 * real) / p.nsplit;
+                        (2.0 + 0.55 * (real - 0.85) / 0.15) / p.nsplit;
     const double fwd_us = 7.0 + (alone > full ? alone : full) + (p.nsplit > 1 ? merge : 0.0);
     Plan f = {Plan::FWD4, 1, 0};
     if (may_split) f.nsplit = fitting(fwd4_splits(B, Hq, Nq, N), rows_all, d, room);
@@ -273,7 +302,7 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
     const double rounds = floor(W / 768) * 3.7 + (rest == 0 ? 0.0 : rest <= 256 ? 1.7 : rest <= 512 ? 2.6 : 3.7);
     const double alone4 = 1.7 * most_t, full4 = causal ? W / 768 * 3.7 * mean_t : rounds * most_t;
     const double fwd4_us = 7.0 + (alone4 > full4 ? alone4 : full4) / f.nsplit + (f.nsplit > 1 ? merge : 0.0);
-    if (rows_us + 5.0 <= 0.92 * (fwd_us < fwd4_us ? fwd_us : fwd4_us)) return r;
+    if (rows_us <= 0.92 * (fwd_us < fwd4_us ? fwd_us : fwd4_us)) return r;
     return fwd4_us <= 1.02 * fwd_us ? f : p;
 }
 
@@ -524,6 +553,7 @@ int fwd_chunk_impl(const void* q, void* o, int B, int Hq, int Hkv, int Nq, int r
     const Plan plan = plan_call(pr.variant, counters, gate == nullptr, B, Hq, Hkv, Nq, p.row0, N, d, causal, workspace_bytes - need);
     const int ns = plan.nsplit;
     p.nsplit = ns;
+    p.halves = plan.kernel == Plan::HALVES;
     char* split_base = static_cast<char*>(workspace) + need;
     p.part_lr = split_base;                                              // [ns][rows][2] doubles
     p.part_o = split_base + (size_t)ns * rows_all * 16;                  // [ns][rows][d] floats

@@ -33,6 +33,7 @@
 #include <stdint.h>
 #include <atomic>
 #include <type_traits>
+#include <utility>
 
 #include "pasa_device.h"
 #include "pasa_kernels.h"
@@ -275,6 +276,9 @@ __device__ inline float exp_nat_half(h2 v)
     return __builtin_amdgcn_exp2f(x);
 }
 
+template <int... I, class F>
+__device__ inline void for_constants(std::integer_sequence<int, I...>, F f) { (f(std::integral_constant<int, I>{}), ...); }
+
 // A workgroup is 8 wavefronts and owns 256 query rows, 32 per wavefront.  Wavefronts 0-3 (group A) and 4-7
 // (group B) sit pairwise on the four SIMDs and run the same program half a tile apart: time is cut into slots
 // separated by workgroup barriers, and in every slot one group is in its matrix part while the other is in its
@@ -301,7 +305,7 @@ __device__ inline float exp_nat_half(h2 v)
 // the price is that P is Algorithm 1's exp(S' - m') times e^{c_j} rounded once, not exp(S' - m') rounded and then
 // scaled, so outputs agree with a step-by-step evaluation to rounding, not bit for bit.  DIRECT (levels m' + c) and
 // NAIVE16 (plain online softmax: P relative to the running maximum, dc = 0) use the same bookkeeping.
-template <int D, int VAR, bool CAUSAL, bool INSTR>
+template <int D, int VAR, bool CAUSAL, bool INSTR, int KSPL>
 __global__ __launch_bounds__(512, 2)
 void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Float16* __restrict__ o,
               const _Float16* __restrict__ kmean, int Hq, int Hkv, int Nq, int row0, int N,
@@ -325,8 +329,9 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     constexpr int SB_OFF = 4 * (T * D * 2) + KM_BYTES;          // per-wave [16 tiles][32 rows] floats behind it
     constexpr int KT_BYTES = T * D * 2;                         // one K' (or V) tile
     constexpr int TILE_BYTES = 2 * KT_BYTES;                    // workspace stride: K' tile then V tile
-    constexpr int CPW = KT_BYTES / 1024 / 8;                    // 1 KiB copies per wave per K' (or V) tile
-    constexpr int RW = 32, RWG = 256;
+    constexpr int CPW = KT_BYTES / 1024 / 8 * KSPL;             // 1 KiB copies per wave per K' (or V) tile
+    constexpr int RW = 32, RWG = 256 / KSPL;
+    static_assert(KSPL == 1 || !STRICT, "the fp16 state has no merge rule");
 
     extern __shared__ __attribute__((aligned(1024))) char smem[];   // K'[2] then V[2]
 
@@ -334,6 +339,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = wave >> 2;
     const int lq = lane & 31, lh = lane >> 5;
+    const int wcopy = KSPL == 1 ? wave : wave & 3;              // this wave's place among those that copy a tile
+    const int jg = KSPL == 1 ? 0 : grp;                         // first tile of the wave's group, relative to j0
 
     // Work decode.  Workgroups are dispatched in index order and dealt round-robin to the 8 XCDs (index % 8), each
     // with its own L2.  Two goals: (1) every XCD walks its share longest-first -- the query tiles with the most key
@@ -390,8 +397,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
 
     // Query row r of the Nq rows given sits at sequence position row0 + r (causal: it sees keys <= its position).
     const int q0 = qt * RWG;
-    const int qw0 = q0 + wave * RW;
-    const bool wave_valid = qw0 < Nq;      // the wave owns at least one real row
+    const int qw0 = q0 + wcopy * RW;
+    bool wave_valid = qw0 < Nq;            // the wave owns at least one real row
     int last_row_wg = q0 + RWG - 1;
     if (last_row_wg > Nq - 1) last_row_wg = Nq - 1;
     int last_row_w = qw0 + RW - 1;
@@ -428,13 +435,15 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
         if (MSBAR && wave * 1024 < KM_BYTES && g < nblk16)
             copy_1k_to_lds<0>(kmbuf, g * KM_BYTES + wave * 1024, smem + 4 * KT_BYTES + wave * 1024, lane);
     };
+    // K' and V buffer of tile j: by turns, or -- key split within the workgroup -- one of each group's own
+    auto buf = [&](int j) { return KSPL == 1 ? (j & 1) : grp; };
     auto issue_k = [&](int j) {
         const int src = j * TILE_BYTES;
-        char* dst = smem + (j & 1) * KT_BYTES;
+        char* dst = smem + buf(j) * KT_BYTES;
 #pragma unroll
-        for (int i = 0; i < CPW; ++i) copy_1k_to_lds<0>(wsbuf, src + (wave * CPW + i) * 1024, dst + (wave * CPW + i) * 1024, lane);
+        for (int i = 0; i < CPW; ++i) copy_1k_to_lds<0>(wsbuf, src + (wcopy * CPW + i) * 1024, dst + (wcopy * CPW + i) * 1024, lane);
     };
-    issue_k(j0);
+    issue_k(j0 + jg);      // (past the last tile: zeros that are not read)
     issue_kmean(j0 >> 4);
 
     // Q fragments: B operand, lane (query lq, half lh) holds channels 16*ks + 8*lh .. +7
@@ -478,39 +487,24 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
             }
     };
 
-    // The copies of the even global slot sg are K'(sg/2 + 1) and V(sg/2); each wave owns 2*CPW of their 1 KiB pieces.
-    // A wave issues its eight pieces back to back at the start of its vector part (one wave-wide copy each, sharing M0
-    // through immediate offsets).
-    auto issue_piece = [&](int sg, auto piece_c) {
+    // The copies of a slot are K'(jl + KSPL) and V(jl); each wave owns 2*CPW of their 1 KiB pieces.
+    // A wave issues its pieces back to back at the start of its vector part (one wave-wide copy each, four of them sharing
+    // M0 through immediate offsets).
+    auto issue_piece = [&](int jl, auto piece_c) {
         constexpr int piece = decltype(piece_c)::value;       // 0 .. 2*CPW-1: K' pieces first, then V pieces
-        const int jl = sg >> 1;
+        constexpr int off = (piece % CPW) % 4 * 1024, base = (piece % CPW) / 4 * 4096;
         if (piece < CPW) {
-            if (jl + 1 < J_wg)
-                copy_1k_to_lds<(piece % CPW) * 1024>(wsbuf, (jl + 1) * TILE_BYTES + wave * (CPW * 1024),
-                                                     smem + ((jl + 1) & 1) * KT_BYTES + wave * (CPW * 1024), lane);
+            if (jl + KSPL < J_wg)
+                copy_1k_to_lds<off>(wsbuf, (jl + KSPL) * TILE_BYTES + wcopy * (CPW * 1024) + base,
+                                    smem + buf(jl + KSPL) * KT_BYTES + wcopy * (CPW * 1024) + base, lane);
         } else {
             if (jl < J_wg)
-                copy_1k_to_lds<(piece % CPW) * 1024>(wsbuf, jl * TILE_BYTES + KT_BYTES + wave * (CPW * 1024),
-                                                     smem + 2 * KT_BYTES + (jl & 1) * KT_BYTES + wave * (CPW * 1024), lane);
+                copy_1k_to_lds<off>(wsbuf, jl * TILE_BYTES + KT_BYTES + wcopy * (CPW * 1024) + base,
+                                    smem + 2 * KT_BYTES + buf(jl) * KT_BYTES + wcopy * (CPW * 1024) + base, lane);
         }
     };
-    // idx is a constant after unrolling; the switch turns it back into a template argument (an instruction immediate)
-    auto issue_copy = [&](int sg, int idx) {
-        switch (idx) {
-            case 0: issue_piece(sg, std::integral_constant<int, 0>{}); break;
-            case 1: issue_piece(sg, std::integral_constant<int, 1>{}); break;
-            case 2: issue_piece(sg, std::integral_constant<int, 2 % (2 * CPW)>{}); break;
-            case 3: issue_piece(sg, std::integral_constant<int, 3 % (2 * CPW)>{}); break;
-            case 4: issue_piece(sg, std::integral_constant<int, 4 % (2 * CPW)>{}); break;
-            case 5: issue_piece(sg, std::integral_constant<int, 5 % (2 * CPW)>{}); break;
-            case 6: issue_piece(sg, std::integral_constant<int, 6 % (2 * CPW)>{}); break;
-            case 7: issue_piece(sg, std::integral_constant<int, 7 % (2 * CPW)>{}); break;
-            default: break;
-        }
-    };
-    auto issue_slot = [&](int sg) {
-#pragma unroll
-        for (int idx = 0; idx < 2 * CPW; ++idx) issue_copy(sg, idx);
+    auto issue_slot = [&](int jl) {
+        for_constants(std::make_integer_sequence<int, 2 * CPW>{}, [&](auto piece) { issue_piece(jl, piece); });
     };
     auto drain_copies = [&]() { __builtin_amdgcn_s_waitcnt(0x0F70); };   // vmcnt(0)
 
@@ -521,7 +515,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     drain_copies();
     __syncthreads();                       // barrier 0: K'(0) is in LDS
     if (grp == 1) {
-        issue_slot(2 * j0);
+        if (KSPL == 1) issue_slot(j0);
         __syncthreads();                   // barrier 1: group B idles through slot 0
     }
 
@@ -556,7 +550,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     constexpr int NM1 = 4 * KS;      // MFMAs of the first GEMM:  n = kb * KS + ks
     constexpr int NM2 = CB * 8;      // MFMAs of the second GEMM
     auto gemm1 = [&](int jt) {   // S'^T of tile jt: 128 keys x 32 queries; MFMA n: key block n % 4, k-step n / 4
-        const _Float16* lds_k = reinterpret_cast<const _Float16*>(smem + (jt & 1) * KT_BYTES);
+        const _Float16* lds_k = reinterpret_cast<const _Float16*>(smem + buf(jt) * KT_BYTES);
         auto frag = [&](int n) { return *reinterpret_cast<const h8*>(lds_k + ((2 * (n / 4) + lh) * T + 32 * (n % 4) + lq) * 8); };
         h8 a[PF];
 #pragma unroll
@@ -575,7 +569,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
         }
     };
     auto gemm2 = [&](int jt) {   // (P V)^T of tile jt: D channels x 32 queries; runs during M(jt+1); MFMA n: channel block n % CB, k-step n / CB
-        const _Float16* lds_v = reinterpret_cast<const _Float16*>(smem + 2 * KT_BYTES + (jt & 1) * KT_BYTES);
+        const _Float16* lds_v = reinterpret_cast<const _Float16*>(smem + 2 * KT_BYTES + buf(jt) * KT_BYTES);
         auto frag = [&](int n) { return *reinterpret_cast<const h8*>(lds_v + ((2 * (n / CB) + lh) * D + 32 * (n % CB) + lq) * 8); };
         h8 a[PF];
 #pragma unroll
@@ -613,14 +607,16 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
         }
     };
 
-    for (int j = j0; j <= J_wg; ++j) {
+    // tiles of this wave, taken or not: the same number of slots for both groups
+    const int j_end = KSPL == 1 ? J_wg : j0 + (J_wg - j0 + 1) / 2 * 2 + jg;
+    for (int j = j0 + jg; j <= j_end; j += KSPL) {
         // =========================== matrix part M(j) ===========================
-        const bool do_g2 = (j > j0 && j - 1 < J_w), do_g1 = (j < J_w);
+        const bool do_g2 = (j > j0 + jg && j - KSPL < J_w), do_g1 = (j < J_w);
         const bool tail = (tail_keys != 0) && (j == ntile - 1); // ragged last tile: padding keys are masked
         const bool diag = (CAUSAL && (j * T + T - 1 > pos_w0)) || tail;   // tile j needs the mask for this wave
         __builtin_amdgcn_s_setprio(1);
         // ---- pseudo-averages of the next 16 tiles: rows of A are the high and low parts of the tiles' mean keys ----
-        if (MSBAR && ((j & 15) == 0 || j == j0) && do_g1) {
+        if (MSBAR && ((j & 15) == jg || j == j0 + jg) && do_g1) {
             const _Float16* lds_km = reinterpret_cast<const _Float16*>(smem + 4 * KT_BYTES);
             f16v acc = (f16v)0.f;
 #pragma unroll
@@ -638,21 +634,21 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
             }
         }
         // ---- pending product of tile j-1 ----
-        if (do_g2) gemm2(j - 1);
+        if (do_g2) gemm2(j - KSPL);
         // ---- S'(j) ----
         if (do_g1) gemm1(j);
         __builtin_amdgcn_s_setprio(0);
-        if (grp == 1) drain_copies();
+        if (KSPL == 1 && grp == 1) drain_copies();
         __syncthreads();
         // This wave's share of the tile copies first: they have the whole vector part to land (issued later, among the
         // exponentials, their latency showed at the drain before the next barrier: 3.8 % of the kernel's cycles).
-        issue_slot(grp ? 2 * j + 2 : 2 * j);
-        if (MSBAR && (j & 15) == 8) issue_kmean((j >> 4) + 1);   // read from M(16 * ((j >> 4) + 1)) on, free since M(j - 8)
+        issue_slot(KSPL == 1 && grp ? j + 1 : j);
+        if (MSBAR && (j & 15) == 8 + jg) issue_kmean((j >> 4) + 1);   // read from M(16 * ((j >> 4) + 1)) on, free since M(j - 8)
         PASA_FENCE();
 
         // =========================== vector part V(j) ===========================
         if (j < J_w) {
-            const bool first = (j == j0);
+            const bool first = (j == j0 + jg);
             if (STRICT && do_g2) fold16(j - 1);      // O <- fp16(e^{dm_j} PV) + fp16(e^{dm_{j-1}} O) for the product of tile j-1
             // ---- S' as stored: fp32, or rounded to fp16 ----
             // STRICT16 keeps the rounded scores packed two per register and works on them with packed fp16
@@ -805,7 +801,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                 // the end) so that it stays in one block with the exponentials.
                 // F is only a reference level (it cancels between the two correction terms), so Eq. (15)'s division by
                 // j is a multiplication by the hardware's reciprocal of j here
-                const float jm1 = (float)(j - j0), rj = __builtin_amdgcn_rcpf((float)(j - j0 + 1));
+                const int seen = KSPL == 1 ? j - j0 : (j - j0) >> 1;
+                const float jm1 = (float)seen, rj = __builtin_amdgcn_rcpf((float)(seen + 1));
                 const float Fn = (jm1 * F + sbar) * rj;
                 const float dpp = inva * (F - Fn);
                 const float dpc = inva * (sbar - Fn);
@@ -878,23 +875,64 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                 l = first ? lsum : l_keep ? l : ln_all;
             }
         }
-        if (grp == 0) drain_copies();
+        if (KSPL == 2 || grp == 0) drain_copies();
         __syncthreads();
     }
     if (grp == 0) __syncthreads();         // group B's last barrier
 
     if (LSUM_MFMA) l = Lacc[0];            // every row of the block is the sum
+    // level of the stored output: running maximum in its frame, the frame's offset, the stored scale (exact in fp64)
+    bool none = !(J_w > j0 + jg) || l == 0.f;
+    double level = none ? -__builtin_inf() : (double)m + (double)inva * (double)F + (double)Lc;
+    // ---------------- key split within the workgroup: group B's state joins group A's ----------------
+    if (KSPL == 2) {
+        __syncthreads();                   // the tiles have been read
+        static_assert(KSPL == 1 || 4 * CB * 4 * 64 * 16 <= 2 * KT_BYTES, "the exchange fits the K' tiles");
+        float4* xo = reinterpret_cast<float4*>(smem) + (wave & 3) * (CB * 4 * 64) + lane;
+        double* xr = reinterpret_cast<double*>(smem + 2 * KT_BYTES) + (wave & 3) * 64 + lane;
+        float* xl = reinterpret_cast<float*>(smem + 2 * KT_BYTES + 2048) + (wave & 3) * 64 + lane;
+        if (grp == 1) {
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int gq = 0; gq < 4; ++gq)
+                    xo[(cb * 4 + gq) * 64] = float4{O[cb][4 * gq], O[cb][4 * gq + 1], O[cb][4 * gq + 2], O[cb][4 * gq + 3]};
+            *xr = level;
+            *xl = none ? 0.f : l;
+        }
+        __syncthreads();
+        if (grp == 0) {
+            const double lev_b = *xr;
+            const double top = __builtin_fmax(level, lev_b);
+            // a state without keys weighs nothing, whatever its level; NaN stays NaN
+            const float wa = none ? 0.f : __builtin_amdgcn_exp2f((float)(level - top) * LOG2E);
+            const float wb = lev_b == -__builtin_inf() ? 0.f : __builtin_amdgcn_exp2f((float)(lev_b - top) * LOG2E);
+            l = (none ? 0.f : l * wa) + *xl * wb;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int gq = 0; gq < 4; ++gq) {
+                    const float4 x = xo[(cb * 4 + gq) * 64];
+                    O[cb][4 * gq] = O[cb][4 * gq] * wa + x.x * wb;
+                    O[cb][4 * gq + 1] = O[cb][4 * gq + 1] * wa + x.y * wb;
+                    O[cb][4 * gq + 2] = O[cb][4 * gq + 2] * wa + x.z * wb;
+                    O[cb][4 * gq + 3] = O[cb][4 * gq + 3] * wa + x.w * wb;
+                }
+            level = top;
+            none = l == 0.f;
+        } else {
+            wave_valid = false;
+        }
+    }
     // ---------------- key split: leave the row state for the merge ----------------
     if (!STRICT && part_o != nullptr) {
         if (wave_valid) {
             const size_t rows_all = (size_t)(gridDim.x / nsplit) / nqt * Nq;                     // B * Hq * Nq
             const size_t grow = (size_t)(b * Hq + hq) * Nq + row;                                // global row index
-            // level of the stored output: running maximum in its frame, the frame's offset, the stored scale (exact in fp64)
-            const bool none = !(J_w > j0) || !(l > 0.f);
             if (row_valid && lh == 0) {
                 part_lr[((size_t)split * rows_all + grow) * 2] = none ? 0.0 : (double)l;
                 part_lr[((size_t)split * rows_all + grow) * 2 + 1] =
-                    none ? -__builtin_inf() : (double)m + (double)inva * (double)F + (double)Lc;
+                    none ? -__builtin_inf() : l == l ? level : (double)l;
             }
             float* pbase = part_o + ((size_t)split * rows_all + grow) * D;
             if (row_valid && !none) {
@@ -954,15 +992,15 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     }
 }
 
-template <int D, int VAR, bool CAUSAL, bool INSTR>
+template <int D, int VAR, bool CAUSAL, bool INSTR, int KSPL = 1>
 hipError_t launch_fwd(const PasaLaunch& p)
 {
-    constexpr int RWG = 256;
+    constexpr int RWG = 256 / KSPL;
     constexpr int LDS_BYTES = 4 * (T * D * 2) + ((VAR == PASA_K_MIXED || VAR == PASA_K_DIRECT) ? 64 * D + 8 * 2048 : 0);
     const int nqt = (p.Nq + RWG - 1) / RWG;
     const int nsplit = (VAR == PASA_K_STRICT16 || p.nsplit < 1) ? 1 : p.nsplit;   // fp16 state has no merge rule
     const dim3 grid((unsigned)(nqt * p.Hq * p.B * nsplit));
-    auto kern = pasa_fwd<D, VAR, CAUSAL, INSTR>;
+    auto kern = pasa_fwd<D, VAR, CAUSAL, INSTR, KSPL>;
     // the dynamic LDS limit of this instantiation is raised once per device, not on every launch
     static std::atomic<unsigned long long> lds_limit_set{0ull};
     int dev = 0;
@@ -987,6 +1025,9 @@ template <int D, int VAR>
 hipError_t launch_fwd_cv(const PasaLaunch& p)
 {
     const bool instr = p.overflow_s != nullptr || p.nonfinite_o != nullptr;
+    if constexpr (D == 128 && VAR != PASA_K_STRICT16 && VAR != PASA_K_NAIVE16) {
+        if (p.halves && !instr) return p.causal ? launch_fwd<D, VAR, true, false, 2>(p) : launch_fwd<D, VAR, false, false, 2>(p);
+    }
     if (p.causal) return instr ? launch_fwd<D, VAR, true, true>(p) : launch_fwd<D, VAR, true, false>(p);
     return instr ? launch_fwd<D, VAR, false, true>(p) : launch_fwd<D, VAR, false, false>(p);
 }

@@ -112,8 +112,9 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
     // Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of its own: every XCD gets a contiguous range of the
     // work, in which the row blocks that read the same keys follow one another.  14 x 28 heads on 4, 64 rows of
     // 6000 keys: 124 us; with neighbours on different XCDs, where every L2 fetches every key, 241 us
+    // Not for a single causal list, whose last range is the longest (one head of 16384 rows 173 -> 123 us).
     int idx = blockIdx.x;
-    {
+    if (!causal || row0 >= Nq || (int)gridDim.x != nblk * nsplit) {
         const int x = idx & 7, whole = gridDim.x >> 3, rest = gridDim.x & 7;
         idx = x * whole + (x < rest ? x : rest) + (idx >> 3);
     }

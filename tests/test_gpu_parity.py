@@ -596,6 +596,34 @@ def test_many_rows_d64(B, H, Nq, N, row0, causal, bf16, variant):
             assert c["maxabs"] <= 2e-3
 
 
+@pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT, P.S16])
+@pytest.mark.parametrize("Nq,N,row0,causal", [
+    (1024, 1024, 0, True),       # eight key tiles; the first row tile has none for the second group
+    (900, 900, 0, False),        # a last row tile of 4 rows; an odd number of key tiles, the last of 4 keys
+    (1000, 2200, 900, True),     # pseudo-averages of a second block of sixteen; rows that straddle tiles
+    (257, 257, 0, True),
+])
+def test_workgroups_of_two_halves(Nq, N, row0, causal, variant):
+    """d = 128, 28 heads on 4: launches of one to two rounds, in which the two groups of wavefronts of a workgroup take the
+    even and the odd key tiles of its 128 rows and merge.  Three heads against the oracle."""
+    import torch
+    rng = np.random.default_rng(N + Nq)
+    Hq, Hkv, d, dev = 28, 4, 128, torch.device("cuda:0")
+    q = rng.standard_normal((1, Hq, Nq, d)).astype(np.float16)
+    k = (rng.standard_normal((1, Hkv, N, d)) + 2).astype(np.float16)
+    v = rng.standard_normal((1, Hkv, N, d)).astype(np.float16)
+    scale = f32(d ** -0.5)
+    o = gpu_attn_chunks(q, k, v, causal, scale, [(0, Nq, row0)], variant=variant)
+    assert np.isfinite(o).all()
+    rows_of = po.direct_rows if variant == P.DIRECT else po.pasa_rows
+    for h in (0, 13, 27):
+        ref = rows_of(q[0, h], k[0, h // 7], v[0, h // 7], scale, causal, BETA, 128, ORACLE_POLICY.get(variant, po.MIXED), row0)
+        c = compare(o[0, h], ref)
+        print(VARIANT_NAME[variant], h, c)
+        # S16: single outputs where S' straddles a rounding boundary at a dominant key (see the file's header)
+        assert (c["maxabs"] <= 2e-3) if variant != P.S16 else (c["p999"] <= 2e-3)
+
+
 # ------------------------------------------------------------------ key split: few workgroups, many key tiles
 
 @pytest.mark.parametrize("variant", [P.MIXED, P.S16, P.DIRECT])
