@@ -57,6 +57,73 @@ __device__ inline _Float16 double_to_half_rn(double x)
     return (_Float16)f;
 }
 
+// The same for eight values.  Rounding twice, fp64 -> fp32 -> fp16, each to nearest, only goes wrong where the fp32 value
+// is the midpoint of two fp16 values (13 last bits 0x1000; below 2^-14, where fp16 is subnormal, at other places): then,
+// three chunks in ten of a wavefront with scaled keys of unit variance, the careful way above for all eight.
+__device__ inline h8 doubles_to_halves_rn(const double (&x)[8])
+{
+    h8 out;
+    unsigned off = 0xffffffffu;
+    float least = 1.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float f = (float)x[e];
+        out[e] = (_Float16)f;
+        const unsigned d = (__float_as_uint(f) ^ 0x1000u) & 0x1fffu;
+        off = d < off ? d : off;
+        least = __builtin_fminf(least, __builtin_fabsf(f));
+    }
+    if (__builtin_amdgcn_ballot_w64(off == 0u || least < 0x1p-14f) != 0ull) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) out[e] = double_to_half_rn(x[e]);
+    }
+    return out;
+}
+
+// Column sums of a wavefront whose lanes hold eight channels each of one or more keys, CH neighbouring lanes a key: by
+// halves between lanes 32 and 16 apart (each keeps the channels of its side), then whole within a row of 16.  Lane l ends
+// up with two channels, 4 (l / 32) + 2 (l / 16 % 2) and the next, of its eight.
+__device__ inline void swap_doubles32(double& a, double& b)
+{
+    uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
+    const auto lo = __builtin_amdgcn_permlane32_swap(x.x, y.x, false, false), hi = __builtin_amdgcn_permlane32_swap(x.y, y.y, false, false);
+    a = __builtin_bit_cast(double, uint2{lo[0], hi[0]});
+    b = __builtin_bit_cast(double, uint2{lo[1], hi[1]});
+}
+__device__ inline void swap_doubles16(double& a, double& b)
+{
+    uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
+    const auto lo = __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false), hi = __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
+    a = __builtin_bit_cast(double, uint2{lo[0], hi[0]});
+    b = __builtin_bit_cast(double, uint2{lo[1], hi[1]});
+}
+template <int ROR>
+__device__ inline double rotated(double x)
+{
+    const uint2 v = __builtin_bit_cast(uint2, x);
+    return __builtin_bit_cast(double, uint2{(unsigned)__builtin_amdgcn_update_dpp(0, (int)v.x, 0x120 + ROR, 0xf, 0xf, false),
+                                            (unsigned)__builtin_amdgcn_update_dpp(0, (int)v.y, 0x120 + ROR, 0xf, 0xf, false)});
+}
+template <int CH>
+__device__ inline void sum_columns(double (&s)[8], double& w0, double& w1)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        swap_doubles32(s[e], s[e + 4]);
+        s[e] += s[e + 4];
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        swap_doubles16(s[e], s[e + 2]);
+        s[e] += s[e + 2];
+        s[e] += rotated<8>(s[e]);
+        s[e] += rotated<4>(s[e]);
+        if (CH == 2) s[e] += rotated<2>(s[e]);
+    }
+    w0 = s[0];
+    w1 = s[1];
+}
+
 // ---------------------------------------------------------------------------------------------
 // Pre-processing kernel.  grid = (B*Hkv*ceil(N/128) tiles, work groups of a tile), 256 threads.
 // plain_out != nullptr: write K' in the plain [.., N, D] layout instead (pasa_shift_keys).
@@ -91,12 +158,24 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
                                                     _Float16* __restrict__ plain_out, _Float16* __restrict__ k0out,
                                                     _Float16* __restrict__ kmean_out,
                                                     int N, int ntile, double beta, double kscale, int shift_mode,
-                                                    int in_bf16, const unsigned long long* gate, int y_off)
+                                                    int in_bf16, const unsigned long long* gate, int tiles, int group, int y_off)
 {
+    // Workgroups are dealt round-robin to the 8 XCDs: blocks of a tile that read parts of the same 128-byte lines of K follow one
+    // another on one XCD and share its L2, neighbouring tiles go to neighbouring XCDs.  `group` blocks of a tile come
+    // together, all of them or the key blocks of all tiles before the value blocks (see the launch).
+    const int per = (tiles + 7) >> 3;                    // tiles of an XCD
+    int pos = blockIdx.x >> 3, part = 0;
+    if (pos >= per * group) {
+        pos -= per * group;
+        part = group;
+    }
+    part += pos % group;
+    const size_t tile = (size_t)(pos / group) * 8 + (blockIdx.x & 7);    // (batch, KV head, key tile)
+    if (tile >= (size_t)tiles) return;
     // adaptive start: nothing overflowed in this (batch, KV head), its shifted pass is not needed
-    if (gate != nullptr && gate[blockIdx.x / ntile] == 0) return;
+    if (gate != nullptr && gate[tile / ntile] == 0) return;
 
-    // A tile's work is cut into 2*NS blocks (blockIdx.y): NS groups of D/NS channels of K (column means are per
+    // A tile's work is cut into 2*NS blocks: NS groups of D/NS channels of K (column means are per
     // channel, so the groups are independent) and NS groups of 128/NS keys of V.  The pass is bound by memory
     // latency and by fp64 arithmetic per thread, not by bandwidth, so it wants many small blocks.
     constexpr int NS = PASA_PREP_SPLIT;
@@ -104,19 +183,17 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
     constexpr int CH = DB / 8;           // 16-byte chunks per key within the group
     constexpr int KL = 256 / CH;         // key lanes
     constexpr int KPT = T / KL;          // keys per thread
-    constexpr int PARTS = 256 / DB;      // second reduction stage: row groups per channel
     constexpr int TB = T / NS;           // keys of V per block
-    constexpr size_t PSUM_BYTES = sizeof(double) * (KL + PARTS + 1) * DB, VS_BYTES = sizeof(_Float16) * TB * (D + 8);
+    constexpr size_t PSUM_BYTES = sizeof(double) * 2 * 4 * DB, VS_BYTES = sizeof(_Float16) * TB * (D + 8);
     __shared__ __attribute__((aligned(16))) char lds_raw[PSUM_BYTES > VS_BYTES ? PSUM_BYTES : VS_BYTES];
 
-    const size_t tile = blockIdx.x;                      // (batch, KV head, key tile)
     const size_t head = tile / ntile;
     const int t = (int)(tile % ntile);
     const int nvalid = (N - t * T) < T ? (N - t * T) : T;    // keys of this tile (< 128 only in a ragged last tile)
     const size_t src_off = (head * (size_t)N + (size_t)t * T) * D;
     const int tid = threadIdx.x;
 
-    const int by = blockIdx.y + y_off;     // y_off = NS: only the value blocks are launched
+    const int by = part + y_off;              // y_off = NS: only the value blocks are launched
     if (by >= NS) {
         // ---- values: keys [n0, n0 + TB) of the tile, all channels ----
         _Float16 (*vs)[D + 8] = reinterpret_cast<_Float16 (*)[D + 8]>(lds_raw);   // +8 halfs: rows 16 bytes apart in bank space
@@ -144,12 +221,12 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
     }
 
     // ---- keys: channels [cg*DB, cg*DB + DB) of the tile, all 128 keys ----
-    double (*psum)[DB] = reinterpret_cast<double (*)[DB]>(lds_raw);              // [KL] partial column sums
-    double (*psum2)[DB] = psum + KL;                                             // [PARTS] second stage
-    double* colv = reinterpret_cast<double*>(psum2 + PARTS);                     // [DB] mean (or sum, or k0) per channel
+    double (*wsum)[4][DB] = reinterpret_cast<double (*)[4][DB]>(lds_raw);        // two sets of the wavefronts' column sums
     const int cg = by;
+    const int wave = tid >> 6, lane = tid & 63;
     const int c8 = tid % CH, kl = tid / CH;
     const int ch0 = cg * DB + 8 * c8;                    // first of this thread's 8 channels
+    const int cw = 8 * c8 + 4 * (lane >> 5) + 2 * ((lane >> 4) & 1);   // first of the two channels it has the wavefront's sums of
     const _Float16* ksrc = k + src_off;
 
     h8 kv[KPT];
@@ -161,60 +238,55 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
 #pragma unroll
         for (int e = 0; e < 8; ++e) s[e] += (double)kv[i][e];   // exact: fp16 values, at most 128 terms
     }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) psum[kl][8 * c8 + e] = s[e];
-    __syncthreads();
-    {   // every partial sum is exact in fp64, so the order of the two stages does not matter
-        const int c = tid % DB, part = tid / DB;
-        double acc = 0;
-        for (int r = part; r < KL; r += PARTS) acc += psum[r][c];
-        psum2[part][c] = acc;
-    }
-    __syncthreads();
-    if (tid < DB) {
-        double tot = 0;
-#pragma unroll
-        for (int r = 0; r < PARTS; ++r) tot += psum2[r][tid];
-        // the tile's own key count, so that Eq. (14) holds for a ragged tile too; the matrix form needs the plain sum
-        double val = shift_mode == PASA_PREP_MATRIX ? tot : tot / (double)nvalid;
-        // direct-bias recovery: the shift vector k0 = fp16(beta * mean) is itself an fp16 vector
-        if (shift_mode == PASA_PREP_DIRECT) {
-            const _Float16 k0h = double_to_half_rn(__dmul_rn(beta, val));
-            val = (double)k0h;
-            k0out[tile * (size_t)D + cg * DB + tid] = k0h;
-            // the main kernel reads the vector from the tile's "high" row of a mean block (below); the "low" row is zero
-            if (kmean_out != nullptr) write_block_rows(kmean_out, head, ntile, t, cg * DB + tid, D, k0h, (_Float16)0);
-        }
-        colv[tid] = val;
+    double w0, w1;
+    sum_columns<CH>(s, w0, w1);
+    if ((lane & 15) < CH) {
+        wsum[0][wave][cw] = w0;
+        wsum[0][wave][cw + 1] = w1;
     }
     __syncthreads();
     double mean[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) mean[e] = colv[8 * c8 + e];
+    for (int e = 0; e < 8; ++e) {                        // every partial sum is exact in fp64: no order matters
+        const double tot = (wsum[0][0][8 * c8 + e] + wsum[0][1][8 * c8 + e]) + (wsum[0][2][8 * c8 + e] + wsum[0][3][8 * c8 + e]);
+        // the tile's own key count, so that Eq. (14) holds for a ragged tile too; the matrix form needs the plain sum
+        double val = shift_mode == PASA_PREP_MATRIX ? tot : nvalid == T ? tot * 0.0078125 : tot / (double)nvalid;
+        if (shift_mode == PASA_PREP_MATRIX) val = __dmul_rn(kscale, val);
+        if (shift_mode == PASA_PREP_MEAN) val = __dmul_rn(beta, val);
+        // direct-bias recovery: the shift vector k0 = fp16(beta * mean) is itself an fp16 vector
+        if (shift_mode == PASA_PREP_DIRECT) {
+            const _Float16 k0h = double_to_half_rn(__dmul_rn(beta, val));
+            val = (double)k0h;
+            if (kl == 0) {
+                k0out[tile * (size_t)D + ch0 + e] = k0h;
+                // the main kernel reads the vector from the tile's "high" row of a mean block (below); the "low" row is zero
+                if (kmean_out != nullptr) write_block_rows(kmean_out, head, ntile, t, ch0 + e, D, k0h, (_Float16)0);
+            }
+        }
+        mean[e] = val;
+    }
     double rs[8] = {0, 0, 0, 0, 0, 0, 0, 0};     // column sums of the ROUNDED K' over this thread's keys (exact in fp64)
 #pragma unroll
     for (int i = 0; i < KPT; ++i) {
         const int n = kl + KL * i;
-        h8 out;
+        double r[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            double r;
-            if (shift_mode == PASA_PREP_DIRECT) {
-                r = __dmul_rn(__dsub_rn((double)kv[i][e], mean[e]), kscale);     // (K - k0) is exact in fp64
-            } else if (shift_mode == PASA_PREP_MATRIX) {
+            if (shift_mode == PASA_PREP_MATRIX) {
                 // K'^T = K^T M with M = a I + b (J - I) entrywise rounded to fp16 (Eq. (10), (11) as a GEMM):
                 // sum_p M[p,q] K[p,c] = (a - b) K[q,c] + b sum_p K[p,c].  Here beta carries (a - b) and kscale
                 // carries b; both products are exact in fp64 and the sum rounds once.
-                r = __dadd_rn(__dmul_rn(beta, (double)kv[i][e]), __dmul_rn(kscale, mean[e]));
+                r[e] = __dadd_rn(__dmul_rn(beta, (double)kv[i][e]), mean[e]);
             } else {
                 // three separately rounded fp64 operations (no contraction): beta*mean, K - that, * kscale
-                const double bm = __dmul_rn(beta, mean[e]);
-                const double df = __dsub_rn((double)kv[i][e], bm);
-                r = __dmul_rn(df, kscale);
+                // (direct-bias recovery: K - k0 is exact)
+                r[e] = __dmul_rn(__dsub_rn((double)kv[i][e], mean[e]), kscale);
             }
-            out[e] = n < nvalid ? double_to_half_rn(r) : (_Float16)0;   // padding keys: exact zeros
-            rs[e] += (double)out[e];
         }
+        h8 out = doubles_to_halves_rn(r);
+        if (n >= nvalid) out = (h8)(_Float16)0;  // padding keys: exact zeros
+#pragma unroll
+        for (int e = 0; e < 8; ++e) rs[e] += (double)out[e];
         if (plain_out != nullptr) {
             if (n < nvalid) *reinterpret_cast<h8*>(plain_out + src_off + (size_t)n * D + ch0) = out;
         } else {
@@ -224,21 +296,14 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
     if (kmean_out == nullptr || shift_mode == PASA_PREP_DIRECT) return;
 
     // ---- mean block: column sum of the rounded K' / 128 (an exact scaling), as an fp16 pair hi + lo ----
-    __syncthreads();                       // psum is reused
-#pragma unroll
-    for (int e = 0; e < 8; ++e) psum[kl][8 * c8 + e] = rs[e];
-    __syncthreads();
-    {
-        const int c = tid % DB, part = tid / DB;
-        double acc = 0;
-        for (int r = part; r < KL; r += PARTS) acc += psum[r][c];
-        psum2[part][c] = acc;
+    sum_columns<CH>(rs, w0, w1);
+    if ((lane & 15) < CH) {
+        wsum[1][wave][cw] = w0;
+        wsum[1][wave][cw + 1] = w1;
     }
     __syncthreads();
     if (tid < DB) {
-        double tot = 0;
-#pragma unroll
-        for (int r = 0; r < PARTS; ++r) tot += psum2[r][tid];
+        const double tot = (wsum[1][0][tid] + wsum[1][1][tid]) + (wsum[1][2][tid] + wsum[1][3][tid]);
         const double m128 = tot * 0.0078125;                 // 2^-7: exact
         // the low part is stored times 2^11 (undone when the two products are added): unscaled it is an fp16
         // subnormal for every mean below 0.125, and the matrix core reads those as zero
@@ -1053,13 +1118,19 @@ hipError_t pasa_launch_prep(const void* k, const void* v, void* ws, void* plain_
 {
     const int ntile = (N + T - 1) / T;
     const int y_off = k == nullptr ? PASA_PREP_SPLIT : 0;     // no keys given: the value blocks alone
-    const dim3 grid((unsigned)((size_t)B * Hkv * ntile), (v != nullptr && k != nullptr ? 2u : 1u) * PASA_PREP_SPLIT);   // y: key channel groups, then value key groups
+    const int parts = (v != nullptr && k != nullptr ? 2 : 1) * PASA_PREP_SPLIT;      // of a tile: key channel groups, then value key groups
+    const int tiles = B * Hkv * ntile;
+    const dim3 grid((unsigned)((tiles + 7) / 8 * 8 * parts));
+    // The key blocks take longer: first where the launch is a few rounds (8 heads of 4096 keys, d = 128, 256 tiles: 8.9 us, mixed
+    // 11.6; 512 tiles 17.6 / 18.8), in longer ones mixed, so that reading, arithmetic and writing overlap (2048 tiles 58.9 /
+    // 55.4; 14 x 5 heads of 9216 keys, d = 64: 82.9 / 80.3; both in plain order 63.5 and 92.5, before that 65.0 and 94.5).
+    const int group = tiles < 1024 ? PASA_PREP_SPLIT : parts;
     if (d == 128)
         hipLaunchKernelGGL(pasa_prep_kv<128>, grid, dim3(256), 0, stream, (const _Float16*)k, (const _Float16*)v,
-                           (_Float16*)ws, (_Float16*)plain_out, (_Float16*)k0out, (_Float16*)kmean_out, N, ntile, beta, kscale, shift_mode, in_bf16, gate, y_off);
+                           (_Float16*)ws, (_Float16*)plain_out, (_Float16*)k0out, (_Float16*)kmean_out, N, ntile, beta, kscale, shift_mode, in_bf16, gate, tiles, group, y_off);
     else
         hipLaunchKernelGGL(pasa_prep_kv<64>, grid, dim3(256), 0, stream, (const _Float16*)k, (const _Float16*)v,
-                           (_Float16*)ws, (_Float16*)plain_out, (_Float16*)k0out, (_Float16*)kmean_out, N, ntile, beta, kscale, shift_mode, in_bf16, gate, y_off);
+                           (_Float16*)ws, (_Float16*)plain_out, (_Float16*)k0out, (_Float16*)kmean_out, N, ntile, beta, kscale, shift_mode, in_bf16, gate, tiles, group, y_off);
     return hipGetLastError();
 }
 
