@@ -4,40 +4,15 @@
 #include <stdint.h>
 #include <type_traits>
 
+#include "pasa_device.h"
 #include "pasa_kernels.h"
 
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-typedef float f2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
-
-#define PASA_FENCE() __builtin_amdgcn_sched_barrier(0)
 
 namespace {
 
-constexpr int T = 128;          // keys per shift tile
 constexpr int U = 64;           // keys per unit of work of one wavefront (half a tile)
-constexpr float LOG2E = 1.4426950408889634f;
 constexpr float CMAX = 8.f;     // P may exceed 1 by at most e^CMAX before a row moves its stored output to a new level
-
-__device__ inline h8 q_from_bf16(u16x8 raw)
-{
-    h8 out;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) out[e] = (_Float16)__uint_as_float((unsigned)raw[e] << 16);
-    return out;
-}
-
-__device__ inline unsigned short bf16_rn(float f)
-{
-    const unsigned u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (unsigned short)((u >> 16) | 0x40u);
-    return (unsigned short)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
-}
 
 __device__ inline h8 load_frag(__amdgpu_buffer_rsrc_t src, int voff, int soff)
 {
@@ -216,7 +191,7 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
         for (int ks = 0; ks < KS; ++ks) {
             if (QLDS && (rb * KS + ks) % NW != wave) continue;      // one fragment for each wavefront
             const h8 raw = *reinterpret_cast<const h8*>(src + 32 * ks);
-            const h8 val = io_bf16 ? q_from_bf16(__builtin_bit_cast(u16x8, raw)) : raw;
+            const h8 val = io_bf16 ? bf16x8_to_h8(__builtin_bit_cast(u16x8, raw)) : raw;
             const h8 qv = real ? val : (h8)(_Float16)0;
             if (QLDS) lds_q[(rb * KS + ks) * 64 + lane] = qv;
             else Qr[QLDS ? 0 : rb][ks] = qv;
@@ -374,7 +349,7 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
             for (int i = 0; i < 4; ++i) {
                 const float x = acc[i] * inv;
                 out[i] = (_Float16)x;
-                outb[i] = bf16_rn(x);
+                outb[i] = f32_to_bf16_rn(x);
             }
             if (io_bf16) *reinterpret_cast<u16x4*>(o + grow * D + c4) = outb;
             else *reinterpret_cast<h4*>(o + grow * D + c4) = out;
@@ -384,37 +359,31 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
 
 // Merge of the key splits of one call: per query row, the splits' stored outputs and sums are brought to the highest of
 // their levels (the log-sum-exp rule on the absolute level a split's stored output refers to: m + Inva * F + Lc in
-// pasa_fwd, R in pasa_rows) and added; then Algorithm 1's final quotient.  D / 8 threads of 8 channels per row, and SL
-// such groups that share the row's splits.
-template <int D, int SL>
+// pasa_fwd, R in pasa_rows and pasa_fwd4) and added; then Algorithm 1's final quotient.  A split that saw none of a row's keys
+// has level -inf and weighs nothing (its output may not be written); NaN stays NaN.
+__device__ inline float merge_weight(double level, double top)
+{
+    return level == -__builtin_inf() ? 0.f : __builtin_amdgcn_exp2f((float)(level - top) * LOG2E);
+}
+
+// Many rows: one thread per 8 channels of a row goes through the splits.
+template <int D>
 __global__ __launch_bounds__(256) void pasa_merge_splits(const float* __restrict__ part_o, const double* __restrict__ part_lr,
                                                          _Float16* __restrict__ o, size_t rows_all, int nsplit, int io_bf16,
                                                          unsigned long long* nonfinite_o)
 {
-    constexpr int TPR = D / 8;                       // threads per row and group
-    constexpr int RPB = 256 / (TPR * SL);            // rows per workgroup
-    __shared__ float lds[SL > 1 ? 256 : 1][9];
-    __shared__ double lds_max[SL > 1 ? RPB : 1][SL];
-    const int tid = threadIdx.x, cl = tid % TPR, sl = (tid / TPR) % SL, rl = tid / (TPR * SL);
-    const size_t row = (size_t)blockIdx.x * RPB + rl;
-    const bool real = row < rows_all;
-    const size_t grow = real ? row : rows_all - 1;
-    const int c0 = cl * 8;
+    constexpr int TPR = D / 8;                       // threads per row
+    const size_t grow = (size_t)blockIdx.x * (256 / TPR) + threadIdx.x / TPR;
+    if (grow >= rows_all) return;
+    const int c0 = (threadIdx.x % TPR) * 8;
     double rmax = -__builtin_inf();
-    for (int s = sl; s < nsplit; s += SL) rmax = __builtin_fmax(rmax, part_lr[((size_t)s * rows_all + grow) * 2 + 1]);
-    if (SL > 1) {
-        if (cl == 0) lds_max[rl][sl] = rmax;
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < SL; ++i) rmax = __builtin_fmax(rmax, lds_max[rl][i]);
-    }
+    for (int s = 0; s < nsplit; ++s) rmax = __builtin_fmax(rmax, part_lr[((size_t)s * rows_all + grow) * 2 + 1]);
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     float lsum = 0.f;
-#pragma unroll 4
-    for (int s = sl; s < nsplit; s += SL) {
+    for (int s = 0; s < nsplit; ++s) {
         const double r = part_lr[((size_t)s * rows_all + grow) * 2 + 1];
-        if (r == -__builtin_inf()) continue;         // this split saw none of the row's keys (its output may not be written)
-        const float wgt = __builtin_amdgcn_exp2f((float)(r - rmax) * LOG2E);
+        if (r == -__builtin_inf()) continue;
+        const float wgt = merge_weight(r, rmax);
         lsum += wgt * (float)part_lr[((size_t)s * rows_all + grow) * 2];
         const f4* src = reinterpret_cast<const f4*>(part_o + ((size_t)s * rows_all + grow) * D + c0);
         const f4 a = src[0], b = src[1];
@@ -424,20 +393,6 @@ __global__ __launch_bounds__(256) void pasa_merge_splits(const float* __restrict
             acc[4 + i] += wgt * b[i];
         }
     }
-    if (SL > 1) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) lds[tid][e] = acc[e];
-        lds[tid][8] = lsum;
-        __syncthreads();
-        if (sl != 0) return;
-#pragma unroll
-        for (int i = 1; i < SL; ++i) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] += lds[tid + i * TPR][e];
-            lsum += lds[tid + i * TPR][8];
-        }
-    }
-    if (!real) return;
     const float inv = 1.0f / lsum;
     h8 out;
     u16x8 outb;
@@ -446,7 +401,7 @@ __global__ __launch_bounds__(256) void pasa_merge_splits(const float* __restrict
     for (int e = 0; e < 8; ++e) {
         const float v32 = acc[e] * inv;
         out[e] = (_Float16)v32;
-        outb[e] = bf16_rn(v32);
+        outb[e] = f32_to_bf16_rn(v32);
         const float fv = io_bf16 ? __uint_as_float((unsigned)outb[e] << 16) : (float)out[e];
         n_bad += (fv != fv || __builtin_fabsf(fv) == __builtin_inff()) ? 1u : 0u;
     }
@@ -455,12 +410,98 @@ __global__ __launch_bounds__(256) void pasa_merge_splits(const float* __restrict
     if (nonfinite_o != nullptr && n_bad) atomicAdd(nonfinite_o, (unsigned long long)n_bad);
 }
 
+// Few rows: one workgroup per row, SL groups of D / 8 threads that take the splits in turn, four at a time with all their
+// loads on the way together; bound by the latency of two rounds through memory and LDS (28 rows of 128 splits: 3.7 us; with
+// one load after another and a serial sum 6.0).
 template <int D, int SL>
+__global__ __launch_bounds__(D / 8 * SL) void pasa_merge_row(const float* __restrict__ part_o, const double* __restrict__ part_lr,
+                                                             _Float16* __restrict__ o, size_t rows_all, int nsplit, int io_bf16,
+                                                             unsigned long long* nonfinite_o)
+{
+    constexpr int TPR = D / 8;
+    __shared__ double lds_r[SL];
+    __shared__ float lds_l[SL];
+    __shared__ __attribute__((aligned(16))) float lds_o[SL][D];
+    const int tid = threadIdx.x, cl = tid % TPR, sl = tid / TPR;
+    const size_t row = blockIdx.x;
+    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    float l = 0.f;
+    double top = -__builtin_inf();                   // of this group's splits so far: what acc and l refer to
+    for (int s0 = sl; s0 < nsplit; s0 += 4 * SL) {
+        double2 lr[4];
+        f4 a[4], b[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const size_t at = (size_t)(s0 + i * SL < nsplit ? s0 + i * SL : s0) * rows_all + row;
+            lr[i] = reinterpret_cast<const double2*>(part_lr)[at];
+            const f4* src = reinterpret_cast<const f4*>(part_o + at * D + 8 * cl);
+            a[i] = src[0];
+            b[i] = src[1];
+        }
+        double t = top;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (s0 + i * SL < nsplit) t = __builtin_fmax(t, lr[i].y);
+        const float keep = merge_weight(top, t);
+        l *= keep;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] *= keep;
+        top = t;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (s0 + i * SL >= nsplit || lr[i].y == -__builtin_inf()) continue;
+            const float w = merge_weight(lr[i].y, t);
+            l += w * (float)lr[i].x;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                acc[e] += w * a[i][e];
+                acc[4 + e] += w * b[i][e];
+            }
+        }
+    }
+    if (cl == 0) {
+        lds_r[sl] = top;
+        lds_l[sl] = l;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; e += 4) *reinterpret_cast<f4*>(&lds_o[sl][8 * cl + e]) = f4{acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
+    __syncthreads();
+    if (tid >= D) return;
+    top = -__builtin_inf();
+#pragma unroll
+    for (int i = 0; i < SL; ++i) top = __builtin_fmax(top, lds_r[i]);
+    float x = 0.f, ls = 0.f;
+#pragma unroll
+    for (int i = 0; i < SL; ++i) {
+        const float w = merge_weight(lds_r[i], top);
+        x += w * lds_o[i][tid];
+        ls += w * lds_l[i];
+    }
+    x *= 1.0f / ls;
+    const _Float16 h = (_Float16)x;
+    const unsigned short hb = f32_to_bf16_rn(x);
+    if (io_bf16) reinterpret_cast<unsigned short*>(o)[row * D + tid] = hb;
+    else o[row * D + tid] = h;
+    const float fv = io_bf16 ? __uint_as_float((unsigned)hb << 16) : (float)h;
+    if (nonfinite_o != nullptr && (fv != fv || __builtin_fabsf(fv) == __builtin_inff())) atomicAdd(nonfinite_o, 1ull);
+}
+
+template <int D>
 void launch_merge(const void* part_o, const void* part_lr, void* o, size_t rows_all, int nsplit, int io_bf16,
                   unsigned long long* nonfinite_o, hipStream_t stream)
 {
-    constexpr int RPB = 256 / (D / 8 * SL);
-    hipLaunchKernelGGL((pasa_merge_splits<D, SL>), dim3((unsigned)((rows_all + RPB - 1) / RPB)), dim3(256), 0, stream,
+    if (nsplit > 2 && rows_all <= 4096) {
+        constexpr int MANY = 32, FEW = 8;
+        if (nsplit > 2 * FEW)
+            hipLaunchKernelGGL((pasa_merge_row<D, MANY>), dim3((unsigned)rows_all), dim3(D / 8 * MANY), 0, stream, (const float*)part_o,
+                               (const double*)part_lr, (_Float16*)o, rows_all, nsplit, io_bf16, nonfinite_o);
+        else
+            hipLaunchKernelGGL((pasa_merge_row<D, 128 / D * FEW>), dim3((unsigned)rows_all), dim3(128 / 8 * FEW), 0, stream, (const float*)part_o,
+                               (const double*)part_lr, (_Float16*)o, rows_all, nsplit, io_bf16, nonfinite_o);
+        return;
+    }
+    constexpr int RPB = 256 / (D / 8);
+    hipLaunchKernelGGL(pasa_merge_splits<D>, dim3((unsigned)((rows_all + RPB - 1) / RPB)), dim3(256), 0, stream,
                        (const float*)part_o, (const double*)part_lr, (_Float16*)o, rows_all, nsplit, io_bf16, nonfinite_o);
 }
 
@@ -487,13 +528,8 @@ hipError_t launch_rows(const PasaLaunch& p)
 hipError_t pasa_launch_merge(const void* part_o, const void* part_lr, void* o, size_t rows_all, int d, int nsplit,
                              int io_bf16, unsigned long long* nonfinite_o, hipStream_t stream)
 {
-    const bool many = rows_all <= 4096 && nsplit > 2;
-    if (d == 128)
-        many ? launch_merge<128, 16>(part_o, part_lr, o, rows_all, nsplit, io_bf16, nonfinite_o, stream)
-             : launch_merge<128, 1>(part_o, part_lr, o, rows_all, nsplit, io_bf16, nonfinite_o, stream);
-    else
-        many ? launch_merge<64, 16>(part_o, part_lr, o, rows_all, nsplit, io_bf16, nonfinite_o, stream)
-             : launch_merge<64, 1>(part_o, part_lr, o, rows_all, nsplit, io_bf16, nonfinite_o, stream);
+    if (d == 128) launch_merge<128>(part_o, part_lr, o, rows_all, nsplit, io_bf16, nonfinite_o, stream);
+    else launch_merge<64>(part_o, part_lr, o, rows_all, nsplit, io_bf16, nonfinite_o, stream);
     return hipGetLastError();
 }
 
