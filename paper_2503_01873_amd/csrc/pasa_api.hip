@@ -226,15 +226,17 @@ int fitting(int ns, size_t rows_all, int d, size_t room)
 
 // pasa_fwd (256 rows of one head per workgroup) takes every call.  Without counters, at d = 128 and not for the variants whose
 // state has no merge (STRICT16) or that only serve comparison (NAIVE16), it can run as workgroups of 128 rows whose two
-// groups of wavefronts take the even and the odd key tiles (HALVES).  MIXED and DIRECT without counters can also go to
-// pasa_rows (16 or 32 query rows, the keys shared out among the wavefronts) and, at d = 64, to pasa_fwd4 (128 rows of one
-// head, four wavefronts).  pasa_rows takes every call whose rows of a KV head fit one block (a decoding step reads its keys
+// groups of wavefronts take the even and the odd key tiles (HALVES).  MIXED, DIRECT and S16 without
+// counters can also go to pasa_rows (16 or 32 query rows, the keys shared out among the wavefronts), MIXED and DIRECT at
+// d = 64 to pasa_fwd4 (128 rows of one head, four wavefronts).  pasa_rows takes every call whose rows of a KV head fit one block (a decoding step reads its keys
 // once and not once per query head); otherwise the estimate below, from measured rates, says which is fastest.
 //
 // 28 heads on 4, d = 128, us of pasa_fwd / HALVES / pasa_rows.  Causal prompts of 512 / 1024 / 2048 / 3000 rows: 20.2 / 16.1 / 11.0,
 // 29.7 / 21.7 / 25.6, 50.7 / 45.9 / 71, 81 / 88 / -.  128 / 512 / 1024 rows at the end of 16384 keys: 262 / 174 / 75, 309 / 174 / 164, 310 /
 // 234 / 323.  8 heads of 3000 / 4096 rows, not causal: 60.5 (split) / 48.0 / 54.9, 80.0 (split) / 72.8 / 94.8.
 // 14 sequences, 1 / 20 / 64 rows of 6000 keys, pasa_fwd / pasa_rows: 189 / 34, 189 / 65, 192 / 124.
+// S16, 28 heads on 4, pasa_fwd / pasa_rows: 1 row of 500 / 6000 / 16000 keys 15.8 / 6.4, 43.9 / 10.6, 47.9 / 12.4; 128 rows 17.3 / 7.7,
+// 114 / 40.1, 290 / 96.8; 16 heads, d = 64, 500 rows of 3000 keys 65.6 / 24.3.
 // d = 64, pasa_fwd / pasa_fwd4: 14 x 5 heads of 1000 / 2000 / 4000 rows, not causal, 50.7 / 34.8, 134 / 103, 420 / 356, causal
 // 26.5 / 24.1, 70 / 60, 224 / 206; 2 x 16 heads of 4000 rows, not causal (a round and a third of pasa_fwd4) 174 / 184;
 // one head of 16384 rows, causal, both split: 79 / 67, and 101 with pasa_rows.
@@ -261,7 +263,8 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
     const double merge = 6.0;                                                               // us
     Plan p = {Plan::FWD, 1, 0};
     if (may_split && variant != PASA_STRICT16) p.nsplit = fitting(wanted_splits(B, Hq, Nq, N), rows_all, d, room);
-    if (counters || variant == PASA_STRICT16 || variant == PASA_NAIVE16 || (variant == PASA_S16 && d == 64)) return p;
+    if (counters || variant == PASA_STRICT16 || variant == PASA_NAIVE16) return p;
+    const bool s16 = variant == PASA_S16;      // its pseudo-average costs pasa_rows a second pass over the keys; blocks of 16 rows only
 
     // keys that the last row sees, and that a row sees on average; in tiles
     const int most = causal && row0 < N - Nq ? row0 + Nq : N, mean = causal && row0 < N - Nq / 2 ? row0 + Nq / 2 : N;
@@ -270,14 +273,14 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
     const double U = (double)B * Hq * ((Nq + 255) / 256), real = Nq < 256 ? 0.85 + 0.15 * Nq / 256.0 : 1.0;
 
     const int G = Hq / Hkv;
-    Plan r = {Plan::ROWS, 1, rows_blocks(B, Hkv, G, Nq)};
-    double rows_us = INFINITY;
-    if (variant != PASA_S16) {
+    Plan r = {Plan::ROWS, 1, s16 ? 1 : rows_blocks(B, Hkv, G, Nq)};
+    double rows_us;
+    {
         if (may_split) r.nsplit = fitting(rows_splits(B, Hkv, G, Nq, r.row_blocks, N, most), rows_all, d, room);
         if ((long)G * Nq <= 16) return r;
         const double uneven = !equal && B * Hq == 1 ? 1.3 : 1.0;     // one causal head: no even ranges for the XCDs
-        const double work = uneven * rows_workgroups(B, Hkv, G, Nq, 2) * (5.5 / 512 + (d == 64 ? 0.52 : 0.68) / 256 * mean_t);
-        const double alone = 0.55 * most_t / r.nsplit;
+        const double work = (!s16 ? 1.0 : d == 64 ? 1.6 : 2.6) * uneven * rows_workgroups(B, Hkv, G, Nq, 2) * (5.5 / 512 + (d == 64 ? 0.52 : 0.68) / 256 * mean_t);
+        const double alone = (s16 ? 0.85 : 0.55) * most_t / r.nsplit;
         rows_us = 4.0 + (work > alone ? work : alone) + (r.nsplit > 1 ? merge : 0.0);
     }
     if (d == 128) {
@@ -292,7 +295,7 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
     }
     // d = 64: a step of pasa_fwd takes 2.0 to 2.55 us, one of pasa_fwd4 1.7 / 2.6 / 3.7 with one / two / three workgroups on every
     // compute unit
-    const double U_ns = U * p.nsplit, alone = 2.0 * most_t / p.nsplit;
+    const double U_ns = U * p.nsplit, alone = (s16 ? 2.5 : 2.0) * most_t / p.nsplit;
     const double full = (causal ? U_ns / 256 * mean_t : U_ns <= 256 ? (0.75 + 0.25 * U_ns / 256) * most_t : ceil(U_ns / 256) * most_t) *
                         (2.0 + 0.55 * (real - 0.85) / 0.15) / p.nsplit;
     const double fwd_us = 7.0 + (alone > full ? alone : full) + (p.nsplit > 1 ? merge : 0.0);
@@ -302,8 +305,8 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
     const double rounds = floor(W / 768) * 3.7 + (rest == 0 ? 0.0 : rest <= 256 ? 1.7 : rest <= 512 ? 2.6 : 3.7);
     const double alone4 = 1.7 * most_t, full4 = causal ? W / 768 * 3.7 * mean_t : rounds * most_t;
     const double fwd4_us = 7.0 + (alone4 > full4 ? alone4 : full4) / f.nsplit + (f.nsplit > 1 ? merge : 0.0);
-    if (rows_us <= 0.92 * (fwd_us < fwd4_us ? fwd_us : fwd4_us)) return r;
-    return fwd4_us <= 1.02 * fwd_us ? f : p;
+    if (rows_us <= 0.92 * (s16 || fwd_us < fwd4_us ? fwd_us : fwd4_us)) return r;
+    return !s16 && fwd4_us <= 1.02 * fwd_us ? f : p;
 }
 
 size_t split_region_bytes(int B, int Hq, int N, int d)

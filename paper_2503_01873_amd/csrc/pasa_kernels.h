@@ -60,7 +60,7 @@ hipError_t pasa_launch_shift_gemm(const void* k, void* ws, void* plain_out, int 
 
 hipError_t pasa_launch_fwd(const PasaLaunch& p);
 
-// The same for few query rows (PASA_K_MIXED and PASA_K_DIRECT, no counters): workgroups of 16 * row_blocks rows (1 or 2), of all the heads of
+// The same for few query rows (PASA_K_MIXED, PASA_K_DIRECT and PASA_K_S16, no counters): workgroups of 16 * row_blocks rows (1 or 2), of all the heads of
 // a KV head together where fewer than 16 are given; p.nsplit workgroups share the keys of each.
 hipError_t pasa_launch_rows(const PasaLaunch& p, int row_blocks);
 

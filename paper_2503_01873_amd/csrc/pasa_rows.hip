@@ -32,7 +32,7 @@ __device__ inline void rows32(float x, float& low, float& high)
     low = __uint_as_float(r[0]);
     high = __uint_as_float(r[1]);
 }
-// largest value over the four lanes l, l^16, l^32, l^48 that share a query row
+// largest value / sum over the four lanes l, l^16, l^32, l^48 that share a query row
 __device__ inline float max_row(float x)
 {
     float a, b;
@@ -40,6 +40,14 @@ __device__ inline float max_row(float x)
     rows32(__builtin_fmaxf(a, b), a, b);
     return __builtin_fmaxf(a, b);
 }
+__device__ inline float sum_row(float x)
+{
+    float a, b;
+    rows16(x, a, b);
+    rows32(a + b, a, b);
+    return a + b;
+}
+
 // One workgroup = NW wavefronts owns 16 * RB rows and a range of the keys in units of 64.  The rows come from lists: with fewer than 16 rows given, the rows of ALL the
 // heads that share a KV head are one list (they are contiguous in q and o), so that a decoding step reads its keys once;
 // otherwise each head is a list, so that a block's rows are neighbours in position.  Every wavefront sweeps units of its
@@ -64,7 +72,7 @@ __device__ inline float max_row(float x)
 // odd rows the low parts), and the level is kept in absolute terms.  (With row sums in lanes and the products for eight
 // tiles at a time shared out by shuffles, 32 rows took twice as long as 16.)  Four wavefronts per workgroup: two workgroups
 // share a compute unit, so that one loads while the other merges (28 heads of 512 rows 16.8 -> 11.7 us against eight).
-template <int D, int RB, int NW>
+template <int D, int RB, int NW, bool S16>
 __global__ __launch_bounds__(64 * NW, 2)
 void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, const _Float16* __restrict__ kmean,
                _Float16* __restrict__ o, int lists, int list_rows, int Nq, int row0, int N, int causal, int nblk, int nsplit,
@@ -173,10 +181,12 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
         for (int cb = 0; cb < CB; ++cb) O[rb][cb] = (f4)0.f;
     }
 
+    // the half tile whose keys A and B take first for unit u
+    auto first_k = [](int u) { return S16 ? u ^ 1 : u; };
     if (u0 < ue) {
-        load_m(u0);
-        load_k(B, u0, 1);
-        load_k(A, u0, 0);
+        if (!S16) load_m(u0);
+        load_k(B, first_k(u0), 1);
+        load_k(A, first_k(u0), 0);
         load_v(C, u0, 0);
     }
     int last[RB];                                // last key that the lane's row sees
@@ -204,15 +214,17 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
             const int t = u >> 1;
             // q . mean of the tile: every lane gets the product with the high part in element 0, with the low part in 1
             f4 M[RB];
+            if (!S16) {
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb) M[rb] = (f4)0.f;
+                for (int rb = 0; rb < RB; ++rb) M[rb] = (f4)0.f;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
+                for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb)
-                    M[rb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Am[ks], Qf(rb, ks), M[rb], 0, 0, 0);
-            PASA_FENCE();
-            if (more) load_m(u + NW);
+                    for (int rb = 0; rb < RB; ++rb)
+                        M[rb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Am[ks], Qf(rb, ks), M[rb], 0, 0, 0);
+                PASA_FENCE();
+                if (more) load_m(u + NW);
+            }
             f4 S[RB][4];
             auto gemm1 = [&](const h8 (&k)[HF], int half, bool clear) {
 #pragma unroll
@@ -229,20 +241,51 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
                 PASA_FENCE();
             };
             PASA_FENCE();
+            // S16: the pseudo-average is the mean of the tile's rounded scores, those of its other half included
+            float sum[RB];
+            auto round_and_add = [&](bool other) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    float x = 0.f;
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            S[rb][b][i] = (float)(_Float16)S[rb][b][i];
+                            x += S[rb][b][i];
+                        }
+                    sum[rb] = other ? x : sum[rb] + x;
+                }
+            };
+            if (S16) {
+                gemm1(B, 1, true);
+                load_k(B, u, 1);
+                PASA_FENCE();
+                gemm1(A, 0, false);
+                load_k(A, u, 0);
+                PASA_FENCE();
+                round_and_add(true);
+            }
             gemm1(B, 1, true);
-            if (more) load_k(B, u + NW, 1);
+            if (more) load_k(B, first_k(u + NW), 1);
             PASA_FENCE();
             gemm1(A, 0, false);
             load_v(A, u, 1);
             PASA_FENCE();
+            if (S16) round_and_add(false);
 
             const int tail = N - t * T;          // keys of this tile, when fewer than 128
             h8 P[RB][2];
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
                 if (rb > 0) PASA_FENCE();
-                float v = M[rb][0] + M[rb][1] * 0.00048828125f;  // low parts are stored times 2^11
-                if (tail_by_count && tail < T) v *= (float)T * (1.0f / (float)tail);
+                float v;
+                if (S16) {
+                    v = sum_row(sum[rb]) * (tail < T ? 1.0f / (float)tail : 1.0f / T);
+                } else {
+                    v = M[rb][0] + M[rb][1] * 0.00048828125f;    // low parts are stored times 2^11
+                    if (tail_by_count && tail < T) v *= (float)T * (1.0f / (float)tail);
+                }
                 if (u * U + U - 1 > first_pos) {
 #pragma unroll
                     for (int b = 0; b < 4; ++b)
@@ -297,7 +340,7 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
             if (more) load_v(C, u + NW, 0);
             PASA_FENCE();
             gemm2(A, 1);
-            if (more) load_k(A, u + NW, 0);
+            if (more) load_k(A, first_k(u + NW), 0);
         };
         int u = u0;
         for (; u + NW < ue; u += NW) unit(u, std::true_type{});
@@ -505,7 +548,7 @@ void launch_merge(const void* part_o, const void* part_lr, void* o, size_t rows_
                        (const float*)part_o, (const double*)part_lr, (_Float16*)o, rows_all, nsplit, io_bf16, nonfinite_o);
 }
 
-template <int D, int RB, int NW>
+template <int D, int RB, int NW, bool S16 = false>
 hipError_t launch_rows(const PasaLaunch& p)
 {
     const int G = p.Hq / p.Hkv, lists = p.Nq < 16 ? 1 : G, list_rows = p.Nq < 16 ? G * p.Nq : p.Nq;
@@ -514,7 +557,7 @@ hipError_t launch_rows(const PasaLaunch& p)
     const int all = (keys + U - 1) / U, units = (all + p.nsplit - 1) / p.nsplit;
     const int nsplit = (all + units - 1) / units;                 // none without keys
     const size_t rows_all = (size_t)p.B * p.Hq * p.Nq;
-    hipLaunchKernelGGL((pasa_rows<D, RB, NW>), dim3((unsigned)((size_t)p.B * p.Hkv * lists * nblk * nsplit)), dim3(64 * NW), 0, p.stream,
+    hipLaunchKernelGGL((pasa_rows<D, RB, NW, S16>), dim3((unsigned)((size_t)p.B * p.Hkv * lists * nblk * nsplit)), dim3(64 * NW), 0, p.stream,
                        (const _Float16*)p.q, (const char*)p.ws, (const _Float16*)p.kmean, (_Float16*)p.o, lists, list_rows, p.Nq, p.row0,
                        p.N, p.causal, nblk, nsplit, units, p.variant == PASA_K_DIRECT ? p.scale : p.inva,
                        p.variant == PASA_K_MIXED ? 1 : 0, p.io_bf16, p.gate, (float*)p.part_o, (double*)p.part_lr, rows_all);
@@ -535,6 +578,7 @@ hipError_t pasa_launch_merge(const void* part_o, const void* part_lr, void* o, s
 
 hipError_t pasa_launch_rows(const PasaLaunch& p, int row_blocks)
 {
+    if (p.variant == PASA_K_S16) return p.d == 128 ? launch_rows<128, 1, 4, true>(p) : launch_rows<64, 1, 4, true>(p);
     if (p.d == 128) return row_blocks == 1 ? launch_rows<128, 1, 4>(p) : launch_rows<128, 2, 4>(p);
     return row_blocks == 1 ? launch_rows<64, 1, 4>(p) : launch_rows<64, 2, 4>(p);
 }

@@ -517,7 +517,7 @@ def test_decoding_against_a_cache(Nq):
 
 # ------------------------------------------------------------------ few query rows: blocks of 16, keys in units of 64
 
-@pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT])
+@pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT, P.S16])
 @pytest.mark.parametrize("Nq,G,N,row0,causal,d", [
     (1, 1, 1, 0, True, 128),            # one row, one key
     (1, 7, 63, 62, True, 64),           # seven heads in one block, one unit that is not full
@@ -544,10 +544,11 @@ def test_few_rows(Nq, G, N, row0, causal, d, variant):
         ref = np.stack([[po.direct_rows(q[b, h], k[b, h // G], v[b, h // G], scale, causal, BETA, 128, po.MIXED, row0)
                          for h in range(Hkv * G)] for b in range(B)])
     else:
-        ref = _rows_ref(q, k, v, scale, causal, 0, Nq, row0)
+        ref = _rows_ref(q, k, v, scale, causal, 0, Nq, row0, policy=ORACLE_POLICY[variant])
     c = compare(o, ref)
     print(VARIANT_NAME[variant], Nq, G, N, row0, c)
-    assert np.isfinite(o).all() and c["maxabs"] <= 2e-3
+    # S16: single outputs where S' straddles a rounding boundary at a dominant key (see the file's header)
+    assert np.isfinite(o).all() and ((c["maxabs"] <= 2e-3) if variant != P.S16 else (c["p999"] <= 2e-3))
 
 
 @pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT])
