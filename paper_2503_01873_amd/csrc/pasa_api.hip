@@ -306,7 +306,7 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
     const double alone4 = 1.7 * most_t, full4 = causal ? W / 768 * 3.7 * mean_t : rounds * most_t;
     const double fwd4_us = 7.0 + (alone4 > full4 ? alone4 : full4) / f.nsplit + (f.nsplit > 1 ? merge : 0.0);
     if (rows_us <= 0.92 * (s16 || fwd_us < fwd4_us ? fwd_us : fwd4_us)) return r;
-    return !s16 && fwd4_us <= 1.02 * fwd_us ? f : p;
+    return !s16 && fwd4_us <= 0.98 * fwd_us ? f : p;
 }
 
 size_t split_region_bytes(int B, int Hq, int N, int d)

@@ -184,7 +184,7 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
     constexpr int KL = 256 / CH;         // key lanes
     constexpr int KPT = T / KL;          // keys per thread
     constexpr int TB = T / NS;           // keys of V per block
-    constexpr size_t PSUM_BYTES = sizeof(double) * 2 * 4 * DB, VS_BYTES = sizeof(_Float16) * TB * (D + 8);
+    constexpr size_t PSUM_BYTES = sizeof(double) * (2 * 4 + 1) * DB, VS_BYTES = sizeof(_Float16) * TB * (D + 8);
     __shared__ __attribute__((aligned(16))) char lds_raw[PSUM_BYTES > VS_BYTES ? PSUM_BYTES : VS_BYTES];
 
     const size_t head = tile / ntile;
@@ -222,6 +222,7 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
 
     // ---- keys: channels [cg*DB, cg*DB + DB) of the tile, all 128 keys ----
     double (*wsum)[4][DB] = reinterpret_cast<double (*)[4][DB]>(lds_raw);        // two sets of the wavefronts' column sums
+    double* ragged = reinterpret_cast<double*>(wsum + 2);                        // [DB] means of a ragged tile
     const int cg = by;
     const int wave = tid >> 6, lane = tid & 63;
     const int c8 = tid % CH, kl = tid / CH;
@@ -245,12 +246,17 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
         wsum[0][wave][cw + 1] = w1;
     }
     __syncthreads();
+    // the tile's own key count, so that Eq. (14) holds for a ragged tile too; the matrix form needs the plain sum
+    const bool divide = nvalid != T && shift_mode != PASA_PREP_MATRIX;
+    if (divide) {                                        // one division a channel (a whole tile's is an exact scaling)
+        if (tid < DB) ragged[tid] = ((wsum[0][0][tid] + wsum[0][1][tid]) + (wsum[0][2][tid] + wsum[0][3][tid])) / (double)nvalid;
+        __syncthreads();
+    }
     double mean[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {                        // every partial sum is exact in fp64: no order matters
         const double tot = (wsum[0][0][8 * c8 + e] + wsum[0][1][8 * c8 + e]) + (wsum[0][2][8 * c8 + e] + wsum[0][3][8 * c8 + e]);
-        // the tile's own key count, so that Eq. (14) holds for a ragged tile too; the matrix form needs the plain sum
-        double val = shift_mode == PASA_PREP_MATRIX ? tot : nvalid == T ? tot * 0.0078125 : tot / (double)nvalid;
+        double val = shift_mode == PASA_PREP_MATRIX ? tot : divide ? ragged[8 * c8 + e] : tot * 0.0078125;
         if (shift_mode == PASA_PREP_MATRIX) val = __dmul_rn(kscale, val);
         if (shift_mode == PASA_PREP_MEAN) val = __dmul_rn(beta, val);
         // direct-bias recovery: the shift vector k0 = fp16(beta * mean) is itself an fp16 vector
