@@ -106,9 +106,8 @@ int pasa_attn_fwd(const void* q, const void* k, const void* v, void* o,
  * group of 16 key tiles the per-channel means of the rounded K' of those tiles as fp16 pairs (64*d bytes per group,
  * B*Hkv*ceil(ceil(N/128)/16) groups; PASA_MIXED takes the pseudo-average of Eq. (14) as the query times that mean,
  * Eq. (12); for PASA_DIRECT the same blocks hold the tiles' shift vectors k0 instead); these regions together are pasa_attn_fwd_workspace_min().  Last comes the
- * region of the key split: when a call would launch fewer than 192 workgroups (one per 256 query rows of a head) on the
- * 256 compute units, the key tiles of every workgroup are divided among up to 16 workgroups in pieces of 16 tiles,
- * each leaves per query row its unnormalised output (d floats) and two doubles (running sum, level), and a second
+ * region of the key split: when a call would leave compute units idle, the keys of every workgroup are divided among
+ * several workgroups, each of which leaves per query row its unnormalised output (d floats) and two doubles (running sum, level), and a second
  * kernel merges them with the log-sum-exp rule (the same algebra that lets the method run as ring attention, section
  * 2.2).  The region is sized for a call with N query rows (at least 1 MiB, so that short query chunks can split);
  * a call given less than that splits fewer ways or not at all, and one given less than pasa_attn_fwd_workspace_min()
@@ -160,8 +159,9 @@ int pasa_attn_fwd_prepared(const void* q, void* o, int B, int Hq, int Hkv, int N
  * n <= row0 + r (row0 = N - Nq aligns the last query with the last key; positions past N - 1 see all keys);
  * with causal == 0 every row sees all N keys and row0 is ignored.  Covers cross-attention, prefill in chunks and
  * decoding against a cache.  pasa_attn_fwd_prepared(..., N, ...) is the case Nq = N, row0 = 0.  A row's result
- * does not depend on the other rows of its chunk: splitting a sequence at multiples of 32 rows gives bit-identical
- * output, any other split the same up to the fp32 summation order of the pseudo-average.  PASA_EINVAL for
+ * does not depend on the other rows of its chunk, up to rounding: launches of different sizes may run on different
+ * kernels or sweep the keys in different pieces, which moves the level that P is rounded at.  Calls that take the same
+ * kernel without a key split give bit-identical rows.  PASA_EINVAL for
  * Nq <= 0 or row0 < 0; otherwise the rules of pasa_attn_fwd_prepared. */
 int pasa_attn_fwd_chunk(const void* q, void* o, int B, int Hq, int Hkv, int Nq, int row0, int N, int d, int causal,
                         float scale, const pasa_opts* opts, void* workspace, size_t workspace_bytes, void* stream);

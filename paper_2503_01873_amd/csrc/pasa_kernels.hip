@@ -376,6 +376,13 @@ __device__ inline void for_constants(std::integer_sequence<int, I...>, F f) { (f
 // the price is that P is Algorithm 1's exp(S' - m') times e^{c_j} rounded once, not exp(S' - m') rounded and then
 // scaled, so outputs agree with a step-by-step evaluation to rounding, not bit for bit.  DIRECT (levels m' + c) and
 // NAIVE16 (plain online softmax: P relative to the running maximum, dc = 0) use the same bookkeeping.
+//
+// KSPL = 2: the workgroup owns 128 rows; both groups of wavefronts hold all of them, group A takes the even key tiles and
+// group B the odd ones, each through a K' and a V buffer of its own, and B's state joins A's through LDS at the end (the rule of
+// the key split).  A step (two slots) passes two tiles, so a workgroup's chain is half as long and there are twice as many
+// workgroups: faster where the longest chain bounds the launch (28 heads on 4, causal, 1024 / 2048 rows 29.7 -> 21.7, 50.9 -> 46.8
+// us), slower where the chip is full (8192 rows 446 -> 491 us: every tile is copied twice as often, and the 8-10 us that a
+// workgroup takes to fill and drain come twice).
 template <int D, int VAR, bool CAUSAL, bool INSTR, int KSPL>
 __global__ __launch_bounds__(512, 2)
 void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Float16* __restrict__ o,
