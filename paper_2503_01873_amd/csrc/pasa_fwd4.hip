@@ -8,6 +8,15 @@
 
 namespace {
 
+// A barrier that waits for no counter (the copies in flight are counted by hand) and that no memory access is moved across:
+// the LDS reads before it have been used by then, those after it come after it.
+__device__ inline void workgroup_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 constexpr float CMAX = 8.f;     // P may exceed 1 by at most e^CMAX before a row moves its stored output to a new level
 
 // One workgroup = four wavefronts = 128 query rows of one head, 32 rows per wavefront; three workgroups share a compute
@@ -146,7 +155,7 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
             }
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): this wavefront's share of K'(j)
-        __builtin_amdgcn_s_barrier();            // K'(j) is there; V(j-1) and K'(j-1) have been read
+        workgroup_barrier();                     // K'(j) is there; V(j-1) and K'(j-1) have been read
         PASA_FENCE();
         issue_v(j);
         issue_k(j + 1);                          // past the last tile: zeros, or a tile that is not used
@@ -217,7 +226,7 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
         }
         PASA_FENCE();
         __builtin_amdgcn_s_waitcnt(0x0F70 | CPW);        // this wavefront's share of V(j); that of K'(j + 1) may be on its way
-        __builtin_amdgcn_s_barrier();
+        workgroup_barrier();
         PASA_FENCE();
         if (j < J_w) {
             const _Float16* lds_v = reinterpret_cast<const _Float16*>(smem + V_OFF);
