@@ -95,7 +95,8 @@ __device__ inline float add_pair(h2 v, float acc)
 // OFF is an immediate added to both addresses, so a wave's consecutive pieces share one M0 value.
 // The buffer form (buffer_load ... lds) is used rather than global_load_lds: the compiler treats the latter as a flat
 // access that may touch LDS and from then on drains the LDS counter to zero before every use of an LDS fragment,
-// which defeats the fragment prefetch of the GEMM loops.  A buffer load out of range returns zeros instead of faulting.
+// which defeats the fragment prefetch of the GEMM loops.  soff has to lie within the buffer: the bounds check covers the
+// lane's offset and the immediate, not the scalar offset.
 template <int OFF>
 __device__ inline void copy_1k_to_lds(__amdgpu_buffer_rsrc_t src, int soff, char* ldst, int lane)
 {

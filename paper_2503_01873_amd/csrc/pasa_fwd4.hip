@@ -105,8 +105,8 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
 
     const __amdgpu_buffer_rsrc_t wsbuf = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<char*>(ws) + grp * (size_t)ntile * TILE_BYTES, 0, ntile * TILE_BYTES, 0x00020000);
-    auto issue_k = [&](int j) {
-        char* dst = smem + (j & 1) * KT_BYTES + wave * (CPW * 1024);
+    auto issue_k = [&](int j, int buf) {
+        char* dst = smem + buf * KT_BYTES + wave * (CPW * 1024);
         const int src = j * TILE_BYTES + wave * (CPW * 1024);
 #pragma unroll
         for (int i = 0; i < CPW; ++i) copy_1k_to_lds<0>(wsbuf, src + i * 1024, dst + i * 1024, lane);
@@ -125,7 +125,7 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) O[cb] = (f16v)0.f;
     if (j0 < J_wg) {
-        issue_k(j0);
+        issue_k(j0, j0 & 1);
         const _Float16* qsrc = q + (head * Nq + (row_valid ? row : 0)) * D + 8 * lh;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -158,7 +158,9 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
         workgroup_barrier();                     // K'(j) is there; V(j-1) and K'(j-1) have been read
         PASA_FENCE();
         issue_v(j);
-        issue_k(j + 1);                          // past the last tile: zeros, or a tile that is not used
+        // Beside the last tile it is fetched once more, into the buffer that nothing reads again: the tile's offset is the
+        // scalar one, which the buffer's bounds check leaves out, and the number of copies in flight stays the same.
+        issue_k(j + 1 < J_wg ? j + 1 : j, (j + 1) & 1);
         PASA_FENCE();
         h8 Pf[8];
         if (j < J_w) {

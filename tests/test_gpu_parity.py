@@ -597,6 +597,30 @@ def test_many_rows_d64(B, H, Nq, N, row0, causal, bf16, variant):
             assert c["maxabs"] <= 2e-3
 
 
+@pytest.mark.parametrize("N,causal", [(1000, False), (1024, False), (1024, True)])
+def test_many_rows_d64_in_the_smallest_workspace(N, causal):
+    """d = 64, many query heads on one KV head: the key tiles end a few KB before the workspace does when the caller gives
+    no more than it must.  Same bits as with the full workspace, and the oracle's values."""
+    import torch
+    rng = np.random.default_rng(N)
+    H, d, scale, dev = 70, 64, f32(0.125), torch.device("cuda:0")
+    q = rng.standard_normal((1, H, N, d)).astype(np.float16)
+    k = (rng.standard_normal((1, 1, N, d)) + 2).astype(np.float16)
+    v = rng.standard_normal((1, 1, N, d)).astype(np.float16)
+    tq, tk, tv = (torch.from_numpy(x).to(dev) for x in (q, k, v))
+    outs = []
+    for size in (P.pasa_attn_fwd_workspace_min(1, 1, N, d), P.pasa_attn_fwd_workspace(1, H, 1, N, d)):
+        ws = torch.empty(size, dtype=torch.uint8, device=dev)
+        to = torch.full_like(tq, float("nan"))
+        P.pasa_attn_fwd_ex(tq, tk, tv, to, 1, H, 1, N, d, causal, scale, ws, size)
+        torch.cuda.synchronize()
+        outs.append(to.cpu().numpy())
+    assert np.array_equal(outs[0].view(np.uint16), outs[1].view(np.uint16))
+    for h in (0, 69):
+        ref = po.pasa_rows(q[0, h], k[0, 0], v[0, 0], scale, causal, BETA, 128, po.MIXED)
+        assert compare(outs[0][0, h], ref)["maxabs"] <= 2e-3
+
+
 @pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT, P.S16])
 @pytest.mark.parametrize("Nq,N,row0,causal", [
     (1024, 1024, 0, True),       # eight key tiles; the first row tile has none for the second group
