@@ -521,7 +521,9 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
 #pragma unroll
         for (int i = 0; i < CPW; ++i) copy_1k_to_lds<0>(wsbuf, src + (wcopy * CPW + i) * 1024, dst + (wcopy * CPW + i) * 1024, lane);
     };
-    issue_k(j0 + jg);      // (past the last tile: zeros that are not read)
+    // not past the last tile (a split with no keys, the second group of a single tile): the tile's offset is the scalar one,
+    // which the buffer's bounds check leaves out
+    if (j0 + jg < J_wg) issue_k(j0 + jg);
     issue_kmean(j0 >> 4);
 
     // Q fragments: B operand, lane (query lq, half lh) holds channels 16*ks + 8*lh .. +7

@@ -691,6 +691,27 @@ def test_key_split_against_the_oracle_and_against_one_workgroup_per_tile(Nq, N, 
     assert cs["maxabs"] <= 2e-3
 
 
+def test_key_split_with_a_range_that_has_no_keys():
+    """63 key tiles in three ranges of at most 32: the third has none.  The workspace ends where the three ranges' states end."""
+    import torch
+    rng = np.random.default_rng(1733)
+    Hq, N, d, dev = 70, 8000, 64, torch.device("cuda:0")
+    q = rng.standard_normal((1, Hq, 1, d)).astype(np.float16)
+    k = (rng.standard_normal((1, 1, N, d)) + 2).astype(np.float16)
+    v = rng.standard_normal((1, 1, N, d)).astype(np.float16)
+    scale = f32(0.125)
+    tq, tk, tv = (torch.from_numpy(x).to(dev) for x in (q, k, v))
+    wsb = P.pasa_attn_fwd_workspace_min(1, 1, N, d) + 3 * Hq * (4 * d + 16)
+    ws = torch.empty(wsb, dtype=torch.uint8, device=dev)
+    to = torch.full_like(tq, float("nan"))
+    cnt = torch.zeros(1, dtype=torch.int64, device=dev)          # with a counter: 256-row workgroups for a single row too
+    P.pasa_prepare_kv(tk, tv, 1, 1, N, d, scale, ws, wsb)
+    P.pasa_attn_fwd_chunk(tq, to, 1, Hq, 1, 1, N - 1, N, d, True, scale, ws, wsb, nonfinite_o=cnt)
+    torch.cuda.synchronize()
+    assert int(cnt) == 0
+    assert compare(to.cpu().numpy(), _rows_ref(q, k, v, scale, True, 0, 1, N - 1))["maxabs"] <= 2e-3
+
+
 def test_key_split_bf16_and_counters():
     """The merge kernel writes the output: bf16 conversion and the non-finite counter live there when the keys are split."""
     import torch
