@@ -74,4 +74,9 @@ hipError_t pasa_launch_merge(const void* part_o, const void* part_lr, void* o, s
 // Sets n 64-bit words to zero with a small kernel (not a memset, so that the call may sit in a captured graph).
 hipError_t pasa_launch_zero(unsigned long long* p, int n, hipStream_t stream);
 
+// For tests, not part of the interface: the kernel that a call without `gate` is planned on (0 pasa_fwd, 1 its workgroups of two
+// halves, 2 pasa_fwd4, 3 pasa_rows) and in how many pieces its keys are swept.  Launches nothing.
+extern "C" int pasa_internal_plan(int variant, int counters, int B, int Hq, int Hkv, int Nq, int row0, int N, int d, int causal,
+                                  size_t workspace_bytes, int* nsplit);
+
 #endif

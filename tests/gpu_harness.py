@@ -93,3 +93,20 @@ def compare(o, ref):
     d = np.abs(o.astype(np.float64) - ref.astype(np.float64))
     return dict(maxabs=float(d.max()), p999=float(np.quantile(d, 0.999)), p99=float(np.quantile(d, 0.99)),
                 mismatch=float((o != ref).mean()))
+
+
+KERNELS = ("fwd", "halves", "fwd4", "rows")
+
+
+def plan_of(variant, B, Hq, Hkv, Nq, row0, N, d, causal, counters=False, workspace_bytes=None):
+    """(kernel, number of key splits) that the library plans a call on; needs no GPU."""
+    import ctypes
+    f = P.lib().pasa_internal_plan
+    f.argtypes = [ctypes.c_int] * 10 + [ctypes.c_size_t, ctypes.POINTER(ctypes.c_int)]
+    f.restype = ctypes.c_int
+    if workspace_bytes is None:
+        workspace_bytes = P.pasa_attn_fwd_workspace(B, Hq, Hkv, N, d)
+    ns = ctypes.c_int(0)
+    k = f(variant, int(counters), B, Hq, Hkv, Nq, row0, N, d, int(causal), workspace_bytes, ctypes.byref(ns))
+    assert k >= 0, "no such call"
+    return KERNELS[k], ns.value

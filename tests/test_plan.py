@@ -1,0 +1,45 @@
+"""The kernel that a call is planned on, for the calls of the GPU tests: those that mean to test one of the kernels reach it.
+No GPU is used."""
+import pytest
+
+import paper_2503_01873_amd as P
+from gpu_harness import plan_of
+
+MSD = (P.MIXED, P.S16, P.DIRECT)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Nq,row0,N,d,causal,variants,kernel,split", [
+    # test_few_rows
+    (2, 2, 2, 1, 0, 1, 128, True, MSD, "rows", False),
+    (2, 8, 2, 5, 4156, 4161, 128, True, MSD, "rows", True),
+    (2, 2, 2, 40, 2030, 2049, 128, True, MSD, "rows", True),
+    (2, 16, 2, 145, 0, 300, 128, True, MSD, "rows", False),
+    (2, 16, 2, 129, 140, 257, 64, True, MSD, "rows", False),
+    # test_many_rows_d64
+    (14, 6, 6, 1000, 0, 1000, 64, False, (P.MIXED, P.DIRECT), "fwd4", False),
+    (14, 8, 8, 1100, 0, 1100, 64, True, (P.MIXED, P.DIRECT), "fwd4", False),
+    (15, 5, 5, 905, 0, 905, 64, True, (P.MIXED, P.DIRECT), "fwd4", False),
+    (14, 8, 8, 900, 350, 1200, 64, True, (P.MIXED, P.DIRECT), "fwd4", False),
+    (1, 2, 2, 9000, 0, 9000, 64, True, (P.MIXED, P.DIRECT), "fwd4", True),
+    # test_many_rows_d64_in_the_smallest_workspace
+    (1, 70, 1, 1000, 0, 1000, 64, False, (P.MIXED,), "fwd4", False),
+    (1, 70, 1, 1024, 0, 1024, 64, False, (P.MIXED,), "fwd4", False),
+    (1, 70, 1, 1024, 0, 1024, 64, True, (P.MIXED,), "fwd4", False),
+    # test_workgroups_of_two_halves
+    (1, 28, 4, 1024, 0, 1024, 128, True, MSD, "halves", False),
+    (1, 28, 4, 900, 0, 900, 128, False, MSD, "halves", False),
+    (1, 28, 4, 1000, 900, 2200, 128, True, MSD, "halves", False),
+])
+def test_calls_reach_the_kernel_they_test(B, Hq, Hkv, Nq, row0, N, d, causal, variants, kernel, split):
+    for variant in variants:
+        got, nsplit = plan_of(variant, B, Hq, Hkv, Nq, row0, N, d, causal)
+        assert got == kernel and (nsplit > 1) == split, (variant, got, nsplit)
+
+
+def test_counters_and_fp16_state_stay_on_the_256_row_kernel():
+    for variant in (P.MIXED, P.S16, P.DIRECT, P.STRICT16, P.NAIVE16):
+        for N in (1, 300, 1024, 9000):
+            for d in (64, 128):
+                assert plan_of(variant, 1, 28, 4, N, 0, N, d, True, counters=True)[0] == "fwd"
+                if variant in (P.STRICT16, P.NAIVE16):
+                    assert plan_of(variant, 1, 28, 4, N, 0, N, d, True)[0] == "fwd"
