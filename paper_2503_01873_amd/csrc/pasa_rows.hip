@@ -299,10 +299,16 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
 #pragma unroll
                     for (int i = 0; i < 4; ++i) mx = __builtin_fmaxf(mx, S[rb][b][i]);
                 mx = max_row(mx);
-                const bool unseen = mx == -__builtin_inff();     // the row sees no key of this unit
-                // c: level of this unit's scores relative to the stored output's (first unit: +inf, which clears the zeros)
+                // A row that sees a single tile needs no bias, which may be infinite: a score that overflowed to -inf only takes
+                // its own weight there.
+                const bool one_tile = last[rb] < T;
+                if (one_tile) v = 0.f;
+                // Not "no score above -inf": those of a key that the row sees may all have overflowed.
+                const bool unseen = last[rb] < u * U || (one_tile && mx == -__builtin_inff());
+                // c: level of this unit's scores relative to the stored output's (first unit: +inf, which clears the zeros).  NaN, and
+                // with it the row, where the maximum or the bias is not finite: scores of keys it sees left the range of their type.
                 const double lev = (double)mx + (double)coef * (double)v;
-                float c = (float)(lev - R[rb]);
+                float c = (float)(lev - R[rb]) + (mx + v) * 0.f;
                 const bool move = c > CMAX;
                 if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
                     const float r = move ? __builtin_amdgcn_exp2f(-c * LOG2E) : 1.f;

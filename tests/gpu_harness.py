@@ -101,6 +101,7 @@ KERNELS = ("fwd", "halves", "fwd4", "rows")
 def plan_of(variant, B, Hq, Hkv, Nq, row0, N, d, causal, counters=False, workspace_bytes=None):
     """(kernel, number of key splits) that the library plans a call on; needs no GPU."""
     import ctypes
+    import torch  # noqa: F401  before the library, which then shares the HIP runtime that torch brings
     f = P.lib().pasa_internal_plan
     f.argtypes = [ctypes.c_int] * 10 + [ctypes.c_size_t, ctypes.POINTER(ctypes.c_int)]
     f.restype = ctypes.c_int

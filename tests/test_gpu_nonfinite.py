@@ -1,0 +1,119 @@
+"""Scores beyond the range of their type on every kernel: a row that sees such a key comes out as NaN, as in the oracle, and
+is never finite with some of its keys left out.  A row that sees a single key tile needs no pseudo-average, so a score that
+overflowed to -inf only takes its own weight there.
+
+Two sources: an infinite key (bf16 beyond 65504 becomes one), whose tile's mean and with it every K' of the tile is infinite in
+that channel; and, with S' rounded to fp16 (S16), finite inputs whose score is below -65520, which makes the tile's
+pseudo-average -inf."""
+import numpy as np
+import pytest
+
+import paper_2503_01873_amd as P
+from oracle import pasa_oracle as po
+from gpu_harness import bf16_bits, compare, f32, gpu_attn, gpu_attn_chunks, plan_of, VARIANT_NAME
+
+pytestmark = pytest.mark.gpu
+
+BETA = po.default_beta()
+POLICY = {P.MIXED: po.MIXED, P.S16: po.PARTIAL16}
+
+
+def _check(o, q, k, v, scale, causal, variant, row0, nan_from, kernel, checked_to=None):
+    """Rows of one head at positions row0 ..: NaN from position nan_from on, before it the oracle's values.  The oracle sees
+    the same NaN rows (its DIRECT form cannot be asked: it takes the largest finite score of every tile)."""
+    pos = row0 + np.arange(len(q))
+    want = (pos >= nan_from)[:, None] & np.ones(q.shape[1], bool)
+    if variant != P.DIRECT:
+        with np.errstate(invalid="ignore"):
+            ref = po.pasa_rows(q, k, v, scale, causal, BETA, 128, POLICY[variant], row0)
+        assert np.array_equal(np.isnan(ref), want)
+    else:
+        n = min(len(k), nan_from)
+        ref = po.direct_rows(q[pos < n], k[:n], v[:n], scale, causal, BETA, 128, po.MIXED, row0) if (pos < n).any() else q[:0]
+    assert np.array_equal(np.isnan(o), want), (kernel, VARIANT_NAME[variant], np.unique(np.nonzero(np.isnan(o) != want)[0])[:8])
+    # Where S' is rounded, single outputs differ at a dominant key whose score straddles a rounding boundary; and in the tile of an
+    # overflowing key the scores are near 780 (its share of the mean), where a step of fp16 is 0.5 and moves a weight by e^0.5:
+    # there only finiteness is asked for.
+    ok = pos < (nan_from if checked_to is None else checked_to)
+    if ok.any():
+        c = compare(o[ok], ref[:ok.sum()])
+        assert (c["maxabs"] <= 2e-3) if variant != P.S16 else (c["p999"] <= 2e-3)
+
+
+def _inputs(rng, B, Hq, Hkv, Nq, N, d):
+    return (rng.standard_normal((B, Hq, Nq, d)).astype(np.float16), (rng.standard_normal((B, Hkv, N, d)) + 1).astype(np.float16),
+            rng.standard_normal((B, Hkv, N, d)).astype(np.float16))
+
+
+# ------------------------------------------------------------------ an infinite key
+
+@pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT, P.S16])
+@pytest.mark.parametrize("d,N,inf_key", [(64, 300, 200), (128, 300, 250), (128, 200, 199), (64, 500, 100)])
+def test_infinite_key_few_rows(d, N, inf_key, variant):
+    rng = np.random.default_rng(N + inf_key)
+    q, k, v = _inputs(rng, 1, 2, 2, N, N, d)
+    k[0, :, inf_key, 5] = np.inf
+    scale = f32(d ** -0.5)
+    assert plan_of(variant, 1, 2, 2, N, 0, N, d, True) == ("rows", 1)
+    o, _ = gpu_attn(q, k, v, True, scale, variant)
+    for h in range(2):
+        _check(o[0, h], q[0, h], k[0, h], v[0, h], scale, True, variant, 0, inf_key // 128 * 128, "rows")
+
+
+@pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT, P.S16])
+def test_infinite_key_decoding_step(variant):
+    """The key lies past the row's position, in its tile; the keys are swept in pieces."""
+    rng = np.random.default_rng(12)
+    N, d, scale = 6000, 128, f32(128 ** -0.5)
+    q, k, v = _inputs(rng, 1, 4, 2, 1, N, d)
+    k[0, 0, 5800, 5] = np.inf
+    row0 = 5760
+    assert plan_of(variant, 1, 4, 2, 1, row0, N, d, True)[1] > 1
+    o = gpu_attn_chunks(q, k, v, True, scale, [(0, 1, row0)], variant=variant)
+    for h in range(4):
+        _check(o[0, h], q[0, h], k[0, h // 2], v[0, h // 2], scale, True, variant, row0, 0 if h < 2 else N, "rows")
+
+
+def test_bf16_key_beyond_the_fp16_range():
+    rng = np.random.default_rng(3)
+    N, d, scale = 256, 128, f32(128 ** -0.5)
+    q, k, v = (po.fl(rng.standard_normal((1, 1, N, d)), "bf16").astype(np.float32) for _ in range(3))
+    k[0, 0, 200, 7] = 131072.0
+    assert plan_of(P.MIXED, 1, 1, 1, N, 0, N, d, True) == ("rows", 1)
+    o, _ = gpu_attn(q, k, v, True, scale, P.MIXED, bf16=True)
+    assert np.isnan(o[0, 0, 128:]).all() and np.isfinite(o[0, 0, :128]).all()
+
+
+# ------------------------------------------------------------------ S16: finite inputs, one score beyond the fp16 range
+
+def _overflowing(rng, Hq, Hkv, Nq, N, d, at, sign=-1.0):
+    """S' of key `at` is about sign * 1e5 for every row; the other keys of its tile move by less than 1000."""
+    q, k, v = _inputs(rng, 1, Hq, Hkv, Nq, N, d)
+    q[..., 5] = 40.0
+    k[0, :, at, 5] = sign * 1e5 / (40.0 * f32(d ** -0.5))
+    return q, k, v
+
+
+@pytest.mark.parametrize("sign", [-1.0, 1.0])
+@pytest.mark.parametrize("d,N,at", [(128, 300, 70), (64, 300, 200), (128, 100, 30), (64, 650, 600), (128, 65, 64)])
+def test_overflowing_score_few_rows(d, N, at, sign):
+    rng = np.random.default_rng(N + at)
+    q, k, v = _overflowing(rng, 2, 2, N, N, d, at, sign)
+    scale = f32(d ** -0.5)
+    assert plan_of(P.S16, 1, 2, 2, N, 0, N, d, True) == ("rows", 1)
+    o, _ = gpu_attn(q, k, v, True, scale, P.S16)
+    # rows of the first tile: -inf is a weight of zero, +inf is NaN for the rows that see the key
+    first = max(at // 128 * 128, 128) if sign < 0 else at if at < 128 else at // 128 * 128
+    for h in range(2):
+        _check(o[0, h], q[0, h], k[0, h], v[0, h], scale, True, P.S16, 0, first, "rows", at // 128 * 128)
+
+
+@pytest.mark.parametrize("at", [100, 3333, 5999])
+def test_overflowing_score_decoding_step(at):
+    rng = np.random.default_rng(at)
+    N, d, scale = 6000, 128, f32(128 ** -0.5)
+    q, k, v = _overflowing(rng, 4, 2, 3, N, d, at)
+    assert plan_of(P.S16, 1, 4, 2, 3, N - 3, N, d, True)[1] > 1
+    o = gpu_attn_chunks(q, k, v, True, scale, [(0, 3, N - 3)], variant=P.S16)
+    for h in range(4):
+        _check(o[0, h], q[0, h], k[0, h // 2], v[0, h // 2], scale, True, P.S16, N - 3, 0, "rows")
