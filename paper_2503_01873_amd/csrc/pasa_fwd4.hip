@@ -198,9 +198,12 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
                 for (int i = 1; i < 16; ++i) pm[kb] = __builtin_fmaxf(pm[kb], S[kb][i]);
             }
             const float mx = max32(__builtin_fmaxf(__builtin_fmaxf(pm[0], pm[1]), __builtin_fmaxf(pm[2], pm[3])));
-            const bool unseen = mx == -__builtin_inff();
+            // By position: the scores of keys that the row sees may all have overflowed to -inf.  A row that sees a single tile
+            // needs no bias, which may be infinite.  c is NaN, and with it the row, where the maximum or the bias is not finite.
+            const bool unseen = last_key < j * T;
+            if (last_key < T) v = 0.f;
             const double lev = (double)mx + (double)coef * (double)v;
-            float c = (float)(lev - R);
+            float c = (float)(lev - R) + (mx + v) * 0.f;
             const bool move = c > CMAX;
             if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
                 asm volatile("" ::: "memory");

@@ -74,6 +74,32 @@ def test_infinite_key_decoding_step(variant):
         _check(o[0, h], q[0, h], k[0, h // 2], v[0, h // 2], scale, True, variant, row0, 0 if h < 2 else N, "rows")
 
 
+@pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT])
+@pytest.mark.parametrize("N,inf_key", [(1000, 700), (1000, 127), (1000, 999)])
+def test_infinite_key_many_rows_d64(N, inf_key, variant):
+    rng = np.random.default_rng(N + inf_key)
+    B, H, d, scale = 14, 6, 64, f32(0.125)
+    q, k, v = _inputs(rng, B, H, H, N, N, d)
+    k[3, 2, inf_key, 5] = np.inf
+    assert plan_of(variant, B, H, H, N, 0, N, d, True) == ("fwd4", 1)
+    o, _ = gpu_attn(q, k, v, True, scale, variant)
+    _check(o[3, 2], q[3, 2], k[3, 2], v[3, 2], scale, True, variant, 0, inf_key // 128 * 128, "fwd4")
+    assert np.isfinite(np.delete(o.reshape(B * H, N, d), 3 * H + 2, 0)).all()
+
+
+@pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT])
+def test_infinite_key_many_rows_d64_keys_in_pieces(variant):
+    rng = np.random.default_rng(77)
+    N, d, scale = 9000, 64, f32(0.125)
+    q, k, v = _inputs(rng, 1, 2, 2, N, N, d)
+    k[0, 1, 8100, 5] = np.inf
+    assert plan_of(variant, 1, 2, 2, N, 0, N, d, True)[0] == "fwd4" and plan_of(variant, 1, 2, 2, N, 0, N, d, True)[1] > 1
+    o, _ = gpu_attn(q, k, v, True, scale, variant)
+    lo = 8000
+    _check(o[0, 1, lo:], q[0, 1, lo:], k[0, 1], v[0, 1], scale, True, variant, lo, 8100 // 128 * 128, "fwd4")
+    assert np.isfinite(o[0, 0]).all() and np.isfinite(o[0, 1, :lo]).all()
+
+
 def test_bf16_key_beyond_the_fp16_range():
     rng = np.random.default_rng(3)
     N, d, scale = 256, 128, f32(128 ** -0.5)
