@@ -963,7 +963,11 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     if (LSUM_MFMA) l = Lacc[0];            // every row of the block is the sum
     // level of the stored output: running maximum in its frame, the frame's offset, the stored scale (exact in fp64)
     bool none = !(J_w > j0 + jg) || l == 0.f;
-    double level = none ? -__builtin_inf() : (double)m + (double)inva * (double)F + (double)Lc;
+    // (a row that sees a single tile needs no pseudo-average, which may be infinite there).  Not finite: a score or a
+    // pseudo-average left the range of its type, and the state must not be taken for one without keys.
+    const bool one_tile = CAUSAL ? row0 + row < T || N <= T : N <= T;
+    double level = none ? -__builtin_inf() : (double)m + (one_tile ? 0.0 : (double)inva * (double)F) + (double)Lc;
+    if (!none && !__builtin_isfinite(level)) level = __builtin_nan("");
     // ---------------- key split within the workgroup: group B's state joins group A's ----------------
     if (KSPL == 2) {
         __syncthreads();                   // the tiles have been read

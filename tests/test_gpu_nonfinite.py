@@ -100,6 +100,19 @@ def test_infinite_key_many_rows_d64_keys_in_pieces(variant):
     assert np.isfinite(o[0, 0]).all() and np.isfinite(o[0, 1, :lo]).all()
 
 
+@pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT, P.S16])
+@pytest.mark.parametrize("inf_key", [1000, 150, 20])
+def test_infinite_key_two_halves(inf_key, variant):
+    rng = np.random.default_rng(inf_key)
+    N, d, scale = 1100, 128, f32(128 ** -0.5)
+    q, k, v = _inputs(rng, 1, 28, 4, N, N, d)
+    k[0, 1, inf_key, 5] = np.inf
+    assert plan_of(variant, 1, 28, 4, N, 0, N, d, True) == ("halves", 1)
+    o, _ = gpu_attn(q, k, v, True, scale, variant)
+    _check(o[0, 9], q[0, 9], k[0, 1], v[0, 1], scale, True, variant, 0, inf_key // 128 * 128, "halves")
+    assert np.isfinite(np.delete(o[0], slice(7, 14), 0)).all()
+
+
 def test_bf16_key_beyond_the_fp16_range():
     rng = np.random.default_rng(3)
     N, d, scale = 256, 128, f32(128 ** -0.5)
@@ -143,3 +156,33 @@ def test_overflowing_score_decoding_step(at):
     o = gpu_attn_chunks(q, k, v, True, scale, [(0, 3, N - 3)], variant=P.S16)
     for h in range(4):
         _check(o[0, h], q[0, h], k[0, h // 2], v[0, h // 2], scale, True, P.S16, N - 3, 0, "rows")
+
+
+@pytest.mark.parametrize("N,at", [(1100, 30), (1100, 150), (1100, 300), (1100, 1050), (1024, 1000)])
+def test_overflowing_score_two_halves(N, at):
+    rng = np.random.default_rng(N + at)
+    d, scale = 128, f32(128 ** -0.5)
+    q, k, v = _overflowing(rng, 28, 4, N, N, d, at)
+    assert plan_of(P.S16, 1, 28, 4, N, 0, N, d, True) == ("halves", 1)
+    o, _ = gpu_attn(q, k, v, True, scale, P.S16)
+    for h in (0, 27):
+        _check(o[0, h], q[0, h], k[0, h // 7], v[0, h // 7], scale, True, P.S16, 0, max(at // 128 * 128, 128), "halves", at // 128 * 128)
+
+
+@pytest.mark.parametrize("at", [2100, 2000, 5])
+def test_overflowing_score_where_a_range_of_the_key_split_is_one_tile(at):
+    """17 key tiles in two ranges, the second of a single tile; with a counter, so that 256-row workgroups take it."""
+    import torch
+    rng = np.random.default_rng(at)
+    N, Nq, d, scale, dev = 2176, 32, 128, f32(128 ** -0.5), torch.device("cuda:0")
+    q, k, v = _overflowing(rng, 2, 1, Nq, N, d, at)
+    assert plan_of(P.S16, 1, 2, 1, Nq, 0, N, d, False, counters=True) == ("fwd", 2)
+    tq, tk, tv = (torch.from_numpy(x).to(dev) for x in (q, k, v))
+    wsb = P.pasa_attn_fwd_workspace(1, 2, 1, N, d)
+    ws, to = torch.empty(wsb, dtype=torch.uint8, device=dev), torch.zeros_like(tq)
+    cnt = torch.zeros(2, dtype=torch.int64, device=dev)
+    P.pasa_prepare_kv(tk, tv, 1, 1, N, d, scale, ws, wsb, variant=P.S16)
+    P.pasa_attn_fwd_chunk(tq, to, 1, 2, 1, Nq, 0, N, d, False, scale, ws, wsb, variant=P.S16, overflow_s=cnt[0:1], nonfinite_o=cnt[1:2])
+    torch.cuda.synchronize()
+    assert np.isnan(po.pasa_rows(q[0, 0], k[0, 0], v[0, 0], scale, False, BETA, 128, po.PARTIAL16)).all()
+    assert torch.isnan(to).all() and cnt.tolist() == [2 * Nq, 2 * Nq * d]
