@@ -158,20 +158,24 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
                                                     _Float16* __restrict__ plain_out, _Float16* __restrict__ k0out,
                                                     _Float16* __restrict__ kmean_out,
                                                     int N, int ntile, double beta, double kscale, int shift_mode,
-                                                    int in_bf16, const unsigned long long* gate, int tiles, int group, int y_off)
+                                                    int in_bf16, const unsigned long long* gate, unsigned tiles, unsigned parts, unsigned group, int y_off)
 {
     // Workgroups are dealt round-robin to the 8 XCDs: blocks of a tile that read parts of the same 128-byte lines of K follow one
     // another on one XCD and share its L2, neighbouring tiles go to neighbouring XCDs.  `group` blocks of a tile come
     // together, all of them or the key blocks of all tiles before the value blocks (see the launch).
-    const int per = (tiles + 7) >> 3;                    // tiles of an XCD
-    int pos = blockIdx.x >> 3, part = 0;
+    // (Index of the block: gridDim.x is a multiple of 8, so the XCD is its remainder in every row of the grid.)
+    const unsigned index = blockIdx.y * gridDim.x + blockIdx.x;
+    const unsigned per = (tiles + 7) >> 3;               // tiles of an XCD
+    unsigned pos = index >> 3;
+    if (pos >= per * parts) return;                      // the grid's last row is not full
+    unsigned part = 0;
     if (pos >= per * group) {
         pos -= per * group;
         part = group;
     }
     part += pos % group;
-    const size_t tile = (size_t)(pos / group) * 8 + (blockIdx.x & 7);    // (batch, KV head, key tile)
-    if (tile >= (size_t)tiles) return;
+    const size_t tile = (size_t)(pos / group) * 8 + (index & 7);    // (batch, KV head, key tile)
+    if (tile >= tiles) return;
     // adaptive start: nothing overflowed in this (batch, KV head), its shifted pass is not needed
     if (gate != nullptr && gate[tile / ntile] == 0) return;
 
@@ -193,7 +197,7 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
     const size_t src_off = (head * (size_t)N + (size_t)t * T) * D;
     const int tid = threadIdx.x;
 
-    const int by = part + y_off;              // y_off = NS: only the value blocks are launched
+    const int by = (int)part + y_off;              // y_off = NS: only the value blocks are launched
     if (by >= NS) {
         // ---- values: keys [n0, n0 + TB) of the tile, all channels ----
         _Float16 (*vs)[D + 8] = reinterpret_cast<_Float16 (*)[D + 8]>(lds_raw);   // +8 halfs: rows 16 bytes apart in bank space
@@ -1137,19 +1141,20 @@ hipError_t pasa_launch_prep(const void* k, const void* v, void* ws, void* plain_
 {
     const int ntile = (N + T - 1) / T;
     const int y_off = k == nullptr ? PASA_PREP_SPLIT : 0;     // no keys given: the value blocks alone
-    const int parts = (v != nullptr && k != nullptr ? 2 : 1) * PASA_PREP_SPLIT;      // of a tile: key channel groups, then value key groups
-    const int tiles = B * Hkv * ntile;
-    const dim3 grid((unsigned)((tiles + 7) / 8 * 8 * parts));
+    const unsigned parts = (v != nullptr && k != nullptr ? 2 : 1) * PASA_PREP_SPLIT;      // of a tile: key channel groups, then value key groups
+    // A dimension of a grid holds fewer than 2^32 work items: beyond 2^20 blocks the launch goes on in a second dimension.
+    const size_t tiles = (size_t)B * Hkv * ntile, blocks = (tiles + 7) / 8 * 8 * parts, row = (size_t)1 << 20;
+    const dim3 grid((unsigned)(blocks < row ? blocks : row), (unsigned)((blocks + row - 1) / row));
     // The key blocks take longer: first where the launch is a few rounds (8 heads of 4096 keys, d = 128, 256 tiles: 8.9 us, mixed
     // 11.6; 512 tiles 17.6 / 18.8), in longer ones mixed, so that reading, arithmetic and writing overlap (2048 tiles 58.9 /
     // 55.4; 14 x 5 heads of 9216 keys, d = 64: 82.9 / 80.3; both in plain order 63.5 and 92.5, before that 65.0 and 94.5).
-    const int group = tiles < 1024 ? PASA_PREP_SPLIT : parts;
+    const unsigned group = tiles < 1024 ? PASA_PREP_SPLIT : parts;
     if (d == 128)
         hipLaunchKernelGGL(pasa_prep_kv<128>, grid, dim3(256), 0, stream, (const _Float16*)k, (const _Float16*)v,
-                           (_Float16*)ws, (_Float16*)plain_out, (_Float16*)k0out, (_Float16*)kmean_out, N, ntile, beta, kscale, shift_mode, in_bf16, gate, tiles, group, y_off);
+                           (_Float16*)ws, (_Float16*)plain_out, (_Float16*)k0out, (_Float16*)kmean_out, N, ntile, beta, kscale, shift_mode, in_bf16, gate, (unsigned)tiles, parts, group, y_off);
     else
         hipLaunchKernelGGL(pasa_prep_kv<64>, grid, dim3(256), 0, stream, (const _Float16*)k, (const _Float16*)v,
-                           (_Float16*)ws, (_Float16*)plain_out, (_Float16*)k0out, (_Float16*)kmean_out, N, ntile, beta, kscale, shift_mode, in_bf16, gate, tiles, group, y_off);
+                           (_Float16*)ws, (_Float16*)plain_out, (_Float16*)k0out, (_Float16*)kmean_out, N, ntile, beta, kscale, shift_mode, in_bf16, gate, (unsigned)tiles, parts, group, y_off);
     return hipGetLastError();
 }
 
