@@ -159,9 +159,11 @@ int pasa_attn_fwd_prepared(const void* q, void* o, int B, int Hq, int Hkv, int N
  * n <= row0 + r (row0 = N - Nq aligns the last query with the last key; positions past N - 1 see all keys);
  * with causal == 0 every row sees all N keys and row0 is ignored.  Covers cross-attention, prefill in chunks and
  * decoding against a cache.  pasa_attn_fwd_prepared(..., N, ...) is the case Nq = N, row0 = 0.  A row's result
- * does not depend on the other rows of its chunk, up to rounding: launches of different sizes may run on different
- * kernels or sweep the keys in different pieces, which moves the level that P is rounded at.  Calls that take the same
- * kernel without a key split give bit-identical rows.  PASA_EINVAL for
+ * does not depend on the other rows of its chunk.  Splitting a sequence at multiples of 32 rows gives bit-identical output
+ * wherever the calls sweep their keys unsplit -- N <= 2048, or at least 192 workgroups of 256 rows (B * Hq * ceil(Nq / 256)) --
+ * for pieces of 32 rows or more and, up to 2048 keys, for the end of a causal sequence whatever its length.  Any other
+ * call (decoding steps, pieces that start elsewhere, launches that split their keys, calls with counters) agrees up to rounding: it may run
+ * on another kernel or sweep the keys in pieces, which moves the level that P is rounded at.  PASA_EINVAL for
  * Nq <= 0 or row0 < 0; otherwise the rules of pasa_attn_fwd_prepared. */
 int pasa_attn_fwd_chunk(const void* q, void* o, int B, int Hq, int Hkv, int Nq, int row0, int N, int d, int causal,
                         float scale, const pasa_opts* opts, void* workspace, size_t workspace_bytes, void* stream);

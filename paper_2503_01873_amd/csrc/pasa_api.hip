@@ -256,9 +256,27 @@ double unequal_rounds(double workgroups, double slots, double fixed, double most
     return chain > work ? chain + 0.1 * work : work + 0.1 * chain;
 }
 
+// Pieces of a sequence whose keys are swept unsplit have the bits of the whole call: the kernels round P relative to different
+// levels, so all pieces go to the kernel of the whole.  That holds for launches of at least kSplitBelow workgroups of 256 rows
+// and for all up to 2048 keys; pieces start at multiples of 32 rows (rows of a wavefront stay together) and have 32 rows or
+// more.  Shorter ones are decoding steps, which would lose five times (16 x 1 row of 4999 keys: 33 us, 173 on the
+// kernel of the whole), except the end of a causal sequence of up to 2048 keys.  The cost: 128 rows of 2048 keys, 28 heads
+// on 4, take HALVES instead of pasa_rows.
+bool keeps_the_bits_of_the_whole(int B, int Hq, int Nq, int row0, int N, int causal)
+{
+    if (wanted_splits(B, Hq, Nq, N) > 1 || (causal && row0 % 32 != 0)) return false;
+    return Nq >= 32 || (causal && N <= 2048 && row0 + Nq >= N);
+}
+
 Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hkv, int Nq, int row0, int N, int d, int causal,
                size_t room)
 {
+    const int rows_given = Nq;
+    if (keeps_the_bits_of_the_whole(B, Hq, Nq, row0, N, causal)) {
+        may_split = false;
+        Nq = N;
+        row0 = 0;
+    }
     const size_t rows_all = (size_t)B * Hq * Nq;
     const double merge = 6.0;                                                               // us
     Plan p = {Plan::FWD, 1, 0};
@@ -273,7 +291,7 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
     const double U = (double)B * Hq * ((Nq + 255) / 256), real = Nq < 256 ? 0.85 + 0.15 * Nq / 256.0 : 1.0;
 
     const int G = Hq / Hkv;
-    Plan r = {Plan::ROWS, 1, s16 ? 1 : rows_blocks(B, Hkv, G, Nq)};
+    Plan r = {Plan::ROWS, 1, s16 ? 1 : rows_blocks(B, Hkv, G, rows_given)};
     double rows_us;
     {
         if (may_split) r.nsplit = fitting(rows_splits(B, Hkv, G, Nq, r.row_blocks, N, most), rows_all, d, room);

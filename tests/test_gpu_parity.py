@@ -529,7 +529,7 @@ def test_decoding_against_a_cache(Nq):
     (40, 1, 2049, 2030, True, 128),     # positions past the last key; the first length whose keys are split
     (5, 4, 4161, 4156, True, 128),      # split, with a last unit of one key in a tile of 65
     (33, 1, 3000, 0, False, 64),
-    (145, 8, 300, 0, True, 128),        # over 256 blocks of 16 rows: blocks of 32 from here on, the last with 17 rows
+    (145, 8, 300, 7, True, 128),        # over 256 blocks of 16 rows: blocks of 32 from here on, the last with 17 rows
     (129, 8, 257, 140, True, 64),       # ... with one row
 ])
 def test_few_rows(Nq, G, N, row0, causal, d, variant):

@@ -13,7 +13,7 @@ CASES = [
     (1, 28, 4, 777, 128, True, (256, 256, 256, 9), "rows"),          # the last piece is shorter than a wavefront's rows
     (1, 28, 4, 1024, 128, True, (32, 96, 512, 384), "halves"),
     (1, 28, 4, 1100, 128, True, (512, 512, 64, 12), "halves"),
-    (1, 28, 4, 2048, 128, True, (1024, 992, 31, 1), "halves"),       # a piece that starts off the multiples of 32 is left out
+    (1, 28, 4, 2048, 128, True, (1024, 992, 32), "halves"),
     (1, 28, 4, 900, 128, False, (33, 500, 367), "halves"),
     (1, 28, 4, 4096, 128, True, (2048, 2048), "fwd"),                # 224 workgroups of 256 rows each: not split
     (14, 6, 6, 1000, 64, True, (32, 480, 480, 8), "fwd4"),
@@ -37,8 +37,7 @@ def test_pieces_have_the_bits_of_the_whole(B, Hq, Hkv, N, d, causal, pieces, ker
     assert np.isfinite(whole).all()
     first, chunks = 0, []
     for n in pieces:
-        if not causal or first % 32 == 0:
-            chunks.append((first, n, first))
+        chunks.append((first, n, first))
         first += n
     assert first == N
     parts = gpu_attn_chunks(q, k, v, causal, scale, chunks, variant=variant)

@@ -13,7 +13,7 @@ MSD = (P.MIXED, P.S16, P.DIRECT)
     (2, 2, 2, 1, 0, 1, 128, True, MSD, "rows", False),
     (2, 8, 2, 5, 4156, 4161, 128, True, MSD, "rows", True),
     (2, 2, 2, 40, 2030, 2049, 128, True, MSD, "rows", True),
-    (2, 16, 2, 145, 0, 300, 128, True, MSD, "rows", False),
+    (2, 16, 2, 145, 7, 300, 128, True, MSD, "rows", False),
     (2, 16, 2, 129, 140, 257, 64, True, MSD, "rows", False),
     # test_many_rows_d64
     (14, 6, 6, 1000, 0, 1000, 64, False, (P.MIXED, P.DIRECT), "fwd4", False),
