@@ -89,6 +89,23 @@ def gpu_attn_chunks(q, k, v, causal, scale, chunks, variant=P.MIXED, beta=-1.0):
     return out
 
 
+def gpu_adaptive(q, k, v, causal, scale, variant=P.MIXED):
+    """pasa_attn_fwd_adaptive; returns (o, raw scores beyond the fp16 range)."""
+    import torch
+    dev = torch.device("cuda:0")
+    B, Hq, N, d = q.shape
+    Hkv = k.shape[1]
+    tq, tk, tv = (torch.from_numpy(np.ascontiguousarray(x)).to(dev) for x in (q, k, v))
+    to = torch.full_like(tq, float("nan"))
+    cnt = torch.zeros(1, dtype=torch.int64, device=dev)
+    wsb = P.pasa_attn_fwd_workspace(B, Hq, Hkv, N, d)
+    ws = torch.empty(wsb, dtype=torch.uint8, device=dev)
+    P.pasa_attn_fwd_adaptive(tq, tk, tv, to, B, Hq, Hkv, N, d, causal, scale, ws, wsb, torch.cuda.current_stream(),
+                             variant=variant, overflow_s=cnt)
+    torch.cuda.synchronize()
+    return to.cpu().numpy(), int(cnt.item())
+
+
 def compare(o, ref):
     d = np.abs(o.astype(np.float64) - ref.astype(np.float64))
     return dict(maxabs=float(d.max()), p999=float(np.quantile(d, 0.999)), p99=float(np.quantile(d, 0.99)),

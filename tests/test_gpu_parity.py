@@ -16,7 +16,7 @@ import pytest
 import paper_2503_01873_amd as P
 from oracle import pasa_oracle as po
 from workloads import Workload, workload, gen_full, gen_q_head, gen_kv_head
-from gpu_harness import bf16_bits, gpu_attn, gpu_attn_chunks, compare, f32, ORACLE_POLICY, VARIANT_NAME
+from gpu_harness import bf16_bits, gpu_adaptive, gpu_attn, gpu_attn_chunks, compare, f32, ORACLE_POLICY, VARIANT_NAME
 
 pytestmark = pytest.mark.gpu
 
@@ -460,7 +460,8 @@ def test_chunked_causal_prefill_equals_one_call():
     q, k, v = gen_full(w)
     scale = f32(w.scale)
     whole, _ = gpu_attn(q, k, v, True, scale, P.MIXED)
-    # chunk starts that are multiples of 32 keep every row in the same wavefront slot: bit-identical results
+    # pieces that start at multiples of 32 rows take the kernel of the whole, and no sum of a row depends on its neighbours:
+    # bit-identical results
     parts = gpu_attn_chunks(q, k, v, True, scale, [(0, 256, 0), (256, 448, 256), (704, 296, 704)])
     assert np.array_equal(whole.view(np.uint16), parts.view(np.uint16))
     # any other split: each row still follows the same algorithm (summation order of Sbar' may differ)
@@ -624,9 +625,10 @@ def test_many_rows_d64_in_the_smallest_workspace(N, causal):
 @pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT, P.S16])
 @pytest.mark.parametrize("Nq,N,row0,causal", [
     (1024, 1024, 0, True),       # eight key tiles; the first row tile has none for the second group
-    (900, 900, 0, False),        # a last row tile of 4 rows; an odd number of key tiles, the last of 4 keys
+    (900, 900, 0, False),        # a last row tile of 4 rows; eight key tiles, the last of 4 keys with the second group
+    (1028, 1028, 0, False),      # nine key tiles, the last of 4 keys with the first group
+    (1100, 1100, 0, True),       # ... of 76 keys
     (1000, 2200, 900, True),     # pseudo-averages of a second block of sixteen; rows that straddle tiles
-    (257, 257, 0, True),
 ])
 def test_workgroups_of_two_halves(Nq, N, row0, causal, variant):
     """d = 128, 28 heads on 4: launches of one to two rounds, in which the two groups of wavefronts of a workgroup take the
@@ -969,27 +971,11 @@ def test_first_two_key_tiles_enter_symmetrically_in_strict16():
 
 # ------------------------------------------------------------------ adaptive start
 
-def _adaptive(q, k, v, causal, scale, variant=P.MIXED):
-    import torch
-    dev = torch.device("cuda:0")
-    B, Hq, N, d = q.shape
-    Hkv = k.shape[1]
-    tq, tk, tv = (torch.from_numpy(np.ascontiguousarray(x)).to(dev) for x in (q, k, v))
-    to = torch.full_like(tq, float("nan"))
-    cnt = torch.zeros(1, dtype=torch.int64, device=dev)
-    wsb = P.pasa_attn_fwd_workspace(B, Hq, Hkv, N, d)
-    ws = torch.empty(wsb, dtype=torch.uint8, device=dev)
-    P.pasa_attn_fwd_adaptive(tq, tk, tv, to, B, Hq, Hkv, N, d, causal, scale, ws, wsb, torch.cuda.current_stream(),
-                             variant=variant, overflow_s=cnt)
-    torch.cuda.synchronize()
-    return to.cpu().numpy(), int(cnt.item())
-
-
 def test_adaptive_start_keeps_the_unshifted_result_when_nothing_overflows():
     w = workload(1)
     q, k, v = gen_full(w)
     scale = f32(w.scale)
-    o, count = _adaptive(q, k, v, w.causal, scale)
+    o, count = gpu_adaptive(q, k, v, w.causal, scale)
     plain, _ = gpu_attn(q, k, v, w.causal, scale, P.NAIVE16)
     ref, trig = po.adaptive_bhnd(q, k, v, scale, w.causal, BETA)
     assert count == 0 and not trig
@@ -1005,7 +991,7 @@ def test_adaptive_start_switches_to_pasa_on_overflow(variant):
     w = _small(2, 512, Hq=2, Hkv=1)
     q, k, v = gen_full(w)
     scale = f32(w.scale)
-    o, count = _adaptive(q, k, v, w.causal, scale, variant)
+    o, count = gpu_adaptive(q, k, v, w.causal, scale, variant)
     shifted, _ = gpu_attn(q, k, v, w.causal, scale, variant)
     assert count > 0 and np.isfinite(o).all()
     assert np.array_equal(o.view(np.uint16), shifted.view(np.uint16))
@@ -1026,7 +1012,7 @@ def test_adaptive_start_switches_only_the_kv_head_that_overflowed():
     q[1, 1] = 30.0
     k[1, 0] = (30.0 + rng.standard_normal((N, d))).astype(np.float16)
     scale = f32(d ** -0.5)
-    o, count = _adaptive(q, k, v, True, scale)
+    o, count = gpu_adaptive(q, k, v, True, scale)
     info = {}
     ref, trig = po.adaptive_bhnd(q, k, v, scale, True, BETA, info=info)
     assert trig and info["groups"].tolist() == [[False, False], [True, False]]

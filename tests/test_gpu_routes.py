@@ -1,0 +1,121 @@
+"""What each kernel of the plan has to do besides the plain call: bf16, the smallest workspace, the gate of the adaptive call;
+and the 256-row kernel where it is still the one that is planned.  Every case says which kernel it is for."""
+import numpy as np
+import pytest
+
+import paper_2503_01873_amd as P
+from oracle import pasa_oracle as po
+from gpu_harness import ORACLE_POLICY, VARIANT_NAME, compare, f32, gpu_adaptive, gpu_attn, plan_of
+
+pytestmark = pytest.mark.gpu
+
+BETA = po.default_beta()
+
+
+def _draw(rng, B, Hq, Hkv, N, d, bias=2.0):
+    return (rng.standard_normal((B, Hq, N, d)).astype(np.float16), (rng.standard_normal((B, Hkv, N, d)) + bias).astype(np.float16),
+            rng.standard_normal((B, Hkv, N, d)).astype(np.float16))
+
+
+def _ref(q, k, v, scale, causal, variant, row0, **kw):
+    if variant == P.DIRECT:
+        return po.direct_rows(q, k, v, scale, causal, BETA, 128, po.MIXED, row0)
+    return po.pasa_rows(q, k, v, scale, causal, BETA, 128, ORACLE_POLICY[variant], row0, **kw)
+
+
+@pytest.mark.parametrize("variant,B,Hq,Hkv,N,d,causal,split", [
+    (P.MIXED, 1, 64, 8, 300, 128, False, False), (P.DIRECT, 1, 64, 8, 300, 128, False, False),
+    (P.MIXED, 14, 6, 6, 300, 128, True, False), (P.DIRECT, 14, 6, 6, 300, 128, True, False),
+    (P.S16, 1, 28, 4, 300, 128, True, False), (P.S16, 2, 16, 16, 300, 64, False, False),
+    (P.MIXED, 1, 8, 8, 2500, 64, False, True), (P.DIRECT, 1, 8, 8, 2500, 64, False, True),
+    (P.MIXED, 1, 2, 1, 6200, 128, False, True), (P.S16, 1, 2, 1, 4300, 128, True, True),
+])
+def test_256_row_workgroups(variant, B, Hq, Hkv, N, d, causal, split):
+    kernel, nsplit = plan_of(variant, B, Hq, Hkv, N, 0, N, d, causal)
+    assert kernel == "fwd" and (nsplit > 1) == split
+    rng = np.random.default_rng(N + Hq)
+    q, k, v = _draw(rng, B, Hq, Hkv, N, d)
+    scale = f32(d ** -0.5)
+    o, _ = gpu_attn(q, k, v, causal, scale, variant)
+    assert np.isfinite(o).all()
+    lo = max(0, N - 300)
+    for b, h in ((0, 0), (B - 1, Hq - 1)):
+        ref = _ref(q[b, h, lo:], k[b, h * Hkv // Hq], v[b, h * Hkv // Hq], scale, causal, variant, lo)
+        c = compare(o[b, h, lo:], ref)
+        print(VARIANT_NAME[variant], (b, h), c)
+        # S16: single outputs where S' straddles a rounding boundary at a dominant key
+        assert (c["maxabs"] <= 2e-3) if variant != P.S16 else (c["p999"] <= 2e-3)
+
+
+@pytest.mark.parametrize("variant", [P.MIXED, P.S16, P.DIRECT])
+@pytest.mark.parametrize("B,Hq,Hkv,N,d,causal,kernel", [
+    (1, 28, 4, 1100, 128, True, "halves"), (1, 28, 4, 900, 128, False, "halves"), (2, 4, 2, 333, 128, True, "rows"),
+])
+def test_bf16(B, Hq, Hkv, N, d, causal, kernel, variant):
+    assert plan_of(variant, B, Hq, Hkv, N, 0, N, d, causal)[0] == kernel
+    rng = np.random.default_rng(N)
+    q, k, v = (po.fl(x.astype(np.float32), "bf16").astype(np.float32) for x in _draw(rng, B, Hq, Hkv, N, d))
+    scale = f32(d ** -0.5)
+    o, _ = gpu_attn(q, k, v, causal, scale, variant, bf16=True)
+    assert np.isfinite(o).all()
+    kw = {} if variant == P.DIRECT else {"out_fmt": "bf16"}
+    for h in (0, Hq - 1):
+        ref = _ref(po.from_bf16(q[0, h]), po.from_bf16(k[0, h * Hkv // Hq]), po.from_bf16(v[0, h * Hkv // Hq]), scale, causal,
+                   variant, 0, **kw)
+        c = compare(o[0, h], ref)
+        print(VARIANT_NAME[variant], h, c)
+        assert c["maxabs"] <= 1.6e-2 and c["p999"] <= 4e-3       # one bf16 step is 7.8e-3 in [1, 2) and 1.6e-2 in [2, 4)
+
+
+@pytest.mark.parametrize("variant,B,Hq,Hkv,N,d,causal,kernel", [
+    (P.MIXED, 1, 28, 4, 1100, 128, True, "halves"), (P.S16, 1, 28, 4, 1100, 128, True, "halves"),
+    (P.MIXED, 1, 28, 4, 777, 128, True, "rows"), (P.DIRECT, 14, 6, 6, 1000, 64, False, "fwd4"),
+    (P.MIXED, 1, 64, 8, 300, 128, False, "fwd"), (P.MIXED, 1, 2, 2, 9000, 64, True, "fwd4"),
+])
+def test_smallest_workspace(variant, B, Hq, Hkv, N, d, causal, kernel):
+    """No more workspace than a call must have: the keys are swept unsplit, nothing is written behind it, and up to 2048 keys the
+    bits are those of the call with all of it."""
+    import torch
+    dev = torch.device("cuda:0")
+    bare, full = P.pasa_attn_fwd_workspace_min(B, Hkv, N, d), P.pasa_attn_fwd_workspace(B, Hq, Hkv, N, d)
+    assert plan_of(variant, B, Hq, Hkv, N, 0, N, d, causal, workspace_bytes=full)[0] == kernel
+    assert plan_of(variant, B, Hq, Hkv, N, 0, N, d, causal, workspace_bytes=bare)[1] == 1
+    rng = np.random.default_rng(N + d)
+    q, k, v = _draw(rng, B, Hq, Hkv, N, d)
+    scale = f32(d ** -0.5)
+    tq, tk, tv = (torch.from_numpy(x).to(dev) for x in (q, k, v))
+    guard = 1 << 16
+    ws = torch.full((bare + guard,), 0x5a, dtype=torch.uint8, device=dev)
+    to = torch.full_like(tq, float("nan"))
+    P.pasa_attn_fwd_ex(tq, tk, tv, to, B, Hq, Hkv, N, d, causal, scale, ws, bare, variant=variant)
+    torch.cuda.synchronize()
+    assert bool((ws[bare:] == 0x5a).all())
+    o, (whole, _) = to.cpu().numpy(), gpu_attn(q, k, v, causal, scale, variant)
+    assert np.isfinite(o).all()
+    if N <= 2048:
+        assert o.tobytes() == whole.tobytes()
+    else:
+        assert compare(o, whole)["maxabs"] <= 2e-3
+
+
+@pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT])
+@pytest.mark.parametrize("B,Hq,Hkv,N,d,causal,kernel", [
+    (1, 28, 4, 1100, 128, True, "halves"), (14, 6, 6, 1000, 64, False, "fwd4"), (1, 28, 4, 777, 128, True, "rows"),
+])
+def test_adaptive_start_recomputes_only_the_kv_heads_that_overflowed(B, Hq, Hkv, N, d, causal, kernel, variant):
+    assert plan_of(variant, B, Hq, Hkv, N, 0, N, d, causal) == (kernel, 1)
+    rng = np.random.default_rng(N)
+    G = Hq // Hkv
+    q, k, v = _draw(rng, B, Hq, Hkv, N, d, bias=0.0)
+    over = np.zeros((B, Hkv), bool)
+    for b, h in ((0, 1), (B - 1, Hkv - 1)):
+        over[b, h] = True
+        q[b, h * G] = 30.0                                        # one query head of the group
+        k[b, h] = (40.0 + rng.standard_normal((N, d))).astype(np.float16)       # raw scores of about 1200 d
+    scale = f32(d ** -0.5)
+    o, count = gpu_adaptive(q, k, v, causal, scale, variant)
+    shifted, _ = gpu_attn(q, k, v, causal, scale, variant)
+    plain, _ = gpu_attn(q, k, v, causal, scale, P.NAIVE16)
+    over = np.repeat(over, G, 1)
+    assert count > 0 and np.isfinite(o).all()
+    assert o[over].tobytes() == shifted[over].tobytes() and o[~over].tobytes() == plain[~over].tobytes()

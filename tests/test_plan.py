@@ -11,8 +11,15 @@ MSD = (P.MIXED, P.S16, P.DIRECT)
 @pytest.mark.parametrize("B,Hq,Hkv,Nq,row0,N,d,causal,variants,kernel,split", [
     # test_few_rows
     (2, 2, 2, 1, 0, 1, 128, True, MSD, "rows", False),
-    (2, 8, 2, 5, 4156, 4161, 128, True, MSD, "rows", True),
+    (2, 14, 2, 1, 62, 63, 64, True, MSD, "rows", False),
+    (2, 16, 2, 2, 62, 64, 128, True, MSD, "rows", False),
+    (2, 14, 2, 3, 62, 65, 64, True, MSD, "rows", False),
+    (2, 6, 2, 15, 600, 1025, 64, True, MSD, "rows", False),
+    (2, 4, 2, 16, 624, 640, 128, True, MSD, "rows", False),
+    (2, 4, 2, 17, 0, 513, 64, True, MSD, "rows", False),
     (2, 2, 2, 40, 2030, 2049, 128, True, MSD, "rows", True),
+    (2, 8, 2, 5, 4156, 4161, 128, True, MSD, "rows", True),
+    (2, 2, 2, 33, 0, 3000, 64, False, MSD, "rows", True),
     (2, 16, 2, 145, 7, 300, 128, True, MSD, "rows", False),
     (2, 16, 2, 129, 140, 257, 64, True, MSD, "rows", False),
     # test_many_rows_d64
@@ -28,6 +35,8 @@ MSD = (P.MIXED, P.S16, P.DIRECT)
     # test_workgroups_of_two_halves
     (1, 28, 4, 1024, 0, 1024, 128, True, MSD, "halves", False),
     (1, 28, 4, 900, 0, 900, 128, False, MSD, "halves", False),
+    (1, 28, 4, 1028, 0, 1028, 128, False, MSD, "halves", False),
+    (1, 28, 4, 1100, 0, 1100, 128, True, MSD, "halves", False),
     (1, 28, 4, 1000, 900, 2200, 128, True, MSD, "halves", False),
 ])
 def test_calls_reach_the_kernel_they_test(B, Hq, Hkv, Nq, row0, N, d, causal, variants, kernel, split):
