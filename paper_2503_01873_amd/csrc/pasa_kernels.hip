@@ -125,12 +125,13 @@ __device__ inline void sum_columns(double (&s)[8], double& w0, double& w1)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Pre-processing kernel.  grid = (B*Hkv*ceil(N/128) tiles, work groups of a tile), 256 threads.
+// Pre-processing kernel.  256 threads; 2 * PASA_PREP_SPLIT blocks for each of the B*Hkv*ceil(N/128) tiles, numbered as below.
 // plain_out != nullptr: write K' in the plain [.., N, D] layout instead (pasa_shift_keys).
 // A ragged last tile is padded with zero keys and zero values in the workspace.
 #ifndef PASA_PREP_SPLIT
 #define PASA_PREP_SPLIT 4
 #endif
+constexpr unsigned PREP_ROW = 1u << 20;     // blocks in a row of the grid, where it has more than one
 
 // One channel c of the two rows that key tile t owns in its "mean block" (a 32-row x D A operand per 16 tiles, in the
 // K' tile's chunk order: chunk (c/8)*32 + row holds channels 8*(c/8)..+7 of row `row`).  Tile t of the group has its
@@ -163,8 +164,8 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
     // Workgroups are dealt round-robin to the 8 XCDs: blocks of a tile that read parts of the same 128-byte lines of K follow one
     // another on one XCD and share its L2, neighbouring tiles go to neighbouring XCDs.  `group` blocks of a tile come
     // together, all of them or the key blocks of all tiles before the value blocks (see the launch).
-    // (Index of the block: gridDim.x is a multiple of 8, so the XCD is its remainder in every row of the grid.)
-    const unsigned index = blockIdx.y * gridDim.x + blockIdx.x;
+    // (Index of the block: where the grid has a second row, its rows hold PREP_ROW blocks, a multiple of 8.)
+    const unsigned index = blockIdx.y * PREP_ROW + blockIdx.x;
     const unsigned per = (tiles + 7) >> 3;               // tiles of an XCD
     unsigned pos = index >> 3;
     if (pos >= per * parts) return;                      // the grid's last row is not full
@@ -1142,8 +1143,8 @@ hipError_t pasa_launch_prep(const void* k, const void* v, void* ws, void* plain_
     const int ntile = (N + T - 1) / T;
     const int y_off = k == nullptr ? PASA_PREP_SPLIT : 0;     // no keys given: the value blocks alone
     const unsigned parts = (v != nullptr && k != nullptr ? 2 : 1) * PASA_PREP_SPLIT;      // of a tile: key channel groups, then value key groups
-    // A dimension of a grid holds fewer than 2^32 work items: beyond 2^20 blocks the launch goes on in a second dimension.
-    const size_t tiles = (size_t)B * Hkv * ntile, blocks = (tiles + 7) / 8 * 8 * parts, row = (size_t)1 << 20;
+    // A dimension of a grid holds fewer than 2^32 work items: beyond PREP_ROW blocks the launch goes on in a second dimension.
+    const size_t tiles = (size_t)B * Hkv * ntile, blocks = (tiles + 7) / 8 * 8 * parts, row = PREP_ROW;
     const dim3 grid((unsigned)(blocks < row ? blocks : row), (unsigned)((blocks + row - 1) / row));
     // The key blocks take longer: first where the launch is a few rounds (8 heads of 4096 keys, d = 128, 256 tiles: 8.9 us, mixed
     // 11.6; 512 tiles 17.6 / 18.8), in longer ones mixed, so that reading, arithmetic and writing overlap (2048 tiles 58.9 /
