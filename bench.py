@@ -32,12 +32,17 @@ WORKLOAD = "qwen2_gqa_n8192"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pasa_fwd_qwen2_gqa_n8192_hbm_traffic.txt")
 
 
-def kernel_source_hash():
+KERNEL_SOURCES = ("pasa_device.h", "pasa_kernels.hip")      # what the main kernel is built from
+
+
+def kernel_source_hash(read=None):
     """Hash of the kernel source as the compiler sees it: `//` comments and blank space do not count."""
     import hashlib
     h = hashlib.sha256()
-    with open(os.path.join(ROOT, "paper_2503_01873_amd", "csrc", "pasa_kernels.hip"), "r") as f:
-        for line in f:
+    for name in KERNEL_SOURCES:
+        path = os.path.join(ROOT, "paper_2503_01873_amd", "csrc", name)
+        text = read(path) if read else open(path).read()
+        for line in text.splitlines():
             code = " ".join(line.split("//")[0].split())
             if code:
                 h.update(code.encode() + b"\n")

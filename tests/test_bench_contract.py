@@ -28,6 +28,20 @@ def test_traffic_figure_comes_from_the_committed_counter_summary():
     assert bench.read_traffic() in (None, t)
 
 
+def test_traffic_stamp_covers_every_source_of_the_main_kernel():
+    sys.path.insert(0, ROOT)
+    import bench
+    csrc = os.path.join(ROOT, "paper_2503_01873_amd", "csrc")
+    main = open(os.path.join(csrc, "pasa_kernels.hip")).read()
+    device_headers = {l.split('"')[1] for l in main.splitlines() if l.startswith('#include "')} - {"pasa_kernels.h"}   # host declarations
+    assert device_headers | {"pasa_kernels.hip"} == set(bench.KERNEL_SOURCES)
+    plain = bench.kernel_source_hash()
+    for name in bench.KERNEL_SOURCES:
+        changed = bench.kernel_source_hash(lambda p: open(p).read() + ("int x;\n" if p.endswith(name) else ""))
+        commented = bench.kernel_source_hash(lambda p: open(p).read() + ("// x\n" if p.endswith(name) else ""))
+        assert changed != plain and commented == plain
+
+
 def test_workload_named_by_bench_is_the_metric_configuration():
     sys.path.insert(0, ROOT)
     import bench
