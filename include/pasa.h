@@ -87,7 +87,9 @@ typedef struct {
     int variant;       /* a pasa_variant */
     int shift_tile;    /* keys per pseudo-average group; 0 or 128 (the only supported size) */
     unsigned long long* overflow_s;  /* optional DEVICE counter (caller zeroes it): score-tile entries whose magnitude
-                                        exceeds 65504 where they would be stored as fp16.  NULL: not counted. */
+                                        exceeds 65504 where they would be stored as fp16.  NULL: not counted.
+                                        A call with either counter runs on the 256-row kernel, which counts: its output
+                                        agrees with that of the call without them up to rounding. */
     unsigned long long* nonfinite_o; /* optional DEVICE counter (caller zeroes it): inf/NaN entries written to o. */
     int shift_mode;    /* a pasa_shift_mode */
     int io_dtype;      /* a pasa_io_dtype; applies to q, k, v, o of the call it is passed to (the workspace is always

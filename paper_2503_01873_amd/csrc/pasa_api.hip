@@ -178,17 +178,18 @@ long rows_workgroups(int B, int Hkv, int G, int Nq, int rb)
 }
 
 // Blocks of 16 rows per workgroup.  One while that gives a workgroup to every compute unit at most: 28 heads on 4, d = 128,
-// us with one / two blocks: 128 rows (224 workgroups of one) of 2048 / 32768 keys 14.6 / 18.3, 157 / 185; 256 rows 22.6 /
-// 18.5, 295 / 189 (all before neighbours shared an L2).
+// 32767 keys, us with one / two blocks: 127 rows (224 workgroups of one) 146 / 187, 255 rows 276 / 190.
 int rows_blocks(int B, int Hkv, int G, int Nq)
 {
     return (long)G * Nq <= 16 || rows_workgroups(B, Hkv, G, Nq, 1) <= kComputeUnits ? 1 : 2;
 }
 
 // Workgroups that share the keys of a row block: as many as make two to a compute unit, each with a unit of 64 keys for
-// each of its four wavefronts at least.  Not up to 2048 keys: the merge kernel and its launch cost as much
-// there (1 row of 28 heads, 2048 keys: 10.2 us split, 13.0 not; 1024 keys: 8.1 not split), and a row's result stays
-// independent of the rows that are given with it.
+// each of its four wavefronts at least.  Not up to 2048 keys, so that a row's result there does not depend on how many rows and
+// sequences are given with it.  That is not where a split begins to pay: with the present merge kernel that is near 1400
+// keys (1 row, 28 heads on 4, d = 128, us not split / split: 500 keys 6.2 / 9.7, 1000 keys 7.7 / 8.9, 1500 keys 9.8 / 9.1,
+// 2047 keys 13.0 / 9.2; 4 sequences of 2047 keys 14.0 / 9.4).  Fewer than these where the workspace ends: its last region is sized by
+// wanted_splits (16 sequences of 1 row of 4999 keys get 4 of 8).
 int rows_splits(int B, int Hkv, int G, int Nq, int rb, int N, int keys)
 {
     const long groups = rows_workgroups(B, Hkv, G, Nq, rb), units = ((long)keys + 63) / 64;
@@ -198,8 +199,8 @@ int rows_splits(int B, int Hkv, int G, int Nq, int rb, int N, int keys)
     return ns < 1 ? 1 : (int)ns;
 }
 
-// pasa_fwd4: as many workgroups as are resident at once (three to a compute unit), pieces of 8 tiles at least.  Like above,
-// not up to 2048 keys.
+// pasa_fwd4: as many workgroups as are resident at once (three to a compute unit), pieces of 8 tiles at least.  Not up to
+// 2048 keys, for the same reason (a split would be two pieces of one).
 int fwd4_splits(int B, int Hq, int Nq, int N)
 {
     const long units = ((long)Nq + 127) / 128 * Hq * B, pieces = ((long)N + 1023) / 1024;
@@ -237,6 +238,9 @@ int fitting(int ns, size_t rows_all, int d, size_t room)
 // 14 sequences, 1 / 20 / 64 rows of 6000 keys, pasa_fwd / pasa_rows: 189 / 34, 189 / 65, 192 / 124.
 // S16, 28 heads on 4, pasa_fwd / pasa_rows: 1 row of 500 / 6000 / 16000 keys 15.8 / 6.4, 43.9 / 10.6, 47.9 / 12.4; 128 rows 17.3 / 7.7,
 // 114 / 40.1, 290 / 96.8; 16 heads, d = 64, 500 rows of 3000 keys 65.6 / 24.3.
+// The factors of the estimates are fitted to such lists, so they rank the kernels and are not times: 14 x 5 heads of 9216 rows,
+// d = 64, not causal, are put at 1843 us (pasa_fwd) and 1793 (pasa_fwd4) and take 1630 and 1490; a call whose estimates lie within
+// a few per cent may go to the slower kernel.
 // d = 64, pasa_fwd / pasa_fwd4: 14 x 5 heads of 1000 / 2000 / 4000 rows, not causal, 50.7 / 34.8, 134 / 103, 420 / 356, causal
 // 26.5 / 24.1, 70 / 60, 224 / 206; 2 x 16 heads of 4000 rows, not causal (a round and a third of pasa_fwd4) 174 / 184;
 // one head of 16384 rows, causal, both split: 79 / 67, and 101 with pasa_rows.
@@ -260,8 +264,9 @@ double unequal_rounds(double workgroups, double slots, double fixed, double most
 // levels, so all pieces go to the kernel of the whole.  That holds for launches of at least kSplitBelow workgroups of 256 rows
 // and for all up to 2048 keys; pieces start at multiples of 32 rows (rows of a wavefront stay together) and have 32 rows or
 // more.  Shorter ones are decoding steps, which would lose five times (16 x 1 row of 4999 keys: 33 us, 173 on the
-// kernel of the whole), except the end of a causal sequence of up to 2048 keys.  The cost: 128 rows of 2048 keys, 28 heads
-// on 4, take HALVES instead of pasa_rows.
+// kernel of the whole), except the end of a causal sequence of up to 2048 keys.  What it costs, us on the kernel of the whole /
+// on the one that is fastest, 28 heads on 4, d = 128: 128 rows of 2048 keys 31.6 / 13.8, 512 rows 31.6 / 26.7, 32 rows of
+// 1024 keys 19.4 / 8.6; 14 sequences, row 800 of 801 keys (every 32nd decoding step) 40 / 9.
 bool keeps_the_bits_of_the_whole(int B, int Hq, int Nq, int row0, int N, int causal)
 {
     if (wanted_splits(B, Hq, Nq, N) > 1 || (causal && row0 % 32 != 0)) return false;
@@ -278,7 +283,7 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
         row0 = 0;
     }
     const size_t rows_all = (size_t)B * Hq * Nq;
-    const double merge = 6.0;                                                               // us
+    const double merge = 6.0;      // us: its launch and 4 us for few rows, 8 for many
     Plan p = {Plan::FWD, 1, 0};
     if (may_split && variant != PASA_STRICT16) p.nsplit = fitting(wanted_splits(B, Hq, Nq, N), rows_all, d, room);
     if (counters || variant == PASA_STRICT16 || variant == PASA_NAIVE16) return p;
