@@ -27,15 +27,21 @@ __device__ inline h8 load_h8(const _Float16* p, int is_bf16)
     return *reinterpret_cast<const h8*>(p);
 }
 
-// fp32 -> bf16 bits, round to nearest even; NaN stays NaN
-__device__ inline unsigned short f32_to_bf16_rn(float f)
-{
-    const unsigned u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (unsigned short)((u >> 16) | 0x40u);
-    return (unsigned short)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
-}
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef float f2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+
+// Two fp32 values -> a pair of bf16 / fp16, nearest even (v_cvt_pk_bf16_f32, v_cvt_pk_f16_f32; NaN stays NaN)
+__device__ inline unsigned pack_bf16(float a, float b)
+{
+    const f2 v = {a, b};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf2));
+}
+__device__ inline unsigned pack_f16(float a, float b)
+{
+    const f2 v = {a, b};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, h2));
+}
 
 
 namespace {
@@ -101,6 +107,41 @@ template <int OFF>
 __device__ inline void copy_1k_to_lds(__amdgpu_buffer_rsrc_t src, int soff, char* ldst, int lane)
 {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)ldst, 16, lane * 16, soff, OFF, 0);
+}
+
+// The output of a wavefront's 32 query rows goes through LDS (`mine`: 64 * D bytes that no other wavefront uses), so that a store
+// writes 1 KiB of neighbouring bytes.  In the accumulator layout lane (lq, lh) holds channels 32 cb + 8 g + 4 lh .. + 3 of row lq:
+// value(cb, i) is the one of element i.  dst: the first row; `rows` of them are real.  16-byte chunks are placed by row ^ chunk,
+// against bank conflicts.  Straight from the accumulators, eight bytes a lane and a row apart, with the conversions of both types
+// in line, the end of a workgroup of 256 rows took 3.5 us.
+template <int D, bool BF16, class Value>
+__device__ inline void store_rows_as(char* mine, Value value, _Float16* dst, int rows, int lane)
+{
+    const int lq = lane & 31, lh = lane >> 5;
+#pragma unroll
+    for (int cb = 0; cb < D / 32; ++cb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            uint2 x;
+            x.x = BF16 ? pack_bf16(value(cb, 4 * g), value(cb, 4 * g + 1)) : pack_f16(value(cb, 4 * g), value(cb, 4 * g + 1));
+            x.y = BF16 ? pack_bf16(value(cb, 4 * g + 2), value(cb, 4 * g + 3)) : pack_f16(value(cb, 4 * g + 2), value(cb, 4 * g + 3));
+            *reinterpret_cast<uint2*>(mine + lq * (2 * D) + (((4 * cb + g) ^ (lq & 7)) * 16) + 8 * lh) = x;
+        }
+    __builtin_amdgcn_wave_barrier();             // a wavefront's LDS accesses are done in order
+    asm volatile("" ::: "memory");
+    constexpr int CH = D / 8, RPI = 64 / CH;     // chunks of a row, rows per store
+#pragma unroll
+    for (int i = 0; i < 32 / RPI; ++i) {
+        const int r = i * RPI + lane / CH, c = lane % CH;
+        const uint4 x = *reinterpret_cast<const uint4*>(mine + r * (2 * D) + ((c ^ (r & 7)) * 16));
+        if (r < rows) *reinterpret_cast<uint4*>(dst + (size_t)r * D + 8 * c) = x;
+    }
+}
+template <int D, class Value>
+__device__ inline void store_rows(char* mine, Value value, _Float16* dst, int rows, int lane, int io_bf16)
+{
+    if (io_bf16) store_rows_as<D, true>(mine, value, dst, rows, lane);
+    else store_rows_as<D, false>(mine, value, dst, rows, lane);
 }
 
 #define PASA_FENCE() __builtin_amdgcn_sched_barrier(0)

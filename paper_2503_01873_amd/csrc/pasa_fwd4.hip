@@ -126,11 +126,14 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
     for (int cb = 0; cb < CB; ++cb) O[cb] = (f16v)0.f;
     if (j0 < J_wg) {
         issue_k(j0, j0 & 1);
-        const _Float16* qsrc = q + (head * Nq + (row_valid ? row : 0)) * D + 8 * lh;
+        const __amdgpu_buffer_rsrc_t qbuf =             // rows past the end come as zeros
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(q + head * Nq * D), 0, Nq * (2 * D), 0x00020000);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const h8 raw = load_h8(qsrc + 16 * ks, io_bf16);
-            Qf[ks] = row_valid ? raw : (h8)(_Float16)0;
+        for (int ks = 0; ks < KS; ++ks)
+            Qf[ks] = __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(qbuf, row * (2 * D) + 16 * lh, 32 * ks, 0));
+        if (io_bf16) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) Qf[ks] = bf16x8_to_h8(__builtin_bit_cast(u16x8, Qf[ks]));
         }
     }
     const int nblk16 = (ntile + 15) >> 4;
@@ -269,24 +272,10 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
                 }
         return;
     }
+    // through the buffer of the last K' tile: all wavefronts have read it, and the copy that went beyond it is in the other one
     const float oscale = 1.0f / l;
-    _Float16* dst = o + (head * Nq + row) * D + 4 * lh;
-    if (row_valid)
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-            for (int gq = 0; gq < 4; ++gq) {
-                h4 out;
-                u16x4 outb;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float x = O[cb][4 * gq + r] * oscale;
-                    out[r] = (_Float16)x;
-                    outb[r] = f32_to_bf16_rn(x);
-                }
-                if (io_bf16) *reinterpret_cast<u16x4*>(dst + 32 * cb + 8 * gq) = outb;
-                else *reinterpret_cast<h4*>(dst + 32 * cb + 8 * gq) = out;
-            }
+    store_rows<D>(smem + ((J_wg - 1) & 1) * KT_BYTES + wave * (64 * D), [&](int cb, int i) { return O[cb][i] * oscale; },
+                  o + (head * Nq + qw0) * D, Nq - qw0, lane, io_bf16);
 }
 
 template <bool CAUSAL>

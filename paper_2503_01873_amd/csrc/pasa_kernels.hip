@@ -531,11 +531,17 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     if (j0 + jg < J_wg) issue_k(j0 + jg);
     issue_kmean(j0 >> 4);
 
-    // Q fragments: B operand, lane (query lq, half lh) holds channels 16*ks + 8*lh .. +7
+    // Q fragments: B operand, lane (query lq, half lh) holds channels 16*ks + 8*lh .. +7; rows past the end are out of the
+    // buffer's bounds and come as zeros
+    const __amdgpu_buffer_rsrc_t qbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(qbase), 0, Nq * (2 * D), 0x00020000);
     h8 Qf[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-        Qf[ks] = row_valid ? load_h8(qbase + (size_t)row * D + 16 * ks + 8 * lh, io_bf16) : (h8)(_Float16)0;
+        Qf[ks] = __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(qbuf, row * (2 * D) + 16 * lh, 32 * ks, 0));
+    if (io_bf16) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) Qf[ks] = bf16x8_to_h8(__builtin_bit_cast(u16x8, Qf[ks]));
+    }
 
     // per-row state (one query row per lane; both halves of the wave hold copies)
     float F = 0.f, m = NAIVE ? -__builtin_inff() : 0.f, l = 0.f;   // STRICT: always fp16-representable values
@@ -1046,33 +1052,23 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     if (wave_valid) {
         if (STRICT) fold16(J_w - 1);
         const float oscale = STRICT ? 0.f : 1.0f / l;
-        _Float16* obase = o + ((size_t)(b * Hq + hq) * Nq) * D;
+        // fp32 variants: the fp32 quotient is rounded once, to the output type; STRICT16: the fp16
+        // quotient of Algorithm 1's last line, converted when the output is bf16
+        auto value = [&](int cb, int i) {
+            return STRICT ? (float)(_Float16)(O16[cb][i >> 1][i & 1] / (_Float16)l) : O[cb][i] * oscale;
+        };
+        if (INSTR && row_valid) {
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
+            for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int gq = 0; gq < 4; ++gq) {
-                h4 out;
-                u16x4 outb;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = 4 * gq + r;
-                    // fp32 variants: the fp32 quotient is rounded once, to the output type; STRICT16: the fp16
-                    // quotient of Algorithm 1's last line, converted when the output is bf16
-                    const float v32 = STRICT ? (float)(_Float16)(O16[cb][i >> 1][i & 1] / (_Float16)l) : O[cb][i] * oscale;
-                    const _Float16 val = (_Float16)v32;
-                    outb[r] = f32_to_bf16_rn(v32);
-                    if (INSTR && row_valid) {
-                        const float fv = io_bf16 ? __uint_as_float((unsigned)outb[r] << 16) : (float)val;
-                        n_bad += (fv != fv || __builtin_fabsf(fv) == __builtin_inff()) ? 1u : 0u;
-                    }
-                    out[r] = val;
+                for (int i = 0; i < 16; ++i) {
+                    const float x = value(cb, i), fv = io_bf16 ? __uint_as_float(pack_bf16(x, 0.f) << 16) : (float)(_Float16)x;
+                    n_bad += (fv != fv || __builtin_fabsf(fv) == __builtin_inff()) ? 1u : 0u;
                 }
-                _Float16* dst = obase + (size_t)row * D + 32 * cb + 8 * gq + 4 * lh;
-                if (row_valid) {
-                    if (io_bf16) *reinterpret_cast<u16x4*>(dst) = outb;
-                    else *reinterpret_cast<h4*>(dst) = out;
-                }
-            }
+        }
+        // the tiles have been read by all wavefronts: both groups are past their last matrix parts (halves: where the wavefront
+        // has just read the other group's output)
+        store_rows<D>(smem + wave * (64 * D * KSPL), value, o + ((size_t)(b * Hq + hq) * Nq + qw0) * D, Nq - qw0, lane, io_bf16);
     }
     if (INSTR) {
         if (ovf_s != nullptr && n_ovf) atomicAdd(ovf_s, n_ovf);

@@ -392,16 +392,9 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
             }
         } else {
             const float inv = 1.0f / ls;
-            h4 out;
-            u16x4 outb;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float x = acc[i] * inv;
-                out[i] = (_Float16)x;
-                outb[i] = f32_to_bf16_rn(x);
-            }
-            if (io_bf16) *reinterpret_cast<u16x4*>(o + grow * D + c4) = outb;
-            else *reinterpret_cast<h4*>(o + grow * D + c4) = out;
+            acc *= inv;
+            *reinterpret_cast<uint2*>(o + grow * D + c4) = io_bf16 ? uint2{pack_bf16(acc[0], acc[1]), pack_bf16(acc[2], acc[3])}
+                                                                   : uint2{pack_f16(acc[0], acc[1]), pack_f16(acc[2], acc[3])};
         }
     }
 }
@@ -413,6 +406,13 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
 __device__ inline float merge_weight(double level, double top)
 {
     return level == -__builtin_inf() ? 0.f : __builtin_amdgcn_exp2f((float)(level - top) * LOG2E);
+}
+
+// infinity or NaN, by the bits of the output type: all exponent bits set
+__device__ inline unsigned not_finite(unsigned bits, int io_bf16)
+{
+    const unsigned exponent = io_bf16 ? 0x7f80u : 0x7c00u;
+    return (bits & exponent) == exponent ? 1u : 0u;
 }
 
 // Many rows: one thread per 8 channels of a row goes through the splits.
@@ -443,19 +443,15 @@ __global__ __launch_bounds__(256) void pasa_merge_splits(const float* __restrict
         }
     }
     const float inv = 1.0f / lsum;
-    h8 out;
-    u16x8 outb;
-    unsigned n_bad = 0;
+    unsigned out[4], n_bad = 0;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float v32 = acc[e] * inv;
-        out[e] = (_Float16)v32;
-        outb[e] = f32_to_bf16_rn(v32);
-        const float fv = io_bf16 ? __uint_as_float((unsigned)outb[e] << 16) : (float)out[e];
-        n_bad += (fv != fv || __builtin_fabsf(fv) == __builtin_inff()) ? 1u : 0u;
+    for (int e = 0; e < 8; ++e) acc[e] *= inv;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        out[e] = io_bf16 ? pack_bf16(acc[2 * e], acc[2 * e + 1]) : pack_f16(acc[2 * e], acc[2 * e + 1]);
+        n_bad += not_finite(out[e] & 0xffffu, io_bf16) + not_finite(out[e] >> 16, io_bf16);
     }
-    if (io_bf16) *reinterpret_cast<u16x8*>(o + grow * D + c0) = outb;
-    else *reinterpret_cast<h8*>(o + grow * D + c0) = out;
+    *reinterpret_cast<uint4*>(o + grow * D + c0) = uint4{out[0], out[1], out[2], out[3]};
     if (nonfinite_o != nullptr && n_bad) atomicAdd(nonfinite_o, (unsigned long long)n_bad);
 }
 
@@ -527,12 +523,9 @@ __global__ __launch_bounds__(D / 8 * SL) void pasa_merge_row(const float* __rest
         ls += w * lds_l[i];
     }
     x *= 1.0f / ls;
-    const _Float16 h = (_Float16)x;
-    const unsigned short hb = f32_to_bf16_rn(x);
-    if (io_bf16) reinterpret_cast<unsigned short*>(o)[row * D + tid] = hb;
-    else o[row * D + tid] = h;
-    const float fv = io_bf16 ? __uint_as_float((unsigned)hb << 16) : (float)h;
-    if (nonfinite_o != nullptr && (fv != fv || __builtin_fabsf(fv) == __builtin_inff())) atomicAdd(nonfinite_o, 1ull);
+    const unsigned bits = (io_bf16 ? pack_bf16(x, 0.f) : pack_f16(x, 0.f)) & 0xffffu;
+    reinterpret_cast<unsigned short*>(o)[row * D + tid] = (unsigned short)bits;
+    if (nonfinite_o != nullptr && not_finite(bits, io_bf16)) atomicAdd(nonfinite_o, 1ull);
 }
 
 template <int D>
