@@ -366,6 +366,8 @@ int pasa_internal_plan(int variant, int counters, int B, int Hq, int Hkv, int Nq
     return p.kernel;
 }
 
+unsigned pasa_internal_quotient(unsigned n, unsigned d) { return fast_div(d).quotient(n); }
+
 }  // extern "C"
 
 namespace {

@@ -75,8 +75,8 @@ __device__ inline float sum_row(float x)
 template <int D, int RB, int NW, bool S16>
 __global__ __launch_bounds__(64 * NW, 2)
 void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, const _Float16* __restrict__ kmean,
-               _Float16* __restrict__ o, int lists, int list_rows, int Nq, int row0, int N, int causal, int nblk, int nsplit,
-               int units, float coef, int tail_by_count, int io_bf16, const unsigned long long* gate,
+               _Float16* __restrict__ o, FastDiv lists, FastDiv Nq_, FastDiv nblk_, FastDiv nsplit_, int grid, int list_rows, int row0, int N,
+               int causal, int units, float coef, int tail_by_count, int io_bf16, const unsigned long long* gate,
                float* __restrict__ part_o, double* __restrict__ part_lr, size_t rows_all)
 {
     constexpr int KS = D / 32;                   // k-steps of the first GEMM
@@ -96,28 +96,31 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
     // work, in which the row blocks that read the same keys follow one another.  14 x 28 heads on 4, 64 rows of
     // 6000 keys: 124 us; with neighbours on different XCDs, where every L2 fetches every key, 241 us
     // Not for a single causal list, whose last range is the longest (one head of 16384 rows 173 -> 123 us).
-    int idx = blockIdx.x;
-    if (!causal || row0 >= Nq || (int)gridDim.x != nblk * nsplit) {
-        const int x = idx & 7, whole = gridDim.x >> 3, rest = gridDim.x & 7;
+    const int Nq = (int)Nq_.d, nblk = (int)nblk_.d, nsplit = (int)nsplit_.d;
+    unsigned idx = blockIdx.x;
+    if (!causal || row0 >= Nq || grid != nblk * nsplit) {
+        const unsigned x = idx & 7, whole = (unsigned)grid >> 3, rest = grid & 7;
         idx = x * whole + (x < rest ? x : rest) + (idx >> 3);
     }
     // causal: the longest blocks of a list first (8 heads of 3000 rows 38.0 -> 36.6 us, 5 of 8000 92.6 -> 86.4); not where a
     // block has four units per wavefront at most (28 heads of 777 rows 19.6 us, longest first 21.1; of 1024 rows 25.7 / 25.1)
-    int blk = idx % nblk;
+    unsigned up = nblk_.quotient(idx);
+    int blk = (int)nblk_.rest(idx, up);
     if (causal && N > 1024) blk = nblk - 1 - blk;
-    idx /= nblk;
-    const int list = idx % lists;
-    idx /= lists;
-    const int split = idx % nsplit;
-    const size_t grp = idx / nsplit;             // b * Hkv + hk
+    idx = up;
+    up = lists.quotient(idx);
+    const int list = (int)lists.rest(idx, up);
+    const unsigned kv_group = nsplit_.quotient(up);
+    const int split = (int)nsplit_.rest(up, kv_group);
+    const size_t grp = kv_group;                 // b * Hkv + hk
     if (gate != nullptr && gate[grp] == 0) return;   // adaptive start: nothing overflowed here
-    const size_t list0 = (grp * lists + list) * (size_t)list_rows;   // first row of the list, in q and o
+    const size_t list0 = (grp * lists.d + list) * (size_t)list_rows;   // first row of the list, in q and o
     const int p0 = blk * ROWS;
     int p1 = p0 + ROWS - 1;
     if (p1 > list_rows - 1) p1 = list_rows - 1;
 
     // keys seen by the block's rows: all up to the last position (causal), from the first position on only in part
-    const int h0 = p0 / Nq, h1 = p1 / Nq;
+    const int h0 = (int)Nq_.quotient(p0), h1 = (int)Nq_.quotient(p1);
     int first_pos = N - 1, last_pos = N - 1;
     if (causal) {
         const int lo = row0 + (h0 == h1 ? p0 - h0 * Nq : 0), hi = row0 + (h0 == h1 ? p1 - h1 * Nq : Nq - 1);
@@ -181,6 +184,19 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
         for (int cb = 0; cb < CB; ++cb) O[rb][cb] = (f4)0.f;
     }
 
+    // Query rows first: loads come back in the order they were asked for, and nothing can begin without these (behind the first keys
+    // and values they took 2.0 us of a workgroup's 8.9 in 28 heads of 777 rows).  Rows past the
+    // list's end are out of the buffer's bounds and come as zeros.
+    const __amdgpu_buffer_rsrc_t rows_in =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(q + list0 * D), 0, list_rows * (2 * D), 0x00020000);
+    constexpr int QN = QLDS ? RB * KS / NW : RB * KS;            // fragments that this wavefront loads: to be shared, or all of its own
+    h8 raw[QN];
+#pragma unroll
+    for (int n = 0; n < QN; ++n) {
+        const int at = QLDS ? n * NW + wave : n;                 // fragment: row block at / KS, k-step at % KS
+        raw[n] = load_frag(rows_in, (p0 + lq) * (2 * D) + 16 * g + at / KS * (32 * D), 64 * (at % KS));
+    }
+    PASA_FENCE();
     // the half tile whose keys A and B take first for unit u
     auto first_k = [](int u) { return S16 ? u ^ 1 : u; };
     if (u0 < ue) {
@@ -189,23 +205,25 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
         load_k(A, first_k(u0), 0);
         load_v(C, u0, 0);
     }
+    PASA_FENCE();
     int last[RB];                                // last key that the lane's row sees
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         const int p = p0 + 16 * rb + lq;
-        const bool real = p < list_rows;
         last[rb] = N - 1;
-        if (causal && real && row0 + p % Nq < N - 1) last[rb] = row0 + p % Nq;
-        const _Float16* src = q + (list0 + (real ? p : p0)) * D + 8 * g;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            if (QLDS && (rb * KS + ks) % NW != wave) continue;      // one fragment for each wavefront
-            const h8 raw = *reinterpret_cast<const h8*>(src + 32 * ks);
-            const h8 val = io_bf16 ? bf16x8_to_h8(__builtin_bit_cast(u16x8, raw)) : raw;
-            const h8 qv = real ? val : (h8)(_Float16)0;
-            if (QLDS) lds_q[(rb * KS + ks) * 64 + lane] = qv;
-            else Qr[QLDS ? 0 : rb][ks] = qv;
+        if (causal && p < list_rows) {
+            const int pos = row0 + (int)Nq_.rest(p, Nq_.quotient(p));
+            if (pos < N - 1) last[rb] = pos;
         }
+    }
+    if (io_bf16) {
+#pragma unroll
+        for (int n = 0; n < QN; ++n) raw[n] = bf16x8_to_h8(__builtin_bit_cast(u16x8, raw[n]));
+    }
+#pragma unroll
+    for (int n = 0; n < QN; ++n) {
+        if (QLDS) lds_q[(n * NW + wave) * 64 + lane] = raw[n];
+        else Qr[QLDS ? 0 : n / KS][n % KS] = raw[n];
     }
     if (QLDS) __syncthreads();
     if (u0 < ue) {
@@ -371,20 +389,29 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
         for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<f4*>(dst + 16 * cb) = O[rb][cb] * wgt;
     }
     __syncthreads();
-    for (int item = tid; item < ROWS * (D / 4); item += 64 * NW) {
-        const int r = item / (D / 4), c4 = (item % (D / 4)) * 4;
-        if (p0 + r >= list_rows) break;           // rows are in order: nothing real follows
-        f4 acc = (f4)0.f;
+    constexpr int STEP = 64 * NW / (D / 8);      // rows that the workgroup writes at a time, eight channels a lane
+#pragma unroll
+    for (int r0 = 0; r0 < ROWS; r0 += STEP) {
+        const int r = r0 + tid / (D / 8), c8 = tid % (D / 8) * 8;
+        f4 acc[2] = {(f4)0.f, (f4)0.f};
         float ls = 0.f;
+        if (ROWS % STEP != 0 && r >= ROWS) break;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            acc += *reinterpret_cast<const f4*>(lds_o + (w * ROWS + r) * LD + c4);
+            const f4* src = reinterpret_cast<const f4*>(lds_o + (w * ROWS + r) * LD + c8);
+            acc[0] += src[0];
+            acc[1] += src[1];
             ls += lds_l[w][r];
         }
         const size_t grow = list0 + p0 + r;
+        const bool real = p0 + r < list_rows;
         if (nsplit > 1) {
-            *reinterpret_cast<f4*>(part_o + ((size_t)split * rows_all + grow) * D + c4) = acc;
-            if (c4 == 0) {
+            if (real) {
+                f4* dst = reinterpret_cast<f4*>(part_o + ((size_t)split * rows_all + grow) * D + c8);
+                dst[0] = acc[0];
+                dst[1] = acc[1];
+            }
+            if (real && c8 == 0) {
                 double rmax = -__builtin_inf();
                 for (int w = 0; w < NW; ++w) rmax = __builtin_fmax(rmax, lds_r[w][r]);
                 part_lr[((size_t)split * rows_all + grow) * 2] = ls;
@@ -392,9 +419,13 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
             }
         } else {
             const float inv = 1.0f / ls;
-            acc *= inv;
-            *reinterpret_cast<uint2*>(o + grow * D + c4) = io_bf16 ? uint2{pack_bf16(acc[0], acc[1]), pack_bf16(acc[2], acc[3])}
-                                                                   : uint2{pack_f16(acc[0], acc[1]), pack_f16(acc[2], acc[3])};
+            unsigned out[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float x = acc[e >> 1][2 * (e & 1)] * inv, y = acc[e >> 1][2 * (e & 1) + 1] * inv;
+                out[e] = io_bf16 ? pack_bf16(x, y) : pack_f16(x, y);
+            }
+            if (real) *reinterpret_cast<uint4*>(o + grow * D + c8) = uint4{out[0], out[1], out[2], out[3]};
         }
     }
 }
@@ -556,9 +587,10 @@ hipError_t launch_rows(const PasaLaunch& p)
     const int all = (keys + U - 1) / U, units = (all + p.nsplit - 1) / p.nsplit;
     const int nsplit = (all + units - 1) / units;                 // none without keys
     const size_t rows_all = (size_t)p.B * p.Hq * p.Nq;
-    hipLaunchKernelGGL((pasa_rows<D, RB, NW, S16>), dim3((unsigned)((size_t)p.B * p.Hkv * lists * nblk * nsplit)), dim3(64 * NW), 0, p.stream,
-                       (const _Float16*)p.q, (const char*)p.ws, (const _Float16*)p.kmean, (_Float16*)p.o, lists, list_rows, p.Nq, p.row0,
-                       p.N, p.causal, nblk, nsplit, units, p.variant == PASA_K_DIRECT ? p.scale : p.inva,
+    const unsigned grid = (unsigned)((size_t)p.B * p.Hkv * lists * nblk * nsplit);
+    hipLaunchKernelGGL((pasa_rows<D, RB, NW, S16>), dim3(grid), dim3(64 * NW), 0, p.stream,
+                       (const _Float16*)p.q, (const char*)p.ws, (const _Float16*)p.kmean, (_Float16*)p.o, fast_div(lists), fast_div(p.Nq),
+                       fast_div(nblk), fast_div(nsplit), (int)grid, list_rows, p.row0, p.N, p.causal, units, p.variant == PASA_K_DIRECT ? p.scale : p.inva,
                        p.variant == PASA_K_MIXED ? 1 : 0, p.io_bf16, p.gate, (float*)p.part_o, (double*)p.part_lr, rows_all);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nsplit == 1) return e;

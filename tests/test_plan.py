@@ -52,3 +52,19 @@ def test_counters_and_fp16_state_stay_on_the_256_row_kernel():
                 assert plan_of(variant, 1, 28, 4, N, 0, N, d, True, counters=True)[0] == "fwd"
                 if variant in (P.STRICT16, P.NAIVE16):
                     assert plan_of(variant, 1, 28, 4, N, 0, N, d, True)[0] == "fwd"
+
+
+def test_division_by_a_number_that_the_host_knows():
+    """Exact for every n below 2^31: multiples of the divisor and their neighbours are where a rounded reciprocal goes wrong."""
+    import ctypes
+    import random
+    import torch  # noqa: F401  before the library, which then shares the HIP runtime that torch brings
+    f = P.lib().pasa_internal_quotient
+    f.argtypes, f.restype = [ctypes.c_uint, ctypes.c_uint], ctypes.c_uint
+    rng = random.Random(3)
+    top = (1 << 31) - 1
+    for d in [1, 2, 3, 5, 7, 28, 64, 65, 641, 262143, 262144, 6700417, (1 << 30) - 1, 1 << 30, (1 << 30) + 1, top] + [rng.randint(1, top) for _ in range(300)]:
+        for q in [0, 1, 2, top // d - 1, top // d] + [rng.randint(0, top // d) for _ in range(20)]:
+            for n in (q * d - 1, q * d, q * d + 1, top):
+                if 0 <= n <= top:
+                    assert f(n, d) == n // d, (n, d)
