@@ -117,6 +117,7 @@ __device__ inline void copy_1k_to_lds(__amdgpu_buffer_rsrc_t src, int soff, char
 template <int D, bool BF16, class Value>
 __device__ inline void store_rows_as(char* mine, Value value, _Float16* dst, int rows, int lane)
 {
+    asm volatile("" : "+v"(lane));               // no address is to be worked out before the main loop and kept through it
     const int lq = lane & 31, lh = lane >> 5;
 #pragma unroll
     for (int cb = 0; cb < D / 32; ++cb)

@@ -388,14 +388,23 @@ __device__ inline void for_constants(std::integer_sequence<int, I...>, F f) { (f
 // workgroups: faster where the longest chain bounds the launch (28 heads on 4, causal, 1024 / 2048 rows 29.7 -> 21.7, 50.9 -> 46.8
 // us), slower where the chip is full (8192 rows 446 -> 491 us: every tile is copied twice as often, and the 8-10 us that a
 // workgroup takes to fill and drain come twice).
+//
+// What a workgroup needs to know its place in the launch (see the decode), worked out on the host: with its divisions in the kernel
+// the first load went out 1.1 us after the workgroup's start.
+struct FwdPlace {
+    FastDiv nsplit, list, G;         // list: entries of a list that share a query tile
+    int mode, span_log2;             // PASA_FWD_*; SHARED: 8 >> span_log2 groups, each on 1 << span_log2 XCDs
+    int nwg, nqt, heads;             // workgroups without the key split, query tiles, B * Hq
+    float inv_tail;                  // 1 / keys of the last tile
+};
+enum { PASA_FWD_OWN_GROUPS, PASA_FWD_SHARED, PASA_FWD_PLAIN };
+
 template <int D, int VAR, bool CAUSAL, bool INSTR, int KSPL>
 __global__ __launch_bounds__(512, 2)
 void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Float16* __restrict__ o,
-              const _Float16* __restrict__ kmean, int Hq, int Hkv, int Nq, int row0, int N,
-              int nqt, float inva, float scale,
-              int io_bf16,
+              const _Float16* __restrict__ kmean, FwdPlace at, int Nq, int row0, int N, float inva, float scale, int io_bf16,
               unsigned long long* ovf_s, unsigned long long* nonfinite_o, unsigned long long* ovf_group,
-              const unsigned long long* gate, int nsplit, float* __restrict__ part_o, double* __restrict__ part_lr)
+              const unsigned long long* gate, float* __restrict__ part_o, double* __restrict__ part_lr)
 {
 
     constexpr int KS = D / 16;   // k-steps of S'^T = K' Q^T
@@ -442,41 +451,31 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     // consecutive places of an XCD's list is taken backwards: the engines' loads even out and items that are
     // neighbours in the list stay neighbours in time, which keeps the query heads of a KV head on the same key tiles
     // at the same time (numberings that balance better but scatter the list ran slower: they lose that L2 reuse).
-    const int split = blockIdx.x % nsplit;
-    int wg = blockIdx.x / nsplit;
+    const int nsplit = (int)at.nsplit.d;
+    unsigned wg = at.nsplit.quotient(blockIdx.x);
+    const int split = (int)at.nsplit.rest(blockIdx.x, wg);
+    const unsigned x = wg & 7;
     {
-        const int nwg = gridDim.x / nsplit, x = wg & 7, r = wg >> 3;
-        const int in_xcd = (nwg - x + 7) >> 3;             // workgroups of this XCD
+        const unsigned r = wg >> 3, in_xcd = ((unsigned)at.nwg - x + 7) >> 3;             // workgroups of this XCD
         if ((r & 4) && (r | 3) < in_xcd) wg = ((r ^ 3) << 3) | x;
     }
-    const int G = Hq / Hkv;                 // query heads per group
-    const int ngroups = (gridDim.x / nsplit) / (nqt * G);
     int qt, grp_id, hin;                    // query tile, group, head within group
-    if (ngroups % 8 == 0) {                 // each XCD owns ngroups/8 whole groups
-        const int x = wg & 7, r = wg >> 3, per = (ngroups >> 3) * G;
-        qt = nqt - 1 - r / per;
-        grp_id = x + 8 * ((r % per) / G);
-        hin = (r % per) % G;
-    } else if (8 % ngroups == 0 && (nqt * G) % (8 / ngroups) == 0) {   // each group is spread over 8/ngroups XCDs
-        const int span = 8 / ngroups, x = wg & 7, r = wg >> 3;
-        const int i = r * span + (x % span);
-        grp_id = x / span;
-        qt = nqt - 1 - i / G;
-        hin = i % G;
-    } else {                                // plain longest-first order
-        const int nbh = ngroups * G;
-        qt = nqt - 1 - wg / nbh;
-        grp_id = (wg % nbh) / G;
-        hin = (wg % nbh) % G;
+    {
+        const unsigned r = wg >> 3, span = 1u << at.span_log2;
+        const unsigned i = at.mode == PASA_FWD_OWN_GROUPS ? r : at.mode == PASA_FWD_SHARED ? r * span + (x & (span - 1)) : wg;
+        const unsigned up = at.list.quotient(i), rest = at.list.rest(i, up), g = at.G.quotient(rest);
+        qt = at.nqt - 1 - (int)up;
+        hin = (int)at.G.rest(rest, g);
+        grp_id = at.mode == PASA_FWD_OWN_GROUPS ? x + 8 * g      // each XCD owns whole groups
+                 : at.mode == PASA_FWD_SHARED ? x >> at.span_log2    // each group is spread over `span` XCDs: rest < G, g = 0
+                                              : g;                   // plain longest-first order
     }
     // adaptive start: nothing overflowed in this (batch, KV head), its shifted pass is not needed (whole workgroup leaves)
     if (gate != nullptr && gate[grp_id] == 0) return;
-    const int b = grp_id / Hkv, hk_ = grp_id % Hkv;
-    const int hq = hk_ * G + hin;
-    const int hk = hk_;
+    const size_t head = (size_t)grp_id * at.G.d + hin;           // b * Hq + hq
     const int ntile = (N + T - 1) / T;
     const int tail_keys = N % T;           // keys of a ragged last tile (0: none)
-    const float inv_tail = 1.0f / (float)(tail_keys ? tail_keys : T);
+    const float inv_tail = at.inv_tail;
 
     // Query row r of the Nq rows given sits at sequence position row0 + r (causal: it sees keys <= its position).
     const int q0 = qt * RWG;
@@ -493,7 +492,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     // this workgroup's key tiles [j0, J_wg): all of the tiles its rows see, or -- split -- one range of them, cut at
     // multiples of 16 tiles so that a range starts with a mean block of its own
     const int J_all = CAUSAL ? tiles_seen(last_row_wg) : ntile;
-    const int per16 = (((J_all + 15) >> 4) + nsplit - 1) / nsplit;
+    const int per16 = (int)at.nsplit.quotient(((J_all + 15) >> 4) + nsplit - 1);
     const bool splitting = !STRICT && nsplit > 1;      // STRICT16 is never launched split: its fp16 state has no merge rule
     const int j0 = splitting ? (split * per16 * 16 < J_all ? split * per16 * 16 : J_all) : 0;
     const int J_wg = splitting ? (j0 + per16 * 16 < J_all ? j0 + per16 * 16 : J_all) : J_all;
@@ -503,8 +502,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     const bool row_valid = row < Nq;       // rows past the end compute on zero queries and are never stored
     const int pos_w0 = row0 + qw0;         // position of the wave's first row
 
-    const _Float16* qbase = q + ((size_t)(b * Hq + hq) * Nq) * D;
-    const char* wsbase = ws + ((size_t)(b * Hkv + hk) * ntile) * TILE_BYTES;
+    const _Float16* qbase = q + head * Nq * D;
+    const char* wsbase = ws + (size_t)grp_id * ntile * TILE_BYTES;
     // raw buffer over this (batch, KV head)'s tiles: at most 2048 tiles of 64 KiB, so every offset fits 32 bits
     const __amdgpu_buffer_rsrc_t wsbuf =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(wsbase), 0, ntile * TILE_BYTES, 0x00020000);
@@ -512,7 +511,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     // mean blocks of this (batch, KV head): block g serves tiles 16g .. 16g+15; one 1 KiB piece per wave (D = 64: waves 0-3)
     const int nblk16 = (ntile + 15) >> 4;
     const __amdgpu_buffer_rsrc_t kmbuf = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<_Float16*>(MSBAR ? kmean + ((size_t)(b * Hkv + hk) * nblk16) * (32 * D) : q), 0, MSBAR ? nblk16 * KM_BYTES : 0,
+        const_cast<_Float16*>(MSBAR ? kmean + (size_t)grp_id * nblk16 * (32 * D) : q), 0, MSBAR ? nblk16 * KM_BYTES : 0,
         0x00020000);
     auto issue_kmean = [&](int g) {
         if (MSBAR && wave * 1024 < KM_BYTES && g < nblk16)
@@ -531,18 +530,21 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     if (j0 + jg < J_wg) issue_k(j0 + jg);
     issue_kmean(j0 >> 4);
 
-    // Q fragments: B operand, lane (query lq, half lh) holds channels 16*ks + 8*lh .. +7; rows past the end are out of the
-    // buffer's bounds and come as zeros
-    const __amdgpu_buffer_rsrc_t qbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(qbase), 0, Nq * (2 * D), 0x00020000);
-    h8 Qf[KS];
+    // Q fragments: B operand, lane (query lq, half lh) holds channels 16*ks + 8*lh .. +7.  The wavefront's rows come through LDS (the V
+    // buffers, which are free until barrier 0) as 1 KiB copies, 16-byte chunks placed by row ^ chunk against bank conflicts: a
+    // fragment's own load would touch 32 lines, and the first-level cache takes a line a clock for all eight wavefronts.
+    {
+        const __amdgpu_buffer_rsrc_t qbuf =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(qbase), 0, Nq * (2 * D), 0x00020000);
+        constexpr int CH = D / 8;
+        char* mine = smem + 2 * KT_BYTES + wave * (64 * D);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-        Qf[ks] = __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(qbuf, row * (2 * D) + 16 * lh, 32 * ks, 0));
-    if (io_bf16) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) Qf[ks] = bf16x8_to_h8(__builtin_bit_cast(u16x8, Qf[ks]));
+        for (int i = 0; i < D / 16; ++i) {
+            const int r = i * (64 / CH) + lane / CH, at_row = qw0 + r < Nq ? qw0 + r : Nq - 1;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(qbuf, (__attribute__((address_space(3))) void*)(mine + i * 1024), 16,
+                                                     at_row * (2 * D) + ((lane % CH) ^ (r & 7)) * 16, 0, 0, 0);
+        }
     }
-
     // per-row state (one query row per lane; both halves of the wave hold copies)
     float F = 0.f, m = NAIVE ? -__builtin_inff() : 0.f, l = 0.f;   // STRICT: always fp16-representable values
     float Lc = 0.f;                  // log of the scale of the stored output (fp32 variants)
@@ -604,6 +606,17 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     // vector part V(j) for group A (slot 2j+1) and V(j-1) for group B (slot 2j) -- the matrix part keeps its MFMA
     // chain free of them -- and drains them before the barrier that starts slot 2j+2, when group A reads them.
     drain_copies();
+    h8 Qf[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const h8 raw = *reinterpret_cast<const h8*>(smem + 2 * KT_BYTES + wave * (64 * D) + lq * (2 * D) + (((2 * ks + lh) ^ (lq & 7)) * 16));
+        Qf[ks] = row_valid ? raw : (h8)(_Float16)0;
+    }
+    if (io_bf16) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) Qf[ks] = bf16x8_to_h8(__builtin_bit_cast(u16x8, Qf[ks]));
+    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0): the rows have been read, the first values may take their place
     __syncthreads();                       // barrier 0: K'(0) is in LDS
     if (grp == 1) {
         if (KSPL == 1) issue_slot(j0);
@@ -1022,8 +1035,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     // ---------------- key split: leave the row state for the merge ----------------
     if (!STRICT && part_o != nullptr) {
         if (wave_valid) {
-            const size_t rows_all = (size_t)(gridDim.x / nsplit) / nqt * Nq;                     // B * Hq * Nq
-            const size_t grow = (size_t)(b * Hq + hq) * Nq + row;                                // global row index
+            const size_t rows_all = (size_t)at.heads * Nq;
+            const size_t grow = head * Nq + row;                                                 // global row index
             if (row_valid && lh == 0) {
                 part_lr[((size_t)split * rows_all + grow) * 2] = none ? 0.0 : (double)l;
                 part_lr[((size_t)split * rows_all + grow) * 2 + 1] =
@@ -1068,7 +1081,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
         }
         // the tiles have been read by all wavefronts: both groups are past their last matrix parts (halves: where the wavefront
         // has just read the other group's output)
-        store_rows<D>(smem + wave * (64 * D * KSPL), value, o + ((size_t)(b * Hq + hq) * Nq + qw0) * D, Nq - qw0, lane, io_bf16);
+        store_rows<D>(smem + wave * (64 * D * KSPL), value, o + (head * Nq + qw0) * D, Nq - qw0, lane, io_bf16);
     }
     if (INSTR) {
         if (ovf_s != nullptr && n_ovf) atomicAdd(ovf_s, n_ovf);
@@ -1097,9 +1110,21 @@ hipError_t launch_fwd(const PasaLaunch& p)
         if (e != hipSuccess) return e;
         lds_limit_set.fetch_or(bit, std::memory_order_release);
     }
+    const int G = p.Hq / p.Hkv, ngroups = p.B * p.Hkv, heads = p.B * p.Hq;
+    FwdPlace at;
+    at.nsplit = fast_div(nsplit);
+    at.G = fast_div(G);
+    at.mode = ngroups % 8 == 0 ? PASA_FWD_OWN_GROUPS
+              : 8 % ngroups == 0 && (nqt * G) % (8 / ngroups) == 0 ? PASA_FWD_SHARED : PASA_FWD_PLAIN;
+    at.list = fast_div(at.mode == PASA_FWD_OWN_GROUPS ? ngroups / 8 * G : at.mode == PASA_FWD_SHARED ? G : heads);
+    at.span_log2 = at.mode != PASA_FWD_SHARED ? 0 : ngroups == 1 ? 3 : ngroups == 2 ? 2 : 1;
+    at.nwg = nqt * heads;
+    at.nqt = nqt;
+    at.heads = heads;
+    at.inv_tail = 1.0f / (float)(p.N % T ? p.N % T : T);
     hipLaunchKernelGGL(kern, grid, dim3(512), LDS_BYTES, p.stream, (const _Float16*)p.q, (const char*)p.ws,
-                       (_Float16*)p.o, (const _Float16*)p.kmean, p.Hq, p.Hkv, p.Nq, p.row0, p.N, nqt, p.inva, p.scale, p.io_bf16, p.overflow_s,
-                       nsplit > 1 ? nullptr : p.nonfinite_o, p.overflow_group, p.gate, nsplit,
+                       (_Float16*)p.o, (const _Float16*)p.kmean, at, p.Nq, p.row0, p.N, p.inva, p.scale, p.io_bf16, p.overflow_s,
+                       nsplit > 1 ? nullptr : p.nonfinite_o, p.overflow_group, p.gate,
                        nsplit > 1 ? (float*)p.part_o : nullptr, nsplit > 1 ? (double*)p.part_lr : nullptr);
     e = hipGetLastError();
     if (e != hipSuccess || nsplit == 1) return e;
