@@ -1,4 +1,5 @@
-"""ctypes binding with the same names as include/pasa.h.  Argument marshalling only.
+"""Binding with the same names as include/pasa.h.  Argument marshalling only: in C (csrc/calls.c) for the calls that a program makes
+once per layer and step, through ctypes for the others.
 
 Tensors are anything with `.data_ptr()` (torch tensors on the GPU); raw integer addresses are accepted
 too.  Nothing here computes: if libpasa.so is missing or cannot be loaded the import of `lib()` fails
@@ -7,6 +8,7 @@ loudly -- there is no fallback path.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 MIXED, STRICT16, NAIVE16, S16, DIRECT = 0, 1, 2, 3, 4
@@ -85,6 +87,14 @@ def lib() -> ctypes.CDLL:
     L.pasa_status_string.restype = ctypes.c_char_p
     L.pasa_version.argtypes = []
     L.pasa_version.restype = ci
+    try:
+        from . import _calls
+    except ImportError as e:
+        raise FileNotFoundError(
+            f"{os.path.join(_PKG, '_calls.so')} is missing: build it with `python -m paper_2503_01873_amd.build`") from e
+    for name, marshal in (("pasa_attn_fwd", _calls.plain), ("pasa_attn_fwd_ex", _calls.whole), ("pasa_attn_fwd_adaptive", _calls.whole),
+                          ("pasa_prepare_kv", _calls.prepare), ("pasa_attn_fwd_chunk", _calls.chunk)):
+        setattr(L, "fast_" + name, functools.partial(marshal, ctypes.cast(getattr(L, name), vp).value))
     _lib = L
     return L
 
@@ -136,19 +146,15 @@ def pasa_attn_fwd_workspace_min(B, Hkv, N, d) -> int:
 
 
 def pasa_attn_fwd(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, stream=None, check=True) -> int:
-    st = lib().pasa_attn_fwd(_ptr(q), _ptr(k), _ptr(v), _ptr(o), B, Hq, Hkv, N, d, int(causal), float(scale),
-                             _stream(stream))
+    st = (_lib or lib()).fast_pasa_attn_fwd(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, stream)
     return _check(st, "pasa_attn_fwd", check)
 
 
 def pasa_attn_fwd_ex(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, workspace, workspace_bytes, stream=None,
                      beta=-1.0, variant=MIXED, shift_tile=128, overflow_s=None, nonfinite_o=None,
                      shift_mode=SHIFT_MEAN, io_dtype=IO_F16, opts_null=False, check=True) -> int:
-    opts = pasa_opts(float(beta), int(variant), int(shift_tile), _ptr(overflow_s), _ptr(nonfinite_o), int(shift_mode),
-                     int(io_dtype))
-    st = lib().pasa_attn_fwd_ex(_ptr(q), _ptr(k), _ptr(v), _ptr(o), B, Hq, Hkv, N, d, int(causal), float(scale),
-                                None if opts_null else ctypes.byref(opts), _ptr(workspace), int(workspace_bytes),
-                                _stream(stream))
+    st = (_lib or lib()).fast_pasa_attn_fwd_ex(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, workspace, workspace_bytes, stream,
+                                 beta, variant, shift_tile, overflow_s, nonfinite_o, shift_mode, io_dtype, opts_null)
     return _check(st, "pasa_attn_fwd_ex", check)
 
 
@@ -167,9 +173,8 @@ def pasa_attn_fwd_static(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, stream=Non
 
 def pasa_prepare_kv(k, v, B, Hkv, N, d, scale, workspace, workspace_bytes, stream=None, beta=-1.0, variant=MIXED,
                     shift_tile=128, shift_mode=SHIFT_MEAN, io_dtype=IO_F16, check=True) -> int:
-    opts = pasa_opts(float(beta), int(variant), int(shift_tile), None, None, int(shift_mode), int(io_dtype))
-    st = lib().pasa_prepare_kv(_ptr(k), _ptr(v), B, Hkv, N, d, float(scale), ctypes.byref(opts), _ptr(workspace),
-                               int(workspace_bytes), _stream(stream))
+    st = (_lib or lib()).fast_pasa_prepare_kv(k, v, B, Hkv, N, d, scale, workspace, workspace_bytes, stream, beta, variant, shift_tile,
+                                              None, None, shift_mode, io_dtype)
     return _check(st, "pasa_prepare_kv", check)
 
 
@@ -203,10 +208,8 @@ def pasa_shift_keys_matrix_mfma(k, kprime, B, Hkv, N, d, beta, kscale, stream=No
 def pasa_attn_fwd_chunk(q, o, B, Hq, Hkv, Nq, row0, N, d, causal, scale, workspace, workspace_bytes, stream=None,
                         beta=-1.0, variant=MIXED, shift_tile=128, overflow_s=None, nonfinite_o=None,
                         shift_mode=SHIFT_MEAN, io_dtype=IO_F16, check=True) -> int:
-    opts = pasa_opts(float(beta), int(variant), int(shift_tile), _ptr(overflow_s), _ptr(nonfinite_o), int(shift_mode),
-                     int(io_dtype))
-    st = lib().pasa_attn_fwd_chunk(_ptr(q), _ptr(o), B, Hq, Hkv, Nq, row0, N, d, int(causal), float(scale),
-                                   ctypes.byref(opts), _ptr(workspace), int(workspace_bytes), _stream(stream))
+    st = (_lib or lib()).fast_pasa_attn_fwd_chunk(q, o, B, Hq, Hkv, Nq, row0, N, d, causal, scale, workspace, workspace_bytes, stream,
+                                                  beta, variant, shift_tile, None, None, shift_mode, io_dtype)
     return _check(st, "pasa_attn_fwd_chunk", check)
 
 
@@ -219,9 +222,6 @@ def pasa_shift_keys_direct(k, kprime, k0, B, Hkv, N, d, beta, kscale, stream=Non
 def pasa_attn_fwd_adaptive(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, workspace, workspace_bytes, stream=None,
                            beta=-1.0, variant=MIXED, shift_tile=128, overflow_s=None, nonfinite_o=None,
                            shift_mode=SHIFT_MEAN, io_dtype=IO_F16, opts_null=False, check=True) -> int:
-    opts = pasa_opts(float(beta), int(variant), int(shift_tile), _ptr(overflow_s), _ptr(nonfinite_o), int(shift_mode),
-                     int(io_dtype))
-    st = lib().pasa_attn_fwd_adaptive(_ptr(q), _ptr(k), _ptr(v), _ptr(o), B, Hq, Hkv, N, d, int(causal), float(scale),
-                                      None if opts_null else ctypes.byref(opts), _ptr(workspace), int(workspace_bytes),
-                                      _stream(stream))
+    st = (_lib or lib()).fast_pasa_attn_fwd_adaptive(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, workspace, workspace_bytes, stream,
+                                 beta, variant, shift_tile, overflow_s, nonfinite_o, shift_mode, io_dtype, opts_null)
     return _check(st, "pasa_attn_fwd_adaptive", check)

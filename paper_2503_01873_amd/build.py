@@ -1,15 +1,17 @@
-"""Builds libpasa.so in-tree with hipcc for gfx950.  `python -m paper_2503_01873_amd.build`."""
+"""Builds libpasa.so (hipcc, gfx950) and the binding's _calls.so (C) in-tree.  `python -m paper_2503_01873_amd.build`."""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libpasa.so")
+CALLS = os.path.join(PKG, "_calls.so")
 SOURCES = ["pasa_api.hip", "pasa_kernels.hip", "pasa_fwd4.hip", "pasa_rows.hip", "pasa_shift_gemm.hip"]
 
 FLAGS = [
@@ -32,11 +34,23 @@ def hipcc() -> str:
     return exe
 
 
+def build_calls(verbose: bool = False) -> str:
+    cmd = [shutil.which("gcc") or hipcc(), "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"],
+           "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "calls.c"), "-o", CALLS]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("the binding's extension does not compile:\n" + res.stdout + res.stderr)
+    return CALLS
+
+
 def build(verbose: bool = False, extra_flags=(), out: str = LIB) -> str:
     cmd = [hipcc(), *FLAGS, *extra_flags, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
            *[os.path.join(CSRC, s) for s in SOURCES], "-o", out]
     if verbose:
         print(" ".join(cmd), flush=True)
+    build_calls(verbose)
     res = subprocess.run(cmd, capture_output=True, text=True)
     log = (res.stdout + res.stderr)
     # hipcc's host pass does not know the packed-fp32 feature name; that warning is expected

@@ -1,0 +1,54 @@
+"""How the binding takes its arguments (the same as through ctypes); nothing is launched: every call is one that is refused."""
+import ctypes
+
+import pytest
+
+import paper_2503_01873_amd as P
+
+A = 1 << 20      # an address that is never followed
+
+
+class Buffer:
+    def data_ptr(self):
+        return A
+
+
+class Stream:
+    cuda_stream = 0
+
+
+def chunk(**kw):
+    a = dict(q=A, o=2 * A, B=1, Hq=2, Hkv=1, Nq=4, row0=0, N=64, d=64, causal=True, scale=0.125, workspace=A, workspace_bytes=1, check=False)
+    a.update(kw)
+    return P.pasa_attn_fwd_chunk(**a)
+
+
+@pytest.mark.parametrize("kw,status", [
+    ({}, 4), ({"q": None}, 1), ({"q": 2 * A}, 1), ({"q": Buffer()}, 4), ({"stream": Stream()}, 4), ({"stream": 0}, 4), ({"d": 96}, 2),
+    ({"N": (1 << 32) + 64}, 4), ({"N": 0}, 1), ({"Nq": -1}, 1), ({"workspace_bytes": 1.0}, 4), ({"scale": 1}, 4), ({"causal": 2}, 1),
+    ({"variant": 9}, 1), ({"beta": 1.0}, 1), ({"shift_tile": 64}, 2), ({"io_dtype": 2}, 1), ({"workspace": None, "workspace_bytes": 1 << 30}, 4),
+])
+def test_arguments_reach_the_library(kw, status):
+    assert chunk(**kw) == status
+
+
+@pytest.mark.parametrize("kw,error", [
+    ({"N": 64.0}, ctypes.ArgumentError), ({"B": "1"}, ctypes.ArgumentError), ({"q": 1.5}, AttributeError), ({"q": "x"}, AttributeError),
+    ({"scale": "x"}, ValueError), ({"causal": None}, TypeError), ({"stream": "x"}, AttributeError), ({"variant": "x"}, ValueError),
+])
+def test_what_is_no_argument_is_refused(kw, error):
+    with pytest.raises(error):
+        chunk(**kw)
+
+
+def test_every_route_raises_with_the_entry_points_name():
+    for name, call in (
+        ("pasa_attn_fwd:", lambda: P.pasa_attn_fwd(None, A, A, A, 1, 1, 1, 64, 64, False, 0.125)),
+        ("pasa_attn_fwd_ex:", lambda: P.pasa_attn_fwd_ex(None, A, A, A, 1, 1, 1, 64, 64, False, 0.125, A, 1)),
+        ("pasa_attn_fwd_adaptive:", lambda: P.pasa_attn_fwd_adaptive(None, A, A, A, 1, 1, 1, 64, 64, False, 0.125, A, 1)),
+        ("pasa_prepare_kv:", lambda: P.pasa_prepare_kv(None, A, 1, 1, 64, 64, 0.125, A, 1)),
+        ("pasa_attn_fwd_chunk:", lambda: chunk(q=None, check=True)),
+    ):
+        with pytest.raises(P.PasaError, match=name) as e:
+            call()
+        assert e.value.status == 1
