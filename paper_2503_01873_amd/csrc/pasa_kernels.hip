@@ -158,8 +158,8 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
                                                     _Float16* __restrict__ wsout,
                                                     _Float16* __restrict__ plain_out, _Float16* __restrict__ k0out,
                                                     _Float16* __restrict__ kmean_out,
-                                                    int N, int ntile, double beta, double kscale, int shift_mode,
-                                                    int in_bf16, const unsigned long long* gate, unsigned tiles, unsigned parts, unsigned group, int y_off)
+                                                    int N, FastDiv ntile_, double beta, double kscale, int shift_mode,
+                                                    int in_bf16, const unsigned long long* gate, unsigned tiles, unsigned parts, unsigned group_log2, int y_off)
 {
     // Workgroups are dealt round-robin to the 8 XCDs: blocks of a tile that read parts of the same 128-byte lines of K follow one
     // another on one XCD and share its L2, neighbouring tiles go to neighbouring XCDs.  `group` blocks of a tile come
@@ -170,15 +170,18 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
     unsigned pos = index >> 3;
     if (pos >= per * parts) return;                      // the grid's last row is not full
     unsigned part = 0;
-    if (pos >= per * group) {
-        pos -= per * group;
-        part = group;
+    if (pos >= per << group_log2) {
+        pos -= per << group_log2;
+        part = 1u << group_log2;
     }
-    part += pos % group;
-    const size_t tile = (size_t)(pos / group) * 8 + (index & 7);    // (batch, KV head, key tile)
-    if (tile >= tiles) return;
+    part += pos & ((1u << group_log2) - 1);
+    const unsigned tile_ = (pos >> group_log2) * 8 + (index & 7);   // (batch, KV head, key tile)
+    if (tile_ >= tiles) return;
+    const int ntile = (int)ntile_.d;
+    const unsigned head_ = ntile_.quotient(tile_);
+    const size_t tile = tile_, head = head_;
     // adaptive start: nothing overflowed in this (batch, KV head), its shifted pass is not needed
-    if (gate != nullptr && gate[tile / ntile] == 0) return;
+    if (gate != nullptr && gate[head] == 0) return;
 
     // A tile's work is cut into 2*NS blocks: NS groups of D/NS channels of K (column means are per
     // channel, so the groups are independent) and NS groups of 128/NS keys of V.  The pass is bound by memory
@@ -192,24 +195,36 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
     constexpr size_t PSUM_BYTES = sizeof(double) * (2 * 4 + 1) * DB, VS_BYTES = sizeof(_Float16) * TB * (D + 8);
     __shared__ __attribute__((aligned(16))) char lds_raw[PSUM_BYTES > VS_BYTES ? PSUM_BYTES : VS_BYTES];
 
-    const size_t head = tile / ntile;
-    const int t = (int)(tile % ntile);
+    const int t = (int)ntile_.rest(tile_, head_);
     const int nvalid = (N - t * T) < T ? (N - t * T) : T;    // keys of this tile (< 128 only in a ragged last tile)
     const size_t src_off = (head * (size_t)N + (size_t)t * T) * D;
     const int tid = threadIdx.x;
 
+    // All loads of a thread are on the way at once: rows past the end are out of the buffer's bounds and come as zeros, bf16 is converted
+    // afterwards.  With a branch for each of both, and the tile's place by division, 8 x 4 heads of 8192 keys took 53.5 us, now 49.5
+    // (4.85 -> 5.4 TB/s); 14 x 5 heads of 5000 keys, d = 64, 8 % less.
+    auto rows_of = [](const _Float16* x, size_t h, int rows) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(x) + h * (size_t)rows * D, 0, rows * (2 * D), 0x00020000);
+    };
+    auto load_row = [](__amdgpu_buffer_rsrc_t src, int row, int c8) {
+        return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(src, row * (2 * D) + 16 * c8, 0, 0));
+    };
     const int by = (int)part + y_off;              // y_off = NS: only the value blocks are launched
     if (by >= NS) {
         // ---- values: keys [n0, n0 + TB) of the tile, all channels ----
         _Float16 (*vs)[D + 8] = reinterpret_cast<_Float16 (*)[D + 8]>(lds_raw);   // +8 halfs: rows 16 bytes apart in bank space
         const int n0 = (by - NS) * TB;
-        const _Float16* vsrc = v + src_off;
-        constexpr int VCH = D / 8;
-        for (int idx = tid; idx < TB * VCH; idx += 256) {
-            const int nl = idx / VCH, c8 = idx % VCH, n = n0 + nl;
-            *reinterpret_cast<h8*>(&vs[nl][8 * c8]) =
-                n < nvalid ? load_h8(vsrc + (size_t)n * D + 8 * c8, in_bf16) : (h8)(_Float16)0;
+        constexpr int VCH = D / 8, VPT = TB * VCH / 256;
+        const __amdgpu_buffer_rsrc_t vsrc = rows_of(v, head, N);
+        h8 raw[VPT];
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) raw[i] = load_row(vsrc, t * T + n0 + (tid + 256 * i) / VCH, (tid + 256 * i) % VCH);
+        if (in_bf16) {
+#pragma unroll
+            for (int i = 0; i < VPT; ++i) raw[i] = bf16x8_to_h8(__builtin_bit_cast(u16x8, raw[i]));
         }
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) *reinterpret_cast<h8*>(&vs[(tid + 256 * i) / VCH][8 * ((tid + 256 * i) % VCH)]) = raw[i];
         __syncthreads();
         _Float16* vdst = wsout + tile * (size_t)(2 * T * D) + T * D;
         const int chunk0 = (n0 / 16) * 2 * D;            // chunk ((n/16)*2 + h)*D + c; this block owns TB/16*2 values of (n/16)*2+h
@@ -233,14 +248,18 @@ __global__ __launch_bounds__(256) void pasa_prep_kv(const _Float16* __restrict__
     const int c8 = tid % CH, kl = tid / CH;
     const int ch0 = cg * DB + 8 * c8;                    // first of this thread's 8 channels
     const int cw = 8 * c8 + 4 * (lane >> 5) + 2 * ((lane >> 4) & 1);   // first of the two channels it has the wavefront's sums of
-    const _Float16* ksrc = k + src_off;
+    const __amdgpu_buffer_rsrc_t ksrc = rows_of(k, head, N);
 
     h8 kv[KPT];
     double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
+    for (int i = 0; i < KPT; ++i) kv[i] = load_row(ksrc, t * T + kl + KL * i, ch0 / 8);
+    if (in_bf16) {
+#pragma unroll
+        for (int i = 0; i < KPT; ++i) kv[i] = bf16x8_to_h8(__builtin_bit_cast(u16x8, kv[i]));
+    }
+#pragma unroll
     for (int i = 0; i < KPT; ++i) {
-        const int n = kl + KL * i;
-        kv[i] = n < nvalid ? load_h8(ksrc + (size_t)n * D + ch0, in_bf16) : (h8)(_Float16)0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) s[e] += (double)kv[i][e];   // exact: fp16 values, at most 128 terms
     }
@@ -1170,13 +1189,14 @@ hipError_t pasa_launch_prep(const void* k, const void* v, void* ws, void* plain_
     // The key blocks take longer: first where the launch is a few rounds (8 heads of 4096 keys, d = 128, 256 tiles: 8.9 us, mixed
     // 11.6; 512 tiles 17.6 / 18.8), in longer ones mixed, so that reading, arithmetic and writing overlap (2048 tiles 58.9 /
     // 55.4; 14 x 5 heads of 9216 keys, d = 64: 82.9 / 80.3; both in plain order 63.5 and 92.5, before that 65.0 and 94.5).
-    const unsigned group = tiles < 1024 ? PASA_PREP_SPLIT : parts;
+    static_assert((PASA_PREP_SPLIT & (PASA_PREP_SPLIT - 1)) == 0, "blocks that come together are counted by shifts");
+    const unsigned group = tiles < 1024 ? PASA_PREP_SPLIT : parts, group_log2 = (unsigned)__builtin_ctz(group);
     if (d == 128)
         hipLaunchKernelGGL(pasa_prep_kv<128>, grid, dim3(256), 0, stream, (const _Float16*)k, (const _Float16*)v,
-                           (_Float16*)ws, (_Float16*)plain_out, (_Float16*)k0out, (_Float16*)kmean_out, N, ntile, beta, kscale, shift_mode, in_bf16, gate, (unsigned)tiles, parts, group, y_off);
+                           (_Float16*)ws, (_Float16*)plain_out, (_Float16*)k0out, (_Float16*)kmean_out, N, fast_div(ntile), beta, kscale, shift_mode, in_bf16, gate, (unsigned)tiles, parts, group_log2, y_off);
     else
         hipLaunchKernelGGL(pasa_prep_kv<64>, grid, dim3(256), 0, stream, (const _Float16*)k, (const _Float16*)v,
-                           (_Float16*)ws, (_Float16*)plain_out, (_Float16*)k0out, (_Float16*)kmean_out, N, ntile, beta, kscale, shift_mode, in_bf16, gate, (unsigned)tiles, parts, group, y_off);
+                           (_Float16*)ws, (_Float16*)plain_out, (_Float16*)k0out, (_Float16*)kmean_out, N, fast_div(ntile), beta, kscale, shift_mode, in_bf16, gate, (unsigned)tiles, parts, group_log2, y_off);
     return hipGetLastError();
 }
 
