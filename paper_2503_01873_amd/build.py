@@ -22,6 +22,7 @@ FLAGS = [
     "-shared",
     "-ffp-contract=off",          # every rounding the method states is a separate operation
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",   # a kernel's first arguments come in registers: a row of 32768 keys 16.05 -> 15.8 us
     "-Wall",
     "-Wno-unused-function",
 ]
