@@ -209,7 +209,7 @@ def pasa_attn_fwd_chunk(q, o, B, Hq, Hkv, Nq, row0, N, d, causal, scale, workspa
                         beta=-1.0, variant=MIXED, shift_tile=128, overflow_s=None, nonfinite_o=None,
                         shift_mode=SHIFT_MEAN, io_dtype=IO_F16, check=True) -> int:
     st = (_lib or lib()).fast_pasa_attn_fwd_chunk(q, o, B, Hq, Hkv, Nq, row0, N, d, causal, scale, workspace, workspace_bytes, stream,
-                                                  beta, variant, shift_tile, None, None, shift_mode, io_dtype)
+                                                  beta, variant, shift_tile, overflow_s, nonfinite_o, shift_mode, io_dtype)
     return _check(st, "pasa_attn_fwd_chunk", check)
 
 

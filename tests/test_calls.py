@@ -52,3 +52,16 @@ def test_every_route_raises_with_the_entry_points_name():
         with pytest.raises(P.PasaError, match=name) as e:
             call()
         assert e.value.status == 1
+
+
+def test_counters_of_a_chunk_reach_the_library():
+    """A chunk with a counter passes every check and is refused by its workspace; the counter's address is looked at on the way."""
+    class Counter:
+        asked = 0
+
+        def data_ptr(self):
+            Counter.asked += 1
+            return A
+
+    c = Counter()
+    assert chunk(overflow_s=c, nonfinite_o=c) == 4 and Counter.asked == 2
