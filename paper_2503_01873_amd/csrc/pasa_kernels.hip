@@ -584,6 +584,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
         for (int t = 0; t < 8; ++t) O16[cb][t] = (h2)(_Float16)0;
     }
 
+    float l_tile = 0.f;              // STRICT, d = 128: sum of the tile's P, pending like its product
     // STRICT: fold the product of tile jt (in O) into the running fp16 output
     auto fold16 = [&](int jt) {
         const _Float16 ec = (_Float16)ec_s, ep = (_Float16)ep_s;
@@ -597,6 +598,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                 const h2 a2 = ep2 * O16[cb][t];
                 O16[cb][t] = a1 + a2;
             }
+        // the running sum (step 4), each operation rounded: l = fp16(fp16(e^{dm_{j-1}} l) + fp16(e^{dm_j} l')); first tile: 0 + l'
+        if (D == 128) l = (float)(_Float16)((_Float16)(ep * (_Float16)l) + (_Float16)(ec * (_Float16)l_tile));
     };
 
     // The copies of a slot are K'(jl + KSPL) and V(jl); each wave owns 2*CPW of their 1 KiB pieces.
@@ -649,13 +652,16 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     // GEMM (which reads the same P fragments): the wave has issue slots to spare there (an MFMA occupies the matrix core
     // for 32 cycles), while in the vector part every instruction counts.  0.7 % on the headline workload, although the
     // vector part loses 64 of its 330 instructions: the kernel's clock, not its cycle count, is the limit.  (MIXED and
-    // DIRECT; S16 and NAIVE16, whose vector part sums with v_dot2_f32_f16, lose 1.2 % by it and keep their sums there.)
+    // DIRECT; S16 and NAIVE16, whose vector part sums with v_dot2_f32_f16, lose 1.2 % by it and keep their sums there.
+    // STRICT16, with two partial sums where the others have four, for want of registers: 28 heads of 4001 rows 154.3 -> 152.5 us, of
+    // 8192 rows 555 -> 549.  With both of its sums on the matrix core, against ones, it takes a fifth longer: the products of a sum
+    // depend on one another and wait behind the other wavefront's.)
     // d = 64: the vector part is 2.7 times as long as the matrix part (the softmax is the same work, the GEMMs half),
     // and the sum moves onto the idle matrix core itself: one more MFMA per k-step of the second GEMM, P^T against a
     // block of ones, accumulates the row sums beside the stored output, at the same scale (every row of the result is
     // the sum).  4 % on the d = 64 workload (the first way is 2 % slower there; this way is 2.4 % slower at d = 128).
     constexpr bool LSUM_MFMA = LAZY && D == 64;
-    constexpr bool LSUM_DEFER = LAZY && D == 128 && MSBAR;
+    constexpr bool LSUM_DEFER = D == 128 && (MSBAR || STRICT);
     f16v Lacc = (f16v)0.f;
     const h8 ones = (h8)(_Float16)1;
     float pl_d[4] = {0.f, 0.f, 0.f, 0.f};
@@ -719,13 +725,15 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                 for (int u = 0; u < PER; ++u) {
                     const int pr = n * PER + u;          // pair pr: Pf[pr / 4], elements 2 * (pr % 4), + 1
                     const h2 p2 = {Pf[pr / 4][2 * (pr % 4)], Pf[pr / 4][2 * (pr % 4) + 1]};
-                    pl_d[pr & 3] = add_pair_mix(p2, pl_d[pr & 3]);
+                    pl_d[pr & (STRICT ? 1 : 3)] = add_pair_mix(p2, pl_d[pr & (STRICT ? 1 : 3)]);
                 }
                 PASA_FENCE();
             }
         }
         if (LSUM_DEFER) {
-            l += sum32((pl_d[0] + pl_d[1]) + (pl_d[2] + pl_d[3]));
+            const float sum = sum32((pl_d[0] + pl_d[1]) + (pl_d[2] + pl_d[3]));
+            if (STRICT) l_tile = sum;
+            else l += sum;
             pl_d[0] = pl_d[1] = pl_d[2] = pl_d[3] = 0.f;
         }
     };
@@ -991,7 +999,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
             // ---- the running sum (step 4); STRICT16: the whole of step 3 and 4 in fp16 ----
             if (LAZY) {
                 l += lsum;                     // the sum is kept at the stored output's scale (first tile: l was 0)
-            } else {
+            } else if (!LSUM_DEFER) {
                 // fp16, each operation rounded: l = fp16(fp16(e^{dm_{j-1}} l) + fp16(e^{dm_j} l')); first tile: l = l'
                 const _Float16 lo = (_Float16)l, ln = (_Float16)lsum;
                 const float ln_all = (float)(_Float16)((_Float16)((_Float16)ep_s * lo) + (_Float16)((_Float16)ec_s * ln));
