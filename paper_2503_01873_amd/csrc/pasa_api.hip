@@ -238,25 +238,28 @@ int fitting(int ns, size_t rows_all, int d, size_t room)
 // 14 sequences, 1 / 20 / 64 rows of 6000 keys, pasa_fwd / pasa_rows: 189 / 34, 189 / 65, 192 / 124.
 // S16, 28 heads on 4, pasa_fwd / pasa_rows: 1 row of 500 / 6000 / 16000 keys 15.8 / 6.4, 43.9 / 10.6, 47.9 / 12.4; 128 rows 17.3 / 7.7,
 // 114 / 40.1, 290 / 96.8; 16 heads, d = 64, 500 rows of 3000 keys 65.6 / 24.3.
-// The factors of the estimates are fitted to such lists, so they rank the kernels and are not times: 14 x 5 heads of 9216 rows,
+// d = 128, causal, pasa_fwd / HALVES / pasa_rows: 28 heads of 614 / 768 / 1035 / 2196 rows 16.0 / 13.6 / 15.1, 20.6 / 15.0 / 16.8, 25.5 / 19.4 /
+// 23.9, 52.9 / 45.1 / 66.2 (of these only 1035 is planned on the fastest); 12 heads on 2 of 2185 rows 47.6 / 30.2 / 35.7; 4 x 8 heads of
+// 651 rows 20.1 / 14.5 / 16.1.
+// The factors of the estimates are fitted to 220 such calls of 150 to 6000 keys (on average 0.2 % behind the fastest kernel), so they rank the kernels and are not times: 14 x 5 heads of 9216 rows,
 // d = 64, not causal, are put at 1843 us (pasa_fwd) and 1793 (pasa_fwd4) and take 1630 and 1490; a call whose estimates lie within
 // a few per cent may go to the slower kernel.
 // d = 64, pasa_fwd / pasa_fwd4: 14 x 5 heads of 1000 / 2000 / 4000 rows, not causal, 50.7 / 34.8, 134 / 103, 420 / 356, causal
 // 26.5 / 24.1, 70 / 60, 224 / 206; 2 x 16 heads of 4000 rows, not causal (a round and a third of pasa_fwd4) 174 / 184;
 // one head of 16384 rows, causal, both split: 79 / 67, and 101 with pasa_rows.
 
-// Equal workgroups, `slots` of them at once, each `fixed` us and `tiles` steps of 2.4 us -- 3.95 when all compute units
-// are busy (power), which takes part of the way with the square of the share that is.
+// Equal workgroups, `slots` of them at once, each `fixed` us and `tiles` steps of 2.5 us -- 2.8 when all compute units
+// are busy (power; sustained it is 3.5, for both kernels alike), which takes part of the way with the square of the share that is.
 double equal_rounds(double workgroups, double slots, double fixed, double tiles)
 {
     const double whole = floor(workgroups / slots), rest = (workgroups - whole * slots) / slots;
-    return whole * (fixed + 3.95 * tiles) + (rest > 0 ? fixed + (2.4 + 1.55 * rest * rest) * tiles : 0.0);
+    return whole * (fixed + 2.8 * tiles) + (rest > 0 ? fixed + (2.5 + 0.3 * rest * rest) * tiles : 0.0);
 }
 
 // Causal: `most` steps in the longest workgroup and `mean` on average, longest first.
 double unequal_rounds(double workgroups, double slots, double fixed, double most, double mean)
 {
-    const double chain = fixed + 2.55 * most, work = workgroups / slots * (fixed + 3.55 * mean);
+    const double chain = fixed + 2.23 * most, work = workgroups / slots * (fixed + 3.41 * mean);
     return chain > work ? chain + 0.1 * work : work + 0.1 * chain;
 }
 
@@ -301,17 +304,21 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
     {
         if (may_split) r.nsplit = fitting(rows_splits(B, Hkv, G, Nq, r.row_blocks, N, most), rows_all, d, room);
         if ((long)G * Nq <= 16) return r;
+        // a split has to save more than its merge costs (d = 64, one head of 2275 rows: 10.1 us in two pieces, 8.7 whole; of 2812 rows,
+        // not causal, 13.0 / 10.6)
+        if (r.nsplit > 1 && (s16 ? 0.85 : 0.55) * most_t * (r.nsplit - 1) < (rows_all > 1024 ? merge + 2.0 : merge) * r.nsplit) r.nsplit = 1;
         const double uneven = !equal && B * Hq == 1 ? 1.3 : 1.0;     // one causal head: no even ranges for the XCDs
-        const double work = (!s16 ? 1.0 : d == 64 ? 1.6 : 2.6) * uneven * rows_workgroups(B, Hkv, G, Nq, 2) * (5.5 / 512 + (d == 64 ? 0.52 : 0.68) / 256 * mean_t);
+        const double work = (!s16 ? 1.0 : d == 64 ? 1.6 : 2.6) * uneven * rows_workgroups(B, Hkv, G, Nq, 2) * (5.5 / 512 + (d == 64 ? 0.52 : causal && N > 1024 ? 0.71 : 0.845) / 256 * mean_t);
         const double alone = (s16 ? 0.85 : 0.55) * most_t / r.nsplit;
+        // (d = 128, causal: its longest blocks come first beyond 1024 keys)
         rows_us = 4.0 + (work > alone ? work : alone) + (r.nsplit > 1 ? merge : 0.0);
     }
     if (d == 128) {
         const double most_h = ceil(ceil(most_t) / 2), mean_h = mean_t / 2 + 0.25, W = (double)B * Hq * ((Nq + 127) / 128);
-        const double fwd_us = (equal ? equal_rounds(U * p.nsplit, 256, 8.0, most_t / p.nsplit)
-                                     : unequal_rounds(U * p.nsplit, 256, 8.0, most_t / p.nsplit, mean_t / p.nsplit)) * real +
+        const double fwd_us = (equal ? equal_rounds(U * p.nsplit, 256, 9.4, most_t / p.nsplit)
+                                     : unequal_rounds(U * p.nsplit, 256, 9.4, most_t / p.nsplit, mean_t / p.nsplit)) * real +
                               (p.nsplit > 1 ? merge : 0.0);
-        const double halves_us = equal ? equal_rounds(W, 256, 10.0, most_h) : unequal_rounds(W, 256, 10.0, most_h, mean_h);
+        const double halves_us = equal ? equal_rounds(W, 256, 10.5, most_h) : unequal_rounds(W, 256, 10.5, most_h, mean_h);
         if (rows_us < 0.98 * (fwd_us < halves_us ? fwd_us : halves_us)) return r;
         if (halves_us < 0.98 * fwd_us) p = {Plan::HALVES, 1, 0};
         return p;
