@@ -185,7 +185,9 @@ int rows_blocks(int B, int Hkv, int G, int Nq)
 }
 
 // Workgroups that share the keys of a row block: as many as make two to a compute unit, each with a unit of 64 keys for
-// each of its four wavefronts at least.  Not up to 2048 keys, so that a row's result there does not depend on how many rows and
+// each of its four wavefronts at least.  Not two: 171 workgroups and more keep the memory busy alone, and a merge costs 5 us (a row
+// each, in two pieces / whole: 24 sequences of 4000 keys, 8 KV heads, 75.0 / 68.1; 14 x 16 heads, d = 64, of 3000 / 12000 keys 28.8 / 25.6,
+// 119.6 / 113.0; but 14 x 8 KV heads of 5000 keys in four pieces / whole 46.1 / 54.5).  Not up to 2048 keys, so that a row's result there does not depend on how many rows and
 // sequences are given with it.  That is not where a split begins to pay: with the present merge kernel that is near 1400
 // keys (1 row, 28 heads on 4, d = 128, us not split / split: 500 keys 6.2 / 9.7, 1000 keys 7.7 / 8.9, 1500 keys 9.8 / 9.1,
 // 2047 keys 13.0 / 9.2; 4 sequences of 2047 keys 14.0 / 9.4).  Fewer than these where the workspace ends: its last region is sized by
@@ -195,6 +197,7 @@ int rows_splits(int B, int Hkv, int G, int Nq, int rb, int N, int keys)
     const long groups = rows_workgroups(B, Hkv, G, Nq, rb), units = ((long)keys + 63) / 64;
     if (N <= 2048) return 1;
     long ns = 2 * kComputeUnits / groups;
+    if (ns == 2) return 1;
     if (ns > (units + 3) / 4) ns = (units + 3) / 4;
     return ns < 1 ? 1 : (int)ns;
 }
