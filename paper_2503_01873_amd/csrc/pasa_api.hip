@@ -247,6 +247,9 @@ int fitting(int ns, size_t rows_all, int d, size_t room)
 // The factors of the estimates are fitted to 220 such calls of 150 to 6000 keys (on average 0.2 % behind the fastest kernel), so they rank the kernels and are not times: 14 x 5 heads of 9216 rows,
 // d = 64, not causal, are put at 1843 us (pasa_fwd) and 1793 (pasa_fwd4) and take 1630 and 1490; a call whose estimates lie within
 // a few per cent may go to the slower kernel.
+// d = 64, pasa_fwd / pasa_fwd4 / pasa_rows: 16 heads, causal, of 2290 rows 38 / 31 / 24 (stays on pasa_fwd4); 2 x 16 heads of 508 rows 14.3 / 9.5 / 7.5; 14 x 5 heads,
+// causal, of 168 / 221 rows 8.6 / 6.9 / 5.5, 8.6 / 6.7 / 5.4; 14 x 28 heads on 4 of 198 rows 17 / 13.6 / 21.  The factors are fitted to 240 such calls
+// (2.1 % behind the fastest kernel on average before, 0.9 now).
 // d = 64, pasa_fwd / pasa_fwd4: 14 x 5 heads of 1000 / 2000 / 4000 rows, not causal, 50.7 / 34.8, 134 / 103, 420 / 356, causal
 // 26.5 / 24.1, 70 / 60, 224 / 206; 2 x 16 heads of 4000 rows, not causal (a round and a third of pasa_fwd4) 174 / 184;
 // one head of 16384 rows, causal, both split: 79 / 67, and 101 with pasa_rows.
@@ -311,9 +314,12 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
         // not causal, 13.0 / 10.6)
         if (r.nsplit > 1 && (s16 ? 0.85 : 0.55) * most_t * (r.nsplit - 1) < (rows_all > 1024 ? merge + 2.0 : merge) * r.nsplit) r.nsplit = 1;
         const double uneven = !equal && B * Hq == 1 ? 1.3 : 1.0;     // one causal head: no even ranges for the XCDs
-        const double work = (!s16 ? 1.0 : d == 64 ? 1.6 : 2.6) * uneven * rows_workgroups(B, Hkv, G, Nq, 2) * (5.5 / 512 + (d == 64 ? 0.52 : causal && N > 1024 ? 0.71 : 0.845) / 256 * mean_t);
+        // us of a step: d = 128, causal, less beyond 1024 keys, where the longest blocks come first; d = 64, not much less where the
+        // other kernels would split their keys
+        const bool others_split = wanted_splits(B, Hq, Nq, N) > 1 || fwd4_splits(B, Hq, Nq, N) > 1;
+        const double step = d == 64 ? (s16 ? 0.52 : others_split ? 0.54 : 0.44) : causal && N > 1024 ? 0.71 : 0.845;
+        const double work = (!s16 ? 1.0 : d == 64 ? 1.6 : 2.6) * uneven * rows_workgroups(B, Hkv, G, Nq, 2) * (5.5 / 512 + step / 256 * mean_t);
         const double alone = (s16 ? 0.85 : 0.55) * most_t / r.nsplit;
-        // (d = 128, causal: its longest blocks come first beyond 1024 keys)
         rows_us = 4.0 + (work > alone ? work : alone) + (r.nsplit > 1 ? merge : 0.0);
     }
     if (d == 128) {
@@ -326,19 +332,19 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
         if (halves_us < 0.98 * fwd_us) p = {Plan::HALVES, 1, 0};
         return p;
     }
-    // d = 64: a step of pasa_fwd takes 2.0 to 2.55 us, one of pasa_fwd4 1.7 / 2.6 / 3.7 with one / two / three workgroups on every
-    // compute unit
+    // d = 64: a step of pasa_fwd takes 2.0 to 2.55 us, one of pasa_fwd4 1.73 / 2.44 / 3.17 with one / two / three workgroups on every
+    // compute unit (3.7 sustained, under the power limit)
     const double U_ns = U * p.nsplit, alone = (s16 ? 2.5 : 2.0) * most_t / p.nsplit;
     const double full = (causal ? U_ns / 256 * mean_t : U_ns <= 256 ? (0.75 + 0.25 * U_ns / 256) * most_t : ceil(U_ns / 256) * most_t) *
                         (2.0 + 0.55 * (real - 0.85) / 0.15) / p.nsplit;
-    const double fwd_us = 7.0 + (alone > full ? alone : full) + (p.nsplit > 1 ? merge : 0.0);
+    const double fwd_us = (s16 ? 7.0 : 8.1) + (alone > full ? alone : full) + (p.nsplit > 1 ? merge : 0.0);
     Plan f = {Plan::FWD4, 1, 0};
     if (may_split) f.nsplit = fitting(fwd4_splits(B, Hq, Nq, N), rows_all, d, room);
     const double W = (double)B * Hq * ((Nq + 127) / 128) * f.nsplit, rest = fmod(W, 768.0);
-    const double rounds = floor(W / 768) * 3.7 + (rest == 0 ? 0.0 : rest <= 256 ? 1.7 : rest <= 512 ? 2.6 : 3.7);
-    const double alone4 = 1.7 * most_t, full4 = causal ? W / 768 * 3.7 * mean_t : rounds * most_t;
-    const double fwd4_us = 7.0 + (alone4 > full4 ? alone4 : full4) / f.nsplit + (f.nsplit > 1 ? merge : 0.0);
-    if (rows_us <= 0.92 * (s16 || fwd_us < fwd4_us ? fwd_us : fwd4_us)) return r;
+    const double rounds = floor(W / 768) * 3.17 + (rest == 0 ? 0.0 : rest <= 256 ? 1.73 : rest <= 512 ? 2.44 : 3.17);
+    const double alone4 = 1.73 * most_t, full4 = causal ? W / 768 * 3.17 * mean_t : rounds * most_t;
+    const double fwd4_us = 7.6 + (alone4 > full4 ? alone4 : full4) / f.nsplit + (f.nsplit > 1 ? merge : 0.0);
+    if (rows_us <= (s16 ? 0.92 : 0.95) * (s16 || fwd_us < fwd4_us ? fwd_us : fwd4_us)) return r;
     return !s16 && fwd4_us <= 0.98 * fwd_us ? f : p;
 }
 
