@@ -8,6 +8,7 @@
 #include <mutex>
 
 #include "pasa.h"
+#include "pasa_device.h"
 #include "pasa_kernels.h"
 
 namespace {

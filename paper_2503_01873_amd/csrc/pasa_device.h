@@ -5,6 +5,21 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+// Division of a number below 2^31 by a number that the host knows (at least 1): q = n * mul >> shift, exact, in three scalar
+// instructions.  The compiler's division of two variables is a chain of forty through the vector unit; the kernels decode their
+// workgroup's place with several, before their first load.
+struct FastDiv {
+    unsigned d, mul, shift;
+    __host__ __device__ unsigned quotient(unsigned n) const { return (unsigned)(((unsigned long long)n * mul) >> shift); }
+    __host__ __device__ unsigned rest(unsigned n, unsigned q) const { return n - q * d; }
+};
+inline FastDiv fast_div(unsigned d)
+{
+    unsigned s = 0;
+    while ((1u << s) < d) ++s;                   // 2^s >= d > 2^(s-1): mul fits 32 bits, and n * (mul * d - 2^(31+s)) < 2^(31+s)
+    return {d, (unsigned)(((1ull << (31 + s)) + d - 1) / d), 31 + s};
+}
+
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));

@@ -9,21 +9,6 @@ enum { PASA_K_MIXED = 0, PASA_K_STRICT16 = 1, PASA_K_NAIVE16 = 2, PASA_K_S16 = 3
 // how the pre-processing kernel forms K'
 enum { PASA_PREP_MEAN = 0, PASA_PREP_MATRIX = 1, PASA_PREP_DIRECT = 2 };
 
-// Division of a number below 2^31 by a number that the host knows (at least 1): q = n * mul >> shift, exact, in three scalar
-// instructions.  The compiler's division of two variables is a chain of forty through the vector unit; the kernels decode their
-// workgroup's place with several, before their first load.
-struct FastDiv {
-    unsigned d, mul, shift;
-    __host__ __device__ unsigned quotient(unsigned n) const { return (unsigned)(((unsigned long long)n * mul) >> shift); }
-    __host__ __device__ unsigned rest(unsigned n, unsigned q) const { return n - q * d; }
-};
-inline FastDiv fast_div(unsigned d)
-{
-    unsigned s = 0;
-    while ((1u << s) < d) ++s;                   // 2^s >= d > 2^(s-1): mul fits 32 bits, and n * (mul * d - 2^(31+s)) < 2^(31+s)
-    return {d, (unsigned)(((1ull << (31 + s)) + d - 1) / d), 31 + s};
-}
-
 struct PasaLaunch {
     const void* q;
     const void* ws;   // per (batch, KV head, key tile): shifted-key tile then value tile, fragment-major layout
