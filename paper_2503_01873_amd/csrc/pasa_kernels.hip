@@ -404,9 +404,9 @@ __device__ inline void for_constants(std::integer_sequence<int, I...>, F f) { (f
 // KSPL = 2: the workgroup owns 128 rows; both groups of wavefronts hold all of them, group A takes the even key tiles and
 // group B the odd ones, each through a K' and a V buffer of its own, and B's state joins A's through LDS at the end (the rule of
 // the key split).  A step (two slots) passes two tiles, so a workgroup's chain is half as long and there are twice as many
-// workgroups: faster where the longest chain bounds the launch (28 heads on 4, causal, 1024 / 2048 rows 29.7 -> 21.7, 50.9 -> 46.8
-// us), slower where the chip is full (8192 rows 446 -> 491 us: every tile is copied twice as often, and the 8-10 us that a
-// workgroup takes to fill and drain come twice).
+// workgroups: faster where the longest chain bounds the launch (28 heads on 4, causal, 1024 / 2048 rows 25.2 -> 17.9, 46.5 -> 39.7
+// us), slower where the chip is full (8192 rows, kernels as they were, 446 -> 491 us: every tile is copied twice as often, and
+// the start and the end of a workgroup come twice).
 //
 // What a workgroup needs to know its place in the launch (see the decode), worked out on the host: with its divisions in the kernel
 // the first load went out 1.1 us after the workgroup's start.
