@@ -186,15 +186,16 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
 
     // Query rows first: loads come back in the order they were asked for, and nothing can begin without these (behind the first keys
     // and values they took 2.0 us of a workgroup's 8.9 in 28 heads of 777 rows).  Rows past the
-    // list's end are out of the buffer's bounds and come as zeros.
+    // list's end are out of the buffer's bounds and come as zeros.  The buffer is the block's, not the list's: a list may be longer than
+    // the 4 GiB that a buffer's size and offsets count.
     const __amdgpu_buffer_rsrc_t rows_in =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(q + list0 * D), 0, list_rows * (2 * D), 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(q + (list0 + p0) * D), 0, (p1 + 1 - p0) * (2 * D), 0x00020000);
     constexpr int QN = QLDS ? RB * KS / NW : RB * KS;            // fragments that this wavefront loads: to be shared, or all of its own
     h8 raw[QN];
 #pragma unroll
     for (int n = 0; n < QN; ++n) {
         const int at = QLDS ? n * NW + wave : n;                 // fragment: row block at / KS, k-step at % KS
-        raw[n] = load_frag(rows_in, (p0 + lq) * (2 * D) + 16 * g + at / KS * (32 * D), 64 * (at % KS));
+        raw[n] = load_frag(rows_in, lq * (2 * D) + 16 * g + at / KS * (32 * D), 64 * (at % KS));
     }
     PASA_FENCE();
     // the half tile whose keys A and B take first for unit u
