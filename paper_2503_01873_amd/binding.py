@@ -92,9 +92,11 @@ def lib() -> ctypes.CDLL:
     except ImportError as e:
         raise FileNotFoundError(
             f"{os.path.join(_PKG, '_calls.so')} is missing: build it with `python -m paper_2503_01873_amd.build`") from e
-    for name, marshal in (("pasa_attn_fwd", _calls.plain), ("pasa_attn_fwd_ex", _calls.whole), ("pasa_attn_fwd_adaptive", _calls.whole),
-                          ("pasa_prepare_kv", _calls.prepare), ("pasa_attn_fwd_chunk", _calls.chunk)):
-        setattr(L, "fast_" + name, functools.partial(marshal, ctypes.cast(getattr(L, name), vp).value))
+    for name, in_c, in_ctypes in (("pasa_attn_fwd", _calls.plain, _plain), ("pasa_attn_fwd_ex", _calls.whole, _whole),
+                                  ("pasa_attn_fwd_adaptive", _calls.whole, _whole), ("pasa_prepare_kv", _calls.prepare, _prepare),
+                                  ("pasa_attn_fwd_chunk", _calls.chunk, _chunk)):
+        f = getattr(L, name)
+        setattr(L, "fast_" + name, functools.partial(in_c, ctypes.cast(f, vp).value, functools.partial(in_ctypes, f)))
     _lib = L
     return L
 
@@ -113,6 +115,33 @@ def _stream(stream):
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None     # torch.cuda.Stream
+
+
+def _opts(beta, variant, shift_tile, overflow_s, nonfinite_o, shift_mode, io_dtype):
+    return ctypes.byref(pasa_opts(float(beta), int(variant), int(shift_tile), _ptr(overflow_s), _ptr(nonfinite_o), int(shift_mode),
+                                  int(io_dtype)))
+
+
+# The calls of csrc/calls.c through ctypes: it hands on the ones whose arguments it does not take, and ctypes takes or refuses them.
+def _plain(f, q, k, v, o, B, Hq, Hkv, N, d, causal, scale, stream):
+    return f(_ptr(q), _ptr(k), _ptr(v), _ptr(o), B, Hq, Hkv, N, d, int(causal), float(scale), _stream(stream))
+
+
+def _whole(f, q, k, v, o, B, Hq, Hkv, N, d, causal, scale, workspace, workspace_bytes, stream, *opts):
+    opts, opts_null = _opts(*opts[:-1]), opts[-1]
+    return f(_ptr(q), _ptr(k), _ptr(v), _ptr(o), B, Hq, Hkv, N, d, int(causal), float(scale), None if opts_null else opts,
+             _ptr(workspace), int(workspace_bytes), _stream(stream))
+
+
+def _prepare(f, k, v, B, Hkv, N, d, scale, workspace, workspace_bytes, stream, *opts):
+    opts = _opts(*opts)
+    return f(_ptr(k), _ptr(v), B, Hkv, N, d, float(scale), opts, _ptr(workspace), int(workspace_bytes), _stream(stream))
+
+
+def _chunk(f, q, o, B, Hq, Hkv, Nq, row0, N, d, causal, scale, workspace, workspace_bytes, stream, *opts):
+    opts = _opts(*opts)
+    return f(_ptr(q), _ptr(o), B, Hq, Hkv, Nq, row0, N, d, int(causal), float(scale), opts, _ptr(workspace), int(workspace_bytes),
+             _stream(stream))
 
 
 def _check(status: int, what: str, check: bool):

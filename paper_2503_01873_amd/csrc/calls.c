@@ -1,18 +1,31 @@
 /* Arguments of the Python binding's calls, from Python objects to C, for the entry points of include/pasa.h that are called once per
- * layer and step.  Each function takes the address of an entry point and its arguments in order (the fields of pasa_opts spread
- * out) and returns its status.  Through ctypes alone a call of pasa_attn_fwd_ex costs 4.4 us on the host before anything is
- * launched, which for the smallest calls is as long as their kernels take; here 1.3. */
+ * layer and step.  Each function takes the address of an entry point, what makes the same call through ctypes, and the arguments in
+ * order (the fields of pasa_opts spread out), and returns the entry point's status.  Through ctypes alone a call of
+ * pasa_attn_fwd_ex costs 4.4 us on the host before anything is launched, which for the smallest calls is as long as their kernels
+ * take; here 1.3.
+ *
+ * Taken here: addresses, and objects whose data_ptr() or cuda_stream is one; sizes that are Python integers; options that int() and
+ * float() take.  A call with anything else (a size that is a numpy integer, say), or that raises on the way, is made again through
+ * ctypes, so that ctypes alone says what is accepted and what is refused, and how. */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
 #include "pasa.h"
 
-static PyObject *s_data_ptr, *s_cuda_stream, *argument_error;
+static PyObject *s_data_ptr, *s_cuda_stream;
 
-static PyObject* refuse(const char* what)
+/* a: address, the call through ctypes, its arguments */
+static PyObject* through_ctypes(PyObject* const* a, Py_ssize_t n)
 {
-    PyErr_SetString(argument_error, what);
-    return NULL;
+    if (n < 2) {
+        PyErr_SetString(PyExc_TypeError, "an address, the call through ctypes and its arguments");
+        return NULL;
+    }
+    if (PyErr_Occurred()) {
+        if (!PyErr_ExceptionMatches(PyExc_Exception)) return NULL;     /* an interrupt is no refusal */
+        PyErr_Clear();
+    }
+    return PyObject_Vectorcall(a[1], a + 2, n - 2, NULL);
 }
 
 /* None, an address or an object with data_ptr() */
@@ -29,7 +42,6 @@ static int get_ptr(PyObject* x, void** out)
     const int ok = PyLong_Check(p) || p == Py_None;
     if (ok && p != Py_None) *out = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(p);
     Py_DECREF(p);
-    if (!ok) refuse("data_ptr() is not an integer");
     return ok && !PyErr_Occurred();
 }
 
@@ -44,17 +56,13 @@ static int get_stream(PyObject* x, void** out)
     const int ok = PyLong_Check(p) || p == Py_None;
     if (ok && p != Py_None) *out = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(p);
     Py_DECREF(p);
-    if (!ok) refuse("cuda_stream is not an integer");
     return ok && !PyErr_Occurred();
 }
 
-/* sizes: integers only, the low 32 bits as ctypes takes them */
+/* sizes: the low 32 bits, as ctypes takes them */
 static int get_size(PyObject* x, int* out)
 {
-    if (!PyLong_Check(x)) {
-        refuse("an integer is required");
-        return 0;
-    }
+    if (!PyLong_Check(x)) return 0;
     *out = (int)(unsigned)PyLong_AsUnsignedLongLongMask(x);
     return !PyErr_Occurred();
 }
@@ -121,23 +129,22 @@ static int get_sizes(PyObject* const* a, int n, int* out)
         Py_END_ALLOW_THREADS         \
     } while (0)
 
-/* address, q, k, v, o, B, Hq, Hkv, N, d, causal, scale, stream */
+/* address, ctypes, q, k, v, o, B, Hq, Hkv, N, d, causal, scale, stream */
 static PyObject* plain(PyObject* self, PyObject* const* a, Py_ssize_t n)
 {
     void *f, *p[4], *stream;
     int s[5], status;
     unsigned long long causal;
     float scale;
-    if (n != 13) return refuse("13 arguments");
-    if (!get_ptr(a[0], &f) || !get_ptrs(a + 1, 4, p) || !get_sizes(a + 5, 5, s) || !get_int(a[10], &causal) ||
-        !get_float(a[11], &scale) || !get_stream(a[12], &stream))
-        return NULL;
+    if (n != 14 || !get_ptr(a[0], &f) || !get_ptrs(a + 2, 4, p) || !get_sizes(a + 6, 5, s) || !get_int(a[11], &causal) ||
+        !get_float(a[12], &scale) || !get_stream(a[13], &stream))
+        return through_ctypes(a, n);
     CALL(status, ((int (*)(const void*, const void*, const void*, void*, int, int, int, int, int, int, float, void*))f)(
                      p[0], p[1], p[2], p[3], s[0], s[1], s[2], s[3], s[4], (int)(unsigned)causal, scale, stream));
     return PyLong_FromLong(status);
 }
 
-/* address, q, k, v, o, B, Hq, Hkv, N, d, causal, scale, workspace, bytes, stream, options, no options at all */
+/* address, ctypes, q, k, v, o, B, Hq, Hkv, N, d, causal, scale, workspace, bytes, stream, options, no options at all */
 static PyObject* whole(PyObject* self, PyObject* const* a, Py_ssize_t n)
 {
     void *f, *p[4], *ws, *stream;
@@ -145,18 +152,17 @@ static PyObject* whole(PyObject* self, PyObject* const* a, Py_ssize_t n)
     unsigned long long causal, bytes;
     float scale;
     pasa_opts opts;
-    if (n != 15 + OPTS + 1) return refuse("23 arguments");
-    if (!get_ptr(a[0], &f) || !get_ptrs(a + 1, 4, p) || !get_sizes(a + 5, 5, s) || !get_int(a[10], &causal) ||
-        !get_float(a[11], &scale) || !get_ptr(a[12], &ws) || !get_int(a[13], &bytes) || !get_stream(a[14], &stream) ||
-        !get_opts(a + 15, &opts) || (none = PyObject_IsTrue(a[15 + OPTS])) < 0)
-        return NULL;
+    if (n != 16 + OPTS + 1 || !get_ptr(a[0], &f) || !get_ptrs(a + 2, 4, p) || !get_sizes(a + 6, 5, s) || !get_int(a[11], &causal) ||
+        !get_float(a[12], &scale) || !get_ptr(a[13], &ws) || !get_int(a[14], &bytes) || !get_stream(a[15], &stream) ||
+        !get_opts(a + 16, &opts) || (none = PyObject_IsTrue(a[16 + OPTS])) < 0)
+        return through_ctypes(a, n);
     CALL(status, ((int (*)(const void*, const void*, const void*, void*, int, int, int, int, int, int, float, const pasa_opts*, void*,
                            size_t, void*))f)(p[0], p[1], p[2], p[3], s[0], s[1], s[2], s[3], s[4], (int)(unsigned)causal, scale,
                                              none ? NULL : &opts, ws, (size_t)bytes, stream));
     return PyLong_FromLong(status);
 }
 
-/* address, k, v, B, Hkv, N, d, scale, workspace, bytes, stream, options */
+/* address, ctypes, k, v, B, Hkv, N, d, scale, workspace, bytes, stream, options */
 static PyObject* prepare(PyObject* self, PyObject* const* a, Py_ssize_t n)
 {
     void *f, *p[2], *ws, *stream;
@@ -164,16 +170,15 @@ static PyObject* prepare(PyObject* self, PyObject* const* a, Py_ssize_t n)
     unsigned long long bytes;
     float scale;
     pasa_opts opts;
-    if (n != 11 + OPTS) return refuse("18 arguments");
-    if (!get_ptr(a[0], &f) || !get_ptrs(a + 1, 2, p) || !get_sizes(a + 3, 4, s) || !get_float(a[7], &scale) || !get_ptr(a[8], &ws) ||
-        !get_int(a[9], &bytes) || !get_stream(a[10], &stream) || !get_opts(a + 11, &opts))
-        return NULL;
+    if (n != 12 + OPTS || !get_ptr(a[0], &f) || !get_ptrs(a + 2, 2, p) || !get_sizes(a + 4, 4, s) || !get_float(a[8], &scale) ||
+        !get_ptr(a[9], &ws) || !get_int(a[10], &bytes) || !get_stream(a[11], &stream) || !get_opts(a + 12, &opts))
+        return through_ctypes(a, n);
     CALL(status, ((int (*)(const void*, const void*, int, int, int, int, float, const pasa_opts*, void*, size_t, void*))f)(
                      p[0], p[1], s[0], s[1], s[2], s[3], scale, &opts, ws, (size_t)bytes, stream));
     return PyLong_FromLong(status);
 }
 
-/* address, q, o, B, Hq, Hkv, Nq, row0, N, d, causal, scale, workspace, bytes, stream, options */
+/* address, ctypes, q, o, B, Hq, Hkv, Nq, row0, N, d, causal, scale, workspace, bytes, stream, options */
 static PyObject* chunk(PyObject* self, PyObject* const* a, Py_ssize_t n)
 {
     void *f, *p[2], *ws, *stream;
@@ -181,11 +186,10 @@ static PyObject* chunk(PyObject* self, PyObject* const* a, Py_ssize_t n)
     unsigned long long causal, bytes;
     float scale;
     pasa_opts opts;
-    if (n != 15 + OPTS) return refuse("22 arguments");
-    if (!get_ptr(a[0], &f) || !get_ptrs(a + 1, 2, p) || !get_sizes(a + 3, 7, s) || !get_int(a[10], &causal) ||
-        !get_float(a[11], &scale) || !get_ptr(a[12], &ws) || !get_int(a[13], &bytes) || !get_stream(a[14], &stream) ||
-        !get_opts(a + 15, &opts))
-        return NULL;
+    if (n != 16 + OPTS || !get_ptr(a[0], &f) || !get_ptrs(a + 2, 2, p) || !get_sizes(a + 4, 7, s) || !get_int(a[11], &causal) ||
+        !get_float(a[12], &scale) || !get_ptr(a[13], &ws) || !get_int(a[14], &bytes) || !get_stream(a[15], &stream) ||
+        !get_opts(a + 16, &opts))
+        return through_ctypes(a, n);
     CALL(status, ((int (*)(const void*, void*, int, int, int, int, int, int, int, int, float, const pasa_opts*, void*, size_t, void*))f)(
                      p[0], p[1], s[0], s[1], s[2], s[3], s[4], s[5], s[6], (int)(unsigned)causal, scale, &opts, ws, (size_t)bytes,
                      stream));
@@ -206,10 +210,6 @@ PyMODINIT_FUNC PyInit__calls(void)
 {
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
     s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
-    PyObject* ctypes = PyImport_ImportModule("ctypes");
-    if (ctypes == NULL) return NULL;
-    argument_error = PyObject_GetAttrString(ctypes, "ArgumentError");
-    Py_DECREF(ctypes);
-    if (argument_error == NULL || s_data_ptr == NULL || s_cuda_stream == NULL) return NULL;
+    if (s_data_ptr == NULL || s_cuda_stream == NULL) return NULL;
     return PyModule_Create(&module);
 }

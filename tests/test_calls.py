@@ -1,7 +1,9 @@
 """How the binding takes its arguments (the same as through ctypes); nothing is launched: every call is one that is refused."""
 import ctypes
 
+import numpy as np
 import pytest
+import torch
 
 import paper_2503_01873_amd as P
 
@@ -17,6 +19,20 @@ class Stream:
     cuda_stream = 0
 
 
+class Index:
+    def __index__(self):
+        return 64
+
+
+class Parameter:
+    _as_parameter_ = 64
+
+
+class Address:
+    def data_ptr(self):
+        return ctypes.c_void_p(A)
+
+
 def chunk(**kw):
     a = dict(q=A, o=2 * A, B=1, Hq=2, Hkv=1, Nq=4, row0=0, N=64, d=64, causal=True, scale=0.125, workspace=A, workspace_bytes=1, check=False)
     a.update(kw)
@@ -30,6 +46,20 @@ def chunk(**kw):
 ])
 def test_arguments_reach_the_library(kw, status):
     assert chunk(**kw) == status
+
+
+@pytest.mark.parametrize("size", [np.int64(64), np.uint8(64), torch.tensor(64), Index(), ctypes.c_int(64), Parameter()])
+def test_sizes_are_whatever_ctypes_takes_for_an_integer(size):
+    assert chunk(N=size) == 4 and chunk(Nq=size, row0=0) == 4
+    kw = dict(workspace=A, workspace_bytes=1, check=False)
+    assert P.pasa_attn_fwd(A, A, A, 2 * A, 1, size, size, 64, 96, False, 0.125, check=False) == 2
+    assert P.pasa_attn_fwd_ex(A, A, A, 2 * A, 1, size, size, size, size, False, 0.125, **kw) == 4
+    assert P.pasa_attn_fwd_adaptive(A, A, A, 2 * A, size, 1, 1, size, size, False, 0.125, overflow_s=A, **kw) == 4
+    assert P.pasa_prepare_kv(A, A, size, size, size, size, 0.125, **kw) == 4
+
+
+def test_addresses_are_whatever_ctypes_takes_for_one():
+    assert chunk(q=Address()) == 4 and chunk(q=Address(), o=A) == 1 and chunk(workspace=Address()) == 4
 
 
 @pytest.mark.parametrize("kw,error", [
