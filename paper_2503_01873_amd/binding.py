@@ -1,5 +1,5 @@
 """Binding with the same names as include/pasa.h.  Argument marshalling only: in C (csrc/calls.c) for the calls that a program makes
-once per layer and step, through ctypes for the others.
+once per layer and step, through ctypes for the others, and for all of them where that extension is not there.
 
 Tensors are anything with `.data_ptr()` (torch tensors on the GPU); raw integer addresses are accepted
 too.  Nothing here computes: if libpasa.so is missing or cannot be loaded the import of `lib()` fails
@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import importlib
 import os
 
 MIXED, STRICT16, NAIVE16, S16, DIRECT = 0, 1, 2, 3, 4
@@ -88,15 +89,17 @@ def lib() -> ctypes.CDLL:
     L.pasa_version.argtypes = []
     L.pasa_version.restype = ci
     try:
-        from . import _calls
-    except ImportError as e:
-        raise FileNotFoundError(
-            f"{os.path.join(_PKG, '_calls.so')} is missing: build it with `python -m paper_2503_01873_amd.build`") from e
-    for name, in_c, in_ctypes in (("pasa_attn_fwd", _calls.plain, _plain), ("pasa_attn_fwd_ex", _calls.whole, _whole),
-                                  ("pasa_attn_fwd_adaptive", _calls.whole, _whole), ("pasa_prepare_kv", _calls.prepare, _prepare),
-                                  ("pasa_attn_fwd_chunk", _calls.chunk, _chunk)):
+        calls = importlib.import_module("._calls", __package__)
+    except ModuleNotFoundError:      # built for another interpreter, or where there were no headers: the same calls through ctypes
+        calls = None
+    for name, in_c, in_ctypes in (("pasa_attn_fwd", "plain", _plain), ("pasa_attn_fwd_ex", "whole", _whole),
+                                  ("pasa_attn_fwd_adaptive", "whole", _whole), ("pasa_prepare_kv", "prepare", _prepare),
+                                  ("pasa_attn_fwd_chunk", "chunk", _chunk)):
         f = getattr(L, name)
-        setattr(L, "fast_" + name, functools.partial(in_c, ctypes.cast(f, vp).value, functools.partial(in_ctypes, f)))
+        call = functools.partial(in_ctypes, f)
+        if calls is not None:
+            call = functools.partial(getattr(calls, in_c), ctypes.cast(f, vp).value, call)
+        setattr(L, "call_" + name, call)
     _lib = L
     return L
 
@@ -175,14 +178,14 @@ def pasa_attn_fwd_workspace_min(B, Hkv, N, d) -> int:
 
 
 def pasa_attn_fwd(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, stream=None, check=True) -> int:
-    st = (_lib or lib()).fast_pasa_attn_fwd(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, stream)
+    st = (_lib or lib()).call_pasa_attn_fwd(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, stream)
     return _check(st, "pasa_attn_fwd", check)
 
 
 def pasa_attn_fwd_ex(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, workspace, workspace_bytes, stream=None,
                      beta=-1.0, variant=MIXED, shift_tile=128, overflow_s=None, nonfinite_o=None,
                      shift_mode=SHIFT_MEAN, io_dtype=IO_F16, opts_null=False, check=True) -> int:
-    st = (_lib or lib()).fast_pasa_attn_fwd_ex(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, workspace, workspace_bytes, stream,
+    st = (_lib or lib()).call_pasa_attn_fwd_ex(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, workspace, workspace_bytes, stream,
                                  beta, variant, shift_tile, overflow_s, nonfinite_o, shift_mode, io_dtype, opts_null)
     return _check(st, "pasa_attn_fwd_ex", check)
 
@@ -202,7 +205,7 @@ def pasa_attn_fwd_static(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, stream=Non
 
 def pasa_prepare_kv(k, v, B, Hkv, N, d, scale, workspace, workspace_bytes, stream=None, beta=-1.0, variant=MIXED,
                     shift_tile=128, shift_mode=SHIFT_MEAN, io_dtype=IO_F16, check=True) -> int:
-    st = (_lib or lib()).fast_pasa_prepare_kv(k, v, B, Hkv, N, d, scale, workspace, workspace_bytes, stream, beta, variant, shift_tile,
+    st = (_lib or lib()).call_pasa_prepare_kv(k, v, B, Hkv, N, d, scale, workspace, workspace_bytes, stream, beta, variant, shift_tile,
                                               None, None, shift_mode, io_dtype)
     return _check(st, "pasa_prepare_kv", check)
 
@@ -237,7 +240,7 @@ def pasa_shift_keys_matrix_mfma(k, kprime, B, Hkv, N, d, beta, kscale, stream=No
 def pasa_attn_fwd_chunk(q, o, B, Hq, Hkv, Nq, row0, N, d, causal, scale, workspace, workspace_bytes, stream=None,
                         beta=-1.0, variant=MIXED, shift_tile=128, overflow_s=None, nonfinite_o=None,
                         shift_mode=SHIFT_MEAN, io_dtype=IO_F16, check=True) -> int:
-    st = (_lib or lib()).fast_pasa_attn_fwd_chunk(q, o, B, Hq, Hkv, Nq, row0, N, d, causal, scale, workspace, workspace_bytes, stream,
+    st = (_lib or lib()).call_pasa_attn_fwd_chunk(q, o, B, Hq, Hkv, Nq, row0, N, d, causal, scale, workspace, workspace_bytes, stream,
                                                   beta, variant, shift_tile, overflow_s, nonfinite_o, shift_mode, io_dtype)
     return _check(st, "pasa_attn_fwd_chunk", check)
 
@@ -251,6 +254,6 @@ def pasa_shift_keys_direct(k, kprime, k0, B, Hkv, N, d, beta, kscale, stream=Non
 def pasa_attn_fwd_adaptive(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, workspace, workspace_bytes, stream=None,
                            beta=-1.0, variant=MIXED, shift_tile=128, overflow_s=None, nonfinite_o=None,
                            shift_mode=SHIFT_MEAN, io_dtype=IO_F16, opts_null=False, check=True) -> int:
-    st = (_lib or lib()).fast_pasa_attn_fwd_adaptive(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, workspace, workspace_bytes, stream,
+    st = (_lib or lib()).call_pasa_attn_fwd_adaptive(q, k, v, o, B, Hq, Hkv, N, d, causal, scale, workspace, workspace_bytes, stream,
                                  beta, variant, shift_tile, overflow_s, nonfinite_o, shift_mode, io_dtype, opts_null)
     return _check(st, "pasa_attn_fwd_adaptive", check)

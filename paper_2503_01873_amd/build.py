@@ -1,4 +1,4 @@
-"""Builds libpasa.so (hipcc, gfx950) and the binding's _calls.so (C) in-tree.  `python -m paper_2503_01873_amd.build`."""
+"""Builds libpasa.so (hipcc, gfx950) and the binding's extension _calls (C) in-tree.  `python -m paper_2503_01873_amd.build`."""
 from __future__ import annotations
 
 import os
@@ -11,7 +11,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libpasa.so")
-CALLS = os.path.join(PKG, "_calls.so")
+CALLS = os.path.join(PKG, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))      # for this interpreter: others do not load it
 SOURCES = ["pasa_api.hip", "pasa_kernels.hip", "pasa_fwd4.hip", "pasa_rows.hip", "pasa_shift_gemm.hip"]
 
 FLAGS = [
@@ -35,8 +35,13 @@ def hipcc() -> str:
     return exe
 
 
-def build_calls(verbose: bool = False) -> str:
-    cmd = [shutil.which("gcc") or hipcc(), "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"],
+def build_calls(verbose: bool = False) -> str | None:
+    """None, with a note, where Python's headers are not installed: the binding does without (through ctypes)."""
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        print(f"no Python.h in {include}: the binding's calls stay with ctypes, 3 us slower each", file=sys.stderr, flush=True)
+        return None
+    cmd = [shutil.which("gcc") or hipcc(), "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-I", include,
            "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "calls.c"), "-o", CALLS]
     if verbose:
         print(" ".join(cmd), flush=True)
@@ -51,7 +56,6 @@ def build(verbose: bool = False, extra_flags=(), out: str = LIB) -> str:
            *[os.path.join(CSRC, s) for s in SOURCES], "-o", out]
     if verbose:
         print(" ".join(cmd), flush=True)
-    build_calls(verbose)
     res = subprocess.run(cmd, capture_output=True, text=True)
     log = (res.stdout + res.stderr)
     # hipcc's host pass does not know the packed-fp32 feature name; that warning is expected
@@ -60,6 +64,7 @@ def build(verbose: bool = False, extra_flags=(), out: str = LIB) -> str:
         raise RuntimeError("hipcc failed:\n" + log)
     if verbose and shown.strip():
         print(shown)
+    build_calls(verbose)
     return out
 
 

@@ -95,3 +95,24 @@ def test_counters_of_a_chunk_reach_the_library():
 
     c = Counter()
     assert chunk(overflow_s=c, nonfinite_o=c) == 4 and Counter.asked == 2
+
+
+def test_without_the_extension_calls_go_through_ctypes(monkeypatch):
+    """An interpreter that the extension was not built for, or a machine without Python's headers."""
+    import sys
+    from paper_2503_01873_amd import binding
+    monkeypatch.setitem(sys.modules, "paper_2503_01873_amd._calls", None)
+    monkeypatch.setattr(binding, "_lib", None)
+    assert binding.lib().call_pasa_attn_fwd_chunk.func is binding._chunk
+    test_every_route_raises_with_the_entry_points_name()
+    assert chunk() == 4 and chunk(N=np.int64(64)) == 4
+    with pytest.raises(ctypes.ArgumentError):
+        chunk(N=64.0)
+
+
+def test_the_extension_is_for_one_interpreter_and_needs_its_headers(monkeypatch, tmp_path):
+    import sysconfig
+    from paper_2503_01873_amd import build
+    assert build.CALLS.endswith("_calls" + sysconfig.get_config_var("EXT_SUFFIX")) and build.CALLS != "_calls.so"
+    monkeypatch.setattr(sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert build.build_calls() is None
