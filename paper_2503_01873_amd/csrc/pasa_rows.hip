@@ -239,6 +239,12 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
     // 20000 keys 92.3 / 89.1).
     if (u0 < ue) {
         if (!QLDS) take_rows();
+        // d = 64: the four wavefronts start a quarter of an iteration apart (1300 clocks, of which their fragments keep the first-level
+        // cache busy for 1150).  In step, all load and all compute at the same time, and they stay in step: workgroups of one launch
+        // took 27 us or 34.  4 heads, 700 rows of 12800 keys 35.9 -> 29.4 us.  Not for a few iterations (no difference up to four), nor
+        // where arithmetic keeps them apart: d = 128 (28 heads on 4, 128 rows of 20000 keys 91.2 -> 94.9), fp16 scores (103.0 -> 105).
+        if (!QLDS && !S16 && D == 64 && ue - us > 4 * NW)
+            for (int i = 0; i < wave; ++i) __builtin_amdgcn_s_sleep(5);      // 320 clocks each
         auto unit = [&](int u, auto more_c) {
             constexpr bool more = decltype(more_c)::value;
             const int t = u >> 1;
