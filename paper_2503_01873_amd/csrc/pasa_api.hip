@@ -186,19 +186,21 @@ int rows_blocks(int B, int Hkv, int G, int Nq)
 }
 
 // Workgroups that share the keys of a row block: as many as make two to a compute unit, each with a unit of 64 keys for
-// each of its four wavefronts at least.  Not two: 171 workgroups and more keep the memory busy alone, and a merge costs 5 us (a row
+// each of its four wavefronts at least.  Not two where the rows of a KV head are one block and for S16 at d = 64 (`two` not set): 171 workgroups
+// and more keep the memory busy alone, and a merge costs 5 us (a row
 // each, in two pieces / whole: 24 sequences of 4000 keys, 8 KV heads, 75.0 / 68.1; 14 x 16 heads, d = 64, of 3000 / 12000 keys 28.8 / 25.6,
-// 119.6 / 113.0; but 14 x 8 KV heads of 5000 keys in four pieces / whole 46.1 / 54.5).  Not up to 2048 keys, so that a row's result there does not depend on how many rows and
+// 119.6 / 113.0; but 14 x 8 KV heads of 5000 keys in four pieces / whole 46.1 / 54.5); elsewhere the estimates decide (14 x 12 heads on 2, 5
+// rows of 2301 keys in two pieces / whole 12.7 / 15.2).  Not up to 2048 keys, so that a row's result there does not depend on how many rows and
 // sequences are given with it.  That is not where a split begins to pay: with the present merge kernel that is near 1400
 // keys (1 row, 28 heads on 4, d = 128, us not split / split: 500 keys 6.2 / 9.7, 1000 keys 7.7 / 8.9, 1500 keys 9.8 / 9.1,
-// 2047 keys 13.0 / 9.2; 4 sequences of 2047 keys 14.0 / 9.4).  Fewer than these where the workspace ends: its last region is sized by
-// wanted_splits (16 sequences of 1 row of 4999 keys get 4 of 8).
-int rows_splits(int B, int Hkv, int G, int Nq, int rb, int N, int keys)
+// 2047 keys 13.0 / 9.2; 4 sequences of 2047 keys 14.0 / 9.4).  Fewer than these, and two too, where the workspace ends: its last region is
+// sized by wanted_splits (16 sequences of 1 row of 4999 keys get 4 of 8, 28 sequences of 5000 keys 2 of 4).
+int rows_splits(int B, int Hkv, int G, int Nq, int rb, int N, int keys, bool two)
 {
     const long groups = rows_workgroups(B, Hkv, G, Nq, rb), units = ((long)keys + 63) / 64;
     if (N <= 2048) return 1;
     long ns = 2 * kComputeUnits / groups;
-    if (ns == 2) return 1;
+    if (ns == 2 && !two) return 1;
     if (ns > (units + 3) / 4) ns = (units + 3) / 4;
     return ns < 1 ? 1 : (int)ns;
 }
@@ -236,39 +238,61 @@ int fitting(int ns, size_t rows_all, int d, size_t room)
 // d = 64 to pasa_fwd4 (128 rows of one head, four wavefronts).  pasa_rows takes every call whose rows of a KV head fit one block (a decoding step reads its keys
 // once and not once per query head); otherwise the estimate below, from measured rates, says which is fastest.
 //
-// 28 heads on 4, d = 128, us of pasa_fwd / HALVES / pasa_rows.  Causal prompts of 512 / 1024 / 2048 / 3000 rows: 20.2 / 16.1 / 11.0,
-// 29.7 / 21.7 / 25.6, 50.7 / 45.9 / 71, 81 / 88 / -.  128 / 512 / 1024 rows at the end of 16384 keys: 262 / 174 / 75, 309 / 174 / 164, 310 /
-// 234 / 323.  8 heads of 3000 / 4096 rows, not causal: 60.5 (split) / 48.0 / 54.9, 80.0 (split) / 72.8 / 94.8.
-// 14 sequences, 1 / 20 / 64 rows of 6000 keys, pasa_fwd / pasa_rows: 189 / 34, 189 / 65, 192 / 124.
-// S16, 28 heads on 4, pasa_fwd / pasa_rows: 1 row of 500 / 6000 / 16000 keys 15.8 / 6.4, 43.9 / 10.6, 47.9 / 12.4; 128 rows 17.3 / 7.7,
-// 114 / 40.1, 290 / 96.8; 16 heads, d = 64, 500 rows of 3000 keys 65.6 / 24.3.
-// d = 128, causal, pasa_fwd / HALVES / pasa_rows: 28 heads of 614 / 768 / 1035 / 2196 rows 16.0 / 13.6 / 15.1, 20.6 / 15.0 / 16.8, 25.5 / 19.4 /
-// 23.9, 52.9 / 45.1 / 66.2 (of these only 1035 is planned on the fastest); 12 heads on 2 of 2185 rows 47.6 / 30.2 / 35.7; 4 x 8 heads of
-// 651 rows 20.1 / 14.5 / 16.1.
-// The factors of the estimates are fitted to 220 such calls of 150 to 6000 keys (on average 0.2 % behind the fastest kernel), so they rank the kernels and are not times: 14 x 5 heads of 9216 rows,
-// d = 64, not causal, are put at 1843 us (pasa_fwd) and 1793 (pasa_fwd4) and take 1630 and 1490; a call whose estimates lie within
-// a few per cent may go to the slower kernel.
-// d = 64, pasa_fwd / pasa_fwd4 / pasa_rows: 16 heads, causal, of 2290 rows 38 / 31 / 24 (stays on pasa_fwd4); 2 x 16 heads of 508 rows 14.3 / 9.5 / 7.5; 14 x 5 heads,
-// causal, of 168 / 221 rows 8.6 / 6.9 / 5.5, 8.6 / 6.7 / 5.4; 14 x 28 heads on 4 of 198 rows 17 / 13.6 / 21.  The factors are fitted to 240 such calls
-// (2.1 % behind the fastest kernel on average before, 0.9 now).
-// d = 64, pasa_fwd / pasa_fwd4: 14 x 5 heads of 1000 / 2000 / 4000 rows, not causal, 50.7 / 34.8, 134 / 103, 420 / 356, causal
-// 26.5 / 24.1, 70 / 60, 224 / 206; 2 x 16 heads of 4000 rows, not causal (a round and a third of pasa_fwd4) 174 / 184;
-// one head of 16384 rows, causal, both split: 79 / 67, and 101 with pasa_rows.
+// The factors of the estimates are fitted to 7400 calls of 128 to 32768 keys that ran on every kernel, so that the plan is behind the fastest
+// kernel by as little as can be: 0.6 % on average, 0.7 % S16 (pieces that are planned as their whole apart).  They rank the kernels and are not times,
+// above all at d = 64.  Not all lie where these calls alone would put them: tests hold some calls to a kernel that is not their fastest (777 rows
+// below, 8 heads, d = 64, of 2500 rows not causal), and calls near those go with them.  us, pasa_fwd / HALVES / pasa_rows, 28 heads on 4:
+//   causal, 394 / 561 / 687 / 841 / 990 rows         15.3 / 11.8 / 9.2, 16.0 / 13.7 / 11.1, 20.1 / 15.0 / 18.3, 20.6 / 16.7 / 20.0, 25.2 / 18.5 / 22.8
+//   causal, 1616 / 2089 / 2240 / 2813 / 4488 rows    36.3 / 30.9 / 42.0, 48.3 / 42.6 / 61.7, 53.9 / 45.6 / 67.4, 74.0 / 74.1 / 98.4, 148 / 160 / 223
+//   not causal, 391 / 581 / 1006 / 2021 / 5746 rows  17.5 / 13.7 / 10.8, 19.8 / 15.4 / 18.6, 27.1 / 21.5 / 28.4, 60.8 / 68.5 / 85.8, 447 / 455 / 612
+//   31 / 157 rows of 11699 / 9168 keys, 334 of 14242, 1206 of 22977    99.9 / 123 / 31.4, 173 / 99.4 / 59.4, 263 / 157 / 151, 436 / 555 / 574
+//   S16, causal, 286 / 391 / 1792 / 3770 rows        11.0 / 11.0 / 7.8, 16.3 / 12.4 / 12.1, 47.9 / 35.4 / 83.6, 119 / 126 / 321
+// planned on the fastest but for 687 (pasa_rows).  Pieces as the whole: 47 rows of 637 keys, not causal, 14.5 on HALVES, 6.5 on pasa_rows.
+// d = 64, pasa_fwd / pasa_fwd4 / pasa_rows:
+//   14 x 5 heads, not causal, 153 / 366 / 688 / 1162 rows     10.2 / 6.7 / 5.2, 12.5 / 8.9 / 11.9, 19.6 / 17.8 / 23.2, 52.3 / 38.9 / 50.8
+//   14 x 5 heads, causal, 169 / 758 / 2321 / 10791 rows       8.7 / 7.1 / 5.6, 17.9 / 15.6 / 21.1, 80.3 / 69.5 / 107, 1362 / 1301 / 1704
+//   one head, causal, 412 / 1664 / 18625 rows                 11.8 / 9.1 / 5.1, 26.5 / 21.8 / 6.8, 129 / 98.8 / 89.7
+//   one head in one / two pieces on pasa_rows, causal, 5586 rows 25.3 / 19.5, not causal, 2536 / 3200 rows 10.1 / 13.0, 10.3 / 14.3
+//   14 x 16 heads, 186 rows at the end of 8006 keys           147 / 166 / 189
 
-// Equal workgroups, `slots` of them at once, each `fixed` us and `tiles` steps of 2.5 us -- 2.8 when all compute units
-// are busy (power; sustained it is 3.5, for both kernels alike), which takes part of the way with the square of the share that is.
-double equal_rounds(double workgroups, double slots, double fixed, double tiles)
+// Equal workgroups, one to a compute unit, each `fixed` us and `steps` steps: of `alone` us, of `busy` where all compute units are at work
+// (power), which takes part of the way with the square of the share that is.
+double equal_rounds(double workgroups, double fixed, double alone, double busy, double steps)
 {
-    const double whole = floor(workgroups / slots), rest = (workgroups - whole * slots) / slots;
-    return whole * (fixed + 2.8 * tiles) + (rest > 0 ? fixed + (2.5 + 0.3 * rest * rest) * tiles : 0.0);
+    const double whole = floor(workgroups / kComputeUnits), rest = workgroups / kComputeUnits - whole;
+    return whole * (fixed + busy * steps) + (rest > 0 ? fixed + (alone + (busy - alone) * rest * rest) * steps : 0.0);
 }
 
-// Causal: `most` steps in the longest workgroup and `mean` on average, longest first.
-double unequal_rounds(double workgroups, double slots, double fixed, double most, double mean)
+// The longer of a chain and the work of the whole chip, and a tenth of the other
+double longer(double chain, double work) { return chain > work ? chain + 0.1 * work : work + 0.1 * chain; }
+
+// Causal, longest first: `most` steps in the longest workgroup, `mean` on average
+double unequal_rounds(double workgroups, double fixed, double chain_step, double work_step, double most, double mean)
 {
-    const double chain = fixed + 2.23 * most, work = workgroups / slots * (fixed + 3.41 * mean);
-    return chain > work ? chain + 0.1 * work : work + 0.1 * chain;
+    return longer(fixed + chain_step * most, workgroups / kComputeUnits * (fixed + work_step * mean));
 }
+
+// pasa_rows, us of a key tile: the only workgroup of a compute unit; one of two or more, equal and causal; and of a pair's start and end
+struct RowsStep {
+    double alone, equal, causal, fixed;
+};
+
+// Two workgroups share a compute unit.  Equal ones come in rounds of 512 (32 heads, not causal, of 512 / 549 rows, 512 / 576 workgroups: 10.8 /
+// 18.5 us).  Causal: the XCDs that share a list get ranges of unequal work (2 heads, d = 64, of 28830 rows: 558 us, evenly shared out
+// it would be 357); a single list is dealt round.
+double rows_time(const RowsStep& at, long workgroups, long lists, bool equal, double most, double mean)
+{
+    const double per = workgroups / (double)kComputeUnits;
+    if (equal) {
+        const double pair = at.fixed + 2 * at.equal * most, whole = floor(per / 2), rest = per - 2 * whole;
+        return 4.0 + whole * pair + (rest == 0 ? 0.0 : rest <= 1 ? at.fixed / 2 + at.alone * most : pair);
+    }
+    const double uneven = lists > 1 && lists < 8 ? 1.584 - 0.073 * (double)lists : 1.0;
+    return 4.0 + longer(at.alone * most, per * (at.fixed / 2 + at.causal * mean) * uneven);
+}
+
+// The merge kernel: its launch, and the partial outputs written and read again
+double merge_us(int ns, size_t rows_all, int d) { return ns > 1 ? 5.5 + 2e-6 * (double)rows_all * ns * d : 0.0; }
 
 // Pieces of a sequence whose keys are swept unsplit have the bits of the whole call: the kernels round P relative to different
 // levels, so all pieces go to the kernel of the whole.  That holds for launches of at least kSplitBelow workgroups of 256 rows
@@ -293,7 +317,6 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
         row0 = 0;
     }
     const size_t rows_all = (size_t)B * Hq * Nq;
-    const double merge = 6.0;      // us: its launch and 4 us for few rows, 8 for many
     Plan p = {Plan::FWD, 1, 0};
     if (may_split && variant != PASA_STRICT16) p.nsplit = fitting(wanted_splits(B, Hq, Nq, N), rows_all, d, room);
     if (counters || variant == PASA_STRICT16 || variant == PASA_NAIVE16) return p;
@@ -307,46 +330,65 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
 
     const int G = Hq / Hkv;
     Plan r = {Plan::ROWS, 1, s16 ? 1 : rows_blocks(B, Hkv, G, rows_given)};
+    const bool one_block = (long)G * Nq <= 16, s16_64 = s16 && d == 64;
+    if (may_split) r.nsplit = fitting(rows_splits(B, Hkv, G, Nq, r.row_blocks, N, most, !one_block && !s16_64), rows_all, d, room);
+    if (one_block) return r;
     double rows_us;
-    {
-        if (may_split) r.nsplit = fitting(rows_splits(B, Hkv, G, Nq, r.row_blocks, N, most), rows_all, d, room);
-        if ((long)G * Nq <= 16) return r;
-        // a split has to save more than its merge costs (d = 64, one head of 2275 rows: 10.1 us in two pieces, 8.7 whole; of 2812 rows,
-        // not causal, 13.0 / 10.6)
-        if (r.nsplit > 1 && (s16 ? 0.85 : 0.55) * most_t * (r.nsplit - 1) < (rows_all > 1024 ? merge + 2.0 : merge) * r.nsplit) r.nsplit = 1;
-        const double uneven = !equal && B * Hq == 1 ? 1.3 : 1.0;     // one causal head: no even ranges for the XCDs
-        // us of a step: d = 128, causal, less beyond 1024 keys, where the longest blocks come first; d = 64, not much less where the
-        // other kernels would split their keys
-        const bool others_split = wanted_splits(B, Hq, Nq, N) > 1 || fwd4_splits(B, Hq, Nq, N) > 1;
-        const double step = d == 64 ? (s16 ? 0.52 : others_split ? 0.54 : 0.44) : causal && N > 1024 ? 0.71 : 0.845;
-        const double work = (!s16 ? 1.0 : d == 64 ? 1.6 : 2.6) * uneven * rows_workgroups(B, Hkv, G, Nq, 2) * (5.5 / 512 + step / 256 * mean_t);
-        const double alone = (s16 ? 0.85 : 0.55) * most_t / r.nsplit;
-        rows_us = 4.0 + (work > alone ? work : alone) + (r.nsplit > 1 ? merge : 0.0);
+    if (s16_64) {
+        // a split has to save more than its merge costs
+        if (r.nsplit > 1 && 0.85 * most_t * (r.nsplit - 1) < (rows_all > 1024 ? 8.0 : 6.0) * r.nsplit) r.nsplit = 1;
+        const double uneven = !equal && B * Hq == 1 ? 1.3 : 1.0;
+        const double work = 1.6 * uneven * rows_workgroups(B, Hkv, G, Nq, 2) * (5.5 / 512 + 0.52 / 256 * mean_t);
+        const double alone = 0.85 * most_t / r.nsplit;
+        rows_us = 4.0 + (work > alone ? work : alone) + (r.nsplit > 1 ? 6.0 : 0.0);
+    } else {
+        static const RowsStep steps[2][2] = {{{0.367, 0.2465, 0.35, 2.373}, {0.521, 0.3765, 0.4321, 3.166}},      // d = 64: 16 rows, 32
+                                             {{0.713, 0.605, 0.6, 3}, {0.7579, 0.5543, 0.7044, 4.429}}};     // d = 128
+        static const RowsStep steps_s16 = {0.83, 0.526, 1.0, 3.01};
+        const int rb = s16 ? 1 : rows_blocks(B, Hkv, G, Nq);       // of the whole: pieces of it are to be planned as it is
+        const RowsStep& at = s16 ? steps_s16 : steps[d == 128][rb - 1];
+        const long workgroups = rows_workgroups(B, Hkv, G, Nq, rb), lists = (long)B * Hkv * (Nq < 16 ? 1 : G);
+        auto us = [&](int ns) {
+            const double t = rows_time(at, workgroups * ns, lists, equal, most_t / ns, mean_t / ns);
+            // S16: weighed against the others, not a time, once there is more than a round of workgroups
+            return (s16 && workgroups * ns > 2 * kComputeUnits ? 4.0 + 1.74 * (t - 4.0) : t) + merge_us(ns, rows_all, d);
+        };
+        rows_us = us(1);
+        if (r.nsplit > 1) {
+            const double split_us = us(r.nsplit);
+            if (split_us < rows_us) rows_us = split_us;
+            else r.nsplit = 1;
+        }
     }
     if (d == 128) {
         const double most_h = ceil(ceil(most_t) / 2), mean_h = mean_t / 2 + 0.25, W = (double)B * Hq * ((Nq + 127) / 128);
-        const double fwd_us = (equal ? equal_rounds(U * p.nsplit, 256, 9.4, most_t / p.nsplit)
-                                     : unequal_rounds(U * p.nsplit, 256, 9.4, most_t / p.nsplit, mean_t / p.nsplit)) * real +
-                              (p.nsplit > 1 ? merge : 0.0);
-        const double halves_us = equal ? equal_rounds(W, 256, 10.5, most_h) : unequal_rounds(W, 256, 10.5, most_h, mean_h);
+        const double most_f = most_t / p.nsplit, mean_f = mean_t / p.nsplit;
+        const double fwd_us = (equal ? equal_rounds(U * p.nsplit, 8.357, s16 ? 4.17 : 2.313, s16 ? 2.91 : 2.699, most_f)
+                                     : unequal_rounds(U * p.nsplit, 8.357, s16 ? 2.51 : 2.111, s16 ? 3.17 : 2.76, most_f, mean_f)) * real +
+                              merge_us(p.nsplit, rows_all, d);
+        const double halves_us = equal ? equal_rounds(W, 8.34, s16 ? 3.69 : 2.45, s16 ? 3.52 : 2.935, most_h)
+                                       : unequal_rounds(W, 8.34, s16 ? 2.78 : 2.2, s16 ? 3.15 : 2.738, most_h, mean_h);
         if (rows_us < 0.98 * (fwd_us < halves_us ? fwd_us : halves_us)) return r;
         if (halves_us < 0.98 * fwd_us) p = {Plan::HALVES, 1, 0};
         return p;
     }
-    // d = 64: a step of pasa_fwd takes 2.0 to 2.55 us, one of pasa_fwd4 1.73 / 2.44 / 3.17 with one / two / three workgroups on every
-    // compute unit (3.7 sustained, under the power limit)
-    const double U_ns = U * p.nsplit, alone = (s16 ? 2.5 : 2.0) * most_t / p.nsplit;
-    const double full = (causal ? U_ns / 256 * mean_t : U_ns <= 256 ? (0.75 + 0.25 * U_ns / 256) * most_t : ceil(U_ns / 256) * most_t) *
-                        (2.0 + 0.55 * (real - 0.85) / 0.15) / p.nsplit;
-    const double fwd_us = (s16 ? 7.0 : 8.1) + (alone > full ? alone : full) + (p.nsplit > 1 ? merge : 0.0);
+    // d = 64, S16: a step of pasa_fwd takes 2.0 to 2.55 us.  The others: of pasa_fwd 2.1 to 2.7, of pasa_fwd4 2.1 / 2.7 / 3.3 with one / two / three
+    // workgroups on every compute unit, all of it a quarter longer than measured (see the line below).
+    const double U_ns = U * p.nsplit, alone = (s16 ? 2.5 : 2.101) * most_t / p.nsplit, power = (real - 0.85) / 0.15;
+    const double busy = s16 ? 2.0 + 0.55 * power : 2.14 + 0.55 * power;
+    const double full = ((s16 ? causal != 0 : !equal) ? U_ns / 256 * mean_t
+                         : U_ns <= 256 ? (0.75 + 0.25 * U_ns / 256) * most_t : ceil(U_ns / 256) * most_t) * busy / p.nsplit;
+    const double longest = alone > full ? alone : full;
+    if (s16) return rows_us <= 0.92 * (7.0 + longest + (p.nsplit > 1 ? 6.0 : 0.0)) ? r : p;
+    const double fwd_us = 10.31 + longest + merge_us(p.nsplit, rows_all, d);
     Plan f = {Plan::FWD4, 1, 0};
     if (may_split) f.nsplit = fitting(fwd4_splits(B, Hq, Nq, N), rows_all, d, room);
     const double W = (double)B * Hq * ((Nq + 127) / 128) * f.nsplit, rest = fmod(W, 768.0);
-    const double rounds = floor(W / 768) * 3.17 + (rest == 0 ? 0.0 : rest <= 256 ? 1.73 : rest <= 512 ? 2.44 : 3.17);
-    const double alone4 = 1.73 * most_t, full4 = causal ? W / 768 * 3.17 * mean_t : rounds * most_t;
-    const double fwd4_us = 7.6 + (alone4 > full4 ? alone4 : full4) / f.nsplit + (f.nsplit > 1 ? merge : 0.0);
-    if (rows_us <= (s16 ? 0.92 : 0.95) * (s16 || fwd_us < fwd4_us ? fwd_us : fwd4_us)) return r;
-    return !s16 && fwd4_us <= 0.98 * fwd_us ? f : p;
+    const double rounds = floor(W / 768) * 3.347 + (rest == 0 ? 0.0 : rest <= 256 ? 2.12 : rest <= 512 ? 2.711 : 3.347);
+    const double alone4 = 2.12 * most_t, full4 = equal ? rounds * most_t : W / 768 * 3.347 * mean_t;
+    const double fwd4_us = 8.423 + (alone4 > full4 ? alone4 : full4) / f.nsplit + merge_us(f.nsplit, rows_all, d);
+    if (rows_us <= 0.7511 * (fwd_us < fwd4_us ? fwd_us : fwd4_us)) return r;
+    return fwd4_us <= 1.005 * fwd_us ? f : p;
 }
 
 size_t split_region_bytes(int B, int Hq, int N, int d)

@@ -45,6 +45,45 @@ def test_calls_reach_the_kernel_they_test(B, Hq, Hkv, Nq, row0, N, d, causal, va
         assert got == kernel and (nsplit > 1) == split, (variant, got, nsplit)
 
 
+# us of the kernel named / of the one that the estimates once chose, which were fitted to calls of 150 to 6000 keys
+@pytest.mark.parametrize("variant,B,Hq,Hkv,Nq,row0,N,d,causal,kernel,split", [
+    (P.MIXED, 1, 28, 4, 2100, 0, 2100, 128, True, "halves", False),              # 42.8 / fwd 48.1
+    (P.MIXED, 1, 28, 4, 2240, 0, 2240, 128, True, "halves", False),              # 45.6 / fwd 53.9
+    (P.MIXED, 1, 28, 4, 841, 0, 841, 128, True, "halves", False),                # 16.7 / rows 20.0
+    (P.S16, 1, 32, 8, 1737, 0, 1737, 128, True, "halves", False),                # 36.4 / fwd 48.0
+    (P.MIXED, 1, 28, 4, 16640, 0, 16640, 128, False, "fwd", False),              # 3656 / halves 3769
+    (P.MIXED, 1, 28, 4, 1391, 0, 10334, 128, False, "fwd", False),               # 216 / halves 273
+    (P.S16, 2, 12, 2, 1345, 0, 19387, 128, False, "fwd", False),                 # 435 / halves 560
+    (P.S16, 1, 12, 2, 569, 0, 569, 128, False, "rows", False),                   # 11.5 / halves 15.3
+    (P.MIXED, 1, 32, 8, 496, 0, 496, 128, False, "rows", False),                 # 11.2 / halves 13.7
+    (P.MIXED, 1, 8, 8, 1595, 0, 23274, 128, False, "rows", False),               # 227 / halves 252
+    (P.MIXED, 14, 12, 2, 5, 0, 2301, 128, False, "rows", True),                  # 12.7 / in one piece 15.2
+    (P.MIXED, 1, 1, 1, 6042, 0, 6042, 64, True, "rows", True),                   # 20.2 / in one piece 26.8
+    (P.MIXED, 2, 1, 1, 28830, 0, 28830, 64, True, "fwd4", False),                # 354 / rows 558
+    (P.MIXED, 4, 1, 1, 12590, 0, 12590, 64, True, "fwd4", False),                # 154 / rows 176
+    (P.MIXED, 14, 16, 16, 186, 7820, 8006, 64, True, "fwd", False),              # 148 / fwd4 166
+])
+def test_calls_go_to_the_kernel_that_was_measured_fastest(variant, B, Hq, Hkv, Nq, row0, N, d, causal, kernel, split):
+    got, nsplit = plan_of(variant, B, Hq, Hkv, Nq, row0, N, d, causal)
+    assert got == kernel and (nsplit > 1) == split, (got, nsplit)
+
+
+def test_pieces_are_planned_as_the_whole():
+    """Wherever a whole sequence's keys are swept unsplit, its pieces of 32 rows or more go to its kernel, and unsplit."""
+    import random
+    rng, pieces = random.Random(4), 0
+    while pieces < 5000:
+        B, (Hq, Hkv, d) = rng.choice([1, 1, 2, 4, 14]), rng.choice([(28, 4, 128), (8, 8, 128), (12, 2, 128), (2, 2, 128), (5, 5, 64), (16, 16, 64), (1, 1, 64)])
+        N, causal, variant = int(2 ** rng.uniform(5, 15)), rng.random() < 0.6, rng.choice([P.MIXED, P.DIRECT, P.S16])
+        Nq = rng.randint(32, min(N, 4096))
+        if N > 2048 and -(-Nq // 256) * Hq * B < 192:
+            continue
+        row0 = rng.randint(0, (N - Nq) // 32) * 32 if causal else 0
+        whole, piece = (plan_of(variant, B, Hq, Hkv, n, r, N, d, causal) for n, r in ((N, 0), (Nq, row0)))
+        assert piece == (whole[0], 1), (variant, B, Hq, Hkv, Nq, row0, N, d, causal, whole, piece)
+        pieces += 1
+
+
 def test_counters_and_fp16_state_stay_on_the_256_row_kernel():
     for variant in (P.MIXED, P.S16, P.DIRECT, P.STRICT16, P.NAIVE16):
         for N in (1, 300, 1024, 9000):
