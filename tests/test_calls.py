@@ -1,4 +1,4 @@
-"""How the binding takes its arguments (the same as through ctypes); nothing is launched: every call is one that is refused."""
+"""How the binding takes its arguments (the same as through ctypes); nothing is launched: a call is refused, or ends in a function of the test."""
 import ctypes
 
 import numpy as np
@@ -82,6 +82,71 @@ def test_every_route_raises_with_the_entry_points_name():
         with pytest.raises(P.PasaError, match=name) as e:
             call()
         assert e.value.status == 1
+
+
+VP, CI, CF, SZ = ctypes.c_void_p, ctypes.c_int, ctypes.c_float, ctypes.c_size_t
+# entry point: its marshaller, C arguments (O: options) and the names of what comes in each place
+ENTRIES = {
+    "pasa_attn_fwd": ("plain", "q k v o B Hq Hkv N d causal scale stream", [VP] * 4 + [CI] * 6 + [CF, VP]),
+    "pasa_attn_fwd_ex": ("whole", "q k v o B Hq Hkv N d causal scale O workspace workspace_bytes stream", [VP] * 4 + [CI] * 6 + [CF, VP, VP, SZ, VP]),
+    "pasa_attn_fwd_adaptive": ("whole", "q k v o B Hq Hkv N d causal scale O workspace workspace_bytes stream", [VP] * 4 + [CI] * 6 + [CF, VP, VP, SZ, VP]),
+    "pasa_prepare_kv": ("prepare", "k v B Hkv N d scale O workspace workspace_bytes stream", [VP] * 2 + [CI] * 4 + [CF, VP, VP, SZ, VP]),
+    "pasa_attn_fwd_chunk": ("chunk", "q o B Hq Hkv Nq row0 N d causal scale O workspace workspace_bytes stream",
+                            [VP] * 2 + [CI] * 8 + [CF, VP, VP, SZ, VP]),
+}
+
+
+class At:
+    def __init__(self, address):
+        self.address = self.cuda_stream = address
+
+    def data_ptr(self):
+        return self.address
+
+
+@pytest.mark.parametrize("route", ["C", "ctypes"])
+@pytest.mark.parametrize("entry", ENTRIES)
+def test_every_argument_arrives_in_its_place(entry, route, monkeypatch):
+    """A function of the test stands in for the entry point and keeps what it was called with."""
+    import functools
+    from paper_2503_01873_amd import _calls, binding
+    marshaller, names, types = ENTRIES[entry]
+    names = names.split()
+    came = {}
+
+    def stand_in(*args):
+        came.update(zip(names, args))
+        if came.get("O"):
+            o = binding.pasa_opts.from_address(came["O"])
+            came["O"] = {f: getattr(o, f) for f, _ in binding.pasa_opts._fields_}
+        return 7
+
+    f = ctypes.CFUNCTYPE(CI, *types)(stand_in)
+    call = functools.partial(getattr(binding, "_" + marshaller), f)
+    if route == "C":
+        def refused(*args):
+            raise AssertionError("ordinary arguments went through ctypes")
+        call = functools.partial(getattr(_calls, marshaller), ctypes.cast(f, VP).value, refused)
+    monkeypatch.setattr(P.lib(), "call_" + entry, call)
+    given = {n: 100 + i for i, n in enumerate(names) if n != "O"}
+    given.update(causal=True, scale=0.375)
+    given.update({n: At((i + 1) << 40 | 0x10) for i, n in enumerate(names) if n in ("q", "v", "o", "workspace", "stream")})
+    given["k"] = 3 << 44                                                  # an address as it is
+    if "workspace_bytes" in names:
+        given["workspace_bytes"] = (5 << 32) + 3
+    given = {n: x for n, x in given.items() if n in names}
+    options = dict(beta=0.25, variant=P.DIRECT, shift_tile=17, overflow_s=At(7 << 41), nonfinite_o=9 << 41, shift_mode=P.SHIFT_MATRIX, io_dtype=P.IO_BF16)
+    if marshaller == "prepare":
+        options["overflow_s"] = options["nonfinite_o"] = None             # it counts nothing: not among its arguments
+    passed = {n: x for n, x in options.items() if x is not None} if "O" in names else {}
+    assert getattr(P, entry)(**given, **passed, check=False) == 7
+    plain = lambda x: x.address if isinstance(x, At) else x
+    for n, x in given.items():
+        assert came[n] == plain(x), n
+    if "O" in names:
+        assert came["O"] == {n: plain(x) for n, x in options.items()}
+    if marshaller == "whole":
+        assert getattr(P, entry)(**given, **passed, opts_null=True, check=False) == 7 and came["O"] is None
 
 
 def test_counters_of_a_chunk_reach_the_library():

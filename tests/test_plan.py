@@ -68,6 +68,15 @@ def test_calls_go_to_the_kernel_that_was_measured_fastest(variant, B, Hq, Hkv, N
     assert got == kernel and (nsplit > 1) == split, (got, nsplit)
 
 
+def test_what_the_workspace_holds_cuts_the_pieces():
+    """Two pieces are not asked for where the rows of a KV head are one block, but may be all that the split region holds."""
+    assert plan_of(P.MIXED, 24, 8, 8, 1, 3999, 4000, 128, True) == ("rows", 1)             # 192 workgroups: not two
+    assert plan_of(P.MIXED, 28, 28, 4, 1, 4999, 5000, 128, True) == ("rows", 2)            # 112 workgroups: four wanted
+    bare = P.pasa_attn_fwd_workspace_min(28, 4, 5000, 128)
+    assert plan_of(P.MIXED, 28, 28, 4, 1, 4999, 5000, 128, True, workspace_bytes=bare) == ("rows", 1)
+    assert plan_of(P.MIXED, 28, 28, 4, 1, 4999, 5000, 128, True, workspace_bytes=bare + (4 << 20)) == ("rows", 4)
+
+
 def test_pieces_are_planned_as_the_whole():
     """Wherever a whole sequence's keys are swept unsplit, its pieces of 32 rows or more go to its kernel, and unsplit."""
     import random
