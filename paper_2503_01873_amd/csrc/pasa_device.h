@@ -21,10 +21,8 @@ inline FastDiv fast_div(unsigned d)
 }
 
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 
 // bf16 inputs are converted to fp16 as they are loaded (the paper's remark on BF16 inputs): round to nearest even,
 // values beyond the fp16 range become infinities.
@@ -34,12 +32,6 @@ __device__ inline h8 bf16x8_to_h8(u16x8 raw)
 #pragma unroll
     for (int e = 0; e < 8; ++e) out[e] = (_Float16)__uint_as_float((unsigned)raw[e] << 16);
     return out;
-}
-
-__device__ inline h8 load_h8(const _Float16* p, int is_bf16)
-{
-    if (is_bf16) return bf16x8_to_h8(*reinterpret_cast<const u16x8*>(p));
-    return *reinterpret_cast<const h8*>(p);
 }
 
 typedef float f16v __attribute__((ext_vector_type(16)));
