@@ -497,8 +497,12 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     const float inv_tail = at.inv_tail;
 
     // Query row r of the Nq rows given sits at sequence position row0 + r (causal: it sees keys <= its position).
+    // Causal, both groups with rows: group A, which runs half a tile ahead, takes the later rows, whose keys reach a tile further.  Its
+    // last matrix part is then the workgroup's last, half a tile before that of group B's with the later rows would be (28 heads on 4, us:
+    // 3000 rows 81.6 -> 81.0, 4096 rows 128.5 -> 127.4, 8192 rows 467.1 -> 465.3; 2 x 16384 rows 3541 -> 3528).
     const int q0 = qt * RWG;
-    const int qw0 = q0 + wcopy * RW;
+    const bool later_first = KSPL == 1 && CAUSAL && q0 + RWG / 2 < Nq;
+    const int qw0 = q0 + (later_first ? wcopy ^ 4 : wcopy) * RW;
     bool wave_valid = qw0 < Nq;            // the wave owns at least one real row
     int last_row_wg = q0 + RWG - 1;
     if (last_row_wg > Nq - 1) last_row_wg = Nq - 1;
@@ -738,8 +742,10 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
         }
     };
 
-    // tiles of this wave, taken or not: the same number of slots for both groups
-    const int j_end = KSPL == 1 ? J_wg : j0 + (J_wg - j0 + 1) / 2 * 2 + jg;
+    // Tiles that each group goes through, taken or not (KSPL = 1: to copy its share of them): as many, or group B one less
+    const int n_a = KSPL == 1 ? J_wg - j0 : (J_wg - j0 + 1) / 2;
+    const int n_b = KSPL == 2 ? (J_wg - j0) / 2 : n_a - (later_first && n_a > 0 && tiles_seen(q0 + RWG / 2 - 1) < J_wg ? 1 : 0);
+    const int j_end = j0 + jg + KSPL * (grp == 0 ? n_a : n_b);
     for (int j = j0 + jg; j <= j_end; j += KSPL) {
         // =========================== matrix part M(j) ===========================
         const bool do_g2 = (j > j0 + jg && j - KSPL < J_w), do_g1 = (j < J_w);
@@ -1009,7 +1015,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
         if (KSPL == 2 || grp == 0) drain_copies();
         __syncthreads();
     }
-    if (grp == 0) __syncthreads();         // group B's last barrier
+    if ((grp == 0) == (n_a == n_b)) __syncthreads();     // the barrier that the other group's last iteration ends with
 
     if (LSUM_MFMA) l = Lacc[0];            // every row of the block is the sum
     // level of the stored output: running maximum in its frame, the frame's offset, the stored scale (exact in fp64)
