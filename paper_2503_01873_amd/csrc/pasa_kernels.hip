@@ -371,6 +371,21 @@ __device__ inline float exp_nat_half(h2 v)
     return __builtin_amdgcn_exp2f(x);
 }
 
+// The largest of a lane's values of P; NaN where one of them is.
+__device__ inline float largest_of(const h8 (&p)[8])
+{
+    h2 top[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        top[e] = h2{p[0][2 * e], p[0][2 * e + 1]};
+#pragma unroll
+        for (int i = 1; i < 8; ++i) top[e] = __builtin_elementwise_maximum(top[e], h2{p[i][2 * e], p[i][2 * e + 1]});
+    }
+    const h2 t = __builtin_elementwise_maximum(__builtin_elementwise_maximum(top[0], top[1]), __builtin_elementwise_maximum(top[2], top[3]));
+    const float a = (float)t[0], b = (float)t[1];
+    return __builtin_elementwise_maximum(a, b);
+}
+
 template <int... I, class F>
 __device__ inline void for_constants(std::integer_sequence<int, I...>, F f) { (f(std::integral_constant<int, I>{}), ...); }
 
@@ -400,6 +415,12 @@ __device__ inline void for_constants(std::integer_sequence<int, I...>, F f) { (f
 // the price is that P is Algorithm 1's exp(S' - m') times e^{c_j} rounded once, not exp(S' - m') rounded and then
 // scaled, so outputs agree with a step-by-step evaluation to rounding, not bit for bit.  DIRECT (levels m' + c) and
 // NAIVE16 (plain online softmax: P relative to the running maximum, dc = 0) use the same bookkeeping.
+// MIXED and S16 keep the level of the stored output as one fp64 number R = m + inva * F + Lc, as the other kernels do, in which the
+// reference level F cancels: P_j = fp16(exp(S' + inva * Sbar' - R)).  So the exponentials need no maximum; whether a row has
+// risen is seen from its P (the largest of packed pairs, three at a time: 18 instructions for 43, nothing exchanged between
+// lanes), and only a wavefront with such a row, or at its first tile, takes the maximum and makes P again.  28 heads on 4, us, both
+// sides in turn: 4096 rows 119.4 -> 118.1, 8192 rows 431.0 -> 426.2; S16, 4096 rows 128.3 -> 124.8, not causal 239.7 -> 234.2; d = 64, 8
+// heads of 2500 rows, not causal, 42.5 -> 40.5.  (DIRECT cannot: there a score may overflow where the tile's bias does not.)
 //
 // KSPL = 2: the workgroup owns 128 rows; both groups of wavefronts hold all of them, group A takes the even key tiles and
 // group B the odd ones, each through a K' and a V buffer of its own, and B's state joins A's through LDS at the end (the rule of
@@ -436,6 +457,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     // instead of summing 128 scores per row and tile on the vector unit
     // DIRECT takes q . k0 of the tiles the same way (their "mean block" holds the shift vectors, low rows zero)
     constexpr bool MSBAR = (VAR == PASA_K_MIXED || VAR == PASA_K_DIRECT);
+    constexpr bool LEVEL = (VAR == PASA_K_MIXED || VAR == PASA_K_S16);     // the level of the stored output is kept as one number
     constexpr int KM_BYTES = 64 * D;                            // one mean block: 32 rows x D halfs
     constexpr int SB_OFF = 4 * (T * D * 2) + KM_BYTES;          // per-wave [16 tiles][32 rows] floats behind it
     constexpr int KT_BYTES = T * D * 2;                         // one K' (or V) tile
@@ -570,7 +592,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     }
     // per-row state (one query row per lane; both halves of the wave hold copies)
     float F = 0.f, m = NAIVE ? -__builtin_inff() : 0.f, l = 0.f;   // STRICT: always fp16-representable values
-    float Lc = 0.f;                  // log of the scale of the stored output (fp32 variants)
+    float Lc = 0.f;                  // log of the scale of the stored output (DIRECT, NAIVE16)
+    double R = -__builtin_inf();     // LEVEL: level of the stored output, m + inva * F + Lc of Algorithm 1's state
     float ec_s = 1.f, ep_s = 0.f;    // STRICT: factors of the pending output combination
     f16v S[4];                       // S'^T accumulators
     h8 Pf[8];                        // P^T, B operand of the second GEMM
@@ -670,7 +693,9 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     const h8 ones = (h8)(_Float16)1;
     float pl_d[4] = {0.f, 0.f, 0.f, 0.f};
     constexpr float CMAX = 8.f;      // LAZY: P may exceed 1 by at most e^CMAX before the row re-references its scale
+    constexpr float PMAX = 2980.f;   // LEVEL: the fp16 value below e^CMAX
     float cj = 0.f;                  // DIRECT: scale * (q . k0) of the tile in the vector part
+    const bool one_tile = CAUSAL ? row0 + row < T || N <= T : N <= T;      // the row sees a single tile
 
     // Both GEMMs run k-step by k-step: the four MFMAs of a k-step share their B operand (the Q or P fragment) and go
     // to the four accumulator blocks in turn, so consecutive MFMAs never depend on each other and the B registers are
@@ -859,21 +884,24 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                     }
             }
             // ---- local maximum m' ----
-            float pm[4];
+            auto row_max = [&] {
+                float pm[4];
 #pragma unroll
-            for (int kb = 0; kb < 4; ++kb) {
-                if (STRICT) {
-                    h2 mm = Sh[kb][0];
+                for (int kb = 0; kb < 4; ++kb) {
+                    if (STRICT) {
+                        h2 mm = Sh[kb][0];
 #pragma unroll
-                    for (int t = 1; t < 8; ++t) mm = __builtin_elementwise_max(mm, Sh[kb][t]);
-                    pm[kb] = __builtin_fmaxf((float)mm[0], (float)mm[1]);
-                    continue;
+                        for (int t = 1; t < 8; ++t) mm = __builtin_elementwise_max(mm, Sh[kb][t]);
+                        pm[kb] = __builtin_fmaxf((float)mm[0], (float)mm[1]);
+                        continue;
+                    }
+                    pm[kb] = S[kb][0];
+#pragma unroll
+                    for (int i = 1; i < 16; ++i) pm[kb] = __builtin_fmaxf(pm[kb], S[kb][i]);
                 }
-                pm[kb] = S[kb][0];
-#pragma unroll
-                for (int i = 1; i < 16; ++i) pm[kb] = __builtin_fmaxf(pm[kb], S[kb][i]);
-            }
-            const float mx = max32(__builtin_fmaxf(__builtin_fmaxf(pm[0], pm[1]), __builtin_fmaxf(pm[2], pm[3])));
+                return max32(__builtin_fmaxf(__builtin_fmaxf(pm[0], pm[1]), __builtin_fmaxf(pm[2], pm[3])));
+            };
+            const float mx = LEVEL ? 0.f : row_max();
             // A wave whose rows straddle a tile boundary (chunks not aligned to 32 rows) reaches tile j although its
             // first rows see none of it: those rows keep their state and add nothing.
             const bool unseen = CAUSAL && diag && (row0 + row < j * T);
@@ -933,31 +961,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                 c_adj = (keep || resc) ? 0.f : c;
                 Lc = first ? 0.f : unseen ? Lc : resc ? dc : lcn;
                 m = first ? lev : unseen ? m : mn;
-            } else if (!STRICT && !NAIVE) {
-                // Written without branches (the first tile and rows that see nothing of the tile select their values at
-                // the end) so that it stays in one block with the exponentials.
-                // F is only a reference level (it cancels between the two correction terms), so Eq. (15)'s division by
-                // j is a multiplication by the hardware's reciprocal of j here
-                const int seen = KSPL == 1 ? j - j0 : (j - j0) >> 1;
-                const float jm1 = (float)seen, rj = __builtin_amdgcn_rcpf((float)(seen + 1));
-                const float Fn = (jm1 * F + sbar) * rj;
-                const float dpp = inva * (F - Fn);
-                const float dpc = inva * (sbar - Fn);
-                const float mn = __builtin_fmaxf(m + dpp, mx + dpc);
-                const float dp = (m - mn) + dpp;
-                const float dc = (mx - mn) + dpc;
-                const bool keep = first || unseen;        // no recovering step for this row
-                // the stored output keeps its scale (its log moves by dp with the frame); the tile's P takes the factor
-                // e^c that places it there, unless that is too large: then the row's output and sum move to this tile
-                const float lcn = Lc + dp, c = dc - lcn;
-                resc = !keep && c > CMAX;
-                lc_resc = -c;
-                c_adj = (keep || resc) ? 0.f : c;
-                Lc = first ? 0.f : unseen ? Lc : resc ? dc : lcn;
-                F = first ? sbar : unseen ? F : Fn;
-                m = first ? mx : unseen ? m : mn;
             }
-            if (LAZY && __builtin_amdgcn_ballot_w64(resc) != 0ull) {
+            if (LAZY && !LEVEL && __builtin_amdgcn_ballot_w64(resc) != 0ull) {
                 // rare (the running maximum rose by more than CMAX above the stored scale); the pending product of
                 // tile j-1 is already in O.  The empty asm keeps this a branch instead of 64 selects on every tile.
                 asm volatile("" ::: "memory");
@@ -974,8 +979,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
             }
             // ---- P = exp(S' - m' [+ c]) rounded to fp16; l' = sum of the rounded P ----
             float lsum = 0.f;
-            {
-                const float nml = (c_adj - mref) * LOG2E;
+            float nml = (c_adj - mref) * LOG2E;
+            auto exponentials = [&] {
                 float pl[4];
 #pragma unroll
                 for (int kb = 0; kb < 4; ++kb) {
@@ -1000,6 +1005,42 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                 }
                 if (!LSUM_MFMA && !LSUM_DEFER) lsum = sum32((pl[0] + pl[1]) + (pl[2] + pl[3]));
                 if (STRICT) lsum = (float)(_Float16)lsum;
+            };
+            if (LEVEL) {
+                // The scores of a tile stand for S' + inva * Sbar' (what the two correction terms of step 3 add up to: F cancels), so
+                // P = exp(S' + inva * Sbar' - R) needs no maximum.  That a row has risen by more than CMAX above its stored output, or
+                // has none yet (R = -inf), shows in P itself, and only then the maximum is taken, the row moved to the level of this
+                // tile and P made again.  NaN, and with it the row, where the pseudo-average is not finite.
+                float off = __builtin_fmaf(sbar, 0.f, (float)__builtin_fma((double)inva, (double)sbar, -R));
+                if (CAUSAL && diag && unseen) off = 0.f;
+                nml = off * LOG2E;
+                unsigned long long high = ~0ull;
+                if (!first) {
+                    exponentials();
+                    high = __builtin_amdgcn_ballot_w64(!(largest_of(Pf) <= PMAX));
+                }
+                if (high != 0ull) {
+                    asm volatile("" ::: "memory");
+                    const bool move = !unseen && (((unsigned)high | (unsigned)(high >> 32)) >> lq & 1u) != 0u;
+                    // a row that sees a single tile needs no pseudo-average, which may be infinite there
+                    const float top = row_max(), bias = one_tile ? 0.f : sbar, bad = (top + bias) * 0.f;
+                    const double lev = (double)top + (double)inva * (double)bias;
+                    const float r = move ? exp_nat((float)(R - lev) + bad) : 1.f;
+                    R = move ? lev : R;
+                    nml = move ? (bad - top) * LOG2E : nml;
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) O[cb][i] *= r;
+                    l *= r;
+                    if (LSUM_MFMA) {
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) Lacc[i] *= r;
+                    }
+                    exponentials();
+                }
+            } else {
+                exponentials();
             }
 
             // ---- the running sum (step 4); STRICT16: the whole of step 3 and 4 in fp16 ----
@@ -1022,8 +1063,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     bool none = !(J_w > j0 + jg) || l == 0.f;
     // (a row that sees a single tile needs no pseudo-average, which may be infinite there).  Not finite: a score or a
     // pseudo-average left the range of its type, and the state must not be taken for one without keys.
-    const bool one_tile = CAUSAL ? row0 + row < T || N <= T : N <= T;
-    double level = none ? -__builtin_inf() : (double)m + (one_tile ? 0.0 : (double)inva * (double)F) + (double)Lc;
+    double level = none ? -__builtin_inf() : LEVEL ? R : (double)m + (one_tile ? 0.0 : (double)inva * (double)F) + (double)Lc;
     if (!none && !__builtin_isfinite(level)) level = __builtin_nan("");
     // ---------------- key split within the workgroup: group B's state joins group A's ----------------
     if (KSPL == 2) {

@@ -16,7 +16,7 @@ import pytest
 import paper_2503_01873_amd as P
 from oracle import pasa_oracle as po
 from workloads import Workload, workload, gen_full, gen_q_head, gen_kv_head
-from gpu_harness import bf16_bits, gpu_adaptive, gpu_attn, gpu_attn_chunks, compare, f32, ORACLE_POLICY, VARIANT_NAME
+from gpu_harness import bf16_bits, gpu_adaptive, gpu_attn, gpu_attn_chunks, compare, f32, plan_of, ORACLE_POLICY, VARIANT_NAME
 
 pytestmark = pytest.mark.gpu
 
@@ -928,6 +928,30 @@ def test_score_level_staircase_in_unaligned_chunks(step, variant):
     # one call over all rows gives the same values as the chunks: the per-row state does not depend on the chunking
     o1, _ = gpu_attn(q, k, v, True, scale, variant)
     assert np.array_equal(o1, o)
+
+
+@pytest.mark.parametrize("variant", [P.MIXED, P.S16, P.DIRECT])
+@pytest.mark.parametrize("B,Hq,Hkv,N,d,causal,kernel", [
+    (1, 28, 4, 1000, 128, True, "halves"), (4, 32, 8, 500, 128, False, "fwd"), (4, 32, 8, 512, 128, True, "fwd"),
+    (14, 6, 6, 1000, 64, False, "fwd4"), (2, 4, 2, 400, 128, True, "rows"), (2, 4, 2, 400, 64, True, "rows"),
+])
+def test_a_row_that_rises_leaves_its_neighbours_alone(B, Hq, Hkv, N, d, causal, kernel, variant):
+    """One row in 32 climbs by 12 per key tile, so that every wavefront re-references a stored output on every tile: the other
+    rows have the bits that they have beside a row that does not climb."""
+    if variant != P.S16:
+        assert plan_of(variant, B, Hq, Hkv, N, 0, N, d, causal)[0] == kernel
+    rng = np.random.default_rng(N + d)
+    q = rng.standard_normal((B, Hq, N, d)).astype(np.float16)
+    k = rng.standard_normal((B, Hkv, N, d)).astype(np.float16)
+    v = rng.standard_normal((B, Hkv, N, d)).astype(np.float16)
+    k[..., 5] = 12.0 * (np.arange(N) // 128) * d ** 0.5 / 4.0
+    q[..., 5] = 0.0
+    flat, _ = gpu_attn(q, k, v, causal, f32(d ** -0.5), variant)
+    up = np.arange(N) % 32 == 7
+    q[:, :, up, 5] = 4.0
+    o, _ = gpu_attn(q, k, v, causal, f32(d ** -0.5), variant)
+    assert np.isfinite(o).all() and not np.array_equal(o[:, :, up], flat[:, :, up])
+    assert o[:, :, ~up].tobytes() == flat[:, :, ~up].tobytes()
 
 
 # ------------------------------------------------------------------ exact symmetries (no oracle involved)
