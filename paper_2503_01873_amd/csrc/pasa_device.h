@@ -103,6 +103,35 @@ __device__ inline float add_pair(h2 v, float acc)
     return __builtin_amdgcn_fdot2(v, one, acc, false);
 }
 
+// The largest of a lane's values of P; NaN where one of them is.
+__device__ inline float largest_of(const h8 (&p)[8])
+{
+    h2 top[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        top[e] = h2{p[0][2 * e], p[0][2 * e + 1]};
+#pragma unroll
+        for (int i = 1; i < 8; ++i) top[e] = __builtin_elementwise_maximum(top[e], h2{p[i][2 * e], p[i][2 * e + 1]});
+    }
+    const h2 t = __builtin_elementwise_maximum(__builtin_elementwise_maximum(top[0], top[1]), __builtin_elementwise_maximum(top[2], top[3]));
+    const float a = (float)t[0], b = (float)t[1];
+    return __builtin_elementwise_maximum(a, b);
+}
+
+// Scores of a block of 32 keys in the accumulator layout: -inf where key 8 (i / 4) + i % 4 (counted from the lane's first) is beyond
+// `last`.  By bits: with a comparison per score the 64 results of a tile are wanted in scalar registers all at once, more than there are.
+__device__ inline void mask_keys(f16v& s, int last)
+{
+    const int keep = last < 0 ? 0 : last > 31 ? 32 : last + 1;
+    const unsigned beyond = (unsigned)(0xffffffffull << keep);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        unsigned m;                              // 0 or all ones; the builtin is turned into a comparison and a selection
+        asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m) : "v"(beyond), "n"(8 * (i >> 2) + (i & 3)));
+        s[i] = __uint_as_float((0xff800000u & m) | (__float_as_uint(s[i]) & ~m));
+    }
+}
+
 // One wave-wide direct global -> LDS copy of 1 KiB: lane i moves 16 bytes from byte soff + 16*i of the buffer to
 // ldst + 16*i.  soff and ldst must be wave-uniform (ldst travels in M0).
 // OFF is an immediate added to both addresses, so a wave's consecutive pieces share one M0 value.

@@ -18,6 +18,7 @@ __device__ inline void workgroup_barrier()
 }
 
 constexpr float CMAX = 8.f;     // P may exceed 1 by at most e^CMAX before a row moves its stored output to a new level
+constexpr float PMAX = 2980.f;  // the fp16 value below e^CMAX
 
 // One workgroup = four wavefronts = 128 query rows of one head, 32 rows per wavefront; three workgroups share a compute
 // unit and three wavefronts a SIMD.  The GEMMs are pasa_fwd's (32x32x16 MFMAs, transposed, fragments from LDS through a ring
@@ -31,11 +32,16 @@ constexpr float CMAX = 8.f;     // P may exceed 1 by at most e^CMAX before a row
 // v_dot2_f32_f16: the matrix core (P against ones) is faster on zeros (1163 against 1230 us) and slower on values (1519 / 1508 on
 // the 14 x 5 heads of 9216 rows with resonant values, 1785 / 1713 with normal ones): power, not cycles, is what is short.
 // That workload, pasa_fwd -> this kernel: 1624 -> 1508 us (1826 -> 1713 with normal values).
-template <bool CAUSAL>
+// MIXED makes P without the maximum of the tile, as pasa_fwd does (see there); a wavefront with a row that rises makes the scores again too,
+// since there are no registers to keep them beside P (kept: spills, 283 -> 319 us on 14 x 5 heads of 5000 rows, causal).  us, both sides in turn, normal
+// values: 14 x 5 heads of 9216 rows 1663 -> 1601, causal 5000 rows 284 -> 274; 16 heads of 8192 rows 315 -> 295, causal 16000 rows 575 -> 554.
+// 64 rows per wavefront and two workgroups to a compute unit on top of it (half the LDS reads): 1 % faster on the 9216 rows,
+// 4 to 20 % slower on all smaller calls.
+template <bool CAUSAL, bool DIRECT>
 __global__ __launch_bounds__(256, 3)
 void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Float16* __restrict__ o,
                const _Float16* __restrict__ kmean, int Hq, int Hkv, int Nq, int row0, int N, int nqt, float coef,
-               int tail_by_count, int io_bf16, const unsigned long long* gate, int nsplit, float* __restrict__ part_o,
+               int io_bf16, const unsigned long long* gate, int nsplit, float* __restrict__ part_o,
                double* __restrict__ part_lr)
 {
     constexpr int D = 64;
@@ -168,7 +174,7 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
         h8 Pf[8];
         if (j < J_w) {
             f16v S[4];
-            {
+            auto scores = [&] {
                 const _Float16* lds_k = reinterpret_cast<const _Float16*>(smem + (j & 1) * KT_BYTES);
                 auto frag = [&](int n) { return *reinterpret_cast<const h8*>(lds_k + ((2 * (n / 4) + lh) * T + 32 * (n % 4) + lq) * 8); };
                 h8 a[PF];
@@ -182,55 +188,83 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
                     if (n + PF < 4 * KS) a[n % PF] = frag(n + PF);
                     PASA_FENCE();
                 }
-            }
-            const bool tail = N - j * T < T;
+                if ((CAUSAL && j * T + T - 1 > pos_w0) || N - j * T < T) {
+#pragma unroll
+                    for (int kb = 0; kb < 4; ++kb) mask_keys(S[kb], last_key - (j * T + 32 * kb + 4 * lh));
+                }
+            };
             float v = sb[(j & 7) * 32 + lq];
-            if (tail_by_count && tail) v *= (float)T * (1.0f / (float)(N - j * T));
-            if ((CAUSAL && j * T + T - 1 > pos_w0) || tail) {
+            if (!DIRECT && N - j * T < T) v *= (float)T * (1.0f / (float)(N - j * T));
+            // By position: the scores of keys that the row sees may all have overflowed to -inf
+            const bool unseen = last_key < j * T;
+            float nml;
+            auto exponentials = [&] {
 #pragma unroll
                 for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        if (j * T + 32 * kb + 8 * (i >> 2) + 4 * lh + (i & 3) > last_key) S[kb][i] = -__builtin_inff();
+                    for (int t2 = 0; t2 < 8; ++t2) {
+                        const h2 p2 = pack_rn(__builtin_amdgcn_exp2f(__builtin_fmaf(S[kb][2 * t2], LOG2E, nml)),
+                                              __builtin_amdgcn_exp2f(__builtin_fmaf(S[kb][2 * t2 + 1], LOG2E, nml)));
+                        Pf[2 * kb + (t2 >> 2)][2 * (t2 & 3)] = p2[0];
+                        Pf[2 * kb + (t2 >> 2)][2 * (t2 & 3) + 1] = p2[1];
+                    }
+            };
+            // Rows that `rises` holds for, and that see keys of the tile, move to its level: the maximum of its scores and their bias.  A
+            // row that sees a single tile needs no bias, which may be infinite.  nml is NaN, and with it the row, where the maximum
+            // or the bias is not finite.
+            auto move_up = [&](auto rises) {
+                float pm[4];
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb) {
+                    pm[kb] = S[kb][0];
+#pragma unroll
+                    for (int i = 1; i < 16; ++i) pm[kb] = __builtin_fmaxf(pm[kb], S[kb][i]);
+                }
+                const float mx = max32(__builtin_fmaxf(__builtin_fmaxf(pm[0], pm[1]), __builtin_fmaxf(pm[2], pm[3])));
+                if (last_key < T) v = 0.f;
+                const double lev = (double)mx + (double)coef * (double)v;
+                const float c = (float)(lev - R) + (mx + v) * 0.f;
+                const bool move = rises(c);
+                if (DIRECT) nml = unseen ? 0.f : (c - mx) * LOG2E;
+                if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
+                    asm volatile("" ::: "memory");
+                    const float r = move ? __builtin_amdgcn_exp2f(-c * LOG2E) : 1.f;
+                    R = move ? lev : R;
+                    nml = move ? ((mx + v) * 0.f - mx) * LOG2E : nml;
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) O[cb][i] *= r;
+#pragma unroll
+                    for (int kb = 0; kb < 4; ++kb) l4[kb] *= r;
+                }
+            };
+            if (DIRECT) {
+                scores();
+                move_up([&](float c) { return c > CMAX; });
+                exponentials();
+            } else {
+                float off = __builtin_fmaf(v, 0.f, (float)__builtin_fma((double)coef, (double)v, -R));
+                if (unseen) off = 0.f;
+                nml = off * LOG2E;
+                unsigned long long high = ~0ull;
+                if (j != j0) {
+                    scores();
+                    exponentials();
+                    high = __builtin_amdgcn_ballot_w64(!(largest_of(Pf) <= PMAX));
+                }
+                if (high != 0ull) {
+                    asm volatile("" ::: "memory");
+                    scores();                // there are no registers to keep them beside P
+                    move_up([&](float) { return !unseen && (((unsigned)high | (unsigned)(high >> 32)) >> lq & 1u) != 0u; });
+                    exponentials();
+                }
             }
-            float pm[4];
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb) {
-                pm[kb] = S[kb][0];
-#pragma unroll
-                for (int i = 1; i < 16; ++i) pm[kb] = __builtin_fmaxf(pm[kb], S[kb][i]);
-            }
-            const float mx = max32(__builtin_fmaxf(__builtin_fmaxf(pm[0], pm[1]), __builtin_fmaxf(pm[2], pm[3])));
-            // By position: the scores of keys that the row sees may all have overflowed to -inf.  A row that sees a single tile
-            // needs no bias, which may be infinite.  c is NaN, and with it the row, where the maximum or the bias is not finite.
-            const bool unseen = last_key < j * T;
-            if (last_key < T) v = 0.f;
-            const double lev = (double)mx + (double)coef * (double)v;
-            float c = (float)(lev - R) + (mx + v) * 0.f;
-            const bool move = c > CMAX;
-            if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
-                asm volatile("" ::: "memory");
-                const float r = move ? __builtin_amdgcn_exp2f(-c * LOG2E) : 1.f;
-                R = move ? lev : R;
-                c = move ? 0.f : c;
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) O[cb][i] *= r;
-#pragma unroll
-                for (int kb = 0; kb < 4; ++kb) l4[kb] *= r;
-            }
-            const float nml = unseen ? 0.f : (c - mx) * LOG2E;
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-                for (int t2 = 0; t2 < 8; ++t2) {
-                    const h2 p2 = pack_rn(__builtin_amdgcn_exp2f(__builtin_fmaf(S[kb][2 * t2], LOG2E, nml)),
-                                          __builtin_amdgcn_exp2f(__builtin_fmaf(S[kb][2 * t2 + 1], LOG2E, nml)));
-                    Pf[2 * kb + (t2 >> 2)][2 * (t2 & 3)] = p2[0];
-                    Pf[2 * kb + (t2 >> 2)][2 * (t2 & 3) + 1] = p2[1];
-                    l4[kb] = add_pair(p2, l4[kb]);
-                }
+                for (int t2 = 0; t2 < 8; ++t2)
+                    l4[kb] = add_pair(h2{Pf[2 * kb + (t2 >> 2)][2 * (t2 & 3)], Pf[2 * kb + (t2 >> 2)][2 * (t2 & 3) + 1]}, l4[kb]);
         }
         PASA_FENCE();
         __builtin_amdgcn_s_waitcnt(0x0F70 | CPW);        // this wavefront's share of V(j); that of K'(j + 1) may be on its way
@@ -278,12 +312,12 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
                   o + (head * Nq + qw0) * D, Nq - qw0, lane, io_bf16);
 }
 
-template <bool CAUSAL>
+template <bool CAUSAL, bool DIRECT>
 hipError_t launch_fwd4(const PasaLaunch& p)
 {
     constexpr int D = 64, LDS_BYTES = 3 * T * D * 2 + 4096;
     const int nqt = (p.Nq + 127) / 128, nsplit = p.nsplit < 1 ? 1 : p.nsplit;
-    auto kern = pasa_fwd4<CAUSAL>;
+    auto kern = pasa_fwd4<CAUSAL, DIRECT>;
     static std::atomic<unsigned long long> lds_limit_set{0ull};      // once per device
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -296,7 +330,7 @@ hipError_t launch_fwd4(const PasaLaunch& p)
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)(nqt * p.Hq * p.B * nsplit)), dim3(256), LDS_BYTES, p.stream, (const _Float16*)p.q,
                        (const char*)p.ws, (_Float16*)p.o, (const _Float16*)p.kmean, p.Hq, p.Hkv, p.Nq, p.row0, p.N, nqt,
-                       p.variant == PASA_K_DIRECT ? p.scale : p.inva, p.variant == PASA_K_MIXED ? 1 : 0, p.io_bf16, p.gate,
+                       DIRECT ? p.scale : p.inva, p.io_bf16, p.gate,
                        nsplit, nsplit > 1 ? (float*)p.part_o : nullptr, nsplit > 1 ? (double*)p.part_lr : nullptr);
     e = hipGetLastError();
     if (e != hipSuccess || nsplit == 1) return e;
@@ -307,5 +341,6 @@ hipError_t launch_fwd4(const PasaLaunch& p)
 
 hipError_t pasa_launch_fwd4(const PasaLaunch& p)
 {
-    return p.causal ? launch_fwd4<true>(p) : launch_fwd4<false>(p);
+    if (p.variant == PASA_K_DIRECT) return p.causal ? launch_fwd4<true, true>(p) : launch_fwd4<false, true>(p);
+    return p.causal ? launch_fwd4<true, false>(p) : launch_fwd4<false, false>(p);
 }

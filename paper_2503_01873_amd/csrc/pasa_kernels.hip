@@ -371,21 +371,6 @@ __device__ inline float exp_nat_half(h2 v)
     return __builtin_amdgcn_exp2f(x);
 }
 
-// The largest of a lane's values of P; NaN where one of them is.
-__device__ inline float largest_of(const h8 (&p)[8])
-{
-    h2 top[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        top[e] = h2{p[0][2 * e], p[0][2 * e + 1]};
-#pragma unroll
-        for (int i = 1; i < 8; ++i) top[e] = __builtin_elementwise_maximum(top[e], h2{p[i][2 * e], p[i][2 * e + 1]});
-    }
-    const h2 t = __builtin_elementwise_maximum(__builtin_elementwise_maximum(top[0], top[1]), __builtin_elementwise_maximum(top[2], top[3]));
-    const float a = (float)t[0], b = (float)t[1];
-    return __builtin_elementwise_maximum(a, b);
-}
-
 template <int... I, class F>
 __device__ inline void for_constants(std::integer_sequence<int, I...>, F f) { (f(std::integral_constant<int, I>{}), ...); }
 
