@@ -104,14 +104,15 @@ __device__ inline float add_pair(h2 v, float acc)
 }
 
 // The largest of a lane's values of P; NaN where one of them is.
-__device__ inline float largest_of(const h8 (&p)[8])
+template <int N>
+__device__ inline float largest_of(const h8 (&p)[N])
 {
     h2 top[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         top[e] = h2{p[0][2 * e], p[0][2 * e + 1]};
 #pragma unroll
-        for (int i = 1; i < 8; ++i) top[e] = __builtin_elementwise_maximum(top[e], h2{p[i][2 * e], p[i][2 * e + 1]});
+        for (int i = 1; i < N; ++i) top[e] = __builtin_elementwise_maximum(top[e], h2{p[i][2 * e], p[i][2 * e + 1]});
     }
     const h2 t = __builtin_elementwise_maximum(__builtin_elementwise_maximum(top[0], top[1]), __builtin_elementwise_maximum(top[2], top[3]));
     const float a = (float)t[0], b = (float)t[1];

@@ -244,11 +244,11 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
                 move_up([&](float c) { return c > CMAX; });
                 exponentials();
             } else {
-                float off = __builtin_fmaf(v, 0.f, (float)__builtin_fma((double)coef, (double)v, -R));
-                if (unseen) off = 0.f;
-                nml = off * LOG2E;
+                nml = 0.f;
                 unsigned long long high = ~0ull;
                 if (j != j0) {
+                    const float off = __builtin_fmaf(v, 0.f, (float)__builtin_fma((double)coef, (double)v, -R));
+                    if (!unseen) nml = off * LOG2E;
                     scores();
                     exponentials();
                     high = __builtin_amdgcn_ballot_w64(!(largest_of(Pf) <= PMAX));

@@ -13,6 +13,7 @@ namespace {
 
 constexpr int U = 64;           // keys per unit of work of one wavefront (half a tile)
 constexpr float CMAX = 8.f;     // P may exceed 1 by at most e^CMAX before a row moves its stored output to a new level
+constexpr float PMAX = 2980.f;  // the fp16 value below e^CMAX
 
 __device__ inline h8 load_frag(__amdgpu_buffer_rsrc_t src, int voff, int soff)
 {
@@ -72,11 +73,11 @@ __device__ inline float sum_row(float x)
 // odd rows the low parts), and the level is kept in absolute terms.  (With row sums in lanes and the products for eight
 // tiles at a time shared out by shuffles, 32 rows took twice as long as 16.)  Four wavefronts per workgroup: two workgroups
 // share a compute unit, so that one loads while the other merges (28 heads of 512 rows 16.8 -> 11.7 us against eight).
-template <int D, int RB, int NW, bool S16>
+template <int D, int RB, int NW, bool S16, bool DIRECT>
 __global__ __launch_bounds__(64 * NW, 2)
 void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, const _Float16* __restrict__ kmean,
                _Float16* __restrict__ o, FastDiv lists, FastDiv Nq_, FastDiv nblk_, FastDiv nsplit_, int grid, int list_rows, int row0, int N,
-               int causal, int units, float coef, int tail_by_count, int io_bf16, const unsigned long long* gate,
+               int causal, int units, float coef, int io_bf16, const unsigned long long* gate,
                float* __restrict__ part_o, double* __restrict__ part_lr, size_t rows_all)
 {
     constexpr int KS = D / 32;                   // k-steps of the first GEMM
@@ -84,6 +85,10 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
     constexpr int ROWS = 16 * RB;
     constexpr int LD = D + 4;                    // LDS row of the merge, in floats
     constexpr int TILE_BYTES = 4 * T * D;        // K' tile then V tile
+    // P without the maximum of its scores, as in pasa_fwd.  us, both sides in turn: 4 heads, 700 rows of 12800 keys 71.9 -> 65.2; 2 x 16 heads, 128
+    // rows of 28000 keys 81.1 -> 79.7; S16, 14 x 5 heads of 366 rows 13.4 -> 12.4.  d = 128 waits for its fragments, not for this chain (128 rows
+    // of 20000 keys 91.4 / 91.0), and with 32 rows has no registers to keep the scores beside P (777 rows 18.5 / 20.9).
+    constexpr bool LEVEL = !DIRECT && D == 64;
     __shared__ __attribute__((aligned(16))) float lds_o[NW * ROWS * LD];
     __shared__ double lds_r[NW][ROWS];
     __shared__ float lds_l[NW][ROWS];
@@ -320,7 +325,7 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
                     v = sum_row(sum[rb]) * (tail < T ? 1.0f / (float)tail : 1.0f / T);
                 } else {
                     v = M[rb][0] + M[rb][1] * 0.00048828125f;    // low parts are stored times 2^11
-                    if (tail_by_count && tail < T) v *= (float)T * (1.0f / (float)tail);
+                    if (!DIRECT && tail < T) v *= (float)T * (1.0f / (float)tail);
                 }
                 if (u * U + U - 1 > first_pos) {
 #pragma unroll
@@ -329,42 +334,71 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
                         for (int i = 0; i < 4; ++i)
                             if (u * U + 32 * (b >> 1) + 16 * (g >> 1) + 8 * (b & 1) + 4 * (g & 1) + i > last[rb]) S[rb][b][i] = -__builtin_inff();
                 }
-                float mx = S[rb][0][0];
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) mx = __builtin_fmaxf(mx, S[rb][b][i]);
-                mx = max_row(mx);
                 // A row that sees a single tile needs no bias, which may be infinite: a score that overflowed to -inf only takes
                 // its own weight there.
                 const bool one_tile = last[rb] < T;
                 if (one_tile) v = 0.f;
-                // Not "no score above -inf": those of a key that the row sees may all have overflowed.
-                const bool unseen = last[rb] < u * U || (one_tile && mx == -__builtin_inff());
-                // c: level of this unit's scores relative to the stored output's (first unit: +inf, which clears the zeros).  NaN, and
-                // with it the row, where the maximum or the bias is not finite: scores of keys it sees left the range of their type.
-                const double lev = (double)mx + (double)coef * (double)v;
-                float c = (float)(lev - R[rb]) + (mx + v) * 0.f;
-                const bool move = c > CMAX;
-                if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
-                    const float r = move ? __builtin_amdgcn_exp2f(-c * LOG2E) : 1.f;
-                    R[rb] = move ? lev : R[rb];
-                    c = move ? 0.f : c;
-                    L[rb] *= r;
+                const bool seen = last[rb] >= u * U;
+                float nml;
+                auto exponentials = [&] {
 #pragma unroll
-                    for (int cb = 0; cb < CB; ++cb) O[rb][cb] *= r;
-                }
-                const float nml = unseen ? 0.f : (c - mx) * LOG2E;
+                    for (int b = 0; b < 4; ++b)
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
+                        for (int i = 0; i < 4; i += 2) {
+                            const f2 e = {__builtin_amdgcn_exp2f(__builtin_fmaf(S[rb][b][i], LOG2E, nml)),
+                                          __builtin_amdgcn_exp2f(__builtin_fmaf(S[rb][b][i + 1], LOG2E, nml))};
+                            const h2 ph = __builtin_convertvector(e, h2);
+                            P[rb][b >> 1][4 * (b & 1) + i] = ph[0];
+                            P[rb][b >> 1][4 * (b & 1) + i + 1] = ph[1];
+                        }
+                };
+                // Rows that `rises` holds for move their stored output to the level of this unit's maximum.  Not "no score above -inf"
+                // for a row without keys here: those of keys that it sees may all have overflowed.  c is the unit's level relative to the
+                // stored output's (first unit: +inf, which clears the zeros); NaN, and with it the row, where the maximum or the bias is not
+                // finite: scores of keys it sees left the range of their type.
+                auto move_up = [&](auto rises) {
+                    float mx = S[rb][0][0];
 #pragma unroll
-                    for (int i = 0; i < 4; i += 2) {
-                        const f2 e = {__builtin_amdgcn_exp2f(__builtin_fmaf(S[rb][b][i], LOG2E, nml)),
-                                      __builtin_amdgcn_exp2f(__builtin_fmaf(S[rb][b][i + 1], LOG2E, nml))};
-                        const h2 ph = __builtin_convertvector(e, h2);
-                        P[rb][b >> 1][4 * (b & 1) + i] = ph[0];
-                        P[rb][b >> 1][4 * (b & 1) + i + 1] = ph[1];
+                    for (int b = 0; b < 4; ++b)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) mx = __builtin_fmaxf(mx, S[rb][b][i]);
+                    mx = max_row(mx);
+                    const bool unseen = !seen || (one_tile && mx == -__builtin_inff());
+                    const double lev = (double)mx + (double)coef * (double)v;
+                    const float bad = (mx + v) * 0.f;
+                    float c = (float)(lev - R[rb]) + bad;
+                    const bool move = rises(c) && (!LEVEL || !unseen);
+                    if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
+                        const float r = move ? __builtin_amdgcn_exp2f(-c * LOG2E) : 1.f;
+                        R[rb] = move ? lev : R[rb];
+                        c = move ? bad : c;
+                        L[rb] *= r;
+#pragma unroll
+                        for (int cb = 0; cb < CB; ++cb) O[rb][cb] *= r;
                     }
+                    if (!LEVEL || move) nml = (c - mx) * LOG2E;
+                    if (unseen) nml = 0.f;
+                };
+                if (!LEVEL) {
+                    move_up([](float c) { return c > CMAX; });
+                    exponentials();
+                } else {
+                    // a row that has risen above its stored output, or has none yet, shows in its P
+                    nml = 0.f;
+                    unsigned long long high = ~0ull;
+                    if (__builtin_amdgcn_ballot_w64(R[rb] != -__builtin_inf()) != 0ull) {      // not at the first unit
+                        const float off = __builtin_fmaf(v, 0.f, (float)__builtin_fma((double)coef, (double)v, -R[rb]));
+                        if (seen) nml = off * LOG2E;
+                        exponentials();
+                        high = __builtin_amdgcn_ballot_w64(!(largest_of(P[rb]) <= PMAX));
+                    }
+                    if (high != 0ull) {
+                        asm volatile("" ::: "memory");
+                        const unsigned both = (unsigned)high | (unsigned)(high >> 32);
+                        move_up([&](float) { return ((both | both >> 16) >> lq & 1u) != 0u; });
+                        exponentials();
+                    }
+                }
             }
             auto gemm2 = [&](const h8 (&v)[HF], int half) {
 #pragma unroll
@@ -596,7 +630,7 @@ void launch_merge(const void* part_o, const void* part_lr, void* o, size_t rows_
                        (const float*)part_o, (const double*)part_lr, (_Float16*)o, rows_all, nsplit, io_bf16, nonfinite_o);
 }
 
-template <int D, int RB, int NW, bool S16 = false>
+template <int D, int RB, int NW, bool S16, bool DIRECT>
 hipError_t launch_rows(const PasaLaunch& p)
 {
     const int G = p.Hq / p.Hkv, lists = p.Nq < 16 ? 1 : G, list_rows = p.Nq < 16 ? G * p.Nq : p.Nq;
@@ -606,13 +640,20 @@ hipError_t launch_rows(const PasaLaunch& p)
     const int nsplit = (all + units - 1) / units;                 // none without keys
     const size_t rows_all = (size_t)p.B * p.Hq * p.Nq;
     const unsigned grid = (unsigned)((size_t)p.B * p.Hkv * lists * nblk * nsplit);
-    hipLaunchKernelGGL((pasa_rows<D, RB, NW, S16>), dim3(grid), dim3(64 * NW), 0, p.stream,
+    hipLaunchKernelGGL((pasa_rows<D, RB, NW, S16, DIRECT>), dim3(grid), dim3(64 * NW), 0, p.stream,
                        (const _Float16*)p.q, (const char*)p.ws, (const _Float16*)p.kmean, (_Float16*)p.o, fast_div(lists), fast_div(p.Nq),
-                       fast_div(nblk), fast_div(nsplit), (int)grid, list_rows, p.row0, p.N, p.causal, units, p.variant == PASA_K_DIRECT ? p.scale : p.inva,
-                       p.variant == PASA_K_MIXED ? 1 : 0, p.io_bf16, p.gate, (float*)p.part_o, (double*)p.part_lr, rows_all);
+                       fast_div(nblk), fast_div(nsplit), (int)grid, list_rows, p.row0, p.N, p.causal, units, DIRECT ? p.scale : p.inva,
+                       p.io_bf16, p.gate, (float*)p.part_o, (double*)p.part_lr, rows_all);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nsplit == 1) return e;
     return pasa_launch_merge(p.part_o, p.part_lr, p.o, rows_all, p.d, nsplit, p.io_bf16, nullptr, p.stream);
+}
+
+template <bool DIRECT>
+hipError_t launch_rows_of(const PasaLaunch& p, int row_blocks)
+{
+    if (p.d == 128) return row_blocks == 1 ? launch_rows<128, 1, 4, false, DIRECT>(p) : launch_rows<128, 2, 4, false, DIRECT>(p);
+    return row_blocks == 1 ? launch_rows<64, 1, 4, false, DIRECT>(p) : launch_rows<64, 2, 4, false, DIRECT>(p);
 }
 
 }  // namespace
@@ -627,7 +668,7 @@ hipError_t pasa_launch_merge(const void* part_o, const void* part_lr, void* o, s
 
 hipError_t pasa_launch_rows(const PasaLaunch& p, int row_blocks)
 {
-    if (p.variant == PASA_K_S16) return p.d == 128 ? launch_rows<128, 1, 4, true>(p) : launch_rows<64, 1, 4, true>(p);
-    if (p.d == 128) return row_blocks == 1 ? launch_rows<128, 1, 4>(p) : launch_rows<128, 2, 4>(p);
-    return row_blocks == 1 ? launch_rows<64, 1, 4>(p) : launch_rows<64, 2, 4>(p);
+    if (p.variant == PASA_K_S16) return p.d == 128 ? launch_rows<128, 1, 4, true, false>(p) : launch_rows<64, 1, 4, true, false>(p);
+    if (p.variant == PASA_K_DIRECT) return launch_rows_of<true>(p, row_blocks);
+    return launch_rows_of<false>(p, row_blocks);
 }
