@@ -74,10 +74,9 @@ __device__ inline float sum_row(float x)
 // tiles at a time shared out by shuffles, 32 rows took twice as long as 16.)  Four wavefronts per workgroup: two workgroups
 // share a compute unit, so that one loads while the other merges (28 heads of 512 rows 16.8 -> 11.7 us against eight).
 template <int D, int RB, int NW, bool S16, bool DIRECT>
-__global__ __launch_bounds__(64 * NW, 2)
-void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, const _Float16* __restrict__ kmean,
+__device__ __forceinline__ void rows_body(const _Float16* __restrict__ q, const char* __restrict__ ws, const _Float16* __restrict__ kmean,
                _Float16* __restrict__ o, FastDiv lists, FastDiv Nq_, FastDiv nblk_, FastDiv nsplit_, int grid, int list_rows, int row0, int N,
-               int causal, int units, float coef, int io_bf16, const unsigned long long* gate,
+               int causal, int units, float coef, int mixed, int io_bf16, const unsigned long long* gate,
                float* __restrict__ part_o, double* __restrict__ part_lr, size_t rows_all)
 {
     constexpr int KS = D / 32;                   // k-steps of the first GEMM
@@ -88,7 +87,8 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
     // P without the maximum of its scores, as in pasa_fwd.  us, both sides in turn: 4 heads, 700 rows of 12800 keys 71.9 -> 65.2; 2 x 16 heads, 128
     // rows of 28000 keys 81.1 -> 79.7; S16, 14 x 5 heads of 366 rows 13.4 -> 12.4.  d = 128 waits for its fragments, not for this chain (128 rows
     // of 20000 keys 91.4 / 91.0), and with 32 rows has no registers to keep the scores beside P (777 rows 18.5 / 20.9).
-    constexpr bool LEVEL = !DIRECT && D == 64;
+    // Not DIRECT, where a score may overflow though the tile's bias does not.
+    constexpr bool LEVEL = D == 64 && !DIRECT;
     __shared__ __attribute__((aligned(16))) float lds_o[NW * ROWS * LD];
     __shared__ double lds_r[NW][ROWS];
     __shared__ float lds_l[NW][ROWS];
@@ -325,7 +325,7 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
                     v = sum_row(sum[rb]) * (tail < T ? 1.0f / (float)tail : 1.0f / T);
                 } else {
                     v = M[rb][0] + M[rb][1] * 0.00048828125f;    // low parts are stored times 2^11
-                    if (!DIRECT && tail < T) v *= (float)T * (1.0f / (float)tail);
+                    if (mixed && tail < T) v *= (float)T * (1.0f / (float)tail);
                 }
                 if (u * U + U - 1 > first_pos) {
 #pragma unroll
@@ -367,7 +367,7 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
                     const double lev = (double)mx + (double)coef * (double)v;
                     const float bad = (mx + v) * 0.f;
                     float c = (float)(lev - R[rb]) + bad;
-                    const bool move = rises(c) && (!LEVEL || !unseen);
+                    const bool move = rises(c) && !(LEVEL && unseen);
                     if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
                         const float r = move ? __builtin_amdgcn_exp2f(-c * LOG2E) : 1.f;
                         R[rb] = move ? lev : R[rb];
@@ -383,10 +383,9 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
                     move_up([](float c) { return c > CMAX; });
                     exponentials();
                 } else {
-                    // a row that has risen above its stored output, or has none yet, shows in its P
                     nml = 0.f;
                     unsigned long long high = ~0ull;
-                    if (__builtin_amdgcn_ballot_w64(R[rb] != -__builtin_inf()) != 0ull) {      // not at the first unit
+                    if (__builtin_amdgcn_ballot_w64(R[rb] != -__builtin_inf()) != 0ull) {     // not at the first unit
                         const float off = __builtin_fmaf(v, 0.f, (float)__builtin_fma((double)coef, (double)v, -R[rb]));
                         if (seen) nml = off * LOG2E;
                         exponentials();
@@ -394,6 +393,7 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
                     }
                     if (high != 0ull) {
                         asm volatile("" ::: "memory");
+                        // a row that has risen above its stored output, or has none yet, shows in the P of one of its four lanes
                         const unsigned both = (unsigned)high | (unsigned)(high >> 32);
                         move_up([&](float) { return ((both | both >> 16) >> lq & 1u) != 0u; });
                         exponentials();
@@ -480,6 +480,26 @@ void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, cons
             if (real) *reinterpret_cast<uint4*>(o + grow * D + c8) = uint4{out[0], out[1], out[2], out[3]};
         }
     }
+}
+
+template <int D, int RB, int NW, bool S16>
+__global__ __launch_bounds__(64 * NW, 2)
+void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, const _Float16* __restrict__ kmean,
+               _Float16* __restrict__ o, FastDiv lists, FastDiv Nq_, FastDiv nblk_, FastDiv nsplit_, int grid, int list_rows, int row0, int N,
+               int causal, int units, float coef, int mixed, int io_bf16, const unsigned long long* gate,
+               float* __restrict__ part_o, double* __restrict__ part_lr, size_t rows_all)
+{
+    rows_body<D, RB, NW, S16, false>(q, ws, kmean, o, lists, Nq_, nblk_, nsplit_, grid, list_rows, row0, N, causal, units, coef, mixed, io_bf16, gate, part_o, part_lr, rows_all);
+}
+
+template <int D, int RB, int NW>
+__global__ __launch_bounds__(64 * NW, 2)
+void pasa_rows_direct(const _Float16* __restrict__ q, const char* __restrict__ ws, const _Float16* __restrict__ kmean,
+                      _Float16* __restrict__ o, FastDiv lists, FastDiv Nq_, FastDiv nblk_, FastDiv nsplit_, int grid, int list_rows, int row0, int N,
+                      int causal, int units, float coef, int mixed, int io_bf16, const unsigned long long* gate,
+                      float* __restrict__ part_o, double* __restrict__ part_lr, size_t rows_all)
+{
+    rows_body<D, RB, NW, false, true>(q, ws, kmean, o, lists, Nq_, nblk_, nsplit_, grid, list_rows, row0, N, causal, units, coef, mixed, io_bf16, gate, part_o, part_lr, rows_all);
 }
 
 // Merge of the key splits of one call: per query row, the splits' stored outputs and sums are brought to the highest of
@@ -630,7 +650,7 @@ void launch_merge(const void* part_o, const void* part_lr, void* o, size_t rows_
                        (const float*)part_o, (const double*)part_lr, (_Float16*)o, rows_all, nsplit, io_bf16, nonfinite_o);
 }
 
-template <int D, int RB, int NW, bool S16, bool DIRECT>
+template <int D, int RB, int NW, bool S16 = false>
 hipError_t launch_rows(const PasaLaunch& p)
 {
     const int G = p.Hq / p.Hkv, lists = p.Nq < 16 ? 1 : G, list_rows = p.Nq < 16 ? G * p.Nq : p.Nq;
@@ -640,20 +660,15 @@ hipError_t launch_rows(const PasaLaunch& p)
     const int nsplit = (all + units - 1) / units;                 // none without keys
     const size_t rows_all = (size_t)p.B * p.Hq * p.Nq;
     const unsigned grid = (unsigned)((size_t)p.B * p.Hkv * lists * nblk * nsplit);
-    hipLaunchKernelGGL((pasa_rows<D, RB, NW, S16, DIRECT>), dim3(grid), dim3(64 * NW), 0, p.stream,
+    auto kern = pasa_rows<D, RB, NW, S16>;
+    if (D == 64 && p.variant == PASA_K_DIRECT) kern = pasa_rows_direct<64, RB, NW>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * NW), 0, p.stream,
                        (const _Float16*)p.q, (const char*)p.ws, (const _Float16*)p.kmean, (_Float16*)p.o, fast_div(lists), fast_div(p.Nq),
-                       fast_div(nblk), fast_div(nsplit), (int)grid, list_rows, p.row0, p.N, p.causal, units, DIRECT ? p.scale : p.inva,
-                       p.io_bf16, p.gate, (float*)p.part_o, (double*)p.part_lr, rows_all);
+                       fast_div(nblk), fast_div(nsplit), (int)grid, list_rows, p.row0, p.N, p.causal, units, p.variant == PASA_K_DIRECT ? p.scale : p.inva,
+                       p.variant == PASA_K_MIXED ? 1 : 0, p.io_bf16, p.gate, (float*)p.part_o, (double*)p.part_lr, rows_all);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nsplit == 1) return e;
     return pasa_launch_merge(p.part_o, p.part_lr, p.o, rows_all, p.d, nsplit, p.io_bf16, nullptr, p.stream);
-}
-
-template <bool DIRECT>
-hipError_t launch_rows_of(const PasaLaunch& p, int row_blocks)
-{
-    if (p.d == 128) return row_blocks == 1 ? launch_rows<128, 1, 4, false, DIRECT>(p) : launch_rows<128, 2, 4, false, DIRECT>(p);
-    return row_blocks == 1 ? launch_rows<64, 1, 4, false, DIRECT>(p) : launch_rows<64, 2, 4, false, DIRECT>(p);
 }
 
 }  // namespace
@@ -668,7 +683,7 @@ hipError_t pasa_launch_merge(const void* part_o, const void* part_lr, void* o, s
 
 hipError_t pasa_launch_rows(const PasaLaunch& p, int row_blocks)
 {
-    if (p.variant == PASA_K_S16) return p.d == 128 ? launch_rows<128, 1, 4, true, false>(p) : launch_rows<64, 1, 4, true, false>(p);
-    if (p.variant == PASA_K_DIRECT) return launch_rows_of<true>(p, row_blocks);
-    return launch_rows_of<false>(p, row_blocks);
+    if (p.variant == PASA_K_S16) return p.d == 128 ? launch_rows<128, 1, 4, true>(p) : launch_rows<64, 1, 4, true>(p);
+    if (p.d == 128) return row_blocks == 1 ? launch_rows<128, 1, 4>(p) : launch_rows<128, 2, 4>(p);
+    return row_blocks == 1 ? launch_rows<64, 1, 4>(p) : launch_rows<64, 2, 4>(p);
 }
