@@ -219,7 +219,7 @@ int fwd4_splits(int B, int Hq, int Nq, int N)
 size_t split_row_bytes(int d) { return (size_t)d * 4 + 16; }
 
 // The kernel of a call, in how many pieces its keys are swept (as many as the kernel's rule wants and the `room` bytes behind
-// the fixed regions of the workspace hold), and the blocks of 16 rows per workgroup of pasa_rows.
+// the fixed regions of the workspace hold), and the blocks of 16 rows per workgroup of pasa_rows, of rows per wavefront of HALVES.
 struct Plan {
     enum { FWD, HALVES, FWD4, ROWS } kernel;
     int nsplit, row_blocks;
@@ -369,7 +369,9 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
         const double halves_us = equal ? equal_rounds(W, 8.34, s16 ? 3.69 : 2.45, s16 ? 3.52 : 2.935, most_h)
                                        : unequal_rounds(W, 8.34, s16 ? 2.78 : 2.2, s16 ? 3.15 : 2.738, most_h, mean_h);
         if (rows_us < 0.98 * (fwd_us < halves_us ? fwd_us : halves_us)) return r;
-        if (halves_us < 0.98 * fwd_us) p = {Plan::HALVES, 1, 0};
+        // MFMAs of 32 rows in workgroups of a single round and four steps at most: there is power to spare, and instructions count (us, 28 heads, causal,
+        // 32 rows / 16: 1024 rows 23.6 / 24.6; 2048 rows 49.6 / 47.7; 8 heads, not causal, 4096 rows 76.1 / 73.7)
+        if (halves_us < 0.98 * fwd_us) p = {Plan::HALVES, 1, W <= kComputeUnits && most_h <= 4 ? 1 : 2};
         return p;
     }
     // d = 64, S16: a step of pasa_fwd takes 2.0 to 2.55 us.  The others: of pasa_fwd 2.1 to 2.7, of pasa_fwd4 2.1 / 2.7 / 3.3 with one / two / three
@@ -650,7 +652,7 @@ int fwd_chunk_impl(const void* q, void* o, int B, int Hq, int Hkv, int Nq, int r
     const Plan plan = plan_call(pr.variant, counters, gate == nullptr, B, Hq, Hkv, Nq, p.row0, N, d, causal, workspace_bytes - need);
     const int ns = plan.nsplit;
     p.nsplit = ns;
-    p.halves = plan.kernel == Plan::HALVES;
+    p.halves = plan.kernel == Plan::HALVES ? plan.row_blocks : 0;
     char* split_base = static_cast<char*>(workspace) + need;
     p.part_lr = split_base;                                              // [ns][rows][2] doubles
     p.part_o = split_base + (size_t)ns * rows_all * 16;                  // [ns][rows][d] floats

@@ -35,6 +35,7 @@ __device__ inline h8 bf16x8_to_h8(u16x8 raw)
 }
 
 typedef float f16v __attribute__((ext_vector_type(16)));
+typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 
@@ -86,6 +87,42 @@ __device__ inline float max32(float x)
     float lo, hi;
     halves32(x, lo, hi);
     return __builtin_fmaxf(lo, hi);
+}
+
+// x of the even and of the odd one of each pair of 16-lane rows, in both; x of the lower and of the upper 32 lanes, in both
+__device__ inline void rows16(float x, float& even, float& odd)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    even = __uint_as_float(r[0]);
+    odd = __uint_as_float(r[1]);
+}
+__device__ inline void rows32(float x, float& low, float& high)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    low = __uint_as_float(r[0]);
+    high = __uint_as_float(r[1]);
+}
+// largest value / sum over the four lanes l, l^16, l^32, l^48 that share a query row
+__device__ inline float max_row(float x)
+{
+    float a, b;
+    rows16(x, a, b);
+    rows32(__builtin_fmaxf(a, b), a, b);
+    return __builtin_fmaxf(a, b);
+}
+__device__ inline float sum_row(float x)
+{
+    float a, b;
+    rows16(x, a, b);
+    rows32(a + b, a, b);
+    return a + b;
+}
+// the odd 16-lane rows of a <-> the even ones of b before them
+__device__ inline void swap16(float& a, float& b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
 }
 
 __device__ inline float exp_nat(float x) { return __builtin_amdgcn_exp2f(x * LOG2E); }
@@ -147,24 +184,29 @@ __device__ inline void copy_1k_to_lds(__amdgpu_buffer_rsrc_t src, int soff, char
 }
 
 // The output of a wavefront's 32 query rows goes through LDS (`mine`: 64 * D bytes that no other wavefront uses), so that a store
-// writes 1 KiB of neighbouring bytes.  In the accumulator layout lane (lq, lh) holds channels 32 cb + 8 g + 4 lh .. + 3 of row lq:
-// value(cb, i) is the one of element i.  dst: the first row; `rows` of them are real.  16-byte chunks are placed by row ^ chunk,
+// writes 1 KiB of neighbouring bytes.  RB = 1, the 32x32 accumulators: lane (lq, g) holds channels 32 cb + 8 (e / 4) + 4 g + e % 4 of row lq.
+// RB = 2, 16x16: channels 16 cb + 4 g + e of rows lq and 16 + lq.  value(rb, cb, e) is the one of element e.  dst: the first row; `rows` of them are
+// real.  16-byte chunks are placed by row ^ chunk,
 // against bank conflicts.  Straight from the accumulators, eight bytes a lane and a row apart, with the conversions of both types
 // in line, the end of a workgroup of 256 rows took 3.5 us.
-template <int D, bool BF16, class Value>
+template <int D, int RB, bool BF16, class Value>
 __device__ inline void store_rows_as(char* mine, Value value, _Float16* dst, int rows, int lane)
 {
     asm volatile("" : "+v"(lane));               // no address is to be worked out before the main loop and kept through it
-    const int lq = lane & 31, lh = lane >> 5;
+    constexpr int RR = 32 / RB, NE = 16 / (RB * RB);
+    const int lq = lane & (RR - 1), g = lane / RR;
 #pragma unroll
-    for (int cb = 0; cb < D / 32; ++cb)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            uint2 x;
-            x.x = BF16 ? pack_bf16(value(cb, 4 * g), value(cb, 4 * g + 1)) : pack_f16(value(cb, 4 * g), value(cb, 4 * g + 1));
-            x.y = BF16 ? pack_bf16(value(cb, 4 * g + 2), value(cb, 4 * g + 3)) : pack_f16(value(cb, 4 * g + 2), value(cb, 4 * g + 3));
-            *reinterpret_cast<uint2*>(mine + lq * (2 * D) + (((4 * cb + g) ^ (lq & 7)) * 16) + 8 * lh) = x;
-        }
+        for (int cb = 0; cb < D / RR; ++cb)
+#pragma unroll
+            for (int e = 0; e < NE; e += 4) {
+                uint2 x;
+                x.x = BF16 ? pack_bf16(value(rb, cb, e), value(rb, cb, e + 1)) : pack_f16(value(rb, cb, e), value(rb, cb, e + 1));
+                x.y = BF16 ? pack_bf16(value(rb, cb, e + 2), value(rb, cb, e + 3)) : pack_f16(value(rb, cb, e + 2), value(rb, cb, e + 3));
+                const int chunk = RB == 1 ? 4 * cb + e / 4 : 2 * cb + (g >> 1);
+                *reinterpret_cast<uint2*>(mine + (RR * rb + lq) * (2 * D) + ((chunk ^ (lq & 7)) * 16) + 8 * (g & 1)) = x;
+            }
     __builtin_amdgcn_wave_barrier();             // a wavefront's LDS accesses are done in order
     asm volatile("" ::: "memory");
     constexpr int CH = D / 8, RPI = 64 / CH;     // chunks of a row, rows per store
@@ -175,11 +217,11 @@ __device__ inline void store_rows_as(char* mine, Value value, _Float16* dst, int
         if (r < rows) *reinterpret_cast<uint4*>(dst + (size_t)r * D + 8 * c) = x;
     }
 }
-template <int D, class Value>
+template <int D, int RB, class Value>
 __device__ inline void store_rows(char* mine, Value value, _Float16* dst, int rows, int lane, int io_bf16)
 {
-    if (io_bf16) store_rows_as<D, true>(mine, value, dst, rows, lane);
-    else store_rows_as<D, false>(mine, value, dst, rows, lane);
+    if (io_bf16) store_rows_as<D, RB, true>(mine, value, dst, rows, lane);
+    else store_rows_as<D, RB, false>(mine, value, dst, rows, lane);
 }
 
 #define PASA_FENCE() __builtin_amdgcn_sched_barrier(0)

@@ -308,7 +308,7 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
     }
     // through the buffer of the last K' tile: all wavefronts have read it, and the copy that went beyond it is in the other one
     const float oscale = 1.0f / l;
-    store_rows<D>(smem + ((J_wg - 1) & 1) * KT_BYTES + wave * (64 * D), [&](int cb, int i) { return O[cb][i] * oscale; },
+    store_rows<D, 1>(smem + ((J_wg - 1) & 1) * KT_BYTES + wave * (64 * D), [&](int, int cb, int i) { return O[cb][i] * oscale; },
                   o + (head * Nq + qw0) * D, Nq - qw0, lane, io_bf16);
 }
 

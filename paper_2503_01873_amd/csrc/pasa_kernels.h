@@ -31,7 +31,7 @@ struct PasaLaunch {
                       // go to part_o ([nsplit, B*Hq*Nq, d] floats) and part_lr ([nsplit, B*Hq*Nq, 2] doubles: sum, level)
                       // and are merged by a second kernel; ignored by PASA_K_STRICT16
     int halves;       // d = 128, not STRICT16 or NAIVE16, no counters: workgroups of 128 rows whose two groups of wavefronts take
-                      // the even and the odd key tiles
+                      // the even and the odd key tiles; 1: with MFMAs of 32 rows, 2: of 16 rows, 0: not
     void* part_o;
     void* part_lr;
     hipStream_t stream;

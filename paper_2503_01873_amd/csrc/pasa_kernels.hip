@@ -8,13 +8,13 @@
 //                 a tile is a straight copy whose MFMA fragments are single conflict-free 128-bit LDS reads.
 //
 //  pasa_fwd       Algorithm 1's main loops.  One workgroup = 8 wavefronts = 256 query rows; each wavefront owns
-//                 32 query rows and sweeps the key tiles.  Both GEMMs are computed transposed on
-//                 v_mfma_f32_32x32x16_f16:
+//                 32 query rows and sweeps the key tiles.  Both GEMMs are computed transposed, at d = 128 on
+//                 v_mfma_f32_16x16x32_f16 (two blocks of 16 rows), at d = 64 on v_mfma_f32_32x32x16_f16 (one of 32):
 //                     S'^T = K' Q^T      (A = K' fragment from LDS, B = Q fragment held in registers)
 //                     O^T += V^T P^T     (A = V^T fragment from LDS, B = P^T taken straight from the S'^T accumulators)
-//                 In the transposed accumulator layout a lane holds 64 keys of ONE query row, so the row
-//                 statistics (pseudo-average Sbar', maximum m', sum l') are in-lane reductions plus one exchange
-//                 with lane^32, and exp(S'-m') converted to fp16 is already the B operand of the second GEMM.
+//                 In the transposed accumulator layout a lane holds a quarter (16 x 16: of two rows) or half of the keys of a query row, so
+//                 the row statistics (pseudo-average Sbar', maximum m', sum l') are in-lane reductions plus an exchange
+//                 between four or two lanes, and exp(S'-m') converted to fp16 is already the B operand of the second GEMM.
 //
 // Workspace: for every (batch, KV head, key tile) the K' tile followed by the V tile, so that one tile pair is
 // one contiguous block that is copied to LDS verbatim with direct global->LDS loads, double buffered.
@@ -25,7 +25,7 @@
 // Tile layouts (one tile = 128 keys x D channels, fp16, 16-byte chunks):
 //   K' tile: chunk index (c/8)*128 + n         holds channels 8*(c/8) .. +7 of key n
 //   V  tile: chunk index ((n/16)*2 + h)*D + c  holds, for channel c, the 8 keys 16*(n/16) + {4h..4h+3, 8+4h..8+4h+3}
-// The second layout is the key order in which a lane of the 32x32 accumulator holds its S'^T rows.
+// The second layout is the key order in which a lane of the 32x32 accumulator holds its S'^T rows; with 16x16 the keys of a block are chosen to fit it.
 //
 // The matrix cores accumulate in fp32 in every variant; "fp16" quantities are rounded (nearest-even) where
 // Algorithm 1 marks them.
@@ -371,6 +371,20 @@ __device__ inline float exp_nat_half(h2 v)
     return __builtin_amdgcn_exp2f(x);
 }
 
+// The same with an offset: 2 to the (float)half * log2(e) + off, a fused multiply-add
+template <int HI>
+__device__ inline float exp_off_half(h2 v, float off)
+{
+    float x;
+    const float k = LOG2E;
+    if (HI) asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(x) : "v"(v), "s"(k), "v"(off));
+    else asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(x) : "v"(v), "s"(k), "v"(off));
+    return __builtin_amdgcn_exp2f(x);
+}
+
+__device__ inline f16v mma(h8 a, h8 b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
+__device__ inline f4 mma(h8 a, h8 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+
 template <int... I, class F>
 __device__ inline void for_constants(std::integer_sequence<int, I...>, F f) { (f(std::integral_constant<int, I>{}), ...); }
 
@@ -402,10 +416,19 @@ __device__ inline void for_constants(std::integer_sequence<int, I...>, F f) { (f
 // NAIVE16 (plain online softmax: P relative to the running maximum, dc = 0) use the same bookkeeping.
 // MIXED and S16 keep the level of the stored output as one fp64 number R = m + inva * F + Lc, as the other kernels do, in which the
 // reference level F cancels: P_j = fp16(exp(S' + inva * Sbar' - R)).  So the exponentials need no maximum; whether a row has
-// risen is seen from its P (the largest of packed pairs, three at a time: 18 instructions for 43, nothing exchanged between
-// lanes), and only a wavefront with such a row, or at its first tile, takes the maximum and makes P again.  28 heads on 4, us, both
-// sides in turn: 4096 rows 119.4 -> 118.1, 8192 rows 431.0 -> 426.2; S16, 4096 rows 128.3 -> 124.8, not causal 239.7 -> 234.2; d = 64, 8
-// heads of 2500 rows, not causal, 42.5 -> 40.5.  (DIRECT cannot: there a score may overflow where the tile's bias does not.)
+// risen is seen from its P (the largest of packed pairs, three at a time, nothing exchanged between lanes), and only a block of rows with such a
+// row, or at its first tile, takes the maximum and makes P again.  Workgroups of two halves, whose chains are short, and MIXED at d = 64 take the
+// maximum on every tile all the same: in the first tiles rows keep rising, and P made twice costs more there (us, without / so: 28 heads,
+// 2048 rows 49.5 / 47.7; 8 heads, 4096 rows, not causal, 77.2 / 73.7, of 2500 rows, d = 64, 50.1 / 47.0).  (DIRECT cannot: there a score may overflow
+// where the tile's bias does not.)
+//
+// RB: the MFMAs.  RB = 1: one block of 32 rows, 32 x 32 x 16; RB = 2: two blocks of 16 rows, 16 x 16 x 32, each fragment of K' and V used twice
+// in a row.  Both have the same rate and read as much LDS per product, but per product 16 x 16 x 32 moves half as many accumulators
+// through the registers (twice as many operands, of half the width): with fragments from LDS and normal values a loop of nothing else reaches
+// 1.71 PFLOP/s against 1.50, on zeros 2.36 against 2.42.  Power is what bounds the long launches at d = 128, so they take it: 28 heads on 4, us, both
+// sides in turn, 8192 rows 449 -> 403, 4096 rows not causal 233 -> 209; S16, 4096 rows 136 -> 124; DIRECT 129 -> 120; 1500 rows of 12000 keys
+// 254 -> 242.  An MFMA holds the issue port though, and there are twice as many: where the vector part is the longer one (d = 64), or launches are short,
+// 32 x 32 x 16 is faster (8 heads, d = 64, 2500 rows 50.1 / 53.6; 2 x 5 heads of 5000 rows, STRICT16 128 / 138).
 //
 // KSPL = 2: the workgroup owns 128 rows; both groups of wavefronts hold all of them, group A takes the even key tiles and
 // group B the odd ones, each through a K' and a V buffer of its own, and B's state joins A's through LDS at the end (the rule of
@@ -424,7 +447,7 @@ struct FwdPlace {
 };
 enum { PASA_FWD_OWN_GROUPS, PASA_FWD_SHARED, PASA_FWD_PLAIN };
 
-template <int D, int VAR, bool CAUSAL, bool INSTR, int KSPL>
+template <int D, int VAR, bool CAUSAL, bool INSTR, int KSPL, int RB>
 __global__ __launch_bounds__(512, 2)
 void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Float16* __restrict__ o,
               const _Float16* __restrict__ kmean, FwdPlace at, int Nq, int row0, int N, float inva, float scale, int io_bf16,
@@ -432,17 +455,25 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
               const unsigned long long* gate, float* __restrict__ part_o, double* __restrict__ part_lr)
 {
 
-    constexpr int KS = D / 16;   // k-steps of S'^T = K' Q^T
-    constexpr int CB = D / 32;   // 32-channel row blocks of O^T
+    constexpr int RR = 32 / RB;                  // rows of a block; keys or channels of a block of A
+    constexpr int NE = 16 / (RB * RB);           // elements of an accumulator block that a lane holds
+    constexpr int NG = 2 * RB;                   // lanes that share a query row; 16-byte chunks of a k-step
+    constexpr int KS = D / (8 * NG);             // k-steps of S'^T = K' Q^T
+    constexpr int CB = D / RR;                   // row blocks of O^T
+    constexpr int KB = T / RR;                   // row blocks of S'^T
+    constexpr int KK = T / (8 * NG);             // k-steps of O^T += V^T P^T
+    using Acc = std::conditional_t<RB == 1, f16v, f4>;
     constexpr bool S16 = (VAR != PASA_K_MIXED && VAR != PASA_K_DIRECT);   // S' rounded to fp16 as it leaves the matrix core
     constexpr bool STRICT = (VAR == PASA_K_STRICT16);
     constexpr bool NAIVE = (VAR == PASA_K_NAIVE16);
+    constexpr bool PACKED = (VAR == PASA_K_STRICT16 || VAR == PASA_K_S16);   // the rounded scores stay packed, two to a register
     constexpr bool DIRECT = (VAR == PASA_K_DIRECT);               // bias added back as scale * (q . k0), no pseudo-average
     // MIXED takes the pseudo-average as q . colmean(K') (Eq. (12), (14)) on the matrix core, 16 tiles at a time,
     // instead of summing 128 scores per row and tile on the vector unit
     // DIRECT takes q . k0 of the tiles the same way (their "mean block" holds the shift vectors, low rows zero)
     constexpr bool MSBAR = (VAR == PASA_K_MIXED || VAR == PASA_K_DIRECT);
     constexpr bool LEVEL = (VAR == PASA_K_MIXED || VAR == PASA_K_S16);     // the level of the stored output is kept as one number
+    constexpr bool EAGER = KSPL == 2 || (D == 64 && MSBAR);     // LEVEL: the maximum on every tile all the same
     constexpr int KM_BYTES = 64 * D;                            // one mean block: 32 rows x D halfs
     constexpr int SB_OFF = 4 * (T * D * 2) + KM_BYTES;          // per-wave [16 tiles][32 rows] floats behind it
     constexpr int KT_BYTES = T * D * 2;                         // one K' (or V) tile
@@ -456,7 +487,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = wave >> 2;
-    const int lq = lane & 31, lh = lane >> 5;
+    const int lq = lane & (RR - 1), g = lane / RR;
     const int wcopy = KSPL == 1 ? wave : wave & 3;              // this wave's place among those that copy a tile
     const int jg = KSPL == 1 ? 0 : grp;                         // first tile of the wave's group, relative to j0
 
@@ -528,8 +559,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     const int J_wg = splitting ? (j0 + per16 * 16 < J_all ? j0 + per16 * 16 : J_all) : J_all;
     int J_w = wave_valid ? (CAUSAL ? tiles_seen(last_row_w) : ntile) : 0;
     if (J_w > J_wg) J_w = J_wg;
-    const int row = qw0 + lq;
-    const bool row_valid = row < Nq;       // rows past the end compute on zero queries and are never stored
+    const int row = qw0 + lq;              // of the first block; those of a second are RR further on
+    // (rows past the end compute on zero queries and are never stored)
     const int pos_w0 = row0 + qw0;         // position of the wave's first row
 
     const _Float16* qbase = q + head * Nq * D;
@@ -575,43 +606,49 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                                                      at_row * (2 * D) + ((lane % CH) ^ (r & 7)) * 16, 0, 0, 0);
         }
     }
-    // per-row state (one query row per lane; both halves of the wave hold copies)
-    float F = 0.f, m = NAIVE ? -__builtin_inff() : 0.f, l = 0.f;   // STRICT: always fp16-representable values
-    float Lc = 0.f;                  // log of the scale of the stored output (DIRECT, NAIVE16)
-    double R = -__builtin_inf();     // LEVEL: level of the stored output, m + inva * F + Lc of Algorithm 1's state
-    float ec_s = 1.f, ep_s = 0.f;    // STRICT: factors of the pending output combination
-    f16v S[4];                       // S'^T accumulators
-    h8 Pf[8];                        // P^T, B operand of the second GEMM
-    f16v O[CB];                      // fp32 variants: stored output; STRICT: product of the latest tile
-    h2 O16[CB][8];                   // STRICT: running output
+    // per-row state (one query row of each block per lane; the four lanes of a row hold copies, but parts of l in the fp32 variants)
+    float F[RB], m[RB], l[RB];       // fp32 variants
+    float Lc[RB];                    // log of the scale of the stored output (DIRECT, NAIVE16)
+    double R[RB];                    // LEVEL: level of the stored output, m + inva * F + Lc of Algorithm 1's state
+    // STRICT: the same of both rows, packed; factors of the pending output combination, sum of the tile's P that goes with it
+    h2 F2 = {}, m2 = {}, l2 = {}, ec2 = {}, ep2 = {}, lt2 = {};
+    h8 Pf[RB][KK];                   // P^T, B operand of the second GEMM
+    Acc O[RB][CB];                   // fp32 variants: stored output; STRICT: product of the latest tile
+    h2 O16[RB][CB][NE / 2];              // STRICT: running output
     unsigned long long n_ovf = 0;
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) S[kb] = (f16v)0.f;
+    for (int rb = 0; rb < RB; ++rb) {
+        F[rb] = l[rb] = Lc[rb] = 0.f;
+        m[rb] = NAIVE ? -__builtin_inff() : 0.f;
+        R[rb] = -__builtin_inf();
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) Pf[kk] = (h8)(_Float16)0;
+        for (int kk = 0; kk < KK; ++kk) Pf[rb][kk] = (h8)(_Float16)0;
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
-        O[cb] = (f16v)0.f;
+        for (int cb = 0; cb < CB; ++cb) {
+            O[rb][cb] = (Acc)0.f;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) O16[cb][t] = (h2)(_Float16)0;
+            for (int t = 0; t < NE / 2; ++t) O16[rb][cb][t] = (h2)(_Float16)0;
+        }
     }
 
-    float l_tile = 0.f;              // STRICT, d = 128: sum of the tile's P, pending like its product
-    // STRICT: fold the product of tile jt (in O) into the running fp16 output
-    auto fold16 = [&](int jt) {
-        const _Float16 ec = (_Float16)ec_s, ep = (_Float16)ep_s;
-        const h2 ec2 = {ec, ec}, ep2 = {ep, ep};
+    // STRICT: fold the product of the latest tile (in O) into the running fp16 output
+    auto fold16 = [&] {
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
+        for (int rb = 0; rb < RB; ++rb) {
+            const h2 ec = {ec2[rb], ec2[rb]}, ep = {ep2[rb], ep2[rb]};
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const h2 ot = pack_rn(O[cb][2 * t], O[cb][2 * t + 1]);
-                const h2 a1 = ec2 * ot;                   // each packed op rounds to fp16 once; first tile: 1 * ot + 0 * 0
-                const h2 a2 = ep2 * O16[cb][t];
-                O16[cb][t] = a1 + a2;
-            }
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int t = 0; t < NE / 2; ++t) {
+                    const h2 ot = pack_rn(O[rb][cb][2 * t], O[rb][cb][2 * t + 1]);
+                    const h2 a1 = ec * ot;                    // each packed op rounds to fp16 once; first tile: 1 * ot + 0 * 0
+                    const h2 a2 = ep * O16[rb][cb][t];
+                    O16[rb][cb][t] = a1 + a2;
+                }
+        }
         // the running sum (step 4), each operation rounded: l = fp16(fp16(e^{dm_{j-1}} l) + fp16(e^{dm_j} l')); first tile: 0 + l'
-        if (D == 128) l = (float)(_Float16)((_Float16)(ep * (_Float16)l) + (_Float16)(ec * (_Float16)l_tile));
+        const h2 b1 = ep2 * l2, b2 = ec2 * lt2;
+        l2 = b1 + b2;
     };
 
     // The copies of a slot are K'(jl + KSPL) and V(jl); each wave owns 2*CPW of their 1 KiB pieces.
@@ -640,15 +677,19 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     // vector part V(j) for group A (slot 2j+1) and V(j-1) for group B (slot 2j) -- the matrix part keeps its MFMA
     // chain free of them -- and drains them before the barrier that starts slot 2j+2, when group A reads them.
     drain_copies();
-    h8 Qf[KS];
+    h8 Qf[RB][KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        const h8 raw = *reinterpret_cast<const h8*>(smem + 2 * KT_BYTES + wave * (64 * D) + lq * (2 * D) + (((2 * ks + lh) ^ (lq & 7)) * 16));
-        Qf[ks] = row_valid ? raw : (h8)(_Float16)0;
-    }
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const h8 raw = *reinterpret_cast<const h8*>(smem + 2 * KT_BYTES + wave * (64 * D) + (RR * rb + lq) * (2 * D) + (((NG * ks + g) ^ (lq & 7)) * 16));
+            Qf[rb][ks] = row + RR * rb < Nq ? raw : (h8)(_Float16)0;
+        }
     if (io_bf16) {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) Qf[ks] = bf16x8_to_h8(__builtin_bit_cast(u16x8, Qf[ks]));
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) Qf[rb][ks] = bf16x8_to_h8(__builtin_bit_cast(u16x8, Qf[rb][ks]));
     }
     __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0): the rows have been read, the first values may take their place
     __syncthreads();                       // barrier 0: K'(0) is in LDS
@@ -659,61 +700,63 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
 
     // Hand-offs between the parts of one wave.
     constexpr bool LAZY = !STRICT;   // fp32 variants: the recovering factor goes to P, not to the stored output
-    // The running sum l of the fp32 variants is not taken in the vector part that makes P.
-    // d = 128: the row sums of a tile's P are added up in the matrix part that follows, between the MFMAs of the second
-    // GEMM (which reads the same P fragments): the wave has issue slots to spare there (an MFMA occupies the matrix core
-    // for 32 cycles), while in the vector part every instruction counts.  0.7 % on the headline workload, although the
-    // vector part loses 64 of its 330 instructions: the kernel's clock, not its cycle count, is the limit.  (MIXED and
-    // DIRECT; S16 and NAIVE16, whose vector part sums with v_dot2_f32_f16, lose 1.2 % by it and keep their sums there.
-    // STRICT16, with two partial sums where the others have four, for want of registers: 28 heads of 4001 rows 154.3 -> 152.5 us, of
-    // 8192 rows 555 -> 549.  With both of its sums on the matrix core, against ones, it takes a fifth longer: the products of a sum
-    // depend on one another and wait behind the other wavefront's.)
-    // d = 64: the vector part is 2.7 times as long as the matrix part (the softmax is the same work, the GEMMs half),
-    // and the sum moves onto the idle matrix core itself: one more MFMA per k-step of the second GEMM, P^T against a
-    // block of ones, accumulates the row sums beside the stored output, at the same scale (every row of the result is
-    // the sum).  4 % on the d = 64 workload (the first way is 2 % slower there; this way is 2.4 % slower at d = 128).
-    constexpr bool LSUM_MFMA = LAZY && D == 64;
-    constexpr bool LSUM_DEFER = D == 128 && (MSBAR || STRICT);
-    f16v Lacc = (f16v)0.f;
-    const h8 ones = (h8)(_Float16)1;
-    float pl_d[4] = {0.f, 0.f, 0.f, 0.f};
+    // The row sums of a tile's P are not taken in the vector part that makes P, but by the matrix core in the matrix part that follows: one
+    // more MFMA per k-step and row block of the second GEMM, P^T against a block of ones, accumulates the sums beside the stored output, at the same
+    // scale (every row of the result is the sum).  28 heads of 4096 rows, not causal, 224.8 -> 213.3 us against additions between the MFMAs, DIRECT,
+    // causal, 122.8 -> 121.2.
+    // STRICT16 at d = 128 has no registers for it and adds them up between the MFMAs of the second GEMM.
+    constexpr bool LSUM_DEFER = D == 128 && STRICT;
+    constexpr bool LSUM_MFMA = !LSUM_DEFER;
+    Acc Lacc[RB];
+    float pl_d[RB][2];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        Lacc[rb] = (Acc)0.f;
+        pl_d[rb][0] = pl_d[rb][1] = 0.f;
+    }
     constexpr float CMAX = 8.f;      // LAZY: P may exceed 1 by at most e^CMAX before the row re-references its scale
     constexpr float PMAX = 2980.f;   // LEVEL: the fp16 value below e^CMAX
-    float cj = 0.f;                  // DIRECT: scale * (q . k0) of the tile in the vector part
-    const bool one_tile = CAUSAL ? row0 + row < T || N <= T : N <= T;      // the row sees a single tile
+    auto one_tile = [&](int rb) { return (CAUSAL && row0 + row + RR * rb < T) || N <= T; };      // the row sees a single tile
 
-    // Both GEMMs run k-step by k-step: the four MFMAs of a k-step share their B operand (the Q or P fragment) and go
-    // to the four accumulator blocks in turn, so consecutive MFMAs never depend on each other and the B registers are
-    // read four times in a row (measured 1.4 % faster than one dependent chain per accumulator block, with the
-    // maxima of finished blocks taken behind the MFMAs of the next).  LDS fragments are fetched PF instructions ahead.
+    // Both GEMMs run k-step by k-step: the fragments of a k-step go to the accumulator blocks in turn, so consecutive MFMAs never depend
+    // on each other; with two row blocks each fragment is used twice, in alternating order, so that one operand stays from each MFMA to the next
+    // (at 32 x 32 1.4 % faster than one dependent chain per accumulator block).  LDS fragments are fetched PF instructions ahead.
 #ifndef PASA_PF
 #define PASA_PF 3
 #endif
     constexpr int PF = PASA_PF;
-    constexpr int NM1 = 4 * KS;      // MFMAs of the first GEMM:  n = kb * KS + ks
-    constexpr int NM2 = CB * 8;      // MFMAs of the second GEMM
-    auto gemm1 = [&](int jt) {   // S'^T of tile jt: 128 keys x 32 queries; MFMA n: key block n % 4, k-step n / 4
+    constexpr int NM1 = KB * KS;     // fragments of the first GEMM
+    constexpr int NM2 = CB * KK;     // fragments of the second GEMM
+    auto sum_of_row = [](float x) { return RB == 1 ? sum32(x) : sum_row(x); };
+    auto gemm1 = [&](int jt, Acc (&S)[RB][KB]) {   // S'^T of tile jt: 128 keys x 32 queries; fragment n: key block n % KB, k-step n / KB
         const _Float16* lds_k = reinterpret_cast<const _Float16*>(smem + buf(jt) * KT_BYTES);
-        auto frag = [&](int n) { return *reinterpret_cast<const h8*>(lds_k + ((2 * (n / 4) + lh) * T + 32 * (n % 4) + lq) * 8); };
+        auto frag = [&](int n) {
+            // 16 x 16: block 2i + s is keys 32i + {0..7, 16..23} + 8s, as in pasa_rows
+            const int kb = n % KB, key = RB == 1 ? 32 * kb + lq : 32 * (kb >> 1) + 8 * (kb & 1) + 16 * (lq >> 3) + (lq & 7);
+            return *reinterpret_cast<const h8*>(lds_k + ((NG * (n / KB) + g) * T + key) * 8);
+        };
         h8 a[PF];
 #pragma unroll
         for (int n = 0; n < PF; ++n) a[n] = frag(n);
         PASA_FENCE();
 #pragma unroll
         for (int n = 0; n < NM1; ++n) {
-            const int kb = n % 4, ks = n / 4;
-            if (ks == 0)
-                S[kb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[n % PF], Qf[ks], (f16v)0.f, 0, 0, 0);
-            else
-                S[kb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[n % PF], Qf[ks], S[kb], 0, 0, 0);
-            PASA_FENCE();
+            const int kb = n % KB, ks = n / KB;
+#pragma unroll
+            for (int i = 0; i < RB; ++i) {
+                const int rb = n & 1 ? RB - 1 - i : i;
+                S[rb][kb] = mma(a[n % PF], Qf[rb][ks], ks == 0 ? (Acc)0.f : S[rb][kb]);
+                PASA_FENCE();
+            }
             if (n + PF < NM1) a[n % PF] = frag(n + PF);
             PASA_FENCE();
         }
     };
-    auto gemm2 = [&](int jt) {   // (P V)^T of tile jt: D channels x 32 queries; runs during M(jt+1); MFMA n: channel block n % CB, k-step n / CB
+    auto gemm2 = [&](int jt) {   // (P V)^T of tile jt: D channels x 32 queries; runs during M(jt+1); fragment n: channel block n % CB, k-step n / CB
         const _Float16* lds_v = reinterpret_cast<const _Float16*>(smem + 2 * KT_BYTES + buf(jt) * KT_BYTES);
-        auto frag = [&](int n) { return *reinterpret_cast<const h8*>(lds_v + ((2 * (n / CB) + lh) * D + 32 * (n % CB) + lq) * 8); };
+        unsigned one2 = 0x3c003c00u;             // a pair of ones
+        if (LSUM_MFMA) asm volatile("" : "+v"(one2));      // made here each time, where there are registers, and not kept through the vector part
+        auto frag = [&](int n) { return *reinterpret_cast<const h8*>(lds_v + ((NG * (n / CB) + g) * D + RR * (n % CB) + lq) * 8); };
         h8 a[PF];
 #pragma unroll
         for (int n = 0; n < PF; ++n) a[n] = frag(n);
@@ -721,34 +764,64 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
 #pragma unroll
         for (int n = 0; n < NM2; ++n) {
             const int cb = n % CB, kk = n / CB;
-            if (STRICT && kk == 0)
-                O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[n % PF], Pf[kk], (f16v)0.f, 0, 0, 0);
-            else
-                O[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[n % PF], Pf[kk], O[cb], 0, 0, 0);
-            PASA_FENCE();
+#pragma unroll
+            for (int i = 0; i < RB; ++i) {
+                const int rb = n & 1 ? RB - 1 - i : i;
+                O[rb][cb] = mma(a[n % PF], Pf[rb][kk], STRICT && kk == 0 ? (Acc)0.f : O[rb][cb]);
+                PASA_FENCE();
+            }
             if (n + PF < NM2) a[n % PF] = frag(n + PF);
             PASA_FENCE();
             if (LSUM_MFMA && cb == CB - 1) {
-                Lacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ones, Pf[kk], Lacc, 0, 0, 0);
+                const h8 ones = __builtin_bit_cast(h8, uint4{one2, one2, one2, one2});
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) Lacc[rb] = mma(ones, Pf[rb][kk], STRICT && kk == 0 ? (Acc)0.f : Lacc[rb]);
                 PASA_FENCE();
             }
             if (LSUM_DEFER) {
-                // 32 packed pairs over NM2 MFMAs
+                // 32 packed pairs over NM2 fragments, pair i of a k-step of row block i / 4
                 constexpr int PER = 32 / NM2;
 #pragma unroll
                 for (int u = 0; u < PER; ++u) {
-                    const int pr = n * PER + u;          // pair pr: Pf[pr / 4], elements 2 * (pr % 4), + 1
-                    const h2 p2 = {Pf[pr / 4][2 * (pr % 4)], Pf[pr / 4][2 * (pr % 4) + 1]};
-                    pl_d[pr & (STRICT ? 1 : 3)] = add_pair_mix(p2, pl_d[pr & (STRICT ? 1 : 3)]);
+                    const int pr = n * PER + u, rb = RB == 1 ? 0 : pr >> 2 & 1, kk = RB == 1 ? pr >> 2 : pr >> 3;
+                    const h2 p2 = {Pf[rb][kk][2 * (pr & 3)], Pf[rb][kk][2 * (pr & 3) + 1]};
+                    pl_d[rb][pr & 1] = add_pair_mix(p2, pl_d[rb][pr & 1]);
                 }
                 PASA_FENCE();
             }
         }
-        if (LSUM_DEFER) {
-            const float sum = sum32((pl_d[0] + pl_d[1]) + (pl_d[2] + pl_d[3]));
-            if (STRICT) l_tile = sum;
-            else l += sum;
-            pl_d[0] = pl_d[1] = pl_d[2] = pl_d[3] = 0.f;
+        if (STRICT) {
+            float sum[RB];
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                sum[rb] = LSUM_MFMA ? Lacc[rb][0] : sum_of_row(pl_d[rb][0] + pl_d[rb][1]);
+                pl_d[rb][0] = pl_d[rb][1] = 0.f;
+            }
+            lt2 = pack_rn(sum[0], sum[RB - 1]);
+        }
+    };
+
+    // The lane's number where it is rarely needed: what the compiler derives from it is not to be kept through the loop
+    auto lane_again = [&] {
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        return ln;
+    };
+
+    // Values that nothing reads before they are made again: without this the compiler keeps their registers, on the way past the code
+    // that makes them, through all that comes before it
+    auto forget_p = [&] {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) asm volatile("" : "=v"(Pf[rb][kk]));
+    };
+    auto forget_product = [&] {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            asm volatile("" : "=v"(Lacc[rb]));
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) asm volatile("" : "=v"(O[rb][cb]));
         }
     };
 
@@ -764,26 +837,38 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
         __builtin_amdgcn_s_setprio(1);
         // ---- pseudo-averages of the next 16 tiles: rows of A are the high and low parts of the tiles' mean keys ----
         if (MSBAR && ((j & 15) == jg || j == j0 + jg) && do_g1) {
+            const int ln = lane_again(), lq = ln & (RR - 1), g = ln / RR;
             const _Float16* lds_km = reinterpret_cast<const _Float16*>(smem + 4 * KT_BYTES);
-            f16v acc = (f16v)0.f;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(*reinterpret_cast<const h8*>(lds_km + ((2 * ks + lh) * 32 + lq) * 8),
-                                                             Qf[ks], acc, 0, 0, 0);
-            // lanes 0-31 hold q . hi of tile i in element i, lanes 32-63 q . lo of the same tile; after the exchange
-            // element i + 8 -> i the sum is tile i in lanes 0-31 and tile i + 8 in lanes 32-63
+            // Half of the lanes hold q . hi of some tiles (32 x 32: those of g = 0, tile i in element i; 16 x 16: of g = 0 and 2, tile 8 ab + 2 g + e
+            // in element e), the other half q . lo of the same; after the exchange their sum is a tile in each.
             float* sb = reinterpret_cast<float*>(smem + SB_OFF + wave * 2048);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                float x = acc[i], y = acc[i + 8];
-                swap32(x, y);
-                sb[(i + 8 * lh) * 32 + lq] = x + y * 0.00048828125f;      // low parts are stored times 2^11
+            for (int ab = 0; ab < RB; ++ab) {
+                Acc acc[RB];
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const h8 mean = *reinterpret_cast<const h8*>(lds_km + ((NG * ks + g) * 32 + RR * ab + lq) * 8);
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb) acc[rb] = mma(mean, Qf[rb][ks], ks == 0 ? (Acc)0.f : acc[rb]);
+                }
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                    for (int e = 0; e < NE / 2; ++e) {
+                        float x = acc[rb][e], y = acc[rb][e + NE / 2];
+                        if (RB == 1) swap32(x, y);
+                        else swap16(x, y);
+                        const int tile = RB == 1 ? e + 8 * g : 8 * ab + 4 * (g >> 1) + 2 * (g & 1) + e;
+                        sb[tile * 32 + RR * rb + lq] = x + y * 0.00048828125f;      // low parts are stored times 2^11
+                    }
             }
         }
         // ---- pending product of tile j-1 ----
         if (do_g2) gemm2(j - KSPL);
+        else if (STRICT) forget_product();
         // ---- S'(j) ----
-        if (do_g1) gemm1(j);
+        Acc S[RB][KB];                   // S'^T accumulators
+        if (do_g1) gemm1(j, S);
         __builtin_amdgcn_s_setprio(0);
         if (KSPL == 1 && grp == 1) drain_copies();
         __syncthreads();
@@ -796,304 +881,329 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
         // =========================== vector part V(j) ===========================
         if (j < J_w) {
             const bool first = (j == j0 + jg);
-            if (STRICT && do_g2) fold16(j - 1);      // O <- fp16(e^{dm_j} PV) + fp16(e^{dm_{j-1}} O) for the product of tile j-1
+            if (STRICT && do_g2) fold16();           // O <- fp16(e^{dm_j} PV) + fp16(e^{dm_{j-1}} O) for the product of tile j-1
+            if (STRICT) PASA_FENCE();
             // ---- S' as stored: fp32, or rounded to fp16 ----
-            // STRICT16 keeps the rounded scores packed two per register and works on them with packed fp16
+            // STRICT16 and S16 keep the rounded scores packed two per register; STRICT16 works on them with packed fp16
             // instructions (same roundings, half the instructions and registers)
-            h2 Sh[4][8];
-            if (STRICT) {
+            h2 Sh[RB][KB][NE / 2];
 #pragma unroll
-                for (int kb = 0; kb < 4; ++kb)
+            for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) {
-                        if (INSTR)
-                            n_ovf += ((__builtin_fabsf(S[kb][2 * t]) >= 65520.f) ? 1u : 0u) +
-                                     ((__builtin_fabsf(S[kb][2 * t + 1]) >= 65520.f) ? 1u : 0u);
-                        Sh[kb][t] = pack_rn(S[kb][2 * t], S[kb][2 * t + 1]);
+                for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                    for (int e = 0; e < NE; ++e) {
+                        if (INSTR) n_ovf += (__builtin_fabsf(S[rb][kb][e]) >= 65520.f) ? 1u : 0u;
+                        if (PACKED) {
+                            if (e & 1) Sh[rb][kb][e >> 1] = pack_rn(S[rb][kb][e - 1], S[rb][kb][e]);
+                        } else if (S16) {
+                            const float sv = (float)(_Float16)S[rb][kb][e];
+                            S[rb][kb][e] = sv * scale;                   // NAIVE16, Eq. (2): static scaling after the GEMM
+                        }
                     }
-            } else if (S16) {
-#pragma unroll
-                for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const float s32 = S[kb][i];
-                        if (INSTR) n_ovf += (__builtin_fabsf(s32) >= 65520.f) ? 1u : 0u;
-                        float sv = (float)(_Float16)s32;
-                        if (NAIVE) sv = sv * scale;          // Eq. (2): static scaling after the GEMM
-                        S[kb][i] = sv;
-                    }
-            } else if (INSTR) {
-#pragma unroll
-                for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) n_ovf += (__builtin_fabsf(S[kb][i]) >= 65520.f) ? 1u : 0u;
-            }
             // ---- pseudo-average over all 128 keys of the tile (before masking) ----
-            float sbar = 0.f;
-            if (MSBAR) {
-                const float v = reinterpret_cast<const float*>(smem + SB_OFF + wave * 2048)[(j & 15) * 32 + lq];
-                if (DIRECT) cj = scale * v;                    // the bias the shift removed from this tile's scores
-                else sbar = tail ? v * ((float)T * inv_tail) : v;   // stored per 128 key slots; a ragged last tile divides by its own key count
-            } else if (!NAIVE && !DIRECT) {
-                float ps[4];
+            float sbar[RB], cj[RB];          // cj: DIRECT, scale * (q . k0) of the tile
 #pragma unroll
-                for (int kb = 0; kb < 4; ++kb) {
-                    if (STRICT) {          // fp16 values summed in fp32
-                        ps[kb] = 0.f;
-#pragma unroll
-                        for (int t = 0; t < 8; ++t) ps[kb] = add_pair_mix(Sh[kb][t], ps[kb]);
-                        continue;
-                    }
-                    ps[kb] = S[kb][0];
-#pragma unroll
-                    for (int i = 1; i < 16; ++i) ps[kb] += S[kb][i];
+            for (int rb = 0; rb < RB; ++rb) {
+                sbar[rb] = cj[rb] = 0.f;
+                if (MSBAR) {
+                    const float v = reinterpret_cast<const float*>(smem + SB_OFF + wave * 2048)[(j & 15) * 32 + RR * rb + lq];
+                    if (DIRECT) cj[rb] = scale * v;                // the bias the shift removed from this tile's scores
+                    else sbar[rb] = tail ? v * ((float)T * inv_tail) : v;   // stored per 128 key slots; a ragged last tile divides by its own key count
                 }
-                // padding keys of a ragged last tile have K' = 0 and add nothing; the divisor is the tile's own key count
-                const float sum = sum32((ps[0] + ps[1]) + (ps[2] + ps[3]));
-                sbar = sum * (tail ? inv_tail : 1.0f / T);
-                if (STRICT) sbar = (float)(_Float16)sbar;
+            }
+            if (PACKED) {
+                // fp16 values summed in fp32 (as eight products of the matrix core with ones, which they lie right for: 4096 rows of S16 130.5 ->
+                // 132.8 us, STRICT16 154.4 -> 156.2, since those wait behind the other wavefront's).
+                // Padding keys of a ragged last tile have K' = 0 and add nothing; the divisor is the tile's own key count.
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    constexpr int W = STRICT && RB == 2 ? 1 : 3;
+                    float ps[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int t = 0; t < KB * NE / 2; ++t) ps[t & W] = add_pair_mix(Sh[rb][t / (NE / 2)][t % (NE / 2)], ps[t & W]);
+                    sbar[rb] = sum_of_row((ps[0] + ps[1]) + (ps[2] + ps[3])) * (tail ? inv_tail : 1.0f / T);
+                }
             }
             // ---- mask: keys after the query (causal, diagonal tiles) or past the end (ragged last tile) ----
             if (diag) {
-                int last_key = N - 1;
-                if (CAUSAL && row0 + row < last_key) last_key = row0 + row;
-                int key0 = j * T + 4 * lh;
-                if (!CAUSAL) {
-                    // Only the last tile is masked, nothing in the comparisons depends on j, and the compiler would take all 64 in front of
-                    // the loop, into more scalar registers than there are: 0.7 us of every workgroup (28 heads on 4, 1024 rows 21.4 -> 19.5 us, 4096
-                    // rows 221.1 -> 216.8; DIRECT, 4000 rows 217.4 -> 213.0)
-                    last_key -= key0;
-                    key0 = 0;
-                    asm volatile("" : "+v"(last_key));
-                }
+                const int ln = lane_again(), gn = ln / RR, posn = row0 + qw0 + (ln & (RR - 1));
 #pragma unroll
-                for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        if (key0 + 32 * kb + 8 * (i >> 2) + (i & 3) > last_key) {
-                            if (STRICT) Sh[kb][i >> 1][i & 1] = (_Float16)(-__builtin_inff());
-                            else S[kb][i] = -__builtin_inff();
-                        }
+                for (int rb = 0; rb < RB; ++rb) {
+                    int last_key = N - 1;
+                    if (CAUSAL && posn + RR * rb < last_key) last_key = posn + RR * rb;
+                    int key0 = j * T + (RB == 1 ? 4 * gn : 16 * (gn >> 1) + 4 * (gn & 1));
+                    if (!CAUSAL) {
+                        // Only the last tile is masked, nothing in the comparisons depends on j, and the compiler would take all 64 in front of
+                        // the loop, into more scalar registers than there are: 0.7 us of every workgroup (28 heads on 4, 1024 rows 21.4 -> 19.5 us, 4096
+                        // rows 221.1 -> 216.8; DIRECT, 4000 rows 217.4 -> 213.0)
+                        last_key -= key0;
+                        key0 = 0;
+                        asm volatile("" : "+v"(last_key));
                     }
+#pragma unroll
+                    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                        for (int e = 0; e < NE; ++e) {
+                            const int key = key0 + (RB == 1 ? 32 * kb + 8 * (e >> 2) + (e & 3) : 32 * (kb >> 1) + 8 * (kb & 1) + e);
+                            if (!PACKED && key > last_key) S[rb][kb][e] = -__builtin_inff();
+                            if (PACKED && (e & 1)) {         // a pair at once: taken apart, the scores would need twice the registers
+                                const unsigned beyond = key > last_key ? (key - 1 > last_key ? 0xffffffffu : 0xffff0000u) : 0u;
+                                unsigned& x = reinterpret_cast<unsigned&>(Sh[rb][kb][e >> 1]);
+                                x = (0xfc00fc00u & beyond) | (x & ~beyond);
+                            }
+                        }
+                }
             }
             // ---- local maximum m' ----
-            auto row_max = [&] {
-                float pm[4];
+            auto row_max = [&](int rb) {
+                float pm;
+                if (PACKED) {
+                    h2 mm = Sh[rb][0][0];
 #pragma unroll
-                for (int kb = 0; kb < 4; ++kb) {
-                    if (STRICT) {
-                        h2 mm = Sh[kb][0];
+                    for (int t = 1; t < KB * NE / 2; ++t) mm = __builtin_elementwise_max(mm, Sh[rb][t / (NE / 2)][t % (NE / 2)]);
+                    pm = __builtin_fmaxf((float)mm[0], (float)mm[1]);
+                } else {
+                    pm = S[rb][0][0];
 #pragma unroll
-                        for (int t = 1; t < 8; ++t) mm = __builtin_elementwise_max(mm, Sh[kb][t]);
-                        pm[kb] = __builtin_fmaxf((float)mm[0], (float)mm[1]);
-                        continue;
-                    }
-                    pm[kb] = S[kb][0];
-#pragma unroll
-                    for (int i = 1; i < 16; ++i) pm[kb] = __builtin_fmaxf(pm[kb], S[kb][i]);
+                    for (int i = 1; i < KB * NE; ++i) pm = __builtin_fmaxf(pm, S[rb][i / NE][i % NE]);
                 }
-                return max32(__builtin_fmaxf(__builtin_fmaxf(pm[0], pm[1]), __builtin_fmaxf(pm[2], pm[3])));
+                return RB == 1 ? max32(pm) : max_row(pm);
             };
-            const float mx = LEVEL ? 0.f : row_max();
-            // A wave whose rows straddle a tile boundary (chunks not aligned to 32 rows) reaches tile j although its
-            // first rows see none of it: those rows keep their state and add nothing.
-            const bool unseen = CAUSAL && diag && (row0 + row < j * T);
-            // ---- reference level for exp: local m' (PASA), running max (plain FlashAttention) ----
-            float mref = unseen ? 0.f : mx;
-            float c_adj = 0.f;    // LAZY: log of the factor this tile's P carries (its level relative to the stored scale)
-            bool resc = false;    // LAZY: this row re-references its stored output and sum to the level of tile j
-            float lc_resc = 0.f;  // LAZY: log of the factor that does it
-            if (NAIVE) {
-                // plain online softmax (Eq. (4)-(8)) on the running maximum, the stored output handled as in MIXED:
-                // its log scale moves by m_{j-1} - m_j, P carries the factor, no per-tile rescale
-                const float mnew = __builtin_fmaxf(m, mx);
-                const bool keep = first || unseen;
-                const float lcn = Lc + (m - mnew), c = -lcn;
-                resc = !keep && c > CMAX;
-                lc_resc = lcn;
-                c_adj = (keep || resc) ? 0.f : c;
-                Lc = first ? 0.f : unseen ? Lc : resc ? 0.f : lcn;
-                m = mnew;
-                mref = mnew;
+            bool unseen[RB], resc[RB];       // resc, LAZY: this row re-references its stored output and sum to the level of tile j
+            float top16[RB];                 // STRICT: m'
+            float mref[RB], c_adj[RB];       // LAZY: log of the factor this tile's P carries (its level relative to the stored scale)
+            float lc_resc[RB];               // LAZY: log of the factor that does it
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                const float mx = LEVEL ? 0.f : row_max(rb);
+                // A wave whose rows straddle a tile boundary (chunks not aligned to 32 rows) reaches tile j although its
+                // first rows see none of it: those rows keep their state and add nothing.
+                unseen[rb] = CAUSAL && diag && (row0 + row + RR * rb < j * T);
+                // ---- reference level for exp: local m' (PASA), running max (plain FlashAttention) ----
+                mref[rb] = unseen[rb] ? 0.f : mx;
+                top16[rb] = mx;
+                c_adj[rb] = lc_resc[rb] = 0.f;
+                resc[rb] = false;
+                // ---- fp32 variants: global recovering (step 3) and the factor of the output or of P now, before the
+                // exponentials.  Only the running sum needs l'; the rest is a chain of dependent scalar operations whose
+                // latency is hidden when the exponentials that follow can issue in between. ----
+                // (values are read before they are chosen from: a choice between elements of arrays comes as branches)
+                const bool out = unseen[rb];
+                const float m0 = m[rb], Lc0 = Lc[rb];
+                if (NAIVE) {
+                    // plain online softmax (Eq. (4)-(8)) on the running maximum, the stored output handled as in MIXED:
+                    // its log scale moves by m_{j-1} - m_j, P carries the factor, no per-tile rescale
+                    const float mnew = __builtin_fmaxf(m0, mx);
+                    const bool keep = first || out;
+                    const float lcn = Lc0 + (m0 - mnew), c = -lcn;
+                    const bool rs = !keep && c > CMAX;
+                    resc[rb] = rs;
+                    lc_resc[rb] = lcn;
+                    c_adj[rb] = (keep || rs) ? 0.f : c;
+                    Lc[rb] = first ? 0.f : out ? Lc0 : rs ? 0.f : lcn;
+                    m[rb] = mnew;
+                    mref[rb] = mnew;
+                } else if (DIRECT) {
+                    // ordinary online softmax on the level m' + c of this tile's maximum; same bookkeeping as below
+                    const float lev = mx + cj[rb];
+                    const float mn = __builtin_fmaxf(m0, lev);
+                    const float dp = m0 - mn;
+                    const float dc = lev - mn;
+                    const bool keep = first || out;
+                    const float lcn = Lc0 + dp, c = dc - lcn;
+                    const bool rs = !keep && c > CMAX;
+                    resc[rb] = rs;
+                    lc_resc[rb] = -c;
+                    c_adj[rb] = (keep || rs) ? 0.f : c;
+                    Lc[rb] = first ? 0.f : out ? Lc0 : rs ? dc : lcn;
+                    m[rb] = first ? lev : out ? m0 : mn;
+                }
             }
-            // ---- fp32 variants: global recovering (step 3) and the factor of the output or of P now, before the
-            // exponentials.  Only the running sum needs l'; the rest is a chain of dependent scalar operations whose
-            // latency is hidden when the exponentials that follow can issue in between. ----
-            bool l_keep = false;             // STRICT16: this row's state is not touched by this tile
+            h2 mref2 = {};           // STRICT: m', 0 for a row that sees none of the tile
             if (STRICT) {
-                // Step 3 with every operation rounded to fp16, in the order Algorithm 1 states them; computed before
-                // the exponentials and without branches (the first tile and rows that see nothing of the tile select
+                // Step 3 with every operation rounded to fp16, in the order Algorithm 1 states them, for both rows at once; computed
+                // before the exponentials and without branches (the first tile and rows that see nothing of the tile select
                 // their values at the end) so that the latency of this chain is hidden.  The factors of the output
-                // combination go to ep_s / ec_s (the pending product of tile j-1 has been folded in above).
-                const _Float16 jm1 = (_Float16)(float)(j - j0), jn = (_Float16)(float)(j - j0 + 1);
-                const _Float16 Fo = (_Float16)F, sb = (_Float16)sbar, mo = (_Float16)m, mxh = (_Float16)mx;
-                const _Float16 iv = (_Float16)inva;
-                const _Float16 Fn = (_Float16)((_Float16)((_Float16)(jm1 * Fo) + sb) / jn);
-                const _Float16 dpp = (_Float16)(iv * (_Float16)(Fo - Fn));
-                const _Float16 dpc = (_Float16)(iv * (_Float16)(sb - Fn));
-                const _Float16 c1 = (_Float16)(mo + dpp), c2 = (_Float16)(mxh + dpc);
-                const _Float16 mn = c1 > c2 ? c1 : c2;
-                const _Float16 dp = (_Float16)((_Float16)(mo - mn) + dpp);
-                const _Float16 dc = (_Float16)((_Float16)(mxh - mn) + dpc);
-                const _Float16 ep = (_Float16)exp_nat((float)dp), ec = (_Float16)exp_nat((float)dc);
-                l_keep = unseen;
-                F = first ? sbar : unseen ? F : (float)Fn;
-                m = first ? mx : unseen ? m : (float)mn;
-                ep_s = first ? 0.f : unseen ? 1.f : (float)ep;     // unseen: O <- fp16(0 * 0) + fp16(1 * O)
-                ec_s = first ? 1.f : unseen ? 0.f : (float)ec;
-            } else if (DIRECT) {
-                // ordinary online softmax on the level m' + c of this tile's maximum; same bookkeeping as below
-                const float lev = mx + cj;
-                const float mn = __builtin_fmaxf(m, lev);
-                const float dp = m - mn;
-                const float dc = lev - mn;
-                const bool keep = first || unseen;
-                const float lcn = Lc + dp, c = dc - lcn;
-                resc = !keep && c > CMAX;
-                lc_resc = -c;
-                c_adj = (keep || resc) ? 0.f : c;
-                Lc = first ? 0.f : unseen ? Lc : resc ? dc : lcn;
-                m = first ? lev : unseen ? m : mn;
+                // combination go to ep2 / ec2 (the pending product of tile j-1 has been folded in above).
+                const _Float16 jm = (_Float16)(float)(j - j0), jn = (_Float16)(float)(j - j0 + 1), iv = (_Float16)inva;
+                const h2 jm2 = {jm, jm}, iv2 = {iv, iv}, sb = pack_rn(sbar[0], sbar[RB - 1]), mx = pack_rn(top16[0], top16[RB - 1]);
+                const h2 f1 = jm2 * F2, f2 = f1 + sb, Fn = {(_Float16)(f2[0] / jn), (_Float16)(f2[RB - 1] / jn)};
+                const h2 gp = F2 - Fn, gc = sb - Fn, dpp = iv2 * gp, dpc = iv2 * gc;
+                const h2 c1 = m2 + dpp, c2 = mx + dpc, mn = {c1[0] > c2[0] ? c1[0] : c2[0], c1[1] > c2[1] ? c1[1] : c2[1]};
+                const h2 h1 = m2 - mn, h3 = mx - mn, dp = h1 + dpp, dc = h3 + dpc;
+                const h2 ep = pack_rn(exp_nat_half<0>(dp), exp_nat_half<RB - 1>(dp)), ec = pack_rn(exp_nat_half<0>(dc), exp_nat_half<RB - 1>(dc));
+                const unsigned out = (unseen[0] ? 0xffffu : 0u) | (unseen[RB - 1] ? 0xffff0000u : 0u);
+                auto choose = [&](h2 at_first, h2 not_seen, h2 seen) {
+                    const unsigned a = __builtin_bit_cast(unsigned, not_seen), b = __builtin_bit_cast(unsigned, seen);
+                    return first ? at_first : __builtin_bit_cast(h2, (a & out) | (b & ~out));
+                };
+                const h2 one = {(_Float16)1, (_Float16)1}, zero = {};
+                F2 = choose(sb, F2, Fn);
+                m2 = choose(mx, m2, mn);
+                ep2 = choose(zero, one, ep);             // unseen: O <- fp16(0 * 0) + fp16(1 * O)
+                ec2 = choose(one, zero, ec);
+                mref2 = __builtin_bit_cast(h2, __builtin_bit_cast(unsigned, mx) & ~out);
             }
-            if (LAZY && !LEVEL && __builtin_amdgcn_ballot_w64(resc) != 0ull) {
-                // rare (the running maximum rose by more than CMAX above the stored scale); the pending product of
-                // tile j-1 is already in O.  The empty asm keeps this a branch instead of 64 selects on every tile.
-                asm volatile("" ::: "memory");
-                const float r = resc ? exp_nat(lc_resc) : 1.f;
+            // what a row has stored so far, times r
+            auto rescale = [&](int rb, float r) {
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) O[cb][i] *= r;
-                l *= r;
-                if (LSUM_MFMA) {
+                    for (int e = 0; e < NE; ++e) O[rb][cb][e] *= r;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) Lacc[i] *= r;
-                }
+                for (int e = 0; e < NE; ++e) Lacc[rb][e] *= r;
+            };
+            if (LAZY && !LEVEL && __builtin_amdgcn_ballot_w64(resc[0] || resc[RB - 1]) != 0ull) {
+                // rare (the running maximum rose by more than CMAX above the stored scale); the pending product of
+                // tile j-1 is already in O.  The empty asm keeps this a branch instead of 64 selects on every tile.
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) rescale(rb, resc[rb] ? exp_nat(lc_resc[rb]) : 1.f);
             }
-            // ---- P = exp(S' - m' [+ c]) rounded to fp16; l' = sum of the rounded P ----
-            float lsum = 0.f;
-            float nml = (c_adj - mref) * LOG2E;
-            auto exponentials = [&] {
-                float pl[4];
+            // ---- P = exp(S' - m' [+ c]) rounded to fp16 ----
+            float nml[RB];
+            auto exponentials = [&](int rb) {
 #pragma unroll
-                for (int kb = 0; kb < 4; ++kb) {
-                    pl[kb] = 0.f;
+                for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-                    for (int t2 = 0; t2 < 8; ++t2) {
+                    for (int t = 0; t < NE / 2; ++t) {
                         float e0, e1;
                         if (STRICT) {   // the difference is itself rounded to fp16 before the exponential
-                            const _Float16 mh = (_Float16)mref;      // exact: m' is one of the fp16 scores (or 0)
-                            const h2 d2 = Sh[kb][t2] - (h2){mh, mh};
+                            const h2 d2 = Sh[rb][kb][t] - (h2){mref2[rb], mref2[rb]};
                             e0 = exp_nat_half<0>(d2);
                             e1 = exp_nat_half<1>(d2);
+                        } else if (PACKED) {
+                            e0 = exp_off_half<0>(Sh[rb][kb][t], nml[rb]);
+                            e1 = exp_off_half<1>(Sh[rb][kb][t], nml[rb]);
                         } else {        // exp(s - m) = 2^(s*log2e - m*log2e), one fused multiply-add per element
-                            e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[kb][2 * t2], LOG2E, nml));
-                            e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[kb][2 * t2 + 1], LOG2E, nml));
+                            e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[rb][kb][2 * t], LOG2E, nml[rb]));
+                            e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[rb][kb][2 * t + 1], LOG2E, nml[rb]));
                         }
                         const h2 p2 = pack_rn(e0, e1);
-                        Pf[2 * kb + (t2 >> 2)][2 * (t2 & 3)] = p2[0];
-                        Pf[2 * kb + (t2 >> 2)][2 * (t2 & 3) + 1] = p2[1];
-                        if (!LSUM_MFMA && !LSUM_DEFER) pl[kb] = (STRICT || MSBAR) ? add_pair_mix(p2, pl[kb]) : add_pair(p2, pl[kb]);
+                        const int at = (kb * NE + 2 * t) / 8;
+                        Pf[rb][at][(kb * NE + 2 * t) % 8] = p2[0];
+                        Pf[rb][at][(kb * NE + 2 * t) % 8 + 1] = p2[1];
                     }
-                }
-                if (!LSUM_MFMA && !LSUM_DEFER) lsum = sum32((pl[0] + pl[1]) + (pl[2] + pl[3]));
-                if (STRICT) lsum = (float)(_Float16)lsum;
             };
             if (LEVEL) {
                 // The scores of a tile stand for S' + inva * Sbar' (what the two correction terms of step 3 add up to: F cancels), so
                 // P = exp(S' + inva * Sbar' - R) needs no maximum.  That a row has risen by more than CMAX above its stored output, or
                 // has none yet (R = -inf), shows in P itself, and only then the maximum is taken, the row moved to the level of this
                 // tile and P made again.  NaN, and with it the row, where the pseudo-average is not finite.
-                float off = __builtin_fmaf(sbar, 0.f, (float)__builtin_fma((double)inva, (double)sbar, -R));
-                if (CAUSAL && diag && unseen) off = 0.f;
-                nml = off * LOG2E;
-                unsigned long long high = ~0ull;
-                if (!first) {
-                    exponentials();
-                    high = __builtin_amdgcn_ballot_w64(!(largest_of(Pf) <= PMAX));
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    float off = __builtin_fmaf(sbar[rb], 0.f, (float)__builtin_fma((double)inva, (double)sbar[rb], -R[rb]));
+                    if (CAUSAL && diag && unseen[rb]) off = 0.f;
+                    nml[rb] = off * LOG2E;
                 }
-                if (high != 0ull) {
-                    asm volatile("" ::: "memory");
-                    const bool move = !unseen && (((unsigned)high | (unsigned)(high >> 32)) >> lq & 1u) != 0u;
+                float c[RB], up[RB];             // level of the tile above that of the stored output; offset of a row that moves to it
+                double lev[RB];
+                bool move[RB];
+                auto look = [&](int rb) {
                     // a row that sees a single tile needs no pseudo-average, which may be infinite there
-                    const float top = row_max(), bias = one_tile ? 0.f : sbar, bad = (top + bias) * 0.f;
-                    const double lev = (double)top + (double)inva * (double)bias;
-                    const float r = move ? exp_nat((float)(R - lev) + bad) : 1.f;
-                    R = move ? lev : R;
-                    nml = move ? (bad - top) * LOG2E : nml;
+                    const float top = row_max(rb), bias = one_tile(rb) ? 0.f : sbar[rb], bad = (top + bias) * 0.f;
+                    lev[rb] = (double)top + (double)inva * (double)bias;
+                    c[rb] = (float)(lev[rb] - R[rb]) + bad;          // +inf for a row without keys so far
+                    up[rb] = (bad - top) * LOG2E;
+                    move[rb] = !unseen[rb] && c[rb] > CMAX;
+                };
+                auto settle = [&](int rb) {
+                    if (!(EAGER && first)) rescale(rb, move[rb] ? exp_nat(-c[rb]) : 1.f);      // (nothing is stored yet)
+                    R[rb] = move[rb] ? lev[rb] : R[rb];
+                    nml[rb] = move[rb] ? up[rb] : nml[rb];
+                };
+                if (EAGER) {
 #pragma unroll
-                    for (int cb = 0; cb < CB; ++cb)
+                    for (int rb = 0; rb < RB; ++rb) look(rb);
+                    if (__builtin_amdgcn_ballot_w64(move[0] || move[RB - 1]) != 0ull) {
+                        asm volatile("" ::: "memory");
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) O[cb][i] *= r;
-                    l *= r;
-                    if (LSUM_MFMA) {
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) Lacc[i] *= r;
+                        for (int rb = 0; rb < RB; ++rb) settle(rb);
                     }
-                    exponentials();
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb) exponentials(rb);
+                } else {
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb) {
+                        exponentials(rb);
+                        if (__builtin_amdgcn_ballot_w64(!(largest_of(Pf[rb]) <= PMAX)) != 0ull) {
+                            asm volatile("" ::: "memory");
+                            look(rb);
+                            settle(rb);
+                            exponentials(rb);
+                        }
+                    }
                 }
             } else {
-                exponentials();
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    nml[rb] = (c_adj[rb] - mref[rb]) * LOG2E;
+                    exponentials(rb);
+                }
             }
 
-            // ---- the running sum (step 4); STRICT16: the whole of step 3 and 4 in fp16 ----
-            if (LAZY) {
-                l += lsum;                     // the sum is kept at the stored output's scale (first tile: l was 0)
-            } else if (!LSUM_DEFER) {
-                // fp16, each operation rounded: l = fp16(fp16(e^{dm_{j-1}} l) + fp16(e^{dm_j} l')); first tile: l = l'
-                const _Float16 lo = (_Float16)l, ln = (_Float16)lsum;
-                const float ln_all = (float)(_Float16)((_Float16)((_Float16)ep_s * lo) + (_Float16)((_Float16)ec_s * ln));
-                l = first ? lsum : l_keep ? l : ln_all;
-            }
+            if (STRICT) forget_product();
+        } else {
+            forget_p();
         }
         if (KSPL == 2 || grp == 0) drain_copies();
         __syncthreads();
     }
     if ((grp == 0) == (n_a == n_b)) __syncthreads();     // the barrier that the other group's last iteration ends with
 
-    if (LSUM_MFMA) l = Lacc[0];            // every row of the block is the sum
     // level of the stored output: running maximum in its frame, the frame's offset, the stored scale (exact in fp64)
-    bool none = !(J_w > j0 + jg) || l == 0.f;
-    // (a row that sees a single tile needs no pseudo-average, which may be infinite there).  Not finite: a score or a
-    // pseudo-average left the range of its type, and the state must not be taken for one without keys.
-    double level = none ? -__builtin_inf() : LEVEL ? R : (double)m + (one_tile ? 0.0 : (double)inva * (double)F) + (double)Lc;
-    if (!none && !__builtin_isfinite(level)) level = __builtin_nan("");
+    bool none[RB];
+    double level[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        l[rb] = STRICT ? (float)l2[rb] : Lacc[rb][0];      // every row of the block is the sum
+        none[rb] = !(J_w > j0 + jg) || l[rb] == 0.f;
+        // (a row that sees a single tile needs no pseudo-average, which may be infinite there).  Not finite: a score or a
+        // pseudo-average left the range of its type, and the state must not be taken for one without keys.
+        level[rb] = none[rb] ? -__builtin_inf() : LEVEL ? R[rb] : (double)m[rb] + (one_tile(rb) ? 0.0 : (double)inva * (double)F[rb]) + (double)Lc[rb];
+        if (!none[rb] && !__builtin_isfinite(level[rb])) level[rb] = __builtin_nan("");
+    }
     // ---------------- key split within the workgroup: group B's state joins group A's ----------------
     if (KSPL == 2) {
         __syncthreads();                   // the tiles have been read
-        static_assert(KSPL == 1 || 4 * CB * 4 * 64 * 16 <= 2 * KT_BYTES, "the exchange fits the K' tiles");
-        float4* xo = reinterpret_cast<float4*>(smem) + (wave & 3) * (CB * 4 * 64) + lane;
-        double* xr = reinterpret_cast<double*>(smem + 2 * KT_BYTES) + (wave & 3) * 64 + lane;
-        float* xl = reinterpret_cast<float*>(smem + 2 * KT_BYTES + 2048) + (wave & 3) * 64 + lane;
+        static_assert(KSPL == 1 || 4 * RB * CB * NE * 64 * 4 <= 2 * KT_BYTES, "the exchange fits the K' tiles");
+        f4* xo = reinterpret_cast<f4*>(smem) + (wave & 3) * (RB * CB * (NE / 4) * 64) + lane;
+        double* xr = reinterpret_cast<double*>(smem + 2 * KT_BYTES) + (wave & 3) * (RB * 64) + lane;
+        float* xl = reinterpret_cast<float*>(smem + 2 * KT_BYTES + 2048 * RB) + (wave & 3) * (RB * 64) + lane;
         if (grp == 1) {
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
+            for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
-                for (int gq = 0; gq < 4; ++gq)
-                    xo[(cb * 4 + gq) * 64] = float4{O[cb][4 * gq], O[cb][4 * gq + 1], O[cb][4 * gq + 2], O[cb][4 * gq + 3]};
-            *xr = level;
-            *xl = none ? 0.f : l;
+                for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                    for (int e = 0; e < NE; e += 4)
+                        xo[((rb * CB + cb) * NE + e) / 4 * 64] = f4{O[rb][cb][e], O[rb][cb][e + 1], O[rb][cb][e + 2], O[rb][cb][e + 3]};
+                xr[rb * 64] = level[rb];
+                xl[rb * 64] = none[rb] ? 0.f : l[rb];
+            }
         }
         __syncthreads();
         if (grp == 0) {
-            const double lev_b = *xr;
-            const double top = __builtin_fmax(level, lev_b);
-            // a state without keys weighs nothing, whatever its level; NaN stays NaN
-            const float wa = none ? 0.f : __builtin_amdgcn_exp2f((float)(level - top) * LOG2E);
-            const float wb = lev_b == -__builtin_inf() ? 0.f : __builtin_amdgcn_exp2f((float)(lev_b - top) * LOG2E);
-            l = (none ? 0.f : l * wa) + *xl * wb;
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
+            for (int rb = 0; rb < RB; ++rb) {
+                const double lev_b = xr[rb * 64];
+                const double top = __builtin_fmax(level[rb], lev_b);
+                // a state without keys weighs nothing, whatever its level; NaN stays NaN
+                const float wa = none[rb] ? 0.f : __builtin_amdgcn_exp2f((float)(level[rb] - top) * LOG2E);
+                const float wb = lev_b == -__builtin_inf() ? 0.f : __builtin_amdgcn_exp2f((float)(lev_b - top) * LOG2E);
+                l[rb] = (none[rb] ? 0.f : l[rb] * wa) + xl[rb * 64] * wb;
 #pragma unroll
-                for (int gq = 0; gq < 4; ++gq) {
-                    const float4 x = xo[(cb * 4 + gq) * 64];
-                    O[cb][4 * gq] = O[cb][4 * gq] * wa + x.x * wb;
-                    O[cb][4 * gq + 1] = O[cb][4 * gq + 1] * wa + x.y * wb;
-                    O[cb][4 * gq + 2] = O[cb][4 * gq + 2] * wa + x.z * wb;
-                    O[cb][4 * gq + 3] = O[cb][4 * gq + 3] * wa + x.w * wb;
-                }
-            level = top;
-            none = l == 0.f;
+                for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                    for (int e = 0; e < NE; e += 4) {
+                        const f4 x = xo[((rb * CB + cb) * NE + e) / 4 * 64];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) O[rb][cb][e + i] = O[rb][cb][e + i] * wa + x[i] * wb;
+                    }
+                level[rb] = top;
+                none[rb] = l[rb] == 0.f;
+            }
         } else {
             wave_valid = false;
         }
@@ -1102,21 +1212,21 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     if (!STRICT && part_o != nullptr) {
         if (wave_valid) {
             const size_t rows_all = (size_t)at.heads * Nq;
-            const size_t grow = head * Nq + row;                                                 // global row index
-            if (row_valid && lh == 0) {
-                part_lr[((size_t)split * rows_all + grow) * 2] = none ? 0.0 : (double)l;
-                part_lr[((size_t)split * rows_all + grow) * 2 + 1] =
-                    none ? -__builtin_inf() : l == l ? level : (double)l;
-            }
-            float* pbase = part_o + ((size_t)split * rows_all + grow) * D;
-            if (row_valid && !none) {
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb)
+            for (int rb = 0; rb < RB; ++rb) {
+                if (row + RR * rb >= Nq) continue;
+                const size_t grow = (size_t)split * rows_all + head * Nq + row + RR * rb;        // row of the partial states
+                if (g == 0) {
+                    part_lr[grow * 2] = none[rb] ? 0.0 : (double)l[rb];
+                    part_lr[grow * 2 + 1] = none[rb] ? -__builtin_inf() : l[rb] == l[rb] ? level[rb] : (double)l[rb];
+                }
+                if (!none[rb]) {
 #pragma unroll
-                    for (int gq = 0; gq < 4; ++gq) {
-                        float4 v4 = {O[cb][4 * gq], O[cb][4 * gq + 1], O[cb][4 * gq + 2], O[cb][4 * gq + 3]};
-                        *reinterpret_cast<float4*>(pbase + 32 * cb + 8 * gq + 4 * lh) = v4;
-                    }
+                    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                        for (int e = 0; e < NE; e += 4)
+                            *reinterpret_cast<f4*>(part_o + grow * D + RR * cb + 2 * e + 4 * g) = f4{O[rb][cb][e], O[rb][cb][e + 1], O[rb][cb][e + 2], O[rb][cb][e + 3]};
+                }
             }
         }
         if (INSTR) {
@@ -1129,25 +1239,29 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     // ---------------- final normalisation and store ----------------
     unsigned long long n_bad = 0;
     if (wave_valid) {
-        if (STRICT) fold16(J_w - 1);
-        const float oscale = STRICT ? 0.f : 1.0f / l;
+        if (STRICT) fold16();
+        float oscale[RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) oscale[rb] = STRICT ? 0.f : 1.0f / l[rb];
         // fp32 variants: the fp32 quotient is rounded once, to the output type; STRICT16: the fp16
         // quotient of Algorithm 1's last line, converted when the output is bf16
-        auto value = [&](int cb, int i) {
-            return STRICT ? (float)(_Float16)(O16[cb][i >> 1][i & 1] / (_Float16)l) : O[cb][i] * oscale;
+        auto value = [&](int rb, int cb, int e) {
+            return STRICT ? (float)(_Float16)(O16[rb][cb][e >> 1][e & 1] / l2[rb]) : O[rb][cb][e] * oscale[rb];
         };
-        if (INSTR && row_valid) {
+        if (INSTR) {
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
+            for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float x = value(cb, i), fv = io_bf16 ? __uint_as_float(pack_bf16(x, 0.f) << 16) : (float)(_Float16)x;
-                    n_bad += (fv != fv || __builtin_fabsf(fv) == __builtin_inff()) ? 1u : 0u;
-                }
+                for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                    for (int e = 0; e < NE; ++e) {
+                        const float x = value(rb, cb, e), fv = io_bf16 ? __uint_as_float(pack_bf16(x, 0.f) << 16) : (float)(_Float16)x;
+                        n_bad += row + RR * rb < Nq && (fv != fv || __builtin_fabsf(fv) == __builtin_inff()) ? 1u : 0u;
+                    }
         }
         // the tiles have been read by all wavefronts: both groups are past their last matrix parts (halves: where the wavefront
         // has just read the other group's output)
-        store_rows<D>(smem + wave * (64 * D * KSPL), value, o + (head * Nq + qw0) * D, Nq - qw0, lane, io_bf16);
+        store_rows<D, RB>(smem + wave * (64 * D * KSPL), value, o + (head * Nq + qw0) * D, Nq - qw0, lane, io_bf16);
     }
     if (INSTR) {
         if (ovf_s != nullptr && n_ovf) atomicAdd(ovf_s, n_ovf);
@@ -1156,7 +1270,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     }
 }
 
-template <int D, int VAR, bool CAUSAL, bool INSTR, int KSPL = 1>
+template <int D, int VAR, bool CAUSAL, bool INSTR, int KSPL = 1, int RB = D / 64>
 hipError_t launch_fwd(const PasaLaunch& p)
 {
     constexpr int RWG = 256 / KSPL;
@@ -1164,7 +1278,7 @@ hipError_t launch_fwd(const PasaLaunch& p)
     const int nqt = (p.Nq + RWG - 1) / RWG;
     const int nsplit = (VAR == PASA_K_STRICT16 || p.nsplit < 1) ? 1 : p.nsplit;   // fp16 state has no merge rule
     const dim3 grid((unsigned)(nqt * p.Hq * p.B * nsplit));
-    auto kern = pasa_fwd<D, VAR, CAUSAL, INSTR, KSPL>;
+    auto kern = pasa_fwd<D, VAR, CAUSAL, INSTR, KSPL, RB>;
     // the dynamic LDS limit of this instantiation is raised once per device, not on every launch
     static std::atomic<unsigned long long> lds_limit_set{0ull};
     int dev = 0;
@@ -1202,7 +1316,8 @@ hipError_t launch_fwd_cv(const PasaLaunch& p)
 {
     const bool instr = p.overflow_s != nullptr || p.nonfinite_o != nullptr;
     if constexpr (D == 128 && VAR != PASA_K_STRICT16 && VAR != PASA_K_NAIVE16) {
-        if (p.halves && !instr) return p.causal ? launch_fwd<D, VAR, true, false, 2>(p) : launch_fwd<D, VAR, false, false, 2>(p);
+        if (p.halves == 1 && !instr) return p.causal ? launch_fwd<D, VAR, true, false, 2, 1>(p) : launch_fwd<D, VAR, false, false, 2, 1>(p);
+        if (p.halves == 2 && !instr) return p.causal ? launch_fwd<D, VAR, true, false, 2, 2>(p) : launch_fwd<D, VAR, false, false, 2, 2>(p);
     }
     if (p.causal) return instr ? launch_fwd<D, VAR, true, true>(p) : launch_fwd<D, VAR, true, false>(p);
     return instr ? launch_fwd<D, VAR, false, true>(p) : launch_fwd<D, VAR, false, false>(p);

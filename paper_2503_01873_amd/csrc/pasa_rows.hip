@@ -7,8 +7,6 @@
 #include "pasa_device.h"
 #include "pasa_kernels.h"
 
-typedef float f4 __attribute__((ext_vector_type(4)));
-
 namespace {
 
 constexpr int U = 64;           // keys per unit of work of one wavefront (half a tile)
@@ -18,35 +16,6 @@ constexpr float PMAX = 2980.f;  // the fp16 value below e^CMAX
 __device__ inline h8 load_frag(__amdgpu_buffer_rsrc_t src, int voff, int soff)
 {
     return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(src, voff, soff, 0));
-}
-
-// x of the even and of the odd one of each pair of 16-lane rows, in both; x of the lower and of the upper 32 lanes, in both
-__device__ inline void rows16(float x, float& even, float& odd)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    even = __uint_as_float(r[0]);
-    odd = __uint_as_float(r[1]);
-}
-__device__ inline void rows32(float x, float& low, float& high)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    low = __uint_as_float(r[0]);
-    high = __uint_as_float(r[1]);
-}
-// largest value / sum over the four lanes l, l^16, l^32, l^48 that share a query row
-__device__ inline float max_row(float x)
-{
-    float a, b;
-    rows16(x, a, b);
-    rows32(__builtin_fmaxf(a, b), a, b);
-    return __builtin_fmaxf(a, b);
-}
-__device__ inline float sum_row(float x)
-{
-    float a, b;
-    rows16(x, a, b);
-    rows32(a + b, a, b);
-    return a + b;
 }
 
 // One workgroup = NW wavefronts owns 16 * RB rows and a range of the keys in units of 64.  The rows come from lists: with fewer than 16 rows given, the rows of ALL the
