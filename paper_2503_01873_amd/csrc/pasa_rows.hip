@@ -42,8 +42,9 @@ __device__ inline h8 load_frag(__amdgpu_buffer_rsrc_t src, int voff, int soff)
 // odd rows the low parts), and the level is kept in absolute terms.  (With row sums in lanes and the products for eight
 // tiles at a time shared out by shuffles, 32 rows took twice as long as 16.)  Four wavefronts per workgroup: two workgroups
 // share a compute unit, so that one loads while the other merges (28 heads of 512 rows 16.8 -> 11.7 us against eight).
-template <int D, int RB, int NW, bool S16, bool DIRECT>
-__device__ __forceinline__ void rows_body(const _Float16* __restrict__ q, const char* __restrict__ ws, const _Float16* __restrict__ kmean,
+template <int D, int RB, int NW, bool S16>
+__global__ __launch_bounds__(64 * NW, 2)
+void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, const _Float16* __restrict__ kmean,
                _Float16* __restrict__ o, FastDiv lists, FastDiv Nq_, FastDiv nblk_, FastDiv nsplit_, int grid, int list_rows, int row0, int N,
                int causal, int units, float coef, int mixed, int io_bf16, const unsigned long long* gate,
                float* __restrict__ part_o, double* __restrict__ part_lr, size_t rows_all)
@@ -53,11 +54,10 @@ __device__ __forceinline__ void rows_body(const _Float16* __restrict__ q, const 
     constexpr int ROWS = 16 * RB;
     constexpr int LD = D + 4;                    // LDS row of the merge, in floats
     constexpr int TILE_BYTES = 4 * T * D;        // K' tile then V tile
-    // P without the maximum of its scores, as in pasa_fwd.  us, both sides in turn: 4 heads, 700 rows of 12800 keys 71.9 -> 65.2; 2 x 16 heads, 128
-    // rows of 28000 keys 81.1 -> 79.7; S16, 14 x 5 heads of 366 rows 13.4 -> 12.4.  d = 128 waits for its fragments, not for this chain (128 rows
-    // of 20000 keys 91.4 / 91.0), and with 32 rows has no registers to keep the scores beside P (777 rows 18.5 / 20.9).
-    // Not DIRECT, where a score may overflow though the tile's bias does not.
-    constexpr bool LEVEL = D == 64 && !DIRECT;
+    // S16, d = 64: P without the maximum of its scores, as in pasa_fwd (14 x 5 heads of 366 rows 22.7 -> 21.5 us).  Not MIXED: 4 heads, 700 rows of 12800
+    // keys 29.3 -> 28.6 us with normal values, but 29.5 -> 32.3 where rows keep rising and P is made twice (resonant values).  d = 128 waits
+    // for its fragments, not for this chain (128 rows of 20000 keys 91.4 / 91.0), and with 32 rows has no registers to keep the scores beside P.
+    constexpr bool LEVEL = D == 64 && S16;
     __shared__ __attribute__((aligned(16))) float lds_o[NW * ROWS * LD];
     __shared__ double lds_r[NW][ROWS];
     __shared__ float lds_l[NW][ROWS];
@@ -451,26 +451,6 @@ __device__ __forceinline__ void rows_body(const _Float16* __restrict__ q, const 
     }
 }
 
-template <int D, int RB, int NW, bool S16>
-__global__ __launch_bounds__(64 * NW, 2)
-void pasa_rows(const _Float16* __restrict__ q, const char* __restrict__ ws, const _Float16* __restrict__ kmean,
-               _Float16* __restrict__ o, FastDiv lists, FastDiv Nq_, FastDiv nblk_, FastDiv nsplit_, int grid, int list_rows, int row0, int N,
-               int causal, int units, float coef, int mixed, int io_bf16, const unsigned long long* gate,
-               float* __restrict__ part_o, double* __restrict__ part_lr, size_t rows_all)
-{
-    rows_body<D, RB, NW, S16, false>(q, ws, kmean, o, lists, Nq_, nblk_, nsplit_, grid, list_rows, row0, N, causal, units, coef, mixed, io_bf16, gate, part_o, part_lr, rows_all);
-}
-
-template <int D, int RB, int NW>
-__global__ __launch_bounds__(64 * NW, 2)
-void pasa_rows_direct(const _Float16* __restrict__ q, const char* __restrict__ ws, const _Float16* __restrict__ kmean,
-                      _Float16* __restrict__ o, FastDiv lists, FastDiv Nq_, FastDiv nblk_, FastDiv nsplit_, int grid, int list_rows, int row0, int N,
-                      int causal, int units, float coef, int mixed, int io_bf16, const unsigned long long* gate,
-                      float* __restrict__ part_o, double* __restrict__ part_lr, size_t rows_all)
-{
-    rows_body<D, RB, NW, false, true>(q, ws, kmean, o, lists, Nq_, nblk_, nsplit_, grid, list_rows, row0, N, causal, units, coef, mixed, io_bf16, gate, part_o, part_lr, rows_all);
-}
-
 // Merge of the key splits of one call: per query row, the splits' stored outputs and sums are brought to the highest of
 // their levels (the log-sum-exp rule on the absolute level a split's stored output refers to: m + Inva * F + Lc in
 // pasa_fwd, R in pasa_rows and pasa_fwd4) and added; then Algorithm 1's final quotient.  A split that saw none of a row's keys
@@ -630,7 +610,6 @@ hipError_t launch_rows(const PasaLaunch& p)
     const size_t rows_all = (size_t)p.B * p.Hq * p.Nq;
     const unsigned grid = (unsigned)((size_t)p.B * p.Hkv * lists * nblk * nsplit);
     auto kern = pasa_rows<D, RB, NW, S16>;
-    if (D == 64 && p.variant == PASA_K_DIRECT) kern = pasa_rows_direct<64, RB, NW>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * NW), 0, p.stream,
                        (const _Float16*)p.q, (const char*)p.ws, (const _Float16*)p.kmean, (_Float16*)p.o, fast_div(lists), fast_div(p.Nq),
                        fast_div(nblk), fast_div(nsplit), (int)grid, list_rows, p.row0, p.N, p.causal, units, p.variant == PASA_K_DIRECT ? p.scale : p.inva,

@@ -34,21 +34,3 @@ def test_no_iteration_waits_for_all_its_loads(tmp_path):
         waits = [int(n) for x in key_loops[0] for n in re.findall(r"s_waitcnt.*vmcnt\((\d+)\)", x)]
         # four fragments of d = 64 are the fewest that are asked for at a time; the newest ones are needed next time round
         assert waits and min(waits) >= 4, (name, waits)
-
-
-@pytest.mark.skipif(not shutil.which("hipcc") and not os.path.exists("/opt/rocm/bin/hipcc"), reason="needs hipcc")
-def test_nor_does_one_of_the_direct_kernels(tmp_path):
-    """pasa_rows_direct, d = 64: the longest block with the matrix products of an iteration."""
-    out = tmp_path / "pasa_rows.s"
-    flags = [f for f in build.FLAGS if f not in ("-shared", "-Wall")]
-    subprocess.run([build.hipcc(), *flags, "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC, "--cuda-device-only", "-S",
-                    os.path.join(build.CSRC, "pasa_rows.hip"), "-o", str(out)], check=True, capture_output=True)
-    text = out.read_text()
-    names = re.findall(r"^(\S*pasa_rows_directI\S*):", text, re.M)
-    assert len(names) == 2
-    for name in names:
-        body = text[text.index("\n" + name + ":"):].split(".Lfunc_end")[0]
-        blocks = re.split(r"^(?=\.LBB\d+_\d+:|; %bb\.\d+:)", body, flags=re.M)
-        loop = [b for b in blocks if "Loop" in b.splitlines()[0] + b.splitlines()[min(1, len(b.splitlines()) - 1)]]
-        waits = [int(n) for b in loop for n in re.findall(r"s_waitcnt.*vmcnt\((\d+)\)", b)]
-        assert sum(b.count("v_mfma") for b in loop) > 8 and waits and min(waits) >= 4, (name, waits)
