@@ -19,6 +19,7 @@ __device__ inline void workgroup_barrier()
 
 constexpr float CMAX = 8.f;     // P may exceed 1 by at most e^CMAX before a row moves its stored output to a new level
 constexpr float PMAX = 2980.f;  // the fp16 value below e^CMAX
+constexpr int EARLY = 16;       // tiles at the start of a row in which it is likely to rise (see below)
 
 // One workgroup = four wavefronts = 128 query rows of one head, 32 rows per wavefront; three workgroups share a compute
 // unit and three wavefronts a SIMD.  The GEMMs are pasa_fwd's (32x32x16 MFMAs, transposed, fragments from LDS through a ring
@@ -35,6 +36,9 @@ constexpr float PMAX = 2980.f;  // the fp16 value below e^CMAX
 // MIXED makes P without the maximum of the tile, as pasa_fwd does (see there); a wavefront with a row that rises makes the scores again too,
 // since there are no registers to keep them beside P (kept: spills, 283 -> 319 us on 14 x 5 heads of 5000 rows, causal).  us, both sides in turn, normal
 // values: 14 x 5 heads of 9216 rows 1663 -> 1601, causal 5000 rows 284 -> 274; 16 heads of 8192 rows 315 -> 295, causal 16000 rows 575 -> 554.
+// In the first tiles of a row, where rows keep rising, P would be made twice on most of them: there the maximum is taken first (resonant
+// values, us, without the maximum from the second tile on / from the 9th / 17th / 33rd: 4 x 16 heads of 930 rows 39.8 / 36.2 / 36.2 / 36.2, 4 x 5 heads of
+// 3786 rows, causal, 69.9 / 69.4 / 68.8 / 67.8; 2 x 5 heads of 9216 rows, normal values, 273.1 / 273.9 / 274.4 / 277.3, the maximum always 286.5).
 // 64 rows per wavefront and two workgroups to a compute unit on top of it (half the LDS reads): 1 % faster on the 9216 rows,
 // 4 to 20 % slower on all smaller calls.
 template <bool CAUSAL, bool DIRECT>
@@ -245,10 +249,10 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
                 exponentials();
             } else {
                 nml = 0.f;
+                const float off = __builtin_fmaf(v, 0.f, (float)__builtin_fma((double)coef, (double)v, -R));
+                if (!unseen) nml = off * LOG2E;
                 unsigned long long high = ~0ull;
-                if (j != j0) {
-                    const float off = __builtin_fmaf(v, 0.f, (float)__builtin_fma((double)coef, (double)v, -R));
-                    if (!unseen) nml = off * LOG2E;
+                if (j - j0 >= EARLY) {
                     scores();
                     exponentials();
                     high = __builtin_amdgcn_ballot_w64(!(largest_of(Pf) <= PMAX));
@@ -256,7 +260,7 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
                 if (high != 0ull) {
                     asm volatile("" ::: "memory");
                     scores();                // there are no registers to keep them beside P
-                    move_up([&](float) { return !unseen && (((unsigned)high | (unsigned)(high >> 32)) >> lq & 1u) != 0u; });
+                    move_up([&](float c) { return !unseen && c > CMAX; });
                     exponentials();
                 }
             }
