@@ -8,8 +8,8 @@
 //                 a tile is a straight copy whose MFMA fragments are single conflict-free 128-bit LDS reads.
 //
 //  pasa_fwd       Algorithm 1's main loops.  One workgroup = 8 wavefronts = 256 query rows; each wavefront owns
-//                 32 query rows and sweeps the key tiles.  Both GEMMs are computed transposed, at d = 128 on
-//                 v_mfma_f32_16x16x32_f16 (two blocks of 16 rows), at d = 64 on v_mfma_f32_32x32x16_f16 (one of 32):
+//                 32 query rows and sweeps the key tiles.  Both GEMMs are computed transposed, on
+//                 v_mfma_f32_16x16x32_f16 (two blocks of 16 rows) or v_mfma_f32_32x32x16_f16 (one of 32; d = 64, STRICT16):
 //                     S'^T = K' Q^T      (A = K' fragment from LDS, B = Q fragment held in registers)
 //                     O^T += V^T P^T     (A = V^T fragment from LDS, B = P^T taken straight from the S'^T accumulators)
 //                 In the transposed accumulator layout a lane holds a quarter (16 x 16: of two rows) or half of the keys of a query row, so
@@ -428,7 +428,8 @@ __device__ inline void for_constants(std::integer_sequence<int, I...>, F f) { (f
 // 1.71 PFLOP/s against 1.50, on zeros 2.36 against 2.42.  Power is what bounds the long launches at d = 128, so they take it: 28 heads on 4, us, both
 // sides in turn, 8192 rows 449 -> 403, 4096 rows not causal 233 -> 209; S16, 4096 rows 136 -> 124; DIRECT 129 -> 120; 1500 rows of 12000 keys
 // 254 -> 242.  An MFMA holds the issue port though, and there are twice as many: where the vector part is the longer one (d = 64), or launches are short,
-// 32 x 32 x 16 is faster (8 heads, d = 64, 2500 rows 50.1 / 53.6; 2 x 5 heads of 5000 rows, STRICT16 128 / 138).
+// 32 x 32 x 16 is faster (8 heads, d = 64, 2500 rows 50.1 / 53.6; STRICT16, 2 x 5 heads of 5000 rows, d = 64, 128 / 138, 12 heads on 2, 2257 rows, d = 128,
+// 76.7 / 84.8).
 //
 // KSPL = 2: the workgroup owns 128 rows; both groups of wavefronts hold all of them, group A takes the even key tiles and
 // group B the odd ones, each through a K' and a V buffer of its own, and B's state joins A's through LDS at the end (the rule of
@@ -882,7 +883,6 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
         if (j < J_w) {
             const bool first = (j == j0 + jg);
             if (STRICT && do_g2) fold16();           // O <- fp16(e^{dm_j} PV) + fp16(e^{dm_{j-1}} O) for the product of tile j-1
-            if (STRICT) PASA_FENCE();
             // ---- S' as stored: fp32, or rounded to fp16 ----
             // STRICT16 and S16 keep the rounded scores packed two per register; STRICT16 works on them with packed fp16
             // instructions (same roundings, half the instructions and registers)
@@ -957,16 +957,25 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
             }
             // ---- local maximum m' ----
             auto row_max = [&](int rb) {
-                float pm;
+                float pm;                    // from four chains: one waits for each of its links
                 if (PACKED) {
-                    h2 mm = Sh[rb][0][0];
+                    h2 mm[4];
 #pragma unroll
-                    for (int t = 1; t < KB * NE / 2; ++t) mm = __builtin_elementwise_max(mm, Sh[rb][t / (NE / 2)][t % (NE / 2)]);
-                    pm = __builtin_fmaxf((float)mm[0], (float)mm[1]);
+                    for (int t = 0; t < KB * NE / 2; ++t) {
+                        const h2 x = Sh[rb][t / (NE / 2)][t % (NE / 2)];
+                        mm[t & 3] = t < 4 ? x : __builtin_elementwise_max(mm[t & 3], x);
+                    }
+                    const h2 top = __builtin_elementwise_max(__builtin_elementwise_max(mm[0], mm[1]), __builtin_elementwise_max(mm[2], mm[3]));
+                    pm = __builtin_fmaxf((float)top[0], (float)top[1]);
                 } else {
-                    pm = S[rb][0][0];
+                    constexpr int PART = KB * NE / 4;
+                    float part[4];
 #pragma unroll
-                    for (int i = 1; i < KB * NE; ++i) pm = __builtin_fmaxf(pm, S[rb][i / NE][i % NE]);
+                    for (int i = 0; i < KB * NE; ++i) {
+                        const float x = S[rb][i / NE][i % NE];
+                        part[i / PART] = i % PART == 0 ? x : __builtin_fmaxf(part[i / PART], x);
+                    }
+                    pm = __builtin_fmaxf(__builtin_fmaxf(part[0], part[1]), __builtin_fmaxf(part[2], part[3]));
                 }
                 return RB == 1 ? max32(pm) : max_row(pm);
             };
@@ -1270,7 +1279,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     }
 }
 
-template <int D, int VAR, bool CAUSAL, bool INSTR, int KSPL = 1, int RB = D / 64>
+template <int D, int VAR, bool CAUSAL, bool INSTR, int KSPL = 1, int RB = (D == 128 && VAR != PASA_K_STRICT16 ? 2 : 1)>
 hipError_t launch_fwd(const PasaLaunch& p)
 {
     constexpr int RWG = 256 / KSPL;
