@@ -369,9 +369,10 @@ Plan plan_call(int variant, bool counters, bool may_split, int B, int Hq, int Hk
         const double halves_us = equal ? equal_rounds(W, 8.34, s16 ? 3.69 : 2.45, s16 ? 3.52 : 2.935, most_h)
                                        : unequal_rounds(W, 8.34, s16 ? 2.78 : 2.2, s16 ? 3.15 : 2.738, most_h, mean_h);
         if (rows_us < 0.98 * (fwd_us < halves_us ? fwd_us : halves_us)) return r;
-        // MFMAs of 32 rows in workgroups of a single round and four steps at most: there is power to spare, and instructions count (us, 28 heads, causal,
-        // 32 rows / 16: 1024 rows 23.6 / 24.6; 2048 rows 49.6 / 47.7; 8 heads, not causal, 4096 rows 76.1 / 73.7)
-        if (halves_us < 0.98 * fwd_us) p = {Plan::HALVES, 1, W <= kComputeUnits && most_h <= 4 ? 1 : 2};
+        // MFMAs of 32 rows where one round of workgroups leaves power to spare, because they are short or, causal, mostly shorter than the longest: there
+        // instructions count (us, 32 rows / 16, one round, causal: 28 heads of 1024 rows 23.6 / 24.6, 12 heads of 2304 rows 37.7 / 39.4, 8 heads of 4000 rows
+        // 67.0 / 68.4; 8 heads, not causal, 4096 rows 76.1 / 73.7; two rounds, causal: 28 heads of 2048 rows 49.6 / 47.7)
+        if (halves_us < 0.98 * fwd_us) p = {Plan::HALVES, 1, W <= kComputeUnits && (most_h <= 4 || !equal) ? 1 : 2};
         return p;
     }
     // d = 64, S16: a step of pasa_fwd takes 2.0 to 2.55 us.  The others: of pasa_fwd 2.1 to 2.7, of pasa_fwd4 2.1 / 2.7 / 3.3 with one / two / three
