@@ -809,8 +809,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
         return ln;
     };
 
-    // Values that nothing reads before they are made again: without this the compiler keeps their registers, on the way past the code
-    // that makes them, through all that comes before it
+    // For where nothing reads these values before they are made again: without this the compiler keeps their registers, on the way past the
+    // code that makes them, through all that comes before it
     auto forget_p = [&] {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
@@ -866,7 +866,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
         }
         // ---- pending product of tile j-1 ----
         if (do_g2) gemm2(j - KSPL);
-        else if (STRICT) forget_product();
+        else if (STRICT && j == j0) forget_product();     // not past the wavefront's last tile: its product is folded in behind the loop
         // ---- S'(j) ----
         Acc S[RB][KB];                   // S'^T accumulators
         if (do_g1) gemm1(j, S);

@@ -63,8 +63,8 @@ def gpu_attn(q, k, v, causal, scale, variant=P.MIXED, beta=-1.0, counters=False,
     return o, (cnt.cpu().numpy() if counters else None)
 
 
-def gpu_attn_chunks(q, k, v, causal, scale, chunks, variant=P.MIXED, beta=-1.0):
-    """K/V prepared once, then one pasa_attn_fwd_chunk call per (first query row, row count, row0) of `chunks`.
+def gpu_attn_chunks(q, k, v, causal, scale, chunks, variant=P.MIXED, beta=-1.0, counters=False):
+    """K/V prepared once, then one pasa_attn_fwd_chunk call per (first query row, row count, row0) of `chunks`, with both counters or none.
     q: [B,Hq,Nq,d] numpy fp16; each chunk's rows are copied to a buffer of their own.  Returns o [B,Hq,Nq,d]."""
     import torch
     dev = torch.device("cuda:0")
@@ -76,12 +76,14 @@ def gpu_attn_chunks(q, k, v, causal, scale, chunks, variant=P.MIXED, beta=-1.0):
     stream = torch.cuda.current_stream()
     P.pasa_prepare_kv(tk, tv, B, Hkv, N, d, scale, ws, wsb, stream, beta=beta, variant=variant)
     out = np.full(q.shape, np.nan, np.float16)
+    cnt = torch.zeros(2, dtype=torch.int64, device=dev) if counters else None
     guard = 4096
     for first, count, row0 in chunks:
         tq = torch.from_numpy(np.ascontiguousarray(q[:, :, first:first + count])).to(dev)
         flat = torch.full((tq.numel() + guard,), float("nan"), dtype=torch.float16, device=dev)
         to = flat[:tq.numel()].view(tq.shape)
         P.pasa_attn_fwd_chunk(tq, to, B, Hq, Hkv, count, row0, N, d, causal, scale, ws, wsb, stream,
+                              overflow_s=cnt[0:1] if counters else None, nonfinite_o=cnt[1:2] if counters else None,
                               beta=beta, variant=variant)
         torch.cuda.synchronize()
         assert bool(torch.isnan(flat[tq.numel():]).all()), "the kernel wrote past the end of the output"

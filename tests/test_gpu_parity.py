@@ -486,6 +486,26 @@ def test_unaligned_chunks_other_variants(variant):
     assert c["maxabs"] <= 2e-3
 
 
+@pytest.mark.parametrize("counters", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("row0,Nq", [(32, 256), (64, 300), (96, 256), (101, 300), (64, 40), (224, 480)])
+def test_strict16_chunks_whose_wavefronts_see_different_numbers_of_tiles(row0, Nq, d, counters):
+    """Wavefronts of one group go through as many turns as the one that sees most tiles: the product of the last tile of the others stays
+    whole meanwhile.  In the whole call all of a group see as many; no operation of a row depends on where it lies: the same bits."""
+    rng = np.random.default_rng(row0 + Nq)
+    N = row0 + Nq
+    q = rng.standard_normal((1, 4, N, d)).astype(np.float16)
+    k = (rng.standard_normal((1, 2, N, d)) + 1).astype(np.float16)
+    v = rng.standard_normal((1, 2, N, d)).astype(np.float16)
+    scale = f32(d ** -0.5)
+    whole, _ = gpu_attn(q, k, v, True, scale, P.STRICT16, counters=counters)
+    c = compare(whole[0, 3], po.pasa_rows(q[0, 3], k[0, 1], v[0, 1], scale, True, BETA, 128, po.STRICT16))
+    assert np.isfinite(whole).all() and c["maxabs"] <= 8e-3 and c["p99"] <= 2e-3      # fp16 sums in another order (see the file's header)
+    o = gpu_attn_chunks(q[:, :, row0:], k, v, True, scale, [(0, Nq, row0)], variant=P.STRICT16, counters=counters)
+    bad = np.argwhere(o.view(np.uint16) != whole[:, :, row0:].view(np.uint16))
+    assert not len(bad), (len(bad), "rows", np.unique(bad[:, 2]) + row0, "channels", np.unique(bad[:, 3]))
+
+
 def test_unaligned_chunks_naive16():
     rng = np.random.default_rng(61)
     N, d = 400, 64
