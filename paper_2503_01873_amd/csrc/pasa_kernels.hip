@@ -616,7 +616,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     h8 Pf[RB][KK];                   // P^T, B operand of the second GEMM
     Acc O[RB][CB];                   // fp32 variants: stored output; STRICT: product of the latest tile
     h2 O16[RB][CB][NE / 2];              // STRICT: running output
-    unsigned long long n_ovf = 0;
+    unsigned long long n_ovf = 0;    // of the whole wavefront
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         F[rb] = l[rb] = Lc[rb] = 0.f;
@@ -887,13 +887,34 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
             // STRICT16 and S16 keep the rounded scores packed two per register; STRICT16 works on them with packed fp16
             // instructions (same roundings, half the instructions and registers)
             h2 Sh[RB][KB][NE / 2];
+            if (INSTR) {
+                // Only where there is something to count, and by the wavefront, a block at a time: a number per lane, and the 64 comparisons of
+                // a tile all at once, took 152 (MIXED) to 187 (DIRECT) vector registers that were not there at d = 128.  28 heads on 4, 4096 rows,
+                // us: MIXED 371 -> 126, DIRECT 455 -> 129, S16 157 -> 133, NAIVE16 204 -> 139; the adaptive start 210 -> 145, 512 rows 40 -> 30.
+                // (Counted on every tile: 144, 150, 151, 159; d = 64, 14 x 5 heads, 2000 rows, adaptive 220 against 169.)
+                float top[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < RB * KB * NE; ++i) top[i & 3] = __builtin_fmaxf(top[i & 3], __builtin_fabsf(S[i / (KB * NE)][i / NE % KB][i % NE]));
+                if (__builtin_amdgcn_ballot_w64(__builtin_fmaxf(__builtin_fmaxf(top[0], top[1]), __builtin_fmaxf(top[2], top[3])) >= 65520.f) != 0ull) {
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                        for (int kb = 0; kb < KB; ++kb) {
+                            asm volatile("" : "+v"(S[rb][kb]));
+                            unsigned n = 0;
+#pragma unroll
+                            for (int e = 0; e < NE; ++e) n += (unsigned)__builtin_popcountll(__builtin_amdgcn_ballot_w64(__builtin_fabsf(S[rb][kb][e]) >= 65520.f));
+                            asm volatile("" : "+s"(n));
+                            n_ovf += n;
+                        }
+                }
+            }
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
                 for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                     for (int e = 0; e < NE; ++e) {
-                        if (INSTR) n_ovf += (__builtin_fabsf(S[rb][kb][e]) >= 65520.f) ? 1u : 0u;
                         if (PACKED) {
                             if (e & 1) Sh[rb][kb][e >> 1] = pack_rn(S[rb][kb][e - 1], S[rb][kb][e]);
                         } else if (S16) {
@@ -1239,8 +1260,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
             }
         }
         if (INSTR) {
-            if (ovf_s != nullptr && n_ovf) atomicAdd(ovf_s, n_ovf);
-            if (ovf_group != nullptr && n_ovf) atomicAdd(ovf_group + grp_id, n_ovf);
+            if (ovf_s != nullptr && lane == 0 && n_ovf) atomicAdd(ovf_s, n_ovf);
+            if (ovf_group != nullptr && lane == 0 && n_ovf) atomicAdd(ovf_group + grp_id, n_ovf);
         }
         return;
     }
@@ -1273,8 +1294,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
         store_rows<D, RB>(smem + wave * (64 * D * KSPL), value, o + (head * Nq + qw0) * D, Nq - qw0, lane, io_bf16);
     }
     if (INSTR) {
-        if (ovf_s != nullptr && n_ovf) atomicAdd(ovf_s, n_ovf);
-        if (ovf_group != nullptr && n_ovf) atomicAdd(ovf_group + grp_id, n_ovf);
+        if (ovf_s != nullptr && lane == 0 && n_ovf) atomicAdd(ovf_s, n_ovf);
+        if (ovf_group != nullptr && lane == 0 && n_ovf) atomicAdd(ovf_group + grp_id, n_ovf);
         if (nonfinite_o != nullptr && n_bad) atomicAdd(nonfinite_o, n_bad);
     }
 }

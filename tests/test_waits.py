@@ -1,4 +1,5 @@
-"""What the compiler makes of pasa_rows' key loop: an iteration must not wait for loads that the next ones need.  Compiles, needs no GPU."""
+"""What the compiler makes of the kernels: an iteration of pasa_rows' key loop must not wait for loads that the next ones need, and no kernel
+keeps vector registers in memory.  Compiles, needs no GPU."""
 import os
 import re
 import shutil
@@ -9,13 +10,19 @@ import pytest
 from paper_2503_01873_amd import build
 
 
-@pytest.mark.skipif(not shutil.which("hipcc") and not os.path.exists("/opt/rocm/bin/hipcc"), reason="needs hipcc")
-def test_no_iteration_waits_for_all_its_loads(tmp_path):
-    out = tmp_path / "pasa_rows.s"
+pytestmark = pytest.mark.skipif(not shutil.which("hipcc") and not os.path.exists("/opt/rocm/bin/hipcc"), reason="needs hipcc")
+
+
+def _assembly(source, tmp_path):
+    out = tmp_path / "kernels.s"
     flags = [f for f in build.FLAGS if f not in ("-shared", "-Wall")]
     subprocess.run([build.hipcc(), *flags, "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC, "--cuda-device-only", "-S",
-                    os.path.join(build.CSRC, "pasa_rows.hip"), "-o", str(out)], check=True, capture_output=True)
-    text = out.read_text()
+                    os.path.join(build.CSRC, source), "-o", str(out)], check=True, capture_output=True)
+    return out.read_text()
+
+
+def test_no_iteration_waits_for_all_its_loads(tmp_path):
+    text = _assembly("pasa_rows.hip", tmp_path)
     names = re.findall(r"^(\S*pasa_rowsI\S*):", text, re.M)
     assert len(names) == 6
     for name in names:
@@ -34,3 +41,10 @@ def test_no_iteration_waits_for_all_its_loads(tmp_path):
         waits = [int(n) for x in key_loops[0] for n in re.findall(r"s_waitcnt.*vmcnt\((\d+)\)", x)]
         # four fragments of d = 64 are the fewest that are asked for at a time; the newest ones are needed next time round
         assert waits and min(waits) >= 4, (name, waits)
+
+
+@pytest.mark.parametrize("source", ["pasa_kernels.hip", "pasa_fwd4.hip", "pasa_rows.hip"])
+def test_no_vector_register_is_kept_in_memory(source, tmp_path):
+    """pasa_fwd with counters too: the first pass of the adaptive start is one of those."""
+    spilled = dict(re.findall(r"\.name: +(\S+)\n(?:(?! +- ).*\n)*? +\.vgpr_spill_count: +(\d+)", _assembly(source, tmp_path)))
+    assert any("pasa_" in name for name in spilled) and not any(int(n) for n in spilled.values()), spilled
