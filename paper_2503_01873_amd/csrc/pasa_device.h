@@ -140,6 +140,9 @@ __device__ inline float add_pair(h2 v, float acc)
     return __builtin_amdgcn_fdot2(v, one, acc, false);
 }
 
+// P of a score, as the kernels make it: scale and offset in one fused multiply-add, the exponential rounded to fp16
+__device__ inline float p_of(float score, float nml) { return (float)(_Float16)__builtin_amdgcn_exp2f(__builtin_fmaf(score, LOG2E, nml)); }
+
 // The largest of a lane's values of P; NaN where one of them is.
 template <int N>
 __device__ inline float largest_of(const h8 (&p)[N])

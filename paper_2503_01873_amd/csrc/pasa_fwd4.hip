@@ -228,7 +228,7 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
                 if (last_key < T) v = 0.f;
                 const double lev = (double)mx + (double)coef * (double)v;
                 const float c = (float)(lev - R) + (mx + v) * 0.f;
-                const bool move = rises(c);
+                const bool move = rises(c, mx);
                 if (DIRECT) nml = unseen ? 0.f : (c - mx) * LOG2E;
                 if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
                     asm volatile("" ::: "memory");
@@ -245,7 +245,7 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
             };
             if (DIRECT) {
                 scores();
-                move_up([&](float c) { return c > CMAX; });
+                move_up([&](float c, float) { return c > CMAX; });
                 exponentials();
             } else {
                 nml = 0.f;
@@ -260,7 +260,8 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
                 if (high != 0ull) {
                     asm volatile("" ::: "memory");
                     scores();                // there are no registers to keep them beside P
-                    move_up([&](float c) { return !unseen && c > CMAX; });
+                    // as the row's own P shows it, which is rounded, so that it does not go by what its neighbours do
+                    move_up([&](float, float mx) { return !unseen && !(p_of(mx, nml) <= PMAX); });
                     exponentials();
                 }
             }

@@ -1136,7 +1136,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                     lev[rb] = (double)top + (double)inva * (double)bias;
                     c[rb] = (float)(lev[rb] - R[rb]) + bad;          // +inf for a row without keys so far
                     up[rb] = (bad - top) * LOG2E;
-                    move[rb] = !unseen[rb] && c[rb] > CMAX;
+                    // not EAGER: as its own P shows it, which is rounded, so that a row does not go by what its neighbours do
+                    move[rb] = !unseen[rb] && (EAGER ? c[rb] > CMAX : !(p_of(top, nml[rb]) <= PMAX));
                 };
                 auto settle = [&](int rb) {
                     if (!(EAGER && first)) rescale(rb, move[rb] ? exp_nat(-c[rb]) : 1.f);      // (nothing is stored yet)

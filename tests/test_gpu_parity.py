@@ -974,6 +974,34 @@ def test_a_row_that_rises_leaves_its_neighbours_alone(B, Hq, Hkv, N, d, causal, 
     assert o[:, :, ~up].tobytes() == flat[:, :, ~up].tobytes()
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,d,kernel", [(4, 32, 8, 500, 128, "fwd"), (14, 6, 6, 2500, 64, "fwd4")])
+def test_a_row_at_the_brink_does_not_rise_with_its_neighbour(B, Hq, Hkv, N, d, kernel):
+    """One row in sixteen whose level rises by about 8 in one tile, so closely spaced that many lie between 8, where a row may move to the new
+    level, and the 8.000014 up to which its P, rounded to fp16, is 2980 and shows nothing: beside a row that does rise there they keep
+    the bits that they have without it.  (A row that moves has the weight e^8 = 2980.96 instead, and the values leave only the difference.)"""
+    assert plan_of(P.MIXED, B, Hq, Hkv, N, 0, N, d, False) == (kernel, 1)
+    rng = np.random.default_rng(N)
+    scale, key = f32(d ** -0.5), 128 * (1 if kernel == "fwd" else 17)
+    k = np.zeros((B, Hkv, N, d), np.float16)
+    k[..., key, 0], k[..., key, 1] = 4.0 / scale, 0.01 / scale
+    kp = po.shift_keys(k[0, 0, key:key + 128], BETA, scale).astype(np.float64)
+    level = kp[0] + 63.5 * kp.mean(0)                        # of a query of one channel
+    v = np.full((B, Hkv, N, d), -np.exp(8.0) / (N - 1), np.float16)
+    v[..., key, :] = 1.0
+    q = np.zeros((B, Hq, N, d), np.float16)
+    near, high = np.arange(N) % 16 == 3, np.arange(N) % 16 == 7
+    first = np.float16(8.0 / level[0])
+    q[:, :, near, 0] = first
+    q[:, :, near, 1] = (8.0 + rng.uniform(-2e-4, 2e-4, (B, Hq, near.sum())) - float(first) * level[0]) / level[1]
+    alone, _ = gpu_attn(q, k, v, False, scale)
+    q[:, :, high, 0] = 4.0
+    beside, _ = gpu_attn(q, k, v, False, scale)
+    assert np.isfinite(beside).all() and not np.array_equal(alone[:, :, high], beside[:, :, high])
+    both = len(np.unique(alone[:, :, near].reshape(-1, d)[:, 0]))           # rows that moved and rows that did not
+    moved = (alone[:, :, ~high].view(np.uint16) != beside[:, :, ~high].view(np.uint16)).any(-1)
+    assert both > 1 and not moved.any(), (both, moved.sum())
+
+
 # ------------------------------------------------------------------ exact symmetries (no oracle involved)
 
 @pytest.mark.parametrize("variant", [P.MIXED, P.S16, P.STRICT16, P.DIRECT, P.NAIVE16])
