@@ -417,7 +417,10 @@ __device__ inline void for_constants(std::integer_sequence<int, I...>, F f) { (f
 // MIXED and S16 keep the level of the stored output as one fp64 number R = m + inva * F + Lc, as the other kernels do, in which the
 // reference level F cancels: P_j = fp16(exp(S' + inva * Sbar' - R)).  So the exponentials need no maximum; whether a row has
 // risen is seen from its P (the largest of packed pairs, three at a time, nothing exchanged between lanes), and only a block of rows with such a
-// row, or at its first tile, takes the maximum and makes P again.  Workgroups of two halves, whose chains are short, and MIXED at d = 64 take the
+// row takes the maximum and makes P again.  Where rows rise they often go on rising, and P made twice on every tile costs a fifth: on the first tile,
+// and on the AFTER tiles behind one that had to be made again, the maximum is taken first (28 heads on 4, us, the maximum always / P tried first on
+// every tile / so: levels that rise by 3 per tile, 8192 rows 507 / 550 / 507, by 9, 4096 rows not causal 252 / 279 / 243; normal values, 8192
+// rows 492 / 442 / 441, 14 x 32 heads of 256 rows 38.3 / 38.8 / 37.7; 8 tiles behind instead of 16: 510 on the first).  Workgroups of two halves, whose chains are short, and MIXED at d = 64 take the
 // maximum on every tile all the same: in the first tiles rows keep rising, and P made twice costs more there (us, without / so: 28 heads,
 // 2048 rows 49.5 / 47.7; 8 heads, 4096 rows, not causal, 77.2 / 73.7, of 2500 rows, d = 64, 50.1 / 47.0).  (DIRECT cannot: there a score may overflow
 // where the tile's bias does not.)
@@ -717,6 +720,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     }
     constexpr float CMAX = 8.f;      // LAZY: P may exceed 1 by at most e^CMAX before the row re-references its scale
     constexpr float PMAX = 2980.f;   // LEVEL: the fp16 value below e^CMAX
+    constexpr int AFTER = 16;        // LEVEL: tiles after one with a row that has risen in which others are likely to
+    int look_to = j0 + 1;            // LEVEL, not EAGER: the maximum is taken first on tiles before this one
     auto one_tile = [&](int rb) { return (CAUSAL && row0 + row + RR * rb < T) || N <= T; };      // the row sees a single tile
 
     // Both GEMMs run k-step by k-step: the fragments of a k-step go to the accumulator blocks in turn, so consecutive MFMAs never depend
@@ -811,11 +816,9 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
 
     // For where nothing reads these values before they are made again: without this the compiler keeps their registers, on the way past the
     // code that makes them, through all that comes before it
-    auto forget_p = [&] {
+    auto forget_p = [&](int rb) {
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk) asm volatile("" : "=v"(Pf[rb][kk]));
+        for (int kk = 0; kk < KK; ++kk) asm volatile("" : "=v"(Pf[rb][kk]));
     };
     auto forget_product = [&] {
 #pragma unroll
@@ -1140,11 +1143,12 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                     move[rb] = !unseen[rb] && (EAGER ? c[rb] > CMAX : !(p_of(top, nml[rb]) <= PMAX));
                 };
                 auto settle = [&](int rb) {
-                    if (!(EAGER && first)) rescale(rb, move[rb] ? exp_nat(-c[rb]) : 1.f);      // (nothing is stored yet)
+                    if (!first) rescale(rb, move[rb] ? exp_nat(-c[rb]) : 1.f);      // (nothing is stored yet)
                     R[rb] = move[rb] ? lev[rb] : R[rb];
                     nml[rb] = move[rb] ? up[rb] : nml[rb];
                 };
-                if (EAGER) {
+                if (EAGER || __builtin_expect(j < look_to, 0)) {
+                    if (!EAGER) asm volatile("" ::: "memory");
 #pragma unroll
                     for (int rb = 0; rb < RB; ++rb) look(rb);
                     if (__builtin_amdgcn_ballot_w64(move[0] || move[RB - 1]) != 0ull) {
@@ -1152,18 +1156,17 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
 #pragma unroll
                         for (int rb = 0; rb < RB; ++rb) settle(rb);
                     }
+                }
 #pragma unroll
-                    for (int rb = 0; rb < RB; ++rb) exponentials(rb);
-                } else {
-#pragma unroll
-                    for (int rb = 0; rb < RB; ++rb) {
+                for (int rb = 0; rb < RB; ++rb) {
+                    exponentials(rb);
+                    if (!EAGER && __builtin_expect(__builtin_amdgcn_ballot_w64(!(largest_of(Pf[rb]) <= PMAX)) != 0ull, 0)) {
+                        asm volatile("" ::: "memory");
+                        look_to = j + 1 + AFTER;
+                        forget_p(rb);
+                        look(rb);
+                        settle(rb);
                         exponentials(rb);
-                        if (__builtin_amdgcn_ballot_w64(!(largest_of(Pf[rb]) <= PMAX)) != 0ull) {
-                            asm volatile("" ::: "memory");
-                            look(rb);
-                            settle(rb);
-                            exponentials(rb);
-                        }
                     }
                 }
             } else {
@@ -1176,7 +1179,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
 
             if (STRICT) forget_product();
         } else {
-            forget_p();
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) forget_p(rb);
         }
         if (KSPL == 2 || grp == 0) drain_copies();
         __syncthreads();

@@ -974,16 +974,51 @@ def test_a_row_that_rises_leaves_its_neighbours_alone(B, Hq, Hkv, N, d, causal, 
     assert o[:, :, ~up].tobytes() == flat[:, :, ~up].tobytes()
 
 
+@pytest.mark.parametrize("variant", [P.MIXED, P.S16, P.DIRECT])
+@pytest.mark.parametrize("B,Hq,Hkv,N,d,causal,kernel", [
+    (1, 28, 4, 3600, 128, False, "fwd"), (1, 28, 4, 3000, 128, True, "fwd"), (14, 6, 6, 3000, 64, False, "fwd4"), (14, 6, 6, 3000, 64, True, "fwd4"),
+    (1, 28, 4, 2000, 128, True, "halves"), (1, 8, 8, 4000, 128, False, "halves"),
+])
+def test_rows_that_rise_late_and_go_on_rising(B, Hq, Hkv, N, d, causal, kernel, variant):
+    """Levels that rise on the 4th tile, and again from the 19th on: some rows by 12 at a time, some by 6, the others not.  Two heads against the
+    oracle, the rows that climb by themselves too."""
+    if variant != P.S16:
+        assert plan_of(variant, B, Hq, Hkv, N, 0, N, d, causal) == (kernel, 1)
+    rng = np.random.default_rng(N + d)
+    q = rng.standard_normal((B, Hq, N, d)).astype(np.float16)
+    k = (rng.standard_normal((B, Hkv, N, d)) + 1).astype(np.float16)
+    v = rng.standard_normal((B, Hkv, N, d)).astype(np.float16)
+    tile = np.arange(N) // 128
+    k[..., 5] = sum((tile >= t).astype(int) for t in (3, 18, 19, 21, 22)) * 12.0 * d ** 0.5 / 4.0
+    climb = np.arange(N) % 16
+    q[..., 5] = np.where(climb == 7, 4.0, np.where(climb == 12, 2.0, 0.0))
+    scale = f32(d ** -0.5)
+    o, _ = gpu_attn(q, k, v, causal, scale, variant)
+    assert np.isfinite(o).all()
+    rows_of = po.direct_rows if variant == P.DIRECT else po.pasa_rows
+    for b, h in ((0, 1), (B - 1, Hq - 1)):
+        for at in (slice(0, 300), slice(N - 500, N)):
+            ref = rows_of(q[b, h, at], k[b, h // (Hq // Hkv)], v[b, h // (Hq // Hkv)], scale, causal, BETA, 128, ORACLE_POLICY.get(variant, po.MIXED), at.start)
+            for which in (climb[at] == 7, climb[at] == 12, climb[at] < 7):
+                c = compare(o[b, h, at][which], ref[which])
+                print(VARIANT_NAME[variant], kernel, (b, h), at, c)
+                # S16: single outputs where S' straddles a rounding boundary at a dominant key (see the file's header)
+                assert (c["maxabs"] <= 2e-3) if variant != P.S16 else (c["p99"] <= 4e-3)
+
+
+@pytest.mark.parametrize("before", [0, 1])
 @pytest.mark.parametrize("B,Hq,Hkv,N,d,kernel", [(4, 32, 8, 500, 128, "fwd"), (14, 6, 6, 2500, 64, "fwd4")])
-def test_a_row_at_the_brink_does_not_rise_with_its_neighbour(B, Hq, Hkv, N, d, kernel):
+def test_a_row_at_the_brink_does_not_rise_with_its_neighbour(B, Hq, Hkv, N, d, kernel, before):
     """One row in sixteen whose level rises by about 8 in one tile, so closely spaced that many lie between 8, where a row may move to the new
-    level, and the 8.000014 up to which its P, rounded to fp16, is 2980 and shows nothing: beside a row that does rise there they keep
-    the bits that they have without it.  (A row that moves has the weight e^8 = 2980.96 instead, and the values leave only the difference.)"""
+    level, and the 8.000014 up to which its P, rounded to fp16, is 2980 and shows nothing: beside a row that does rise there, or on the
+    tile before (after which the maximum is taken first), they keep the bits that they have without it.  (A row that moves has the weight
+    e^8 = 2980.96 instead, and the values leave only the difference.)"""
     assert plan_of(P.MIXED, B, Hq, Hkv, N, 0, N, d, False) == (kernel, 1)
     rng = np.random.default_rng(N)
-    scale, key = f32(d ** -0.5), 128 * (1 if kernel == "fwd" else 17)
+    scale, key = f32(d ** -0.5), 128 * (2 if kernel == "fwd" else 18)
     k = np.zeros((B, Hkv, N, d), np.float16)
     k[..., key, 0], k[..., key, 1] = 4.0 / scale, 0.01 / scale
+    k[..., key - 128 * before, 2] = 4.0 / scale
     kp = po.shift_keys(k[0, 0, key:key + 128], BETA, scale).astype(np.float64)
     level = kp[0] + 63.5 * kp.mean(0)                        # of a query of one channel
     v = np.full((B, Hkv, N, d), -np.exp(8.0) / (N - 1), np.float16)
@@ -994,7 +1029,7 @@ def test_a_row_at_the_brink_does_not_rise_with_its_neighbour(B, Hq, Hkv, N, d, k
     q[:, :, near, 0] = first
     q[:, :, near, 1] = (8.0 + rng.uniform(-2e-4, 2e-4, (B, Hq, near.sum())) - float(first) * level[0]) / level[1]
     alone, _ = gpu_attn(q, k, v, False, scale)
-    q[:, :, high, 0] = 4.0
+    q[:, :, high, 2] = 4.0
     beside, _ = gpu_attn(q, k, v, False, scale)
     assert np.isfinite(beside).all() and not np.array_equal(alone[:, :, high], beside[:, :, high])
     both = len(np.unique(alone[:, :, near].reshape(-1, d)[:, 0]))           # rows that moved and rows that did not
