@@ -485,6 +485,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     constexpr int CPW = KT_BYTES / 1024 / 8 * KSPL;             // 1 KiB copies per wave per K' (or V) tile
     constexpr int RW = 32, RWG = 256 / KSPL;
     static_assert(KSPL == 1 || !STRICT, "the fp16 state has no merge rule");
+    static_assert(RB == 1 || !STRICT, "the fp16 state is that of one row");
 
     extern __shared__ __attribute__((aligned(1024))) char smem[];   // K'[2] then V[2]
 
@@ -610,19 +611,19 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                                                      at_row * (2 * D) + ((lane % CH) ^ (r & 7)) * 16, 0, 0, 0);
         }
     }
-    // per-row state (one query row of each block per lane; the four lanes of a row hold copies, but parts of l in the fp32 variants)
-    float F[RB], m[RB], l[RB];       // fp32 variants
+    // per-row state (one query row of each block per lane; the two or four lanes of a row hold copies)
+    float m[RB], l[RB];              // fp32 variants
     float Lc[RB];                    // log of the scale of the stored output (DIRECT, NAIVE16)
     double R[RB];                    // LEVEL: level of the stored output, m + inva * F + Lc of Algorithm 1's state
-    // STRICT: the same of both rows, packed; factors of the pending output combination, sum of the tile's P that goes with it
-    h2 F2 = {}, m2 = {}, l2 = {}, ec2 = {}, ep2 = {}, lt2 = {};
+    // STRICT: Algorithm 1's state; factors of the pending output combination, sum of the tile's P that goes with it
+    _Float16 F16 = 0, m16 = 0, l16 = 0, ec16 = 0, ep16 = 0, lt16 = 0;
     h8 Pf[RB][KK];                   // P^T, B operand of the second GEMM
     Acc O[RB][CB];                   // fp32 variants: stored output; STRICT: product of the latest tile
     h2 O16[RB][CB][NE / 2];              // STRICT: running output
     unsigned long long n_ovf = 0;    // of the whole wavefront
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        F[rb] = l[rb] = Lc[rb] = 0.f;
+        l[rb] = Lc[rb] = 0.f;
         m[rb] = NAIVE ? -__builtin_inff() : 0.f;
         R[rb] = -__builtin_inf();
 #pragma unroll
@@ -637,22 +638,18 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
 
     // STRICT: fold the product of the latest tile (in O) into the running fp16 output
     auto fold16 = [&] {
+        const h2 ec = {ec16, ec16}, ep = {ep16, ep16};
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            const h2 ec = {ec2[rb], ec2[rb]}, ep = {ep2[rb], ep2[rb]};
+        for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                for (int t = 0; t < NE / 2; ++t) {
-                    const h2 ot = pack_rn(O[rb][cb][2 * t], O[rb][cb][2 * t + 1]);
-                    const h2 a1 = ec * ot;                    // each packed op rounds to fp16 once; first tile: 1 * ot + 0 * 0
-                    const h2 a2 = ep * O16[rb][cb][t];
-                    O16[rb][cb][t] = a1 + a2;
-                }
-        }
+            for (int t = 0; t < NE / 2; ++t) {
+                const h2 ot = pack_rn(O[0][cb][2 * t], O[0][cb][2 * t + 1]);
+                const h2 a1 = ec * ot;                        // each packed op rounds to fp16 once; first tile: 1 * ot + 0 * 0
+                const h2 a2 = ep * O16[0][cb][t];
+                O16[0][cb][t] = a1 + a2;
+            }
         // the running sum (step 4), each operation rounded: l = fp16(fp16(e^{dm_{j-1}} l) + fp16(e^{dm_j} l')); first tile: 0 + l'
-        const h2 b1 = ep2 * l2, b2 = ec2 * lt2;
-        l2 = b1 + b2;
+        l16 = (_Float16)((_Float16)(ep16 * l16) + (_Float16)(ec16 * lt16));
     };
 
     // The copies of a slot are K'(jl + KSPL) and V(jl); each wave owns 2*CPW of their 1 KiB pieces.
@@ -712,12 +709,9 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     constexpr bool LSUM_DEFER = D == 128 && STRICT;
     constexpr bool LSUM_MFMA = !LSUM_DEFER;
     Acc Lacc[RB];
-    float pl_d[RB][2];
+    float pl_d[2] = {0.f, 0.f};
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-        Lacc[rb] = (Acc)0.f;
-        pl_d[rb][0] = pl_d[rb][1] = 0.f;
-    }
+    for (int rb = 0; rb < RB; ++rb) Lacc[rb] = (Acc)0.f;
     constexpr float CMAX = 8.f;      // LAZY: P may exceed 1 by at most e^CMAX before the row re-references its scale
     constexpr float PMAX = 2980.f;   // LEVEL: the fp16 value below e^CMAX
     constexpr int AFTER = 16;        // LEVEL: tiles after one with a row that has risen in which others are likely to
@@ -785,25 +779,20 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                 PASA_FENCE();
             }
             if (LSUM_DEFER) {
-                // 32 packed pairs over NM2 fragments, pair i of a k-step of row block i / 4
+                // 32 packed pairs over NM2 fragments
                 constexpr int PER = 32 / NM2;
 #pragma unroll
                 for (int u = 0; u < PER; ++u) {
-                    const int pr = n * PER + u, rb = RB == 1 ? 0 : pr >> 2 & 1, kk = RB == 1 ? pr >> 2 : pr >> 3;
-                    const h2 p2 = {Pf[rb][kk][2 * (pr & 3)], Pf[rb][kk][2 * (pr & 3) + 1]};
-                    pl_d[rb][pr & 1] = add_pair_mix(p2, pl_d[rb][pr & 1]);
+                    const int pr = n * PER + u;
+                    const h2 p2 = {Pf[0][pr >> 2][2 * (pr & 3)], Pf[0][pr >> 2][2 * (pr & 3) + 1]};
+                    pl_d[pr & 1] = add_pair_mix(p2, pl_d[pr & 1]);
                 }
                 PASA_FENCE();
             }
         }
         if (STRICT) {
-            float sum[RB];
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                sum[rb] = LSUM_MFMA ? Lacc[rb][0] : sum_of_row(pl_d[rb][0] + pl_d[rb][1]);
-                pl_d[rb][0] = pl_d[rb][1] = 0.f;
-            }
-            lt2 = pack_rn(sum[0], sum[RB - 1]);
+            lt16 = (_Float16)(LSUM_MFMA ? Lacc[0][0] : sum32(pl_d[0] + pl_d[1]));
+            pl_d[0] = pl_d[1] = 0.f;
         }
     };
 
@@ -942,10 +931,9 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                 // Padding keys of a ragged last tile have K' = 0 and add nothing; the divisor is the tile's own key count.
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) {
-                    constexpr int W = STRICT && RB == 2 ? 1 : 3;
                     float ps[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int t = 0; t < KB * NE / 2; ++t) ps[t & W] = add_pair_mix(Sh[rb][t / (NE / 2)][t % (NE / 2)], ps[t & W]);
+                    for (int t = 0; t < KB * NE / 2; ++t) ps[t & 3] = add_pair_mix(Sh[rb][t / (NE / 2)][t % (NE / 2)], ps[t & 3]);
                     sbar[rb] = sum_of_row((ps[0] + ps[1]) + (ps[2] + ps[3])) * (tail ? inv_tail : 1.0f / T);
                 }
             }
@@ -1004,7 +992,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                 return RB == 1 ? max32(pm) : max_row(pm);
             };
             bool unseen[RB], resc[RB];       // resc, LAZY: this row re-references its stored output and sum to the level of tile j
-            float top16[RB];                 // STRICT: m'
+            float top16 = 0.f;               // STRICT: m'
             float mref[RB], c_adj[RB];       // LAZY: log of the factor this tile's P carries (its level relative to the stored scale)
             float lc_resc[RB];               // LAZY: log of the factor that does it
 #pragma unroll
@@ -1015,7 +1003,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                 unseen[rb] = CAUSAL && diag && (row0 + row + RR * rb < j * T);
                 // ---- reference level for exp: local m' (PASA), running max (plain FlashAttention) ----
                 mref[rb] = unseen[rb] ? 0.f : mx;
-                top16[rb] = mx;
+                if (STRICT) top16 = mx;
                 c_adj[rb] = lc_resc[rb] = 0.f;
                 resc[rb] = false;
                 // ---- fp32 variants: global recovering (step 3) and the factor of the output or of P now, before the
@@ -1053,30 +1041,24 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                     m[rb] = first ? lev : out ? m0 : mn;
                 }
             }
-            h2 mref2 = {};           // STRICT: m', 0 for a row that sees none of the tile
             if (STRICT) {
-                // Step 3 with every operation rounded to fp16, in the order Algorithm 1 states them, for both rows at once; computed
-                // before the exponentials and without branches (the first tile and rows that see nothing of the tile select
-                // their values at the end) so that the latency of this chain is hidden.  The factors of the output
-                // combination go to ep2 / ec2 (the pending product of tile j-1 has been folded in above).
+                // Step 3 with every operation rounded to fp16, in the order Algorithm 1 states them; computed before the
+                // exponentials and without branches (the first tile and rows that see nothing of the tile select their values
+                // at the end) so that the latency of this chain is hidden.  The factors of the output combination go to ep16 /
+                // ec16 (the pending product of tile j-1 has been folded in above).
                 const _Float16 jm = (_Float16)(float)(j - j0), jn = (_Float16)(float)(j - j0 + 1), iv = (_Float16)inva;
-                const h2 jm2 = {jm, jm}, iv2 = {iv, iv}, sb = pack_rn(sbar[0], sbar[RB - 1]), mx = pack_rn(top16[0], top16[RB - 1]);
-                const h2 f1 = jm2 * F2, f2 = f1 + sb, Fn = {(_Float16)(f2[0] / jn), (_Float16)(f2[RB - 1] / jn)};
-                const h2 gp = F2 - Fn, gc = sb - Fn, dpp = iv2 * gp, dpc = iv2 * gc;
-                const h2 c1 = m2 + dpp, c2 = mx + dpc, mn = {c1[0] > c2[0] ? c1[0] : c2[0], c1[1] > c2[1] ? c1[1] : c2[1]};
-                const h2 h1 = m2 - mn, h3 = mx - mn, dp = h1 + dpp, dc = h3 + dpc;
-                const h2 ep = pack_rn(exp_nat_half<0>(dp), exp_nat_half<RB - 1>(dp)), ec = pack_rn(exp_nat_half<0>(dc), exp_nat_half<RB - 1>(dc));
-                const unsigned out = (unseen[0] ? 0xffffu : 0u) | (unseen[RB - 1] ? 0xffff0000u : 0u);
-                auto choose = [&](h2 at_first, h2 not_seen, h2 seen) {
-                    const unsigned a = __builtin_bit_cast(unsigned, not_seen), b = __builtin_bit_cast(unsigned, seen);
-                    return first ? at_first : __builtin_bit_cast(h2, (a & out) | (b & ~out));
-                };
-                const h2 one = {(_Float16)1, (_Float16)1}, zero = {};
-                F2 = choose(sb, F2, Fn);
-                m2 = choose(mx, m2, mn);
-                ep2 = choose(zero, one, ep);             // unseen: O <- fp16(0 * 0) + fp16(1 * O)
-                ec2 = choose(one, zero, ec);
-                mref2 = __builtin_bit_cast(h2, __builtin_bit_cast(unsigned, mx) & ~out);
+                const _Float16 sb = (_Float16)sbar[0], mx = (_Float16)top16;
+                const _Float16 Fn = (_Float16)((_Float16)((_Float16)(jm * F16) + sb) / jn);
+                const _Float16 dpp = (_Float16)(iv * (_Float16)(F16 - Fn)), dpc = (_Float16)(iv * (_Float16)(sb - Fn));
+                const _Float16 c1 = (_Float16)(m16 + dpp), c2 = (_Float16)(mx + dpc), mn = c1 > c2 ? c1 : c2;
+                const _Float16 dp = (_Float16)((_Float16)(m16 - mn) + dpp), dc = (_Float16)((_Float16)(mx - mn) + dpc);
+                const _Float16 ep = (_Float16)exp_nat((float)dp), ec = (_Float16)exp_nat((float)dc);
+                const _Float16 one = 1, zero = 0;
+                const bool out = unseen[0];
+                F16 = first ? sb : out ? F16 : Fn;
+                m16 = first ? mx : out ? m16 : mn;
+                ep16 = first ? zero : out ? one : ep;    // unseen: O <- fp16(0 * 0) + fp16(1 * O)
+                ec16 = first ? one : out ? zero : ec;
             }
             // what a row has stored so far, times r
             auto rescale = [&](int rb, float r) {
@@ -1103,7 +1085,8 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                     for (int t = 0; t < NE / 2; ++t) {
                         float e0, e1;
                         if (STRICT) {   // the difference is itself rounded to fp16 before the exponential
-                            const h2 d2 = Sh[rb][kb][t] - (h2){mref2[rb], mref2[rb]};
+                            const _Float16 mh = (_Float16)mref[rb];      // exact: one of the fp16 scores (or 0)
+                            const h2 d2 = Sh[rb][kb][t] - (h2){mh, mh};
                             e0 = exp_nat_half<0>(d2);
                             e1 = exp_nat_half<1>(d2);
                         } else if (PACKED) {
@@ -1187,16 +1170,15 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     }
     if ((grp == 0) == (n_a == n_b)) __syncthreads();     // the barrier that the other group's last iteration ends with
 
-    // level of the stored output: running maximum in its frame, the frame's offset, the stored scale (exact in fp64)
+    // level of the stored output; DIRECT, NAIVE16: running maximum and stored scale (exact in fp64)
     bool none[RB];
     double level[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        l[rb] = STRICT ? (float)l2[rb] : Lacc[rb][0];      // every row of the block is the sum
+        l[rb] = STRICT ? (float)l16 : Lacc[rb][0];      // every row of the block is the sum
         none[rb] = !(J_w > j0 + jg) || l[rb] == 0.f;
-        // (a row that sees a single tile needs no pseudo-average, which may be infinite there).  Not finite: a score or a
-        // pseudo-average left the range of its type, and the state must not be taken for one without keys.
-        level[rb] = none[rb] ? -__builtin_inf() : LEVEL ? R[rb] : (double)m[rb] + (one_tile(rb) ? 0.0 : (double)inva * (double)F[rb]) + (double)Lc[rb];
+        // Not finite: a score or a pseudo-average left the range of its type, and the state must not be taken for one without keys.
+        level[rb] = none[rb] ? -__builtin_inf() : LEVEL ? R[rb] : (double)m[rb] + (double)Lc[rb];
         if (!none[rb] && !__builtin_isfinite(level[rb])) level[rb] = __builtin_nan("");
     }
     // ---------------- key split within the workgroup: group B's state joins group A's ----------------
@@ -1281,7 +1263,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
         // fp32 variants: the fp32 quotient is rounded once, to the output type; STRICT16: the fp16
         // quotient of Algorithm 1's last line, converted when the output is bf16
         auto value = [&](int rb, int cb, int e) {
-            return STRICT ? (float)(_Float16)(O16[rb][cb][e >> 1][e & 1] / l2[rb]) : O[rb][cb][e] * oscale[rb];
+            return STRICT ? (float)(_Float16)(O16[rb][cb][e >> 1][e & 1] / l16) : O[rb][cb][e] * oscale[rb];
         };
         if (INSTR) {
 #pragma unroll
