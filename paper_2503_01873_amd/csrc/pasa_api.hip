@@ -418,6 +418,7 @@ size_t pasa_attn_fwd_workspace_min(int B, int Hkv, int N, int d)
     return workspace_min_bytes(B, Hkv, N, d);
 }
 
+// For tests: the kernel of a call (bits 0 to 3) and its blocks of rows, -1 for none
 int pasa_internal_plan(int variant, int counters, int B, int Hq, int Hkv, int Nq, int row0, int N, int d, int causal,
                        size_t workspace_bytes, int* nsplit)
 {
@@ -425,7 +426,7 @@ int pasa_internal_plan(int variant, int counters, int B, int Hq, int Hkv, int Nq
     if (check_shape(B, Hq, Hkv, N, d) != PASA_OK || workspace_bytes < need) return -1;
     const Plan p = plan_call(variant, counters != 0, true, B, Hq, Hkv, Nq, causal ? row0 : 0, N, d, causal, workspace_bytes - need);
     if (nsplit != nullptr) *nsplit = p.nsplit;
-    return p.kernel;
+    return p.kernel | p.row_blocks << 4;
 }
 
 unsigned pasa_internal_quotient(unsigned n, unsigned d) { return fast_div(d).quotient(n); }

@@ -117,8 +117,7 @@ def compare(o, ref):
 KERNELS = ("fwd", "halves", "fwd4", "rows")
 
 
-def plan_of(variant, B, Hq, Hkv, Nq, row0, N, d, causal, counters=False, workspace_bytes=None):
-    """(kernel, number of key splits) that the library plans a call on; needs no GPU."""
+def _plan(variant, B, Hq, Hkv, Nq, row0, N, d, causal, counters, workspace_bytes):
     import ctypes
     import torch  # noqa: F401  before the library, which then shares the HIP runtime that torch brings
     f = P.lib().pasa_internal_plan
@@ -129,4 +128,14 @@ def plan_of(variant, B, Hq, Hkv, Nq, row0, N, d, causal, counters=False, workspa
     ns = ctypes.c_int(0)
     k = f(variant, int(counters), B, Hq, Hkv, Nq, row0, N, d, int(causal), workspace_bytes, ctypes.byref(ns))
     assert k >= 0, "no such call"
-    return KERNELS[k], ns.value
+    return KERNELS[k & 15], ns.value, k >> 4
+
+
+def plan_of(variant, B, Hq, Hkv, Nq, row0, N, d, causal, counters=False, workspace_bytes=None):
+    """(kernel, number of key splits) that the library plans a call on; needs no GPU."""
+    return _plan(variant, B, Hq, Hkv, Nq, row0, N, d, causal, counters, workspace_bytes)[:2]
+
+
+def row_blocks_of(variant, B, Hq, Hkv, Nq, row0, N, d, causal):
+    """Blocks of rows per wavefront of halves (1: MFMAs of 32 rows, 2: of 16), per workgroup of pasa_rows."""
+    return _plan(variant, B, Hq, Hkv, Nq, row0, N, d, causal, False, None)[2]

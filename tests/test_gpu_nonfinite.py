@@ -113,6 +113,25 @@ def test_infinite_key_two_halves(inf_key, variant):
     assert np.isfinite(np.delete(o[0], slice(7, 14), 0)).all()
 
 
+@pytest.mark.parametrize("variant", [P.MIXED, P.DIRECT, P.S16])
+@pytest.mark.parametrize("B,Hq,Hkv,N,d,inf_key,kernel", [
+    (1, 28, 4, 2100, 128, 1990, "halves"), (1, 28, 4, 2100, 128, 150, "halves"),           # with MFMAs of 16 rows
+    (1, 28, 4, 3000, 128, 2900, "fwd"), (1, 28, 4, 3000, 128, 300, "fwd"),
+    (14, 6, 6, 2500, 64, 2400, "fwd4"),                                                    # on the tiles whose P is made without the maximum
+])
+def test_infinite_key_longer_sequences(B, Hq, Hkv, N, d, inf_key, kernel, variant):
+    rng = np.random.default_rng(N + inf_key)
+    scale, G = f32(d ** -0.5), Hq // Hkv
+    q, k, v = _inputs(rng, B, Hq, Hkv, N, N, d)
+    k[0, 1, inf_key, 5] = np.inf
+    if variant != P.S16:
+        assert plan_of(variant, B, Hq, Hkv, N, 0, N, d, True) == (kernel, 1)
+    o, _ = gpu_attn(q, k, v, True, scale, variant)
+    for at in (slice(0, 400), slice(N - 500, N)):
+        _check(o[0, G, at], q[0, G, at], k[0, 1], v[0, 1], scale, True, variant, at.start, inf_key // 128 * 128, kernel)
+    assert np.isfinite(np.delete(o[0], slice(G, 2 * G), 0)).all() and np.isfinite(o[1:]).all()
+
+
 def test_bf16_key_beyond_the_fp16_range():
     rng = np.random.default_rng(3)
     N, d, scale = 256, 128, f32(128 ** -0.5)

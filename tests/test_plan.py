@@ -3,7 +3,7 @@ No GPU is used."""
 import pytest
 
 import paper_2503_01873_amd as P
-from gpu_harness import plan_of
+from gpu_harness import plan_of, row_blocks_of
 
 MSD = (P.MIXED, P.S16, P.DIRECT)
 
@@ -43,6 +43,15 @@ def test_calls_reach_the_kernel_they_test(B, Hq, Hkv, Nq, row0, N, d, causal, va
     for variant in variants:
         got, nsplit = plan_of(variant, B, Hq, Hkv, Nq, row0, N, d, causal)
         assert got == kernel and (nsplit > 1) == split, (variant, got, nsplit)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,N,causal,blocks", [
+    (1, 28, 4, 1024, True, 1), (1, 28, 4, 900, False, 1), (1, 28, 4, 1028, False, 2), (1, 28, 4, 1100, True, 1),
+    (1, 12, 2, 2304, True, 1), (1, 8, 8, 4000, True, 1), (1, 8, 8, 4000, False, 2), (1, 28, 4, 1500, True, 2), (1, 28, 4, 2048, True, 2),
+])
+def test_workgroups_of_two_halves_take_the_mfmas_that_were_measured_fastest(B, Hq, Hkv, N, causal, blocks):
+    for variant in MSD:
+        assert plan_of(variant, B, Hq, Hkv, N, 0, N, 128, causal)[0] == "halves" and row_blocks_of(variant, B, Hq, Hkv, N, 0, N, 128, causal) == blocks
 
 
 # us of the kernel named / of the one that the estimates once chose, which were fitted to calls of 150 to 6000 keys
