@@ -143,6 +143,20 @@ __device__ inline float add_pair(h2 v, float acc)
 // P of a score, as the kernels make it: scale and offset in one fused multiply-add, the exponential rounded to fp16
 __device__ inline float p_of(float score, float nml) { return (float)(_Float16)__builtin_amdgcn_exp2f(__builtin_fmaf(score, LOG2E, nml)); }
 
+// The tiles on which a wavefront takes the maximum before it makes P: those before `end`.  A tile on which a row rises all the same is made again,
+// which costs as much as the maximum of several.  Where such tiles follow one another within three, or that close behind the last one looked at, the
+// next 2, 4, 8 and then 16 are looked at.  A single one changes nothing: rows of real values rise now and then, and the other wavefronts
+// of the workgroup wait at its barriers for each tile that one of them looks at.
+struct LookFirst {
+    int end, tiles;
+    __device__ inline void risen(int j)
+    {
+        if (end > j) return;                     // by the other block of rows of the same tile
+        tiles = j - end >= 3 ? 0 : tiles == 0 ? 2 : tiles < 8 ? 2 * tiles : 16;
+        end = j + 1 + tiles;
+    }
+};
+
 // The largest of a lane's values of P; NaN where one of them is.
 template <int N>
 __device__ inline float largest_of(const h8 (&p)[N])

@@ -19,7 +19,7 @@ __device__ inline void workgroup_barrier()
 
 constexpr float CMAX = 8.f;     // P may exceed 1 by at most e^CMAX before a row moves its stored output to a new level
 constexpr float PMAX = 2980.f;  // the fp16 value below e^CMAX
-constexpr int RISING = 16;      // tiles at the start of a row, and behind one in which it rose, in which it is likely to rise (see below)
+constexpr int EARLY = 16;       // tiles at the start of a row in which it is likely to rise (see below)
 
 // One workgroup = four wavefronts = 128 query rows of one head, 32 rows per wavefront; three workgroups share a compute
 // unit and three wavefronts a SIMD.  The GEMMs are pasa_fwd's (32x32x16 MFMAs, transposed, fragments from LDS through a ring
@@ -39,8 +39,8 @@ constexpr int RISING = 16;      // tiles at the start of a row, and behind one i
 // In the first tiles of a row, where rows keep rising, P would be made twice on most of them: there the maximum is taken first (resonant
 // values, us, without the maximum from the second tile on / from the 9th / 17th / 33rd: 4 x 16 heads of 930 rows 39.8 / 36.2 / 36.2 / 36.2, 4 x 5 heads of
 // 3786 rows, causal, 69.9 / 69.4 / 68.8 / 67.8; 2 x 5 heads of 9216 rows, normal values, 273.1 / 273.9 / 274.4 / 277.3, the maximum always 286.5).
-// So it is for as many tiles behind one on which a row of the wavefront rose (14 x 5 heads of 5000 rows, causal, us, the maximum always / not so / so: levels
-// that rise by 1 per tile 372 / 403 / 376, by 3 375 / 422 / 381; normal values 367 / 362 / 362).
+// So it is later where rows of the wavefront rise on tile after tile, as LookFirst says (14 x 5 heads of 5000 rows, causal, us, not so / on the 16 tiles
+// behind every one on which a row rose / so: levels that rise by 1 per tile 329 / 303 / 312, by 3 349 / 309 / 313; normal values 289 / 289 / 290).
 // 64 rows per wavefront and two workgroups to a compute unit on top of it (half the LDS reads): 1 % faster on the 9216 rows,
 // 4 to 20 % slower on all smaller calls.
 template <bool CAUSAL, bool DIRECT>
@@ -153,7 +153,7 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
     float* sb = reinterpret_cast<float*>(smem + SB_OFF + wave * 1024);       // [8 tiles][32 rows]
 
     constexpr int PF = 3;
-    int look_to = j0 + RISING;
+    LookFirst look_first = {j0 + EARLY, 0};
     for (int j = j0; j < J_wg; ++j) {
         // pseudo-averages of the next eight tiles (a block of A holds sixteen: the other half is not kept)
         if ((j & 7) == 0 && j < J_w) {
@@ -255,11 +255,11 @@ void pasa_fwd4(const _Float16* __restrict__ q, const char* __restrict__ ws, _Flo
                 const float off = __builtin_fmaf(v, 0.f, (float)__builtin_fma((double)coef, (double)v, -R));
                 if (!unseen) nml = off * LOG2E;
                 unsigned long long high = ~0ull;
-                if (__builtin_expect(j >= look_to, 1)) {
+                if (__builtin_expect(j >= look_first.end, 1)) {
                     scores();
                     exponentials();
                     high = __builtin_amdgcn_ballot_w64(!(largest_of(Pf) <= PMAX));
-                    if (high != 0ull) look_to = j + 1 + RISING;
+                    if (high != 0ull) look_first.risen(j);
                 }
                 if (__builtin_expect(high != 0ull, 0)) {
                     asm volatile("" ::: "memory");

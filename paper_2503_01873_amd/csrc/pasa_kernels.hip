@@ -417,18 +417,19 @@ __device__ inline void for_constants(std::integer_sequence<int, I...>, F f) { (f
 // MIXED and S16 keep the level of the stored output as one fp64 number R = m + inva * F + Lc, as the other kernels do, in which the
 // reference level F cancels: P_j = fp16(exp(S' + inva * Sbar' - R)).  So the exponentials need no maximum; whether a row has
 // risen is seen from its P (the largest of packed pairs, three at a time, nothing exchanged between lanes), and only a block of rows with such a
-// row takes the maximum and makes P again.  Where rows rise they often go on rising, and P made twice on every tile costs a fifth: on the first tile,
-// and on the AFTER tiles behind one that had to be made again, the maximum is taken first (28 heads on 4, us, the maximum always / P tried first on
-// every tile / so: levels that rise by 3 per tile, 8192 rows 507 / 550 / 507, by 9, 4096 rows not causal 252 / 279 / 243; normal values, 8192
-// rows 492 / 442 / 441, 14 x 32 heads of 256 rows 38.3 / 38.8 / 37.7; 8 tiles behind instead of 16: 510 on the first).  Workgroups of two halves, whose chains are short, and MIXED at d = 64 take the
-// maximum on every tile all the same: in the first tiles rows keep rising, and P made twice costs more there (us, without / so: 28 heads,
-// 2048 rows 49.5 / 47.7; 8 heads, 4096 rows, not causal, 77.2 / 73.7, of 2500 rows, d = 64, 50.1 / 47.0).  (DIRECT cannot: there a score may overflow
-// where the tile's bias does not.)
+// row takes the maximum and makes P again.  Where rows rise on tile after tile, P made twice on all of them costs a fifth: the
+// maximum is taken first on the first tile and on those that LookFirst names.  28 heads on 4, us, P first on every tile but the first / the maximum
+// first on the 16 tiles behind every one made again / so (the maximum always: a tenth more on normal values): levels that rise by 3 per tile, 8192
+// rows 509 / 471 / 472, by 9, 4096 rows not causal 269 / 237 / 241; normal values, 8192 rows 416 / 415 / 415; keys with outlier channels 421 / 436 / 422;
+// 16384 rows, a key bias that changes every 1024 keys, 1585 / 1629 / 1592.
+// Workgroups of two halves, whose chains are short, and MIXED at d = 64 take the maximum on every tile all the same: in the first tiles rows keep
+// rising, and P made twice costs more there (us, without / so: 28 heads, 2048 rows 49.5 / 47.7; 8 heads, 4096 rows, not causal, 77.2 / 73.7, of 2500
+// rows, d = 64, 50.1 / 47.0).  (DIRECT cannot: there a score may overflow where the tile's bias does not.)
 //
 // RB: the MFMAs.  RB = 1: one block of 32 rows, 32 x 32 x 16; RB = 2: two blocks of 16 rows, 16 x 16 x 32, each fragment of K' and V used twice
 // in a row.  Both have the same rate and read as much LDS per product, but per product 16 x 16 x 32 moves half as many accumulators
 // through the registers (twice as many operands, of half the width): with fragments from LDS and normal values a loop of nothing else reaches
-// 1.71 PFLOP/s against 1.50, on zeros 2.36 against 2.42.  Power is what bounds the long launches at d = 128, so they take it: 28 heads on 4, us, both
+// 1.68 PFLOP/s against 1.48, on zeros 2.37 against 2.40 (profiles/mfma_rate_of_two_shapes.txt).  Power is what bounds the long launches at d = 128, so they take it: 28 heads on 4, us, both
 // sides in turn, 8192 rows 449 -> 403, 4096 rows not causal 233 -> 209; S16, 4096 rows 136 -> 124; DIRECT 129 -> 120; 1500 rows of 12000 keys
 // 254 -> 242.  An MFMA holds the issue port though, and there are twice as many: where the vector part is the longer one (d = 64), or launches are short,
 // 32 x 32 x 16 is faster (8 heads, d = 64, 2500 rows 50.1 / 53.6; STRICT16, 2 x 5 heads of 5000 rows, d = 64, 128 / 138, 12 heads on 2, 2257 rows, d = 128,
@@ -714,8 +715,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
     for (int rb = 0; rb < RB; ++rb) Lacc[rb] = (Acc)0.f;
     constexpr float CMAX = 8.f;      // LAZY: P may exceed 1 by at most e^CMAX before the row re-references its scale
     constexpr float PMAX = 2980.f;   // LEVEL: the fp16 value below e^CMAX
-    constexpr int AFTER = 16;        // LEVEL: tiles after one with a row that has risen in which others are likely to
-    int look_to = j0 + 1;            // LEVEL, not EAGER: the maximum is taken first on tiles before this one
+    LookFirst look_first = {j0 + 1, 0};      // LEVEL, not EAGER: the tiles on which the maximum is taken first
     auto one_tile = [&](int rb) { return (CAUSAL && row0 + row + RR * rb < T) || N <= T; };      // the row sees a single tile
 
     // Both GEMMs run k-step by k-step: the fragments of a k-step go to the accumulator blocks in turn, so consecutive MFMAs never depend
@@ -1130,7 +1130,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                     R[rb] = move[rb] ? lev[rb] : R[rb];
                     nml[rb] = move[rb] ? up[rb] : nml[rb];
                 };
-                if (EAGER || __builtin_expect(j < look_to, 0)) {
+                if (EAGER || __builtin_expect(j < look_first.end, 0)) {
                     if (!EAGER) asm volatile("" ::: "memory");
 #pragma unroll
                     for (int rb = 0; rb < RB; ++rb) look(rb);
@@ -1145,7 +1145,7 @@ void pasa_fwd(const _Float16* __restrict__ q, const char* __restrict__ ws, _Floa
                     exponentials(rb);
                     if (!EAGER && __builtin_expect(__builtin_amdgcn_ballot_w64(!(largest_of(Pf[rb]) <= PMAX)) != 0ull, 0)) {
                         asm volatile("" ::: "memory");
-                        look_to = j + 1 + AFTER;
+                        look_first.risen(j);
                         forget_p(rb);
                         look(rb);
                         settle(rb);
