@@ -238,22 +238,25 @@ int fitting(int ns, size_t rows_all, int d, size_t room)
 // d = 64 to pasa_fwd4 (128 rows of one head, four wavefronts).  pasa_rows takes every call whose rows of a KV head fit one block (a decoding step reads its keys
 // once and not once per query head); otherwise the estimate below, from measured rates, says which is fastest.
 //
-// The factors of the estimates are fitted to 7400 calls of 128 to 32768 keys that ran on every kernel, so that the plan is behind the fastest
-// kernel by as little as can be: 0.6 % on average, 0.7 % S16 (pieces that are planned as their whole apart).  They rank the kernels and are not times,
-// above all at d = 64.  Not all lie where these calls alone would put them: tests hold some calls to a kernel that is not their fastest (777 rows
-// below, 8 heads, d = 64, of 2500 rows not causal), and calls near those go with them.  us, pasa_fwd / HALVES / pasa_rows, 28 heads on 4:
-//   causal, 394 / 561 / 687 / 841 / 990 rows         15.3 / 11.8 / 9.2, 16.0 / 13.7 / 11.1, 20.1 / 15.0 / 18.3, 20.6 / 16.7 / 20.0, 25.2 / 18.5 / 22.8
-//   causal, 1616 / 2089 / 2240 / 2813 / 4488 rows    36.3 / 30.9 / 42.0, 48.3 / 42.6 / 61.7, 53.9 / 45.6 / 67.4, 74.0 / 74.1 / 98.4, 148 / 160 / 223
-//   not causal, 391 / 581 / 1006 / 2021 / 5746 rows  17.5 / 13.7 / 10.8, 19.8 / 15.4 / 18.6, 27.1 / 21.5 / 28.4, 60.8 / 68.5 / 85.8, 447 / 455 / 612
-//   31 / 157 rows of 11699 / 9168 keys, 334 of 14242, 1206 of 22977    99.9 / 123 / 31.4, 173 / 99.4 / 59.4, 263 / 157 / 151, 436 / 555 / 574
-//   S16, causal, 286 / 391 / 1792 / 3770 rows        11.0 / 11.0 / 7.8, 16.3 / 12.4 / 12.1, 47.9 / 35.4 / 83.6, 119 / 126 / 321
-// planned on the fastest but for 687 (pasa_rows).  Pieces as the whole: 47 rows of 637 keys, not causal, 14.5 on HALVES, 6.5 on pasa_rows.
+// The factors of the estimates were fitted to 7400 calls of 128 to 32768 keys that ran on every kernel, as the kernels were before pasa_fwd
+// took MFMAs of 16 x 16 x 32 and, with pasa_fwd4, exponentials without a maximum: the plan was 0.6 % behind the fastest kernel on average, 0.7 %
+// S16.  With the kernels as they are it is 0.5 % behind on 203 prompts drawn like those (d = 128 0.6 %, S16 0.6 %, d = 64 0.4 %), four of them by a
+// tenth to a sixth, and 6 % on 57 pieces, most of it in two that are planned as their whole.  The factors rank the kernels and are not
+// times, above all at d = 64 and for the long launches of pasa_fwd, which take a tenth less.  Not all lie where these calls alone would put them:
+// tests hold some calls to a kernel that is not their fastest (777 rows below, 8 heads, d = 64, of 2500 rows not causal), and calls near those go with
+// them.  us, pasa_fwd / HALVES / pasa_rows, 28 heads on 4:
+//   causal, 394 / 561 / 687 / 841 / 990 rows         15.3 / 11.7 / 9.1, 15.6 / 13.3 / 10.9, 20.2 / 15.0 / 18.4, 20.5 / 16.4 / 20.2, 25.2 / 18.4 / 22.6
+//   causal, 1616 / 2089 / 2240 / 2813 / 4488 rows    36.8 / 29.7 / 41.9, 47.1 / 43.4 / 62.6, 52.9 / 46.1 / 68.9, 68.4 / 69.8 / 97.5, 134 / 153 / 223
+//   not causal, 391 / 581 / 1006 / 2021 / 5746 rows  16.3 / 12.4 / 10.3, 18.6 / 13.9 / 18.5, 26.3 / 21.2 / 28.3, 54.0 / 64.0 / 86.6, 418 / 437 / 633
+//   31 / 157 rows of 11699 / 9168 keys, 334 of 14242, 1206 of 22977    101 / 121 / 32.7, 179 / 98.9 / 58.6, 272 / 155 / 149, 448 / 565 / 591
+//   S16, causal, 286 / 391 / 1792 / 3770 rows        10.9 / 10.9 / 7.6, 16.1 / 12.3 / 12.1, 46.0 / 34.8 / 84.6, 104 / 119 / 319
+// planned on the fastest but for 687 (pasa_rows).  Pieces as the whole: 47 rows of 637 keys, not causal, 12.8 on HALVES, 6.6 on pasa_rows.
 // d = 64, pasa_fwd / pasa_fwd4 / pasa_rows:
-//   14 x 5 heads, not causal, 153 / 366 / 688 / 1162 rows     10.2 / 6.7 / 5.2, 12.5 / 8.9 / 11.9, 19.6 / 17.8 / 23.2, 52.3 / 38.9 / 50.8
-//   14 x 5 heads, causal, 169 / 758 / 2321 / 10791 rows       8.7 / 7.1 / 5.6, 17.9 / 15.6 / 21.1, 80.3 / 69.5 / 107, 1362 / 1301 / 1704
-//   one head, causal, 412 / 1664 / 18625 rows                 11.8 / 9.1 / 5.1, 26.5 / 21.8 / 6.8, 129 / 98.8 / 89.7
+//   14 x 5 heads, not causal, 153 / 366 / 688 / 1162 rows     9.0 / 6.8 / 5.2, 11.2 / 8.5 / 11.9, 18.9 / 18.4 / 23.5, 49.2 / 39.7 / 52.9
+//   14 x 5 heads, causal, 169 / 758 / 2321 / 10791 rows       8.1 / 6.7 / 5.6, 17.0 / 15.6 / 21.3, 81.0 / 74.3 / 109, 1346 / 1267 / 1676
+//   one head, causal, 412 / 1664 / 18625 rows                 11.0 / 8.5 / 5.1, 25.3 / 21.5 / 6.8, 125 / 94.2 / 87.6
 //   one head in one / two pieces on pasa_rows, causal, 5586 rows 25.3 / 19.5, not causal, 2536 / 3200 rows 10.1 / 13.0, 10.3 / 14.3
-//   14 x 16 heads, 186 rows at the end of 8006 keys           147 / 166 / 189
+//   14 x 16 heads, 186 rows at the end of 8006 keys           154 / 166 / 195
 
 // Equal workgroups, one to a compute unit, each `fixed` us and `steps` steps: of `alone` us, of `busy` where all compute units are at work
 // (power), which takes part of the way with the square of the share that is.
@@ -299,8 +302,8 @@ double merge_us(int ns, size_t rows_all, int d) { return ns > 1 ? 5.5 + 2e-6 * (
 // and for all up to 2048 keys; pieces start at multiples of 32 rows (rows of a wavefront stay together) and have 32 rows or
 // more.  Shorter ones are decoding steps, which would lose five times (16 x 1 row of 4999 keys: 33 us, 173 on the
 // kernel of the whole), except the end of a causal sequence of up to 2048 keys.  What it costs, us on the kernel of the whole /
-// on the one that is fastest, 28 heads on 4, d = 128: 128 rows of 2048 keys 31.6 / 13.8, 512 rows 31.6 / 26.7, 32 rows of
-// 1024 keys 19.4 / 8.6; 14 sequences, row 800 of 801 keys (every 32nd decoding step) 40 / 9.
+// on the one that is fastest, 28 heads on 4, d = 128: 128 rows of 2048 keys 29.4 / 12.9, 512 rows 29.3 / 26.2, 32 rows of
+// 1024 keys 16.2 / 7.8; 14 sequences, row 800 of 801 keys (every 32nd decoding step) 35.7 / 7.1.
 bool keeps_the_bits_of_the_whole(int B, int Hq, int Nq, int row0, int N, int causal)
 {
     if (wanted_splits(B, Hq, Nq, N) > 1 || (causal && row0 % 32 != 0)) return false;
